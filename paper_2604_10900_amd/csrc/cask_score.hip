@@ -64,24 +64,31 @@ __device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int
   return unit < n_units;
 }
 
-// ------------------------------------------------------------------ MFMA path (bf16, d=128)
+// ------------------------------------------------------------------ MFMA path (bf16)
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kD = 128;
-constexpr int kRowBytes = kD * 2;
 constexpr int kWaves = 4;                    // waves per workgroup, 1 per SIMD; two workgroups share a CU
 constexpr int kThreads = kWaves * 64;
 constexpr int kResRows = kWaves * 64;        // resident rows per workgroup (64 per wave)
 constexpr int kStageRows = 64;               // stream rows per ring slot
-constexpr int kGroupPitch = 1024 + 64;       // LDS pitch of a 4-row group (see stage layout)
-constexpr int kDataBytes = (kStageRows / 4) * kGroupPitch;
-constexpr int kStageBytes = kDataBytes + kStageRows * 4;   // + one float per row: -L_row (sweep B)
 constexpr int kDepth = 4;                    // ring slots: loads run kDepth - 1 stages ahead
-constexpr int kLoadsPerThread = kStageRows * 16 / kThreads;  // 16-byte pieces per thread per stage
+
+// What the head dimension decides about a ring slot (see the stage layout below).
+template <int D>
+struct StageGeom {
+  static constexpr int kRowBytes = D * 2;
+  static constexpr int kGroupRows = 1024 / kRowBytes;            // rows one load instruction of a wave lands: 4 or 8
+  static constexpr int kGroupPitch = 1024 + kGroupRows * 16;     // LDS pitch of such a group
+  static constexpr int kDataBytes = (kStageRows / kGroupRows) * kGroupPitch;
+  static constexpr int kStageBytes = kDataBytes + kStageRows * 4;  // + one float per row: -L_row (sweep B)
+  static constexpr int kLoadsPerThread = kStageRows * (kRowBytes / 16) / kThreads;  // 16-byte pieces per thread per stage
+  static constexpr int kStepBytes = 2 * kGroupRows * 16;         // LDS distance of two k-steps of a row
+  static constexpr int kTileBytes = (32 / kGroupRows) * kGroupPitch;  // LDS distance of the two tile rows of a stage
+};
 
 // Pad value of -L for window rows past W*G: far enough down that exp2 flushes to zero.
 constexpr float kPadNegL = -1.0e30f;
@@ -126,11 +133,12 @@ __global__ __launch_bounds__(kBiasThreads) void score_bias_kernel(KParams kp, in
 // kDepth - 1 stages ahead of the stage being consumed; one barrier per stage both publishes a
 // slot and frees the one consumed before it.
 //
-// Stage layout in LDS: each load instruction of a wave lands 1 KB = four 256-byte rows; lane s
-// fetches 16-byte piece s / 4 of row s % 4, so the group holds piece-major data
-// (piece g of row r at g * 64 + r * 16).  A wave reading A-operands (lane = row) then touches
-// 16 consecutive bytes per row and groups 1088 bytes apart: conflict-free, and the eight
-// k-steps are plain immediate offsets (128 bytes apart).
+// Stage layout in LDS: each load instruction of a wave lands 1 KB = R = four 256-byte rows (d =
+// 128) or eight 128-byte rows (d = 64); lane s fetches 16-byte piece s / R of row s % R, so the
+// group holds piece-major data (piece g of row r at (g R + r) * 16).  A wave reading A-operands
+// (lane = row) then touches 16 consecutive bytes per row and groups 1024 + 16 R bytes apart: any
+// sixteen consecutive lanes cover all banks once, and the k-steps are plain immediate offsets
+// (32 R bytes apart).
 //
 // Per stage a wave runs 2 CT tiles of 32x32, (rt0,ct0) ... (rt0,ct CT-1) (rt1,ct0) ...,
 // software-pipelined: the MFMA chain of a tile is issued interleaved, two logits per MFMA, with
@@ -145,18 +153,26 @@ __global__ __launch_bounds__(kBiasThreads) void score_bias_kernel(KParams kp, in
 //            operands straight from memory (rare, slow, exact);
 //   sweep B  fma, exp2, add: the fma adds -L_row, read from LDS next to the stage's rows (a lane's
 //            16 rows of a tile are four float4 reads).
+// With d = 64 a tile is a chain of four MFMA instead of eight under the same 48 vector instructions:
+// the vector issue is the bound there (256 of 288 cycles a tile), and two pieces of the epilogue
+// ride on each MFMA.
 // Stages that touch masked entries (causal tail, ragged end, keys inside the window) run the same
 // pipeline with two more instructions per logit (a compare of the logit's constant row offset
 // with a per-lane limit, a select); only a sweep-A workgroup without a single clean stage, which
 // has no reference logit yet, takes a plain unpipelined path with a true running maximum.
-template <int MODE, int CT = 2, bool RING_RES = false>
+template <int D, int MODE, int CT = 2, bool RING_RES = false>
 __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     KParams kp, int n_units, int tiles_per_unit, int n_splits, int split_len, int q_splits, int mq_pad,
     const int64_t* __restrict__ row_off, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ Q, float2* __restrict__ rowstat,
     const float* __restrict__ bias, float* __restrict__ bias_out, float* __restrict__ scores,
     float* __restrict__ parts, int part_pitch) {
-  constexpr int NK = 8;  // k-steps per tile
+  using SG = StageGeom<D>;
+  constexpr int kRowBytes = SG::kRowBytes, kGroupRows = SG::kGroupRows, kGroupPitch = SG::kGroupPitch;
+  constexpr int kDataBytes = SG::kDataBytes, kStageBytes = SG::kStageBytes, kLoadsPerThread = SG::kLoadsPerThread;
+  constexpr int kStepBytes = SG::kStepBytes, kTileBytes = SG::kTileBytes;
+  constexpr int NK = D / 16;   // k-steps per tile
+  constexpr int NP = 8 / NK;   // epilogue pieces (two logits each) that ride on one k-step
   // MODE 2 = both sweeps in one launch for short units (one key split): the first pass is
   // MODE 0; the second keeps the same resident window rows and streams the keys again, leaving
   // one partial column sum per wave.  MODE 3 = the same for units of any length when W*G <= 512
@@ -186,8 +202,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   const int N = (int)(row_off[unit + 1] - row0);
   const int Mq = kp.Mq, W = kp.W, Gq = kp.G;
   const float c = kp.scale_log2;
-  const uint16_t* Ku = K + (size_t)row0 * kD;
-  const uint16_t* Qu = Q + (size_t)unit * Mq * kD;
+  const uint16_t* Ku = K + (size_t)row0 * D;
+  const uint16_t* Qu = Q + (size_t)unit * Mq * D;
 
   // ---- what this workgroup covers
   const uint16_t* res_ptr;
@@ -232,12 +248,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   }
 
   // ---- ring loads: thread t, piece j covers 16-byte LDS slot t + kThreads * j of the stage:
-  //      row = 4 * (slot / 64) + slot % 4, 16-byte piece = (slot % 64) / 4
+  //      row = kGroupRows * (slot / 64) + slot % kGroupRows, 16-byte piece = (slot % 64) / kGroupRows
   const __amdgpu_buffer_rsrc_t rsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(str_ptr), 0,
                                         max(s_end, 0) * kRowBytes, 0x00020000);
-  // (load j of a wave fills 4-row group wv + kWaves * j: the same lane offset, 4 * kWaves rows on)
-  const int ld_voff = (wv * 4 + (lane & 3)) * kRowBytes + (lane >> 2) * 16;
+  // (load j of a wave fills group wv + kWaves * j: the same lane offset, kWaves KB of rows on)
+  const int ld_voff = (wv * kGroupRows + lane % kGroupRows) * kRowBytes + (lane / kGroupRows) * 16;
   // sweep B: the -L_row of a stage's 64 rows is one more 256-byte load, taken in turn by the
   // waves (stage % kWaves), so every wave has at most one extra load in flight
   const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -260,7 +276,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const int grp = wv + kWaves * j;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           res_rsrc, (__attribute__((address_space(3))) void*)(slot + grp * kGroupPitch),
-          16, ld_voff, roff + j * (4 * kWaves * kRowBytes), 0, 0);
+          16, ld_voff, roff + j * (kWaves * 1024), 0, 0);
     }
   };
   auto issue_stage = [&](int stage) {  // ring stage >= kResStages; rows past s_end read as zero
@@ -278,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const int grp = wv + kWaves * j;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rsrc, (__attribute__((address_space(3))) void*)(slot + grp * kGroupPitch),
-          16, ld_voff, soff + j * (4 * kWaves * kRowBytes), 0, 0);
+          16, ld_voff, soff + j * (kWaves * 1024), 0, 0);
     }
   };
   // Once per ring stage g: this thread's pieces of stages g and g + 1 have landed when at most
@@ -306,11 +322,11 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
 
   // Operand rows of this lane inside a stage: row rt * 32 + c32 -> group, row-in-group
   // (lane (c32, h) holds row c32 of a 32-row tile, k-chunk h: the same layout for both operands)
-  const int a_off = (c32 >> 2) * kGroupPitch + (c32 & 3) * 16 + h * 64;
+  const int a_off = (c32 / kGroupRows) * kGroupPitch + (c32 % kGroupRows) * 16 + h * (kGroupRows * 16);
   auto load_a = [&](bf16x8(&a)[NK], const unsigned char* slot, int rt) {
-    const unsigned char* p = slot + rt * 8 * kGroupPitch + a_off;
+    const unsigned char* p = slot + rt * kTileBytes + a_off;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(p + ks * 128);
+    for (int ks = 0; ks < NK; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(p + ks * kStepBytes);
   };
 
   // ---- resident fragments: wave w owns ring stages [w CT / 2, (w + 1) CT / 2) of the resident
@@ -324,7 +340,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     for (int ct = 0; ct < CT; ++ct) {
       const int r = res_row_of(ct);
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
+      for (int ks = 0; ks < NK; ++ks) {
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(res_rsrc, r * kRowBytes + h * 16, ks * 32, 0);
         bres[ct][ks] = __builtin_bit_cast(bf16x8, v);
       }
@@ -489,7 +505,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     const int d = mask_d(ct_old, trow_old);
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
-      piece(masked, acc_old, nl_old, ct_old, ks, d);
+#pragma unroll
+      for (int e = 0; e < NP; ++e) piece(masked, acc_old, nl_old, ct_old, ks * NP + e, d);
       acc_new = (ks == 0)
                     ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bres[ct_new][0], f32x16{0}, 0, 0, 0)
                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], bres[ct_new][ks], acc_new, 0, 0, 0);
@@ -511,7 +528,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) asm volatile("" ::"v"(bres[ct][ks]));
+    for (int ks = 0; ks < NK; ++ks) asm volatile("" ::"v"(bres[ct][ks]));
   // Stream stage `it` is ring stage kResStages + it.  Being one stage ahead (see ring_sync) lets
   // a wave fetch the next stage's first operands from LDS while it is still busy with this one.
   auto stage_sync = [&](int it) { ring_sync(kResStages + it); };
@@ -617,13 +634,14 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     const int d = mask_d(ct_old, trow_old);
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
-      piece(masked, acc_old, nl, ct_old, ks, d);
+#pragma unroll
+      for (int e = 0; e < NP; ++e) piece(masked, acc_old, nl, ct_old, ks * NP + e, d);
       acc_new = (ks == 0)
                     ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], bres[ct_new][0], f32x16{0}, 0, 0, 0)
                     : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], bres[ct_new][ks], acc_new, 0, 0, 0);
-      if (kA) a[ks] = *reinterpret_cast<const bf16x8*>(next_rows + ks * 128);
-      if (kNl && (ks & 1)) {
-        const int g = ks >> 1;
+      if (kA) a[ks] = *reinterpret_cast<const bf16x8*>(next_rows + ks * kStepBytes);
+      if (kNl && ((ks + 1) * NP) % 2 == 0) {
+        const int g = (ks + 1) * NP / 2 - 1;
         const bf16x8 raw = *reinterpret_cast<const bf16x8*>(next_nl + (g * 8 + h * 4) * 4);
         const f32x4 v = __builtin_bit_cast(f32x4, raw);
         nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
@@ -658,7 +676,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       fused(masked, acc1, a0, 1, acc0, nl0, 0, base);
       fused(masked, acc0, a0, 2, acc1, nl0, 1, base);
       // a0 <- tile row 1 behind the last chain of tile row 0
-      fused_refill(masked, yes, no, acc1, a0, 3, acc0, nl0, 2, base, cur + 8 * kGroupPitch + a_off, nullptr);
+      fused_refill(masked, yes, no, acc1, a0, 3, acc0, nl0, 2, base, cur + kTileBytes + a_off, nullptr);
       // the last epilogue of tile row 0 hands its -L registers over to tile row 1
       fused_refill(masked, no, yes, acc0, a0, 0, acc1, nl0, 3, base, nullptr, cur + kDataBytes + 32 * 4);
       fused(masked, acc1, a0, 1, acc0, nl0, 0, base + 32);
@@ -734,7 +752,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
           const int trow0 = s_begin + stg * kStageRows + rt * 32;
           if (trow0 >= s_end) continue;
 #pragma unroll
-          for (int ks = 0; ks < 8; ++ks) {
+          for (int ks = 0; ks < NK; ++ks) {
             const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (trow0 + c32) * kRowBytes + h * 16, ks * 32, 0);
             a0[ks] = __builtin_bit_cast(bf16x8, v);
           }
@@ -818,7 +836,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const int d = mask_d2(ct_old, key_old);
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks) {
-        piece2(masked, acc_old, ct_old, ks, d);
+#pragma unroll
+        for (int e = 0; e < NP; ++e) piece2(masked, acc_old, ct_old, ks * NP + e, d);
         acc_new = (ks == 0)
                       ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(bres[ct_new][0], a[0], f32x16{0}, 0, 0, 0)
                       : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bres[ct_new][ks], a[ks], acc_new, 0, 0, 0);
@@ -1052,71 +1071,67 @@ hipError_t launch_fma(const KParams& kp, const Batch& b, const Workspace& wl, ch
 
 }  // namespace
 
-bool score_uses_mfma(const KParams& kp) {
-  return kp.dtype == CASK_BF16 && kp.d == 128;
+bool score_uses_mfma(const KParams& kp) { return kp.dtype == CASK_BF16; }
+
+namespace {
+// One instance of the scoring kernel on a stream; raises its LDS limit on the first launch.
+template <int D, int MODE, int CT, bool RING_RES>
+hipError_t launch_sweep(int blocks, size_t lds, hipStream_t st, const KParams& kp, int n_units, int tiles,
+                        int n_splits, int split_len, int q_splits, int mq_pad, const int64_t* row_off,
+                        const void* K, const void* Q, float2* rowstat, const float* bias, float* bias_out,
+                        float* scores, float* parts, int parts_pitch) {
+  static LdsLimitOnce lim;
+  const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<D, MODE, CT, RING_RES>), 160 * 1024);
+  if (e != hipSuccess) return e;
+  score_mfma_kernel<D, MODE, CT, RING_RES><<<dim3(blocks), dim3(kThreads), lds, st>>>(
+      kp, n_units, tiles, n_splits, split_len, q_splits, mq_pad, row_off, static_cast<const uint16_t*>(K),
+      static_cast<const uint16_t*>(Q), rowstat, bias, bias_out, scores, parts, parts_pitch);
+  return hipSuccess;
 }
 
-hipError_t launch_score(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
-                        float* scores, hipStream_t st, hipEvent_t between) {
-  if (!score_uses_mfma(kp)) {
-    if (kp.dtype == CASK_F32)
-      return kp.d == 64 ? launch_fma<float, 64>(kp, b, wl, ws, scores, st, between)
-                        : launch_fma<float, 128>(kp, b, wl, ws, scores, st, between);
-    return kp.d == 64 ? launch_fma<uint16_t, 64>(kp, b, wl, ws, scores, st, between)
-                      : launch_fma<uint16_t, 128>(kp, b, wl, ws, scores, st, between);
-  }
+template <int D>
+hipError_t launch_score_mfma(const KParams& kp, const Batch& b, const Workspace& wl, char* ws, float* scores,
+                             hipStream_t st, hipEvent_t between) {
   float2* rowstat = reinterpret_cast<float2*>(ws + wl.rowstat);
   float* bias = reinterpret_cast<float*>(ws + wl.bias);
   const int units8 = (b.n_units + 7) / 8 * 8;
-  const uint16_t* K = static_cast<const uint16_t*>(b.K);
-  const uint16_t* Q = static_cast<const uint16_t*>(b.Q);
-  const size_t ldsA = (size_t)kDepth * kStageBytes;
-  const size_t ldsB = ldsA;
-  static LdsLimitOnce limA, limB;
-  hipError_t e = limA.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<0>), 160 * 1024);
-  if (e == hipSuccess) e = limB.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<1>), 160 * 1024);
-  if (e != hipSuccess) return e;
-  const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
+  const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes;
   // W*G <= 512 (one wide row block per unit, eight stream stages per workgroup of sweep B): the
   // resident rows come through the ring (measured: both sweeps 3 - 4 % faster on the Llama-shaped
   // batch, up to 4 % slower at W*G = 896)
   const bool ring_res = kp.Mq <= 2 * kResRows;
-  if (wl.wide_rows) {
-    static LdsLimitOnce limAw, limAr;
-    e = ring_res ? limAr.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<0, 4, true>), 160 * 1024)
-                 : limAw.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<0, 4>), 160 * 1024);
-    if (e != hipSuccess) return e;
-    const int tilesAw = (kp.Mq + 2 * kResRows - 1) / (2 * kResRows) * wl.n_splits;
-    auto kern = ring_res ? &score_mfma_kernel<0, 4, true> : &score_mfma_kernel<0, 4>;
-    kern<<<dim3(units8 * tilesAw), dim3(kThreads), ldsA, st>>>(
-        kp, b.n_units, tilesAw, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad, b.row_off, K, Q, rowstat,
-        nullptr, bias, scores, nullptr, 0);
-  } else {
-    const int tilesA = qblocks * wl.n_splits;
-    score_mfma_kernel<0><<<dim3(units8 * tilesA), dim3(kThreads), ldsA, st>>>(
-        kp, b.n_units, tilesA, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad, b.row_off, K, Q, rowstat,
-        nullptr, bias, scores, nullptr, 0);
-  }
+  auto sweep_a = [&](auto kern, int block_rows) {
+    const int tiles = (kp.Mq + block_rows - 1) / block_rows * wl.n_splits;
+    return kern(units8 * tiles, lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
+                b.row_off, b.K, b.Q, rowstat, nullptr, bias, scores, nullptr, 0);
+  };
+  auto sweep_b = [&](auto kern, int block_rows) {
+    const int tiles = (b.max_unit_len + block_rows - 1) / block_rows * wl.q_splits;
+    return kern(units8 * tiles, lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
+                b.row_off, b.K, b.Q, rowstat, bias, nullptr, scores, nullptr, 0);
+  };
+  hipError_t e;
+  if (!wl.wide_rows) e = sweep_a(&launch_sweep<D, 0, 2, false>, kResRows);
+  else if (ring_res) e = sweep_a(&launch_sweep<D, 0, 4, true>, 2 * kResRows);
+  else e = sweep_a(&launch_sweep<D, 0, 4, false>, 2 * kResRows);
+  if (e != hipSuccess) return e;
   if (between) (void)hipEventRecord(between, st);  // right behind sweep A: the stage is that kernel alone
   if (wl.n_splits > 1)  // with one split sweep A has written -L itself
     score_bias_kernel<<<dim3(b.n_units), dim3(kBiasThreads), 0, st>>>(kp, wl.n_splits, wl.mq_pad, rowstat, bias);
-  if (wl.wide_cols) {
-    static LdsLimitOnce limBw, limBr;
-    e = ring_res ? limBr.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<1, 4, true>), 160 * 1024)
-                 : limBw.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<1, 4>), 160 * 1024);
-    if (e != hipSuccess) return e;
-    const int tilesBw = (b.max_unit_len + 2 * kResRows - 1) / (2 * kResRows) * wl.q_splits;
-    auto kern = ring_res ? &score_mfma_kernel<1, 4, true> : &score_mfma_kernel<1, 4>;
-    kern<<<dim3(units8 * tilesBw), dim3(kThreads), ldsB, st>>>(
-        kp, b.n_units, tilesBw, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad, b.row_off, K, Q, rowstat,
-        bias, nullptr, scores, nullptr, 0);
-  } else {
-    const int tilesB = (b.max_unit_len + kResRows - 1) / kResRows * wl.q_splits;
-    score_mfma_kernel<1><<<dim3(units8 * tilesB), dim3(kThreads), ldsB, st>>>(
-        kp, b.n_units, tilesB, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad, b.row_off, K, Q, rowstat,
-        bias, nullptr, scores, nullptr, 0);
-  }
-  return hipGetLastError();
+  if (!wl.wide_cols) e = sweep_b(&launch_sweep<D, 1, 2, false>, kResRows);
+  else if (ring_res) e = sweep_b(&launch_sweep<D, 1, 4, true>, 2 * kResRows);
+  else e = sweep_b(&launch_sweep<D, 1, 4, false>, 2 * kResRows);
+  return e != hipSuccess ? e : hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_score(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
+                        float* scores, hipStream_t st, hipEvent_t between) {
+  if (kp.dtype == CASK_F32)
+    return kp.d == 64 ? launch_fma<float, 64>(kp, b, wl, ws, scores, st, between)
+                      : launch_fma<float, 128>(kp, b, wl, ws, scores, st, between);
+  return kp.d == 64 ? launch_score_mfma<64>(kp, b, wl, ws, scores, st, between)
+                    : launch_score_mfma<128>(kp, b, wl, ws, scores, st, between);
 }
 
 namespace {
@@ -1146,16 +1161,30 @@ bool score_fused_fits(const KParams& kp, const Batch& b) {
   return (int64_t)b.n_units * row_blocks >= 1024;
 }
 
+namespace {
+template <int D>
+hipError_t launch_fused_sweeps(const KParams& kp, const Batch& b, const Workspace& wl, float* scores, hipStream_t st) {
+  const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes + kResRows * sizeof(float) + 4 * kWaves * 64 * sizeof(float);
+  const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
+  const int whole = (b.max_unit_len + kStageRows - 1) / kStageRows * kStageRows;
+  return launch_sweep<D, 3, 2, false>((b.n_units + 7) / 8 * 8 * qblocks, lds, st, kp, b.n_units, qblocks, 1, whole, 1,
+                                      wl.mq_pad, b.row_off, b.K, b.Q, nullptr, nullptr, nullptr, scores, nullptr, 0);
+}
+
+template <int D>
+hipError_t launch_sweeps_to_parts(const KParams& kp, const Batch& b, const Workspace& wl, float* parts, hipStream_t st) {
+  const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes + kResRows * sizeof(float);
+  const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
+  return launch_sweep<D, 2, 2, false>((b.n_units + 7) / 8 * 8 * qblocks, lds, st, kp, b.n_units, qblocks, 1, wl.split_len,
+                                      1, wl.mq_pad, b.row_off, b.K, b.Q, nullptr, nullptr, nullptr, nullptr, parts,
+                                      wl.parts_pitch);
+}
+}  // namespace
+
 hipError_t launch_score_fused(const KParams& kp, const Batch& b, const Workspace& wl, float* scores,
                               hipStream_t st) {
   if (!score_fused_fits(kp, b)) return hipErrorInvalidValue;
-  const size_t lds = (size_t)kDepth * kStageBytes + kResRows * sizeof(float) + 4 * kWaves * 64 * sizeof(float);
-  static LdsLimitOnce lim;
-  const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<3>), 160 * 1024);
-  if (e != hipSuccess) return e;
-  const int units8 = (b.n_units + 7) / 8 * 8;
-  const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
-  if (qblocks == 2) {
+  if (kp.Mq > kResRows) {
     // two workgroups add onto each key's score; scores is 4-byte aligned only: float4 stores need 16
     const bool al16 = (reinterpret_cast<uintptr_t>(scores) & 15u) == 0;
     if (al16) {
@@ -1166,11 +1195,9 @@ hipError_t launch_score_fused(const KParams& kp, const Batch& b, const Workspace
       return hipErrorInvalidValue;
     }
   }
-  const int whole = (b.max_unit_len + kStageRows - 1) / kStageRows * kStageRows;
-  score_mfma_kernel<3><<<dim3(units8 * qblocks), dim3(kThreads), lds, st>>>(
-      kp, b.n_units, qblocks, 1, whole, 1, wl.mq_pad, b.row_off, static_cast<const uint16_t*>(b.K),
-      static_cast<const uint16_t*>(b.Q), nullptr, nullptr, nullptr, scores, nullptr, 0);
-  return hipGetLastError();
+  const hipError_t e = kp.d == 64 ? launch_fused_sweeps<64>(kp, b, wl, scores, st)
+                                  : launch_fused_sweeps<128>(kp, b, wl, scores, st);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 bool score_parts_fits(const KParams& kp, const Batch& b, const Workspace& wl) {
@@ -1183,17 +1210,10 @@ bool score_parts_fits(const KParams& kp, const Batch& b, const Workspace& wl) {
 hipError_t launch_score_parts(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
                               hipStream_t st) {
   if (!score_parts_fits(kp, b, wl)) return hipErrorInvalidValue;
-  const size_t lds = (size_t)kDepth * kStageBytes + kResRows * sizeof(float);
-  static LdsLimitOnce lim;
-  const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&score_mfma_kernel<2>), 160 * 1024);
-  if (e != hipSuccess) return e;
-  const int units8 = (b.n_units + 7) / 8 * 8;
-  const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
-  score_mfma_kernel<2><<<dim3(units8 * qblocks), dim3(kThreads), lds, st>>>(
-      kp, b.n_units, qblocks, 1, wl.split_len, 1, wl.mq_pad, b.row_off,
-      static_cast<const uint16_t*>(b.K), static_cast<const uint16_t*>(b.Q), nullptr, nullptr, nullptr,
-      nullptr, reinterpret_cast<float*>(ws + wl.parts), wl.parts_pitch);
-  return hipGetLastError();
+  float* parts = reinterpret_cast<float*>(ws + wl.parts);
+  const hipError_t e = kp.d == 64 ? launch_sweeps_to_parts<64>(kp, b, wl, parts, st)
+                                  : launch_sweeps_to_parts<128>(kp, b, wl, parts, st);
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace cask

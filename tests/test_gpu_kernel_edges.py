@@ -1,0 +1,51 @@
+"""GPU tests of single kernels at the sizes where their tiling can go wrong, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_2604_10900_amd as cask  # noqa: E402
+from oracle import ref  # noqa: E402
+from synth import caches  # noqa: E402
+from tests import parity  # noqa: E402
+
+W = caches.WORKLOADS
+B = cask.binding
+
+
+def _note(*a):
+    print(*a, flush=True)
+
+
+def _units(lens, prefixes, seed=3, **kw):
+    """A ragged batch, one generator group per unit."""
+    parts = [caches.make(caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=1, prefix=p, decode=n - p, wid=300 + i, **kw), seed=seed)
+             for i, (n, p) in enumerate(zip(lens, prefixes))]
+    row_off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+    return dict(K=torch.cat([c["K"] for c in parts]), V=torch.cat([c["V"] for c in parts]), Q=torch.cat([c["Q"] for c in parts]),
+                row_off=row_off, prefix_len=torch.tensor(prefixes, dtype=torch.int32))
+
+
+SCORE_FORMS = {"chosen": 0, "narrow": B.PATH_NARROW_ROWS, "wide": B.PATH_WIDE_ROWS | B.PATH_NO_FUSED_SWEEPS,
+               "one_launch": B.PATH_FORCE_FUSED_SWEEPS}
+
+
+@pytest.mark.parametrize("form", sorted(SCORE_FORMS))
+@pytest.mark.parametrize("G,Wn,causal,splits", [(4, 64, 1, 0), (7, 100, 1, 3), (1, 17, 1, 0), (4, 128, 0, 2)])
+def test_scores_with_64_channels(G, Wn, causal, splits, form):
+    """bf16 scores with d = 64 (four k-steps a tile): units of a window, a tile, a stage and a block of
+    rows and one more, in every form of the sweeps.  Bar: 1e-4 of the unit's largest score, as for
+    d = 128 (fp32 sums of 64 exact products, the same two-level row sums)."""
+    lens = [Wn, Wn + 1, 129, 256, 257, 1025, 1599, 4097]
+    pref = [0, 1, 0, 40, 100, 0, 333, 50]
+    c = _units(lens, pref, head_dim=64, q_per_kv=G, window=Wn)
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=G, window=Wn, causal=causal, budget=Wn + 60,
+                    path_flags=SCORE_FORMS[form], score_splits=splits)
+    row_off, _, K, _, Q = parity.host_arrays(c)
+    b = parity.to_device(c, p)
+    s = cask.score(b)
+    s2 = cask.score(b, torch.full_like(s, 7.0))
+    torch.cuda.synchronize()
+    assert torch.equal(s, s2)
+    _note(form, G, Wn, causal, "score error / max", parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off))
