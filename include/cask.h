@@ -119,7 +119,7 @@ enum {
   CASK_PATH_NO_FUSED_TAIL = 1,  /* short units: the general kernels instead of the one-launch tail */
   CASK_PATH_NO_FUSED_SCORE = 2, /* short units: two scoring launches instead of one */
   CASK_PATH_DEDUP_VECTOR = 4,   /* bf16 de-duplicated seeding on the vector kernel fp32 caches use */
-  CASK_PATH_ATTEND_VECTOR = 8,  /* bf16 cask_attend on the vector kernel fp32 caches use */
+  CASK_PATH_ATTEND_VECTOR = 8,  /* accepted, no effect (cask_attend has one kernel for every dtype) */
   CASK_PATH_NO_FUSED_SWEEPS = 16, /* many long units with W*G <= 512: two scoring launches instead of one */
   CASK_PATH_FORCE_FUSED_SWEEPS = 32, /* W*G <= 512: one scoring launch whatever the number of units */
   CASK_PATH_NARROW_ROWS = 64, /* both scoring sweeps: 64 resident rows per wave (256 per workgroup) whatever the shape */
@@ -291,13 +291,21 @@ int cask_group_diagnostics(const cask_params* params, const cask_batch* batch, c
  *   out   [n_units, G, d]               device, cache dtype (fp32 accumulation, rounded once)
  * All data pointers 16-byte aligned.  scale = softmax_scale, 1/sqrt(d) when that is <= 0.  Needs
  * no workspace.  Decoded tokens appended behind the compressed rows attend the same way (their
- * count is 1): pass the buffer with its row stride and the enlarged len.  bf16 caches run on
- * the matrix cores (CASK_PATH_ATTEND_VECTOR in path_flags sends them through the vector kernel
- * that serves fp32 caches, for comparisons).  (Graph capture: see the
+ * count is 1): pass the buffer with its row stride and the enlarged len.  (Graph capture: see the
  * note on LDS limits at the top of this header.) */
 int cask_attend(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
                 const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
                 int32_t count_pitch, void* out, void* hip_stream);
+
+/* cask_attend with a workspace: where few units hold many rows each, several workgroups share a
+ * unit and leave partial results in `ws` (device, 16-byte aligned) for a second launch to add.
+ * Same arguments and results otherwise (up to the order of the fp32 sums); a NULL or smaller
+ * workspace than cask_attend_workspace_bytes() gives cask_attend's single launch. */
+int cask_attend_ws(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
+                   const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
+                   int32_t count_pitch, void* out, void* ws, size_t ws_bytes, void* hip_stream);
+/* HOST: bytes cask_attend_ws makes use of; 0 where one workgroup per unit is the better choice. */
+size_t cask_attend_workspace_bytes(const cask_params* params, int32_t n_units, int32_t stride_rows);
 
 /* Measurement aid (not part of the method): per-stage timing of cask_compress with HIP
  * events recorded on the caller's stream between its kernels.  Stage order: 0 score sweep A

@@ -30,7 +30,8 @@ PATH_WIDE_ROWS = 128
 
 EXPORTS = ["cask_plan", "cask_workspace_bytes", "cask_score", "cask_prefix_evict",
            "cask_partition", "cask_consolidate", "cask_compress", "cask_compress_static", "cask_compress_step",
-           "cask_mass_diagnostics", "cask_group_diagnostics", "cask_attend", "cask_strerror",
+           "cask_mass_diagnostics", "cask_group_diagnostics", "cask_attend", "cask_attend_ws",
+           "cask_attend_workspace_bytes", "cask_strerror",
            "cask_timing_enable", "cask_timing_enable_stages", "cask_timing_read",
            "cask_probe_issue", "cask_probe_copy", "cask_probe_read"]
 STAGES = ["score_rows", "score_cols", "select", "index_roles", "similarity", "gather", "emit"]
@@ -110,7 +111,7 @@ def _env_int(name: str) -> int:
 def _env_path_flags() -> int:
     """Measurement switches of the Python layer (the library itself reads no environment):
     CASK_FUSED_TAIL=0, CASK_FUSED_SCORE=0, CASK_FUSED_SWEEPS=0, CASK_DEDUP_VECTOR=1,
-    CASK_ATTEND_VECTOR=1, CASK_NARROW_ROWS=1, CASK_WIDE_ROWS=1 set the matching PATH_* bit of every call made through this binding."""
+    CASK_NARROW_ROWS=1, CASK_WIDE_ROWS=1 set the matching PATH_* bit of every call made through this binding."""
     env = os.environ
     f = 0
     if env.get("CASK_FUSED_TAIL", "1")[:1] == "0":
@@ -121,8 +122,6 @@ def _env_path_flags() -> int:
         f |= PATH_NO_FUSED_SWEEPS
     if env.get("CASK_DEDUP_VECTOR", "0")[:1] == "1":
         f |= PATH_DEDUP_VECTOR
-    if env.get("CASK_ATTEND_VECTOR", "0")[:1] == "1":
-        f |= PATH_ATTEND_VECTOR
     if env.get("CASK_NARROW_ROWS", "0")[:1] == "1":
         f |= PATH_NARROW_ROWS
     if env.get("CASK_WIDE_ROWS", "0")[:1] == "1":
@@ -159,6 +158,8 @@ def load():
             "cask_mass_diagnostics": (C.c_int, [vp] * 8),
             "cask_group_diagnostics": (C.c_int, [vp, vp, vp, vp, vp, i32, vp, vp, vp]),
             "cask_attend": (C.c_int, [vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, vp]),
+            "cask_attend_ws": (C.c_int, [vp, i32, vp, vp, vp, i32, vp, vp, i32, vp, vp, sz, vp]),
+            "cask_attend_workspace_bytes": (sz, [vp, i32, i32]),
             "cask_strerror": (C.c_char_p, [C.c_int]),
             "cask_timing_enable": (C.c_int, [C.c_int]),
             "cask_timing_enable_stages": (C.c_int, [C.c_int, C.c_int]),
@@ -367,10 +368,12 @@ def attend(p: Params, Q: torch.Tensor, K_c: torch.Tensor, V_c: torch.Tensor, len
         assert count.dtype == torch.int32 and count.dim() == 2 and count.shape[0] == n_units and count.is_contiguous()
     if out is None:
         out = torch.empty_like(Q)
-    cp = p.c()
-    rc = load().cask_attend(C.byref(cp), C.c_int32(n_units), _dptr(Q), _dptr(K_c), _dptr(V_c),
-                            C.c_int32(K_c.shape[1]), _dptr(length), _dptr(count) if count is not None else None,
-                            C.c_int32(count.shape[1] if count is not None else 0), _dptr(out), _stream())
+    cp, lib = p.c(), load()
+    n_ws = lib.cask_attend_workspace_bytes(C.byref(cp), n_units, K_c.shape[1])
+    ws = torch.empty(n_ws, dtype=torch.uint8, device=Q.device) if n_ws else None
+    rc = lib.cask_attend_ws(C.byref(cp), n_units, _dptr(Q), _dptr(K_c), _dptr(V_c), K_c.shape[1], _dptr(length),
+                            _dptr(count), count.shape[1] if count is not None else 0, _dptr(out),
+                            _dptr(ws), n_ws, _stream())
     if rc:
         raise CaskError("cask_attend", rc)
     return out

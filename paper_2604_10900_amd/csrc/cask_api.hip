@@ -376,9 +376,9 @@ int cask_group_diagnostics(const cask_params* params, const cask_batch* batch, c
                                   lost_mass, static_cast<hipStream_t>(hip_stream)));
 }
 
-int cask_attend(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
-                const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
-                int32_t count_pitch, void* out, void* hip_stream) {
+static int attend_call(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
+                       const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
+                       int32_t count_pitch, void* out, void* ws, size_t ws_bytes, void* hip_stream) {
   KParams kp;
   int rc = resolve_params(params, &kp, false);
   if (rc) return rc;
@@ -387,10 +387,30 @@ int cask_attend(const cask_params* params, int32_t n_units, const void* Q, const
   if (!Q || !K_c || !V_c || !len || !out || stride_rows < 1) return CASK_EINVAL;
   if (count && count_pitch < 1) return CASK_EINVAL;
   if (((reinterpret_cast<uintptr_t>(Q) | reinterpret_cast<uintptr_t>(K_c) | reinterpret_cast<uintptr_t>(V_c) |
-        reinterpret_cast<uintptr_t>(out)) & 15u) != 0)
+        reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(ws)) & 15u) != 0)
     return CASK_EINVAL;
-  return dev_rc(launch_attend(kp, n_units, Q, K_c, V_c, stride_rows, len, count, count_pitch, out,
-                              static_cast<hipStream_t>(hip_stream)));
+  int splits = ws ? attend_splits(kp, n_units, stride_rows) : 1;
+  if (attend_part_bytes(kp, n_units, splits) > ws_bytes) splits = 1;
+  return dev_rc(launch_attend(kp, n_units, Q, K_c, V_c, stride_rows, len, count, count_pitch, out, splits,
+                              static_cast<float*>(ws), static_cast<hipStream_t>(hip_stream)));
+}
+
+int cask_attend(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
+                const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
+                int32_t count_pitch, void* out, void* hip_stream) {
+  return attend_call(params, n_units, Q, K_c, V_c, stride_rows, len, count, count_pitch, out, nullptr, 0, hip_stream);
+}
+
+int cask_attend_ws(const cask_params* params, int32_t n_units, const void* Q, const void* K_c,
+                   const void* V_c, int32_t stride_rows, const int32_t* len, const int32_t* count,
+                   int32_t count_pitch, void* out, void* ws, size_t ws_bytes, void* hip_stream) {
+  return attend_call(params, n_units, Q, K_c, V_c, stride_rows, len, count, count_pitch, out, ws, ws_bytes, hip_stream);
+}
+
+size_t cask_attend_workspace_bytes(const cask_params* params, int32_t n_units, int32_t stride_rows) {
+  KParams kp;
+  if (resolve_params(params, &kp, false) != CASK_OK || n_units < 1 || stride_rows < 1) return 0;
+  return attend_part_bytes(kp, n_units, attend_splits(kp, n_units, stride_rows));
 }
 
 int cask_compress(const cask_params* params, const cask_batch* batch, void* K_out, void* V_out,

@@ -4,7 +4,7 @@
 // which a fold of identical tokens is lossless).
 #include <hip/hip_runtime.h>
 
-#include <cstdlib>
+#include <type_traits>
 
 #include "cask.h"
 #include "cask_common.h"
@@ -13,307 +13,194 @@ namespace cask {
 
 namespace {
 
-constexpr int kAttThreads = 256;
-constexpr int kAttGroups = kAttThreads / 16;  // sixteen lanes per cache row
-constexpr int kAttHeads = 4;                  // query heads per pass over the cache
-constexpr int kAttAhead = 4;                  // rows a group has in flight
-constexpr float kNegInf = -__builtin_inff();
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// One workgroup per unit.  Sixteen lanes hold one cache row (D / 16 elements each), so a
-// workgroup reads sixteen rows per step, kAttAhead steps in flight; every group keeps an online
-// softmax (maximum, denominator, weighted value sum, in base-2 units) for up to kAttHeads query
-// heads over the rows it saw.  At the end groups 8-15 hand their state to groups 0-7 through
-// LDS, which merge it into their own, and the eight merged states are added in group order:
-// the same bits every run.  More query heads than kAttHeads take another pass over the cache
-// (served by the L2).
+constexpr float kNegInf = -__builtin_inff();
+constexpr int kAttHeads = 16;  // query heads per pass over the cache: the columns of a 16x16 product
+
+// Sizes that follow from the cache's element type and head dimension.
 template <typename T, int D>
-__global__ __launch_bounds__(kAttThreads) void attend_kernel(
-    KParams kp, const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
-    int stride, const int32_t* __restrict__ len, const int32_t* __restrict__ count,
-    int count_pitch, T* __restrict__ out) {
-  constexpr int EPL = D / 16;
-  constexpr int WORDS = EPL * sizeof(T) / 4;
-  struct alignas(WORDS * 4 > 16 ? 16 : WORDS * 4) Raw { uint32_t w[WORDS]; };
-  constexpr int kHalf = kAttGroups / 2;
-  __shared__ float red_m[kHalf][kAttHeads], red_l[kHalf][kAttHeads];
-  __shared__ float red_acc[kHalf][kAttHeads][D];
-  const int u = blockIdx.x, tid = threadIdx.x, grp = tid >> 4, gl = tid & 15;
-  int L = len[u];
-  L = L < 0 ? 0 : (L > stride ? stride : L);
+struct AttGeom {
+  static constexpr bool kBf16 = sizeof(T) == 2;
+  static constexpr int kTileRows = kBf16 ? 32 : 16;          // cache rows a wave takes at a time
+  static constexpr int kKeys = kTileRows / 4;                // of them per lane group (16 lanes)
+  static constexpr int kSub = kTileRows / 16;                // 16-row subtiles of the logit product
+  static constexpr int kSteps = D * (int)sizeof(T) / 64;     // 16-byte pieces of a key row per lane
+  static constexpr int EPV = (kBf16 && D == 128) ? 8 : 4;    // elements of a value row per lane and load
+  static constexpr int kValLoads = D / (16 * EPV);           // loads per value row
+  static constexpr int kBlocks = D / 16;                     // 16-channel blocks of the value product
+  typedef typename std::conditional<EPV * sizeof(T) == 16, u32x4, u32x2>::type ValVec;
+  // channel of row m of block b of the value product
+  __device__ static int channel(int b, int m) { return (b / EPV) * (16 * EPV) + m * EPV + b % EPV; }
+};
+
+// A workgroup takes the tiles of one unit (or, with `splits` > 1, every splits-th round of them),
+// dealt to its waves round robin.  Per tile two products on 16x16 matrix tiles:
+//   logits   S[key][head]     = K_tile . Q^T       (lane: key or head = lane % 16, 16 bytes of channels)
+//   values   O[channel][head] += V_tile^T . P      (lane: channel or head = lane % 16, keys of group lane / 16)
+// A lane ends the first product with one head's logits of the kKeys keys 16 t + 4 (lane / 16) + r,
+// takes the online-softmax step on them and holds its weights as the second product's operand as
+// they stand.  The values need no turning round either: lane (m, group) loads its 16-channel-wide
+// share of the value rows of its group's own keys, and the product's channel rows are numbered so
+// that row m of block b is the channel the lane already holds (AttGeom::channel): an 8-key operand
+// is put together from two rows' words by one byte permutation per word.  Nothing but a tile's 32
+// biases passes through LDS inside the loop, and nothing there is a workgroup barrier.
+// (The former kernel wrote the value rows transposed to LDS two bytes at a time, 64 stores per
+// lane and tile, and used 8 columns of 32x32 products.)
+// bf16 weights enter as two terms, p = hi + lo (lo the rounded remainder: 2^-17 in all).
+//
+// The first tile's rows are requested before the unit's length arrives (any row below `stride`
+// is readable; rows past the end get weight zero and zeroed values); after that the next tile's keys are requested behind the first product, its values behind the second.
+// At the end the waves' states are merged in wave order (with splits: written out unnormalised for
+// attend_combine_kernel, which adds them in split order): the same bits every run.
+template <typename T, int D, int WAVES, bool NT>
+__global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attend_kernel(
+    KParams kp, const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc, int stride,
+    const int32_t* __restrict__ len, const int32_t* __restrict__ count, int count_pitch, T* __restrict__ out,
+    int splits, float* __restrict__ part) {
+  using A = AttGeom<T, D>;
+  typedef typename A::ValVec ValVec;
+  constexpr int TR = A::kTileRows, KEYS = A::kKeys, SUB = A::kSub, KS = A::kSteps, NB = A::kBlocks, EPV = A::EPV, NV = A::kValLoads;
+  constexpr int kAccPitch = D + 4;
+  constexpr int ROWB = D * (int)sizeof(T);
+  constexpr int kAux = NT ? 2 : 0;  // cache policy of the row loads: non-temporal or default
+  extern __shared__ __align__(16) unsigned char att_lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int u = blockIdx.x / splits, sp = blockIdx.x % splits;
   const int G = kp.G;
+  const int heads = G < kAttHeads ? G : kAttHeads;
+  float* bias_s = reinterpret_cast<float*>(att_lds) + wv * 32;
+  float* st_m = reinterpret_cast<float*>(att_lds) + WAVES * 32;  // [WAVES][16]
+  float* st_l = st_m + WAVES * kAttHeads;
+  float* st_acc = st_l + WAVES * kAttHeads;                      // [WAVES][heads][kAccPitch]
   const T* Ku = Kc + (size_t)u * stride * D;
   const T* Vu = Vc + (size_t)u * stride * D;
   const int32_t* cu = count ? count + (size_t)u * count_pitch : nullptr;
   const float c = kp.scale_log2;  // softmax scale * log2(e)
+  const int step = splits * WAVES;
+  const int first = sp * WAVES + wv;  // the wave's first tile
+
+  u32x4 ka[SUB][KS];
+  ValVec va[KEYS][NV];
+  int cn = 1;
+  // A tile's rows through a descriptor of their own that ends with the unit (`rows` of it): rows past
+  // the end read as zero, tiles past the end touch no memory, and a lane needs one 32-bit offset
+  // for all of its loads, however long the unit.
+  auto tile_rsrc = [&](const T* base, int t, int rows) {
+    const int left = rows - t * TR;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + (size_t)(left > 0 ? t * TR : 0) * D), 0,
+                                             (left > TR ? TR : (left > 0 ? left : 0)) * ROWB, 0x00020000);
+  };
+  const int k_off = l16 * ROWB + g * 16, v_off = g * 4 * ROWB + l16 * (EPV * (int)sizeof(T));
+  auto load_keys = [&](int t, int rows) {
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(Ku, t, rows);
+#pragma unroll
+    for (int y = 0; y < SUB; ++y)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        ka[y][ks] = __builtin_amdgcn_raw_buffer_load_b128(rs, k_off + ks * 64, y * 16 * ROWB, kAux);
+    if (cu) {
+      const int r = t * TR + (lane & (TR - 1));
+      cn = cu[min(r, count_pitch - 1)];
+      if (r >= count_pitch) cn = 1;  // rows behind the counted ones stand for themselves
+    }
+  };
+  auto load_values = [&](int t, int rows) {
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc(Vu, t, rows);
+#pragma unroll
+    for (int j = 0; j < KEYS; ++j)
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        const int at = (j & 3) * ROWB + q * (16 * EPV * (int)sizeof(T)), sub = (j >> 2) * 16 * ROWB;
+        if constexpr (sizeof(ValVec) == 16) va[j][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, v_off + at, sub, kAux);
+        else va[j][q] = __builtin_amdgcn_raw_buffer_load_b64(rs, v_off + at, sub, kAux);
+      }
+  };
 
   for (int g0 = 0; g0 < G; g0 += kAttHeads) {
-    float q[kAttHeads][EPL];
-#pragma unroll
-    for (int h = 0; h < kAttHeads; ++h) {
-      Raw qr;
-#pragma unroll
-      for (int w = 0; w < WORDS; ++w) qr.w[w] = 0u;
-      if (g0 + h < G) qr = *reinterpret_cast<const Raw*>(Q + ((size_t)u * G + g0 + h) * D + gl * EPL);
-      const T* qp = reinterpret_cast<const T*>(&qr);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) q[h][e] = Elem<T>::load(qp + e) * c;  // the scale rides on q
-    }
-    float m[kAttHeads], l[kAttHeads], acc[kAttHeads][EPL];
-#pragma unroll
-    for (int h = 0; h < kAttHeads; ++h) {
-      m[h] = kNegInf;
-      l[h] = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[h][e] = 0.f;
-    }
-    for (int t0 = grp; t0 < L; t0 += kAttGroups * kAttAhead) {
-      Raw kr[kAttAhead], vr[kAttAhead];
-      int cn[kAttAhead];
-#pragma unroll
-      for (int a = 0; a < kAttAhead; ++a) {  // clamped, not branched: all loads in flight together
-        const int t = min(t0 + a * kAttGroups, L - 1);
-        kr[a] = *reinterpret_cast<const Raw*>(Ku + (size_t)t * D + gl * EPL);
-        vr[a] = *reinterpret_cast<const Raw*>(Vu + (size_t)t * D + gl * EPL);
-        cn[a] = cu ? cu[min(t, count_pitch - 1)] : 1;
-        if (t >= count_pitch) cn[a] = 1;
-      }
-#pragma unroll
-      for (int a = 0; a < kAttAhead; ++a) {
-        if (t0 + a * kAttGroups < L) {  // the same for all sixteen lanes of the group
-          const T* kp_ = reinterpret_cast<const T*>(&kr[a]);
-          const T* vp_ = reinterpret_cast<const T*>(&vr[a]);
-          float kf[EPL], vf[EPL];
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            kf[e] = Elem<T>::load(kp_ + e);
-            vf[e] = Elem<T>::load(vp_ + e);
-          }
-          const float bias = cn[a] > 1 ? __log2f((float)cn[a]) : 0.f;
-#pragma unroll
-          for (int h = 0; h < kAttHeads; ++h) {
-            float dot = 0.f;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) dot = __builtin_fmaf(q[h][e], kf[e], dot);
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
-            const float x = dot + bias;
-            const float mn = fmaxf(m[h], x);
-            const float fa = __builtin_amdgcn_exp2f(m[h] - mn);  // exp2(-inf) = 0 on the first row
-            const float fp = __builtin_amdgcn_exp2f(x - mn);
-            l[h] = l[h] * fa + fp;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[h][e] = acc[h][e] * fa + fp * vf[e];
-            m[h] = mn;
-          }
-        }
-      }
-    }
-    auto put = [&](int slot) {
-#pragma unroll
-      for (int h = 0; h < kAttHeads; ++h) {
-        if (gl == 0) {
-          red_m[slot][h] = m[h];
-          red_l[slot][h] = l[h];
-        }
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) red_acc[slot][h][gl * EPL + e] = acc[h][e];
-      }
-    };
-    if (grp >= kHalf) put(grp - kHalf);
-    __syncthreads();
-    if (grp < kHalf) {  // merge the partner group's state into this one
-#pragma unroll
-      for (int h = 0; h < kAttHeads; ++h) {
-        const float m2 = red_m[grp][h], l2 = red_l[grp][h];
-        const float mn = fmaxf(m[h], m2);
-        const float f1 = m[h] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m[h] - mn);
-        const float f2 = m2 == kNegInf ? 0.f : __builtin_amdgcn_exp2f(m2 - mn);
-        l[h] = l[h] * f1 + l2 * f2;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[h][e] = acc[h][e] * f1 + red_acc[grp][h][gl * EPL + e] * f2;
-        m[h] = mn;
-      }
-    }
-    __syncthreads();
-    if (grp < kHalf) put(grp);
-    __syncthreads();
-    for (int o = tid; o < kAttHeads * D; o += kAttThreads) {
-      const int h = o / D, ch = o % D;
-      if (g0 + h >= G) continue;
-      float top = kNegInf;
-      for (int g = 0; g < kHalf; ++g) top = fmaxf(top, red_m[g][h]);
-      float num = 0.f, den = 0.f;
-      for (int g = 0; g < kHalf; ++g) {  // group order: the same bits every run
-        const float f = red_m[g][h] == kNegInf ? 0.f : __builtin_amdgcn_exp2f(red_m[g][h] - top);
-        den = __builtin_fmaf(red_l[g][h], f, den);
-        num = __builtin_fmaf(red_acc[g][h][ch], f, num);
-      }
-      Elem<T>::store(out + ((size_t)u * G + g0 + h) * D + ch, den > 0.f ? num / den : 0.f);
-    }
-    __syncthreads();
-  }
-}
-
-
-// ------------------------------------------------------------------ bf16 path: logits on MFMA
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// One workgroup per unit, one tile of 32 cache rows per wave and step, tiles dealt to the waves
-// round robin.  Per tile, two MFMA products with the head dimension, then the keys, contracted:
-//   logits   S[key][head]  = K_tile (32 x D) . Q^T (D x up to HP heads, zero columns beyond);
-//            the two lane halves hold the two halves of the head dimension, in the same order
-//            for keys and queries,
-//   values   O[dim][head] += V_tile^T (D x 32) . P (32 x heads), 32 dims per product.
-// The lane pair of a head column holds that head's 32 logits in registers and takes the block
-// step of the online softmax there (running maximum, correction factor, weights); the weights,
-// each split into two bf16 terms, are the second product's operand as they stand, because the
-// order in which a lane holds its keys is a permutation the value operand simply repeats.  The
-// query operand, the same for every wave and tile, waits in LDS.  The value rows
-// reach their operand layout (a lane: 8 keys of one dim) through a wave-private LDS area,
-// written transposed 2 bytes at a time and read back 16 bytes at a time.  The result columns of
-// a head live in the same lanes as its softmax state, so nothing but the value rows crosses
-// lanes inside the tile loop, and nothing there is a workgroup barrier.  The key rows of the
-// next tile are requested as soon as the first product has consumed this tile's, the value rows
-// as soon as they are in LDS, so a wave always has a tile of loads in flight.  At the end the
-// waves' states are merged in wave order: the same bits every run.
-template <int D>
-constexpr int att_vt_bytes() { return D * 64 + (D / 4) * 16; }  // [dim][32 keys] bf16, 16 B pad per 4 dims
-template <int D, int HP, int WAVES>
-constexpr int att_lds_bytes() {
-  return WAVES * att_vt_bytes<D>() + WAVES * 32 * 4 + 2 * WAVES * HP * 4 + (D / 16) * 64 * 16;
-}
-
-template <int D, int HP, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attend_mfma_kernel(
-    KParams kp, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
-    const uint16_t* __restrict__ Vc, int stride, const int32_t* __restrict__ len,
-    const int32_t* __restrict__ count, int count_pitch, uint16_t* __restrict__ out) {
-  constexpr int KS = D / 16;     // k-steps of the logit product
-  constexpr int NB = D / 32;     // 32-dim blocks of the value product
-  constexpr int LPR = D / 8;     // lanes per value row
-  constexpr int GPW = 64 / LPR;  // value rows one load instruction of a wave covers
-  constexpr int RPG = 32 / GPW;  // value rows per lane group and tile
-  constexpr int kVt = att_vt_bytes<D>();
-  static_assert(HP * D * 4 <= kVt, "a wave's final state reuses its value area");
-  extern __shared__ __align__(16) unsigned char att_lds[];
-  const int u = blockIdx.x, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
-  const int c32 = lane & 31, hh = lane >> 5;
-  const int g = lane / LPR, gl = lane % LPR;
-  unsigned char* vt = att_lds + wv * kVt;
-  float* bias_s = reinterpret_cast<float*>(att_lds + WAVES * kVt) + wv * 32;
-  float* st_m = reinterpret_cast<float*>(att_lds + WAVES * kVt) + WAVES * 32;  // [WAVES][HP]
-  float* st_l = st_m + WAVES * HP;
-  u32x4* q_s = reinterpret_cast<u32x4*>(st_l + WAVES * HP);  // [KS][64]: the query operand, lane by lane
-  int L = len[u];
-  L = L < 0 ? 0 : (L > stride ? stride : L);
-  const int n_tiles = (L + 31) >> 5;
-  const int G = kp.G;
-  const uint16_t* Ku = Kc + (size_t)u * stride * D;
-  const uint16_t* Vu = Vc + (size_t)u * stride * D;
-  const int32_t* cu = count ? count + (size_t)u * count_pitch : nullptr;
-  const float c = kp.scale_log2;  // softmax scale * log2(e)
-  const int last = L > 0 ? L - 1 : 0;
-  // Value area: dim x at byte x * 64 + (x / 4) * 16, key slots of 2 bytes inside.
-  const uint32_t vt_wr = gl * (8 * 64 + 2 * 16);
-  const uint32_t vt_rd = c32 * 64 + (c32 >> 2) * 16 + hh * 16;
-
-  for (int g0 = 0; g0 < G; g0 += HP) {
-    if (wv == 0) {  // the query operand is the same for every wave and tile: it waits in LDS
-      const bool head = c32 < HP && g0 + c32 < G;
-      const uint16_t* qp = Q + ((size_t)u * G + (head ? g0 + c32 : 0)) * D + hh * (D / 2);
+    load_keys(first, stride);
+    load_values(first, stride);
+    // the query operand: head l16, the same channels in the same order as the keys
+    u32x4 q[KS];
+    {
+      const bool head = g0 + l16 < G;
+      const T* qp = Q + ((size_t)u * G + (head ? g0 + l16 : 0)) * D;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        u32x4 qv = *reinterpret_cast<const u32x4*>(qp + ks * 8);
-        if (!head) qv = u32x4{0u, 0u, 0u, 0u};
-        q_s[ks * 64 + lane] = qv;
+        q[ks] = *reinterpret_cast<const u32x4*>(qp + (ks * 4 + g) * (16 / sizeof(T)));
+        if (!head) q[ks] = u32x4{0u, 0u, 0u, 0u};
       }
     }
-    asm volatile("" ::: "memory");
-    __syncthreads();
-    float m_run = kNegInf, l_run = 0.f;  // of head c32, over the keys this lane has seen
-    f32x16 acc[NB];                      // acc[b][r] = O[dim b*32 + (r/4)*8 + hh*4 + r%4][head c32]
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x16{0};
+    int L = len[u];
+    L = L < 0 ? 0 : (L > stride ? stride : L);
+    const int n_tiles = (L + TR - 1) / TR;
 
-    u32x4 ka[KS], va[RPG];
-    int cn;
-    // Rows past the end are clamped to the last row (never branched over: every load is in
-    // flight at once); past the last tile all lanes read that one row.
-    auto load_keys = [&](int t) {
-      const int r = min(t * 32 + c32, last);
+    float m_run = kNegInf, l_run = 0.f;  // of head l16, l_run over the keys of this lane
+    f32x4 acc[NB];                       // acc[b][r] = O[channel(b, 4 g + r)][head l16]
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        ka[ks] = *reinterpret_cast<const u32x4*>(Ku + (size_t)r * D + hh * (D / 2) + ks * 8);
-      cn = cu ? cu[min(r, count_pitch - 1)] : 1;
-      if (r >= count_pitch) cn = 1;  // rows behind the counted ones stand for themselves
-    };
-    auto load_values = [&](int t) {
-#pragma unroll
-      for (int j = 0; j < RPG; ++j) {
-        const int r = min(t * 32 + j * GPW + g, last);
-        va[j] = *reinterpret_cast<const u32x4*>(Vu + (size_t)r * D + gl * 8);
+    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int t = first; t < n_tiles; t += step) {
+      const bool partial = t * TR + TR > L;
+      if (cu || partial) {  // bias of a row of the tile: log2(count), or -inf past the end of the unit
+        const int r = lane & (TR - 1);
+        const float b = t * TR + r < L ? (cn > 1 ? __log2f((float)cn) : 0.f) : kNegInf;
+        if (lane < TR) bias_s[r] = b;
       }
-    };
-    if (L > 0) {
-      load_keys(wv);
-      load_values(wv);
-    }
-    for (int t = wv; t < n_tiles; t += WAVES) {
-      {  // bias of key c32 of the tile: log2(count), or -inf past the end of the unit
-        const float b = t * 32 + c32 < L ? (cn > 1 ? __log2f((float)cn) : 0.f) : kNegInf;
-        if (hh == 0) bias_s[c32] = b;
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      f32x16 s = {0};
+      f32x4 s[SUB];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ka[ks]),
-                                                    __builtin_bit_cast(bf16x8, q_s[ks * 64 + lane]), s, 0, 0, 0);
-      // s[r] = <key (r / 4) * 8 + hh * 4 + r % 4, head c32>
-      float x[16], mx = kNegInf;
+      for (int y = 0; y < SUB; ++y) {
+        s[y] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const float4 b4 = *reinterpret_cast<const float4*>(&bias_s[r4 * 8 + hh * 4]);
-        x[r4 * 4 + 0] = __builtin_fmaf(s[r4 * 4 + 0], c, b4.x);
-        x[r4 * 4 + 1] = __builtin_fmaf(s[r4 * 4 + 1], c, b4.y);
-        x[r4 * 4 + 2] = __builtin_fmaf(s[r4 * 4 + 2], c, b4.z);
-        x[r4 * 4 + 3] = __builtin_fmaf(s[r4 * 4 + 3], c, b4.w);
-      }
-      load_keys(t + WAVES);  // the product is done with this tile's key rows
-      // Value rows into the wave's LDS area, transposed: key k sits in slot
-      // (k / 16) * 16 + (k / 4 % 2) * 8 + (k / 8 % 2) * 4 + k % 4, the order in which a lane's
-      // logit registers enumerate the keys of its half.
+        for (int ks = 0; ks < KS; ++ks) {
+          if constexpr (A::kBf16) {
+            s[y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ka[y][ks]),
+                                                           __builtin_bit_cast(bf16x8, q[ks]), s[y], 0, 0, 0);
+          } else {
+            const f32x4 kf = __builtin_bit_cast(f32x4, ka[y][ks]), qf = __builtin_bit_cast(f32x4, q[ks]);
 #pragma unroll
-      for (int j = 0; j < RPG; ++j) {
-        const int k = j * GPW + g;
-        const int slot = ((k >> 4) & 1) * 16 + ((k >> 2) & 1) * 8 + ((k >> 3) & 1) * 4 + (k & 3);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t w = va[j][e >> 1];
-          *reinterpret_cast<uint16_t*>(vt + vt_wr + e * 64 + (e >> 2) * 16 + slot * 2) =
-              (e & 1) ? (uint16_t)(w >> 16) : (uint16_t)w;
+            for (int e = 0; e < 4; ++e) s[y] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[e], qf[e], s[y], 0, 0, 0);
+          }
         }
       }
-      load_values(t + WAVES);  // this tile's value rows are in LDS
+      load_keys(t + step, L);  // the product is done with this tile's key rows
+      // s[y][r] = <key 16 y + 4 g + r, head l16>
+      float p[KEYS], mx = kNegInf;
+      if (cu || partial) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, x[r]);
+        for (int y = 0; y < SUB; ++y) {
+          const f32x4 b4 = *reinterpret_cast<const f32x4*>(&bias_s[y * 16 + g * 4]);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)  // (a row past the end may hold anything)
+            p[y * 4 + r] = b4[r] == kNegInf ? kNegInf : __builtin_fmaf(s[y][r], c, b4[r]);
+        }
+        if (partial && t == first) {  // (later tiles were read with the unit's length known)
+#pragma unroll
+          for (int j = 0; j < KEYS; ++j)
+            if (t * TR + (j >> 2) * 16 + g * 4 + (j & 3) >= L)
+#pragma unroll
+              for (int y = 0; y < NV; ++y) va[j][y] = ValVec(0u);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < KEYS; ++j) p[j] = s[j >> 2][j & 3] * c;
+      }
+#pragma unroll
+      for (int j = 0; j < KEYS; ++j) mx = fmaxf(mx, p[j]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mn = fmaxf(m_run, mx);  // finite: key 0 of a tile in range is in range
+      const float mn = fmaxf(m_run, mx);  // finite: row 0 of a tile in range is in range
       const float corr = __builtin_amdgcn_exp2f(m_run - mn);  // exp2(-inf) = 0 on the first tile
-      // A weight enters the value product as two bf16 terms, p = hi + lo (lo the rounded
-      // remainder: 16 mantissa bits in all), so that the product sees it to 2^-17.
-      bf16x8 pb[2], pl[2];
       float ps = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(x[r] - mn);
-        const __bf16 hi = (__bf16)pr;
-        pb[r >> 3][r & 7] = hi;
-        pl[r >> 3][r & 7] = (__bf16)(pr - (float)hi);
-        ps += pr;
+      for (int j = 0; j < KEYS; ++j) {
+        p[j] = __builtin_amdgcn_exp2f(p[j] - mn);
+        ps += p[j];
       }
       l_run = __builtin_fmaf(l_run, corr, ps);
       m_run = mn;
@@ -321,113 +208,179 @@ __global__ __launch_bounds__(WAVES * 64, 8 / WAVES) void attend_mfma_kernel(
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[b][r] *= corr;
+          for (int r = 0; r < 4; ++r) acc[b][r] *= corr;
       }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if constexpr (A::kBf16) {
+        bf16x8 ph, pl;
 #pragma unroll
-      for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const u32x4 vop = *reinterpret_cast<const u32x4*>(vt + vt_rd + b * (32 * 64 + 8 * 16) + ks * 32);
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vop), pb[ks], acc[b], 0, 0, 0);
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vop), pl[ks], acc[b], 0, 0, 0);
+        for (int j = 0; j < 8; ++j) {
+          const __bf16 hi = (__bf16)p[j];
+          ph[j] = hi;
+          pl[j] = (__bf16)(p[j] - (float)hi);
         }
-      asm volatile("" ::: "memory");  // the next tile's LDS writes stay behind these reads
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+          const int w = (b % EPV) >> 1;
+          u32x4 v;
+#pragma unroll
+          for (int k2 = 0; k2 < 4; ++k2)  // the halves of two keys' words that hold the block's channel
+            v[k2] = __builtin_amdgcn_perm(va[2 * k2 + 1][b / EPV][w], va[2 * k2][b / EPV][w],
+                                          (b & 1) ? 0x07060302u : 0x05040100u);
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), ph, acc[b], 0, 0, 0);
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), pl, acc[b], 0, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < KEYS; ++j)
+#pragma unroll
+          for (int b = 0; b < NB; ++b)
+            acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(va[j][b / EPV][b % EPV]), p[j], acc[b], 0, 0, 0);
+      }
+      load_values(t + step, L);
     }
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    float* st_acc = reinterpret_cast<float*>(vt);  // [HP][D]: the wave's value area is free now
-    if (c32 < HP) {
-      if (hh == 0) {
-        st_m[wv * HP + c32] = m_run;
-        st_l[wv * HP + c32] = l_tot;
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (l16 < heads) {
+      if (g == 0) {
+        st_m[wv * kAttHeads + l16] = m_run;
+        st_l[wv * kAttHeads + l16] = l_run;
       }
 #pragma unroll
       for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          *reinterpret_cast<float4*>(&st_acc[c32 * D + b * 32 + r4 * 8 + hh * 4]) =
-              float4{acc[b][r4 * 4], acc[b][r4 * 4 + 1], acc[b][r4 * 4 + 2], acc[b][r4 * 4 + 3]};
+        *reinterpret_cast<f32x4*>(&st_acc[(wv * heads + l16) * kAccPitch + b * 16 + g * 4]) = acc[b];
     }
-    asm volatile("" ::: "memory");
     __syncthreads();
-    for (int o = tid; o < HP * D; o += WAVES * 64) {
+    const int pass_heads = min(heads, G - g0);
+    for (int o = tid; o < pass_heads * D; o += WAVES * 64) {
       const int h = o / D, ch = o % D;
-      if (g0 + h >= G) continue;
+      // where channel `ch` waits: block b, row m with AttGeom::channel(b, m) == ch
+      const int at = ((ch / (16 * EPV)) * EPV + ch % EPV) * 16 + (ch % (16 * EPV)) / EPV;
       float top = kNegInf;
-      for (int w = 0; w < WAVES; ++w) top = fmaxf(top, st_m[w * HP + h]);
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) top = fmaxf(top, st_m[w * kAttHeads + h]);
       float num = 0.f, den = 0.f;
+#pragma unroll
       for (int w = 0; w < WAVES; ++w) {  // wave order: the same bits every run
-        const float mw = st_m[w * HP + h];
+        const float mw = st_m[w * kAttHeads + h];
         const float f = mw == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mw - top);
-        den = __builtin_fmaf(st_l[w * HP + h], f, den);
-        num = __builtin_fmaf(reinterpret_cast<const float*>(att_lds + w * kVt)[h * D + ch], f, num);
+        den = __builtin_fmaf(st_l[w * kAttHeads + h], f, den);
+        num = __builtin_fmaf(st_acc[(w * heads + h) * kAccPitch + at], f, num);
       }
-      out[((size_t)u * G + g0 + h) * D + ch] = float_to_bf16_bits(den > 0.f ? num / den : 0.f);
+      if (splits == 1) {
+        Elem<T>::store(out + ((size_t)u * G + g0 + h) * D + ch, den > 0.f ? num / den : 0.f);
+      } else {  // [unit][split][head]: D sums, then the reference and the denominator
+        float* pp = part + (((size_t)u * splits + sp) * G + g0 + h) * (D + 2);
+        pp[ch] = num;
+        if (ch == 0) {
+          pp[D] = top;
+          pp[D + 1] = den;
+        }
+      }
     }
-    asm volatile("" ::: "memory");
     __syncthreads();
   }
 }
 
-template <int D, int HP, int WAVES>
-hipError_t launch_attend_mfma_w(const KParams& kp, int n_units, const void* Q, const void* Kc,
-                                const void* Vc, int stride, const int32_t* len, const int32_t* count,
-                                int count_pitch, void* out, hipStream_t st) {
-  constexpr int lds = att_lds_bytes<D, HP, WAVES>();
-  static LdsLimitOnce lim;  // one per instantiation
-  if (lds > 48 * 1024) {
-    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&attend_mfma_kernel<D, HP, WAVES>), (int)lds);
-    if (e != hipSuccess) return e;
+// Adds the splits of attend_kernel in split order.  A thread per (head, channel) of a unit.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void attend_combine_kernel(int rows, int splits, int G, const float* __restrict__ part,
+                                                             T* __restrict__ out) {
+  const int o = blockIdx.x * 256 + threadIdx.x;
+  if (o >= rows * D) return;
+  const int row = o / D, ch = o % D, u = row / G, h = row % G;
+  const float* pp = part + ((size_t)u * splits * G + h) * (D + 2);
+  const size_t pitch = (size_t)G * (D + 2);
+  float m = kNegInf, num = 0.f, den = 0.f;
+  for (int s0 = 0; s0 < splits; s0 += 8) {  // eight partials in flight
+    float pm[8], pd[8], pn[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float* ps = pp + min(s0 + e, splits - 1) * pitch;
+      pn[e] = ps[ch];
+      pm[e] = ps[D];
+      pd[e] = ps[D + 1];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if (s0 + e >= splits || pm[e] == kNegInf) continue;
+      const float mn = fmaxf(m, pm[e]);
+      const float fa = __builtin_amdgcn_exp2f(m - mn), fb = __builtin_amdgcn_exp2f(pm[e] - mn);
+      den = __builtin_fmaf(den, fa, pd[e] * fb);
+      num = __builtin_fmaf(num, fa, pn[e] * fb);
+      m = mn;
+    }
   }
-  attend_mfma_kernel<D, HP, WAVES><<<dim3(n_units), dim3(WAVES * 64), lds, st>>>(
-      kp, static_cast<const uint16_t*>(Q), static_cast<const uint16_t*>(Kc),
-      static_cast<const uint16_t*>(Vc), stride, len, count, count_pitch, static_cast<uint16_t*>(out));
+  Elem<T>::store(out + o, den > 0.f ? num / den : 0.f);
+}
+
+template <typename T, int D, int WAVES, bool NT>
+hipError_t launch_attend_as(const KParams& kp, int n_units, const void* Q, const void* Kc, const void* Vc, int stride,
+                            const int32_t* len, const int32_t* count, int count_pitch, void* out, int splits,
+                            float* part, hipStream_t st) {
+  const int heads = kp.G < kAttHeads ? kp.G : kAttHeads;
+  const int lds = WAVES * (32 + 2 * kAttHeads + heads * (D + 4)) * (int)sizeof(float);
+  static LdsLimitOnce lim;  // one per instantiation
+  const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&attend_kernel<T, D, WAVES, NT>), 160 * 1024);
+  if (e != hipSuccess) return e;
+  attend_kernel<T, D, WAVES, NT><<<dim3(n_units * splits), dim3(WAVES * 64), lds, st>>>(
+      kp, static_cast<const T*>(Q), static_cast<const T*>(Kc), static_cast<const T*>(Vc), stride, len, count, count_pitch,
+      static_cast<T*>(out), splits, part);
+  if (splits > 1)
+    attend_combine_kernel<T, D><<<dim3((n_units * kp.G * D + 255) / 256), dim3(256), 0, st>>>(
+        n_units * kp.G, splits, kp.G, part, static_cast<T*>(out));
   return hipSuccess;
 }
 
-// Few units: eight waves per workgroup (more rows of a unit in flight); many: four, so that
-// two workgroups share a compute unit and one's merge overlaps the other's loads.
-template <int D, int HP>
-hipError_t launch_attend_mfma(const KParams& kp, int n_units, const void* Q, const void* Kc, const void* Vc,
-                              int stride, const int32_t* len, const int32_t* count, int count_pitch,
-                              void* out, hipStream_t st) {
-  if (n_units >= 512)
-    return launch_attend_mfma_w<D, HP, 4>(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, st);
-  return launch_attend_mfma_w<D, HP, 8>(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, st);
+// Waves per workgroup.  Few units: eight (more rows of a unit in flight); many: four, so that
+// several workgroups share a compute unit and one's merge overlaps the others' loads.
+// Non-temporal loads where the caches of the call exceed the 256 MB last-level cache, so that no
+// call can find them there (554 MB: 102 -> 91 us; 1 GB of fp32: 185 -> 169 us); below that a
+// call that repeats finds its rows there and the hint costs up to a quarter.
+template <typename T, int D>
+hipError_t launch_attend_t(const KParams& kp, int n_units, const void* Q, const void* Kc, const void* Vc, int stride,
+                           const int32_t* len, const int32_t* count, int count_pitch, void* out, int splits,
+                           float* part, hipStream_t st) {
+  const bool nt = (int64_t)n_units * stride * (2 * D * (int)sizeof(T)) > (256ll << 20);
+  const bool four = (int64_t)n_units * splits >= 512;
+  auto go = [&](auto f) { return f(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, splits, part, st); };
+  if (four) return nt ? go(&launch_attend_as<T, D, 4, true>) : go(&launch_attend_as<T, D, 4, false>);
+  return nt ? go(&launch_attend_as<T, D, 8, true>) : go(&launch_attend_as<T, D, 8, false>);
 }
 
 }  // namespace
 
+// Workgroups that share a unit.  Without a workspace one; with it enough to fill the chip, as long
+// as each still has two rounds of tiles and the unit at least six (the combining launch behind them
+// costs about 4 us, a round of eight waves about 2.5 us).  Measured, one workgroup per unit -> split:
+// 8 units x 16 000 rows 159 -> 21 us, 16 x 4000 45 -> 13.7, 45 x 15 648 218 -> 73, 4 x 1500 21.7 ->
+// 13; 256 x 2000 (two each) 43 -> 47, so not beyond 128 units.
+int attend_splits(const KParams& kp, int n_units, int stride) {
+  if (n_units <= 0 || n_units > 128) return 1;
+  const int tile = kp.dtype == CASK_BF16 ? 32 : 16;
+  const int rounds = (stride + tile * 8 - 1) / (tile * 8);  // of eight waves, all rows used
+  if (rounds < 6) return 1;
+  int s = 512 / n_units;
+  if (s > rounds / 2) s = rounds / 2;
+  return s > 64 ? 64 : s;
+}
+
+size_t attend_part_bytes(const KParams& kp, int n_units, int splits) {
+  return splits <= 1 ? 0 : (size_t)n_units * splits * kp.G * (kp.d + 2) * sizeof(float);
+}
+
 hipError_t launch_attend(const KParams& kp, int n_units, const void* Q, const void* Kc, const void* Vc,
                          int stride, const int32_t* len, const int32_t* count, int count_pitch,
-                         void* out, hipStream_t st) {
+                         void* out, int splits, float* part, hipStream_t st) {
   if (n_units == 0) return hipSuccess;
-  hipError_t e = hipSuccess;
-#define CASK_ATT(T, D)                                                                       \
-  attend_kernel<T, D><<<dim3(n_units), dim3(kAttThreads), 0, st>>>(                          \
-      kp, static_cast<const T*>(Q), static_cast<const T*>(Kc), static_cast<const T*>(Vc),    \
-      stride, len, count, count_pitch, static_cast<T*>(out))
-#define CASK_ATT_MFMA(D, HP) \
-  e = launch_attend_mfma<D, HP>(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, st)
+  hipError_t e;
+#define CASK_ATT(T, D) e = launch_attend_t<T, D>(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, splits, part, st)
   if (kp.dtype == CASK_F32) {
     if (kp.d == 64) CASK_ATT(float, 64); else CASK_ATT(float, 128);
-  } else if (kp.path_flags & CASK_PATH_ATTEND_VECTOR) {  // the vector-ALU kernel, for comparisons
-    if (kp.d == 64) CASK_ATT(uint16_t, 64); else CASK_ATT(uint16_t, 128);
   } else {
-    const int hp = kp.G >= 5 ? 8 : kp.G >= 3 ? 4 : kp.G;  // query heads per pass over the cache
-    if (kp.d == 64) {
-      if (hp == 8) CASK_ATT_MFMA(64, 8); else if (hp == 4) CASK_ATT_MFMA(64, 4);
-      else if (hp == 2) CASK_ATT_MFMA(64, 2); else CASK_ATT_MFMA(64, 1);
-    } else {
-      if (hp == 8) CASK_ATT_MFMA(128, 8); else if (hp == 4) CASK_ATT_MFMA(128, 4);
-      else if (hp == 2) CASK_ATT_MFMA(128, 2); else CASK_ATT_MFMA(128, 1);
-    }
+    if (kp.d == 64) CASK_ATT(uint16_t, 64); else CASK_ATT(uint16_t, 128);
   }
-#undef CASK_ATT_MFMA
 #undef CASK_ATT
-  if (e != hipSuccess) return e;
-  return hipGetLastError();
+  return e != hipSuccess ? e : hipGetLastError();
 }
 
 }  // namespace cask

@@ -288,9 +288,13 @@ hipError_t launch_tail_small(const KParams& kp, const Batch& b, float* scores, c
                              int32_t* out_len, int32_t* out_src, float* out_mass,
                              int32_t* out_count, int32_t* assign, int32_t* status,
                              hipStream_t st);
+// Workgroups a unit's rows are shared by when the caller gives a workspace for their partial results
+// (`attend_part_bytes` of it, passed as `part`); 1: no workspace is used.
+int attend_splits(const KParams& kp, int n_units, int stride);
+size_t attend_part_bytes(const KParams& kp, int n_units, int splits);
 hipError_t launch_attend(const KParams& kp, int n_units, const void* Q, const void* Kc, const void* Vc,
                          int stride, const int32_t* len, const int32_t* count, int count_pitch,
-                         void* out, hipStream_t st);
+                         void* out, int splits, float* part, hipStream_t st);
 hipError_t launch_group_diag(const KParams& kp, const Batch& b, const float* scores,
                              const int32_t* assign, const void* K_out, int out_stride,
                              float* dispersion, float* lost_mass, hipStream_t st);

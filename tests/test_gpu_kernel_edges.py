@@ -9,6 +9,7 @@ import paper_2604_10900_amd as cask  # noqa: E402
 from oracle import ref  # noqa: E402
 from synth import caches  # noqa: E402
 from tests import parity  # noqa: E402
+from tests.test_gpu_parity import _attend_check  # noqa: E402
 
 W = caches.WORKLOADS
 B = cask.binding
@@ -49,3 +50,38 @@ def test_scores_with_64_channels(G, Wn, causal, splits, form):
     torch.cuda.synchronize()
     assert torch.equal(s, s2)
     _note(form, G, Wn, causal, "score error / max", parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,G,stride,n", [(128, 7, 1025, 12), (64, 16, 530, 12), (128, 17, 97, 12), (64, 1, 2000, 3), (128, 5, 9001, 3)])
+def test_attention_tiles_splits_and_rows_past_the_end(d, G, stride, n, dtype):
+    """cask_attend at lengths around a 16- or 32-row tile and a round of eight waves, up to 17 heads
+    (two passes), units split over several workgroups (the longer strides with few units), counts on
+    part of the rows; rows past a unit's length hold NaN and must not be seen.  Tolerance: derived at
+    _attend_check."""
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(17)
+    cand = [1, 15, 16, 17, 31, 32, 33, 255, 256, 257, 511, 513, 1024, 4097]
+    lens = np.array([min(stride, cand[i % len(cand)]) for i in range(n - 2)] + [stride, max(1, stride - 1)], dtype=np.int32)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator().manual_seed(d + G)
+    Q = (1.5 * torch.randn(n, G, d, generator=g)).to(dt).to(dev)
+    Kc = torch.randn(n, stride, d, generator=g).to(dt)
+    Vc = torch.randn(n, stride, d, generator=g).to(dt)
+    pitch = max(1, stride - 40)
+    count = rng.integers(1, 20, (n, pitch)).astype(np.int32)
+    padded = np.ones((n, stride), dtype=np.int32)
+    padded[:, :pitch] = count
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=1, budget=stride)
+    rp = parity.ref_params(p)
+    Qh, Kh, Vh = caches.host_bits(Q), caches.host_bits(Kc), caches.host_bits(Vc)
+    for i, L in enumerate(lens):
+        Kc[i, L:] = float("nan")
+        Vc[i, L:] = float("nan")
+    Kc, Vc = Kc.to(dev), Vc.to(dev)
+    split = B.load().cask_attend_workspace_bytes(B.C.byref(p.c()), n, stride) > 0
+    assert split or stride < 2000
+    for cnt, pad in ((None, None), (count, padded)):
+        got = cask.attend(p, Q, Kc, Vc, torch.from_numpy(lens).to(dev), count=None if cnt is None else torch.from_numpy(cnt).to(dev))
+        torch.cuda.synchronize()
+        _note(dtype, d, G, stride, split, _attend_check(p, rp, got, ref.attend(rp, Qh, Kh, Vh, lens, count=pad), Qh, Kh, Vh, lens, pad))
