@@ -87,18 +87,46 @@ class Params:
     score_splits: int = 0          # forced key splits of the first scoring sweep (0: the library's choice)
     score_qsplit: int = 0          # forced sharing of a key tile in the second sweep (0: the library's choice)
 
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        object.__setattr__(self, "_packed", None)   # the C image of the fields is stale
+
     def c(self, scores_given: int = 0) -> _Params:
-        bw = None
-        if self.band_weight is not None:
-            t = self.band_weight
+        """The C struct of one call: the fields (packed when they last changed), the environment's
+        switches, and the band weights' present address."""
+        packed = self._packed
+        if packed is None:
+            packed = bytes(_Params(self.dtype, self.head_dim, self.q_per_kv, self.window, self.recent, self.budget, self.core,
+                                   self.prefix_budget, self.sim_threshold, self.softmax_scale, self.causal, 0,
+                                   self.merge_radius, self.merge_geometry, self.dist_threshold, None, self.seed_dedup,
+                                   self.path_flags, self.score_splits, self.score_qsplit))
+            object.__setattr__(self, "_packed", packed)
+        out = _Params.from_buffer_copy(packed)
+        if scores_given:
+            out.scores_given = scores_given
+        t = self.band_weight
+        if t is not None:
             assert t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() and t.numel() == self.head_dim // 2
-            bw = t.data_ptr()
-        return _Params(self.dtype, self.head_dim, self.q_per_kv, self.window, self.recent,
-                       self.budget, self.core, self.prefix_budget, self.sim_threshold,
-                       self.softmax_scale, self.causal, scores_given, self.merge_radius,
-                       self.merge_geometry, self.dist_threshold, bw, self.seed_dedup,
-                       self.path_flags | _env_path_flags(), self.score_splits or _env_int("CASK_SPLITS"),
-                       self.score_qsplit or _env_int("CASK_QSPLIT"))
+            out.band_weight = t.data_ptr()
+        if _env_any():
+            out.path_flags |= _env_path_flags()
+            out.score_splits = self.score_splits or _env_int("CASK_SPLITS")
+            out.score_qsplit = self.score_qsplit or _env_int("CASK_QSPLIT")
+        return out
+
+
+_ENV_NAMES = ("CASK_FUSED_TAIL", "CASK_FUSED_SCORE", "CASK_FUSED_SWEEPS", "CASK_DEDUP_VECTOR", "CASK_NARROW_ROWS",
+              "CASK_WIDE_ROWS", "CASK_SPLITS", "CASK_QSPLIT")
+# os.environ's own dict, looked up without its per-access encoding (eight lookups 0.4 us, through the
+# mapping 5 us): an event of a short unit takes 40 us in all
+_env_raw = getattr(os.environ, "_data", None)
+_env_keys = tuple(os.environ.encodekey(n) for n in _ENV_NAMES) if _env_raw is not None else _ENV_NAMES
+_env_lookup = _env_raw.get if _env_raw is not None else os.environ.get
+
+
+def _env_any() -> bool:
+    """Whether any of the measurement switches is set."""
+    return any(map(_env_lookup, _env_keys))
 
 
 def _env_int(name: str) -> int:
@@ -215,11 +243,18 @@ def _dptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensor expected"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream() -> int:
+    """Handle of the current stream (without building a Stream object where torch can give the handle itself)."""
+    if _raw_stream is not None and _raw_device is not None:
+        return _raw_stream(_raw_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 class Batch:
