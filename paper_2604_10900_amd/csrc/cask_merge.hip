@@ -1,6 +1,6 @@
 // Selective consolidation of the mergeable scratch (Sections 2.1, 2.4, 2.5 of the paper):
 //   similarity   every donor against every seed of its unit by key cosine; best seed kept
-//                when the cosine reaches tau (bf16 d=128: MFMA contraction seeds x donors^T,
+//                when the cosine reaches tau (bf16: MFMA contraction seeds x donors^T,
 //                each lane owns one donor and scans its seeds in ascending order);
 //   gather       ordered list of the donors that merge (ascending row), per unit, then the
 //                same list grouped by seed; spare workgroups of the launch copy the kept
@@ -26,12 +26,21 @@ __device__ inline bool better(float sim, int ord, float best, int best_ord) {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kD = 128;
-constexpr int kRowBytes = kD * 2;
-constexpr int kGroupPitch = 1024 + 64;  // LDS pitch of a 4-row group (layout: see below)
+// What the head dimension decides about the rows a wave turns round in LDS (layout: see below).
+template <int D>
+struct TurnGeom {
+  static constexpr int kRowBytes = D * 2;
+  static constexpr int kPieces = kRowBytes / 16;          // 16-byte pieces of a row: 16 or 8
+  static constexpr int kGroupRows = 64 / kPieces;         // rows one load instruction of a wave covers: 4 or 8
+  static constexpr int kGroups = 32 / kGroupRows;         // such groups in a wave's 32 rows
+  // LDS pitch of a group: consecutive groups start 64 bytes (four 256-byte rows) or half the banks
+  // (eight 128-byte rows) apart
+  static constexpr int kGroupPitch = 1024 + (D == 128 ? 64 : 128);
+  static constexpr int kAddr = kGroupRows / 2;            // k-steps with addresses of their own; the rest are offsets
+  static constexpr int kPrefetch = D == 128 ? 2 : 4;      // donor tiles in flight ahead of the one being contracted
+};
 constexpr int kSeedBlock = 128;         // seeds held in LDS at a time
 constexpr int kDonorTile = 128;         // donor rows per tile: 4 waves x 32
-constexpr int kPrefetch = 2;            // donor tiles in flight ahead of the one being contracted
 constexpr int kMultiTiles = 4;          // tiles per workgroup where a unit's seeds take several blocks
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -49,7 +58,8 @@ __device__ inline float sumsq_bf16x8(const uint4& v) {
 // Workgroup = `tiles_per_wg` consecutive donor tiles of one unit; wave w owns rows
 // [32 w, 32 w + 32) of every tile.
 //
-// Memory side: a wave reads its 32 rows with 8 fully coalesced loads (4 whole 256-byte rows
+// Memory side (d = 128; d = 64 has eight 128-byte rows to a load, four loads, and as many bytes
+// in flight): a wave reads its 32 rows with 8 fully coalesced loads (4 whole 256-byte rows
 // per instruction: lane l takes 16-byte piece l % 16 of row l / 16), kPrefetch tiles ahead, so
 // K streams at memory speed.  The registers then hold rows across lanes, not MFMA operands;
 // the wave turns them round through a private LDS region: a 4-row group is kept row by row,
@@ -63,16 +73,22 @@ __device__ inline float sumsq_bf16x8(const uint4& v) {
 // cos = (dot * |seed|^-1) * |donor|^-1 in fp32, first maximum wins.
 // ONE_BLOCK: every unit has at most kSeedBlock seeds, so they are staged once per workgroup and
 // the tile loop contains nothing but the donor stream (the host knows the bound).
+// Measured, d = 64 (128 units of 5378 rows, 84 MB of keys): 30 us; a thread per donor on the
+// vector units, its key in registers, took 105 us.
 // RADIUS: a merge radius is set (the epilogue then looks up every seed's cache row).
-template <bool ONE_BLOCK, bool RADIUS>
+template <int D, bool ONE_BLOCK, bool RADIUS>
 __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
     KParams kp, int n_units, int chunks_per_unit, int tiles_per_wg,
     const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
     const uint16_t* __restrict__ K, const uint8_t* __restrict__ role,
     const int32_t* __restrict__ seed_rows, const int32_t* __restrict__ n_seeds,
     int32_t* __restrict__ assign_ord) {
-  __shared__ __attribute__((aligned(16))) unsigned char seeds[(kSeedBlock / 4) * kGroupPitch];
-  __shared__ __attribute__((aligned(16))) unsigned char turn[4][8 * kGroupPitch];
+  using TG = TurnGeom<D>;
+  constexpr int kRowBytes = TG::kRowBytes, kPieces = TG::kPieces, kGroupRows = TG::kGroupRows;
+  constexpr int kGroups = TG::kGroups, kGroupPitch = TG::kGroupPitch, kAddr = TG::kAddr, kPrefetch = TG::kPrefetch;
+  constexpr int NK = D / 16;  // k-steps
+  __shared__ __attribute__((aligned(16))) unsigned char seeds[(kSeedBlock / kGroupRows) * kGroupPitch];
+  __shared__ __attribute__((aligned(16))) unsigned char turn[4][kGroups * kGroupPitch];
   __shared__ __attribute__((aligned(16))) float seed_inv[kSeedBlock];
   __shared__ __attribute__((aligned(16))) int seed_pos[kSeedBlock];  // cache row of each staged seed
   const int bid = blockIdx.x;
@@ -97,7 +113,7 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   }
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: feeds scalar load offsets
   const int c32 = lane & 31, h = lane >> 5;
-  const uint16_t* Ku = K + (size_t)row0 * kD;
+  const uint16_t* Ku = K + (size_t)row0 * D;
   const uint8_t* ro = role + row0;
   const int32_t* srow = seed_rows + (size_t)u * kp.B;
   // rows past this workgroup's share of the donor range read as zero through the descriptor's
@@ -106,48 +122,50 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   const __amdgpu_buffer_rsrc_t krsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(Ku), 0, last * kRowBytes, 0x00020000);
 
-  // ---- donor stream: the wave's 32 rows of tile t, 4 rows per load
+  // ---- donor stream: the wave's 32 rows of tile t, kGroupRows rows per load
   // (the role of the lane's donor row rides along, so that nothing at the end of a tile has
   // to wait on memory behind the loads already issued for the tiles after it)
-  uint4 dreg[kPrefetch][8];
+  uint4 dreg[kPrefetch][kGroups];
   int rreg[kPrefetch];
-  auto fetch_donors = [&](int t, uint4 (&d)[8], int& rl) {
+  auto fetch_donors = [&](int t, uint4 (&d)[kGroups], int& rl) {
     // Always issued, also for tiles past the end (their rows read as zero and are never
     // stored): with an unconditional load count the waits for a tile can leave the loads of
     // the tiles after it in flight.
     const int r0 = first + t * kDonorTile + wv * 32;
     rl = (int)ro[min(r0 + c32, N - 1)];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < kGroups; ++j) {
       const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(
-          krsrc, lane * 16, (int)((unsigned)(r0 + 4 * j) * (unsigned)kRowBytes), 2);  // nt: a stream read once
+          krsrc, lane * 16, (int)((unsigned)(r0 + kGroupRows * j) * (unsigned)kRowBytes), 2);  // nt: a stream read once
       d[j] = make_uint4(v[0], v[1], v[2], v[3]);
     }
   };
-  // ---- seeds [sb, sb + kSeedBlock) -> LDS (16 threads per row, 16 rows per pass) + inverse norms
+  // ---- seeds [sb, sb + kSeedBlock) -> LDS (a thread per 16-byte piece) + inverse norms
   auto stage_seeds = [&](int sb) {
-    for (int s0 = 0; s0 < kSeedBlock && sb + s0 < M; s0 += 64) {
+    constexpr int kPassRows = 256 / kPieces;
+    const int piece = tid % kPieces, prow = tid / kPieces;
+    for (int s0 = 0; s0 < kSeedBlock && sb + s0 < M; s0 += 4 * kPassRows) {
       int idx[4];
       uint4 v[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int ord = sb + s0 + i * 16 + (tid >> 4);
+        const int ord = sb + s0 + i * kPassRows + prow;
         idx[i] = ord < M ? srow[ord] : -1;
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         v[i] = make_uint4(0, 0, 0, 0);
-        if (idx[i] >= 0) v[i] = reinterpret_cast<const uint4*>(Ku + (size_t)idx[i] * kD)[tid & 15];
+        if (idx[i] >= 0) v[i] = reinterpret_cast<const uint4*>(Ku + (size_t)idx[i] * D)[piece];
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int sr = s0 + i * 16 + (tid >> 4);
+        const int sr = s0 + i * kPassRows + prow, gr = sr % kGroupRows;
         // (row by row with piece g of row r at slot g ^ r, like the waves' turning regions)
-        *reinterpret_cast<uint4*>(seeds + (sr >> 2) * kGroupPitch + (sr & 3) * 256 + (((tid & 15) ^ (sr & 3)) * 16)) = v[i];
+        *reinterpret_cast<uint4*>(seeds + (sr / kGroupRows) * kGroupPitch + gr * kRowBytes + ((piece ^ gr) * 16)) = v[i];
         float ss = sumsq_bf16x8(v[i]);
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-        if ((tid & 15) == 0) {
+        for (int o = kPieces / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        if (piece == 0) {
           seed_inv[sr] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
           seed_pos[sr] = idx[i];
         }
@@ -158,27 +176,29 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   const int radius = kp.radius > 0 ? kp.radius : 0x7fffffff;
 
   unsigned char* my_turn = turn[wv];
-  // The wave's turning region holds a 4-row group row by row, the 16-byte piece g of row r at
-  // slot g ^ r of the row: the store of a load's 64 pieces (lane = row l / 16, piece l % 16) and
+  // The wave's turning region holds a group row by row, the 16-byte piece g of row r at
+  // slot g ^ r of the row: the store of a load's 64 pieces (lane = row l / kPieces, piece l % kPieces) and
   // the operand reads (lane = row c32, pieces h, h + 2, ...) then both spread any eight
   // consecutive lanes over all banks.  (Piece-major -- piece g of row r at g * 64 + r * 16 -- the
   // stores ran four lanes to a bank: 44 % of the kernel's LDS cycles were bank conflicts.)
-  const int turn_st = (lane >> 4) * 256 + (((lane & 15) ^ (lane >> 4)) * 16);
-  const int turn_row = (c32 >> 2) * kGroupPitch + (c32 & 3) * 256;
-  const int turn_ld0 = turn_row + ((h ^ (c32 & 3)) * 16);        // k-steps 0, 2, ...: piece 2 ks + h
-  const int turn_ld1 = turn_row + (((2 + h) ^ (c32 & 3)) * 16);  // k-steps 1, 3, ...
+  const int turn_st = (lane / kPieces) * kRowBytes + (((lane % kPieces) ^ (lane / kPieces)) * 16);
+  const int turn_row = (c32 / kGroupRows) * kGroupPitch + (c32 % kGroupRows) * kRowBytes;
+  int turn_ld[kAddr];  // k-steps 0 .. kAddr - 1: piece 2 ks + h; a later one lies whole rounds of them behind
+#pragma unroll
+  for (int q = 0; q < kAddr; ++q) turn_ld[q] = turn_row + (((2 * q + h) ^ (c32 % kGroupRows)) * 16);
+  auto turn_at = [&](int ks) { return turn_ld[ks % kAddr] + (ks / kAddr) * (kAddr * 32); };
 
   // registers -> private LDS region -> B operand of this lane's donor; refills the registers
   // with tile t + kPrefetch; returns the donor's inverse norm
-  auto turn_donors = [&](int t, uint4 (&d)[8], int& rl, bf16x8 (&bres)[8]) -> float {
+  auto turn_donors = [&](int t, uint4 (&d)[kGroups], int& rl, bf16x8 (&bres)[NK]) -> float {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < kGroups; ++j)
       *reinterpret_cast<uint4*>(my_turn + j * kGroupPitch + turn_st) = d[j];
     fetch_donors(t + kPrefetch, d, rl);  // refill the registers just freed
     float ss = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const uint4 v = *reinterpret_cast<const uint4*>(my_turn + ((ks & 1) ? turn_ld1 : turn_ld0) + (ks >> 1) * 64);
+    for (int ks = 0; ks < NK; ++ks) {
+      const uint4 v = *reinterpret_cast<const uint4*>(my_turn + turn_at(ks));
       ss += sumsq_bf16x8(v);
       bres[ks] = __builtin_bit_cast(bf16x8, v);
     }
@@ -188,16 +208,15 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   // The lane's donor against the staged seeds [sb, sb + m_blk), ascending ordinal: first maximum
   // wins.  `best` is the cosine without the donor's own inverse norm: a positive factor common
   // to all of a donor's seeds, applied once when the winner is settled.
-  auto against_block = [&](int sb, int m_blk, const bf16x8 (&bres)[8], int drow, float& best, int& best_ord) {
+  auto against_block = [&](int sb, int m_blk, const bf16x8 (&bres)[NK], int drow, float& best, int& best_ord) {
     for (int s0 = 0; s0 < m_blk; s0 += 32) {
-      bf16x8 a[8];
-      const unsigned char* ap = seeds + (s0 >> 2) * kGroupPitch;
+      bf16x8 a[NK];
+      const unsigned char* ap = seeds + (s0 / kGroupRows) * kGroupPitch;
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        a[ks] = *reinterpret_cast<const bf16x8*>(ap + ((ks & 1) ? turn_ld1 : turn_ld0) + (ks >> 1) * 64);
+      for (int ks = 0; ks < NK; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(ap + turn_at(ks));
       f32x16 acc = {0};
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
+      for (int ks = 0; ks < NK; ++ks)
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], bres[ks], acc, 0, 0, 0);
       auto pick = [&](auto whole_tag) {  // whole: all 32 seeds of this step exist
         constexpr bool kWhole = decltype(whole_tag)::value;
@@ -244,9 +263,9 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
     for (int t = 0; t < kPrefetch; ++t) fetch_donors(t, dreg[t], rreg[t]);
     stage_seeds(0);
     __syncthreads();
-    auto tile_body = [&](int t, uint4 (&d)[8], int& rl) {
+    auto tile_body = [&](int t, uint4 (&d)[kGroups], int& rl) {
       const bool donor = rl == CASK_ROLE_DONOR;
-      bf16x8 bres[8];
+      bf16x8 bres[NK];
       const float dinv = turn_donors(t, d, rl, bres);
       const int drow = first + t * kDonorTile + wv * 32 + c32;
       float best = kNegInf;
@@ -285,7 +304,7 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
       for (int t = 0; t < kMultiTiles; ++t) {
         if (t < n_tiles) {  // (the same for the whole workgroup)
           donor[t] = rreg[t % kPrefetch] == CASK_ROLE_DONOR;
-          bf16x8 bres[8];
+          bf16x8 bres[NK];
           dinv[t] = turn_donors(t, dreg[t % kPrefetch], rreg[t % kPrefetch], bres);
           against_block(sb, m_blk, bres, first + t * kDonorTile + wv * 32 + c32, best[t], best_ord[t]);
         }
@@ -1147,7 +1166,7 @@ hipError_t launch_similarity(const KParams& kp, const Batch& b, const uint8_t* r
     return kp.d == 64 ? launch_similarity_kappa<uint16_t, 64>(kp, b, role, seed_rows, n_seeds, assign_ord, st)
                       : launch_similarity_kappa<uint16_t, 128>(kp, b, role, seed_rows, n_seeds, assign_ord, st);
   }
-  if (kp.dtype == CASK_BF16 && kp.d == 128) {
+  if (kp.dtype == CASK_BF16) {
     // a few workgroups per unit, about two per compute unit in all, each walking its share of
     // the unit's donor tiles
     const int tiles = (b.max_decode_len + kDonorTile - 1) / kDonorTile;
@@ -1165,22 +1184,23 @@ hipError_t launch_similarity(const KParams& kp, const Batch& b, const uint8_t* r
     if (!one && tiles_per_wg > kMultiTiles) tiles_per_wg = kMultiTiles;  // its tiles' results wait in registers
     chunks = (tiles + tiles_per_wg - 1) / tiles_per_wg;
     const int units8 = (b.n_units + 7) / 8 * 8;
-#define CASK_SIM(ONE, RAD)                                                             \
-  similarity_mfma_kernel<ONE, RAD><<<dim3(units8 * chunks), dim3(256), 0, st>>>(       \
+#define CASK_SIM(D, ONE, RAD)                                                          \
+  similarity_mfma_kernel<D, ONE, RAD><<<dim3(units8 * chunks), dim3(256), 0, st>>>(    \
       kp, b.n_units, chunks, tiles_per_wg, b.row_off, b.prefix_len,                    \
       static_cast<const uint16_t*>(b.K), role, seed_rows, n_seeds, assign_ord)
-    if (kp.radius > 0) {
-      if (one) CASK_SIM(true, true); else CASK_SIM(false, true);
-    } else {
-      if (one) CASK_SIM(true, false); else CASK_SIM(false, false);
-    }
+#define CASK_SIM_D(D)                                                        \
+  if (kp.radius > 0) {                                                       \
+    if (one) CASK_SIM(D, true, true); else CASK_SIM(D, false, true);         \
+  } else {                                                                   \
+    if (one) CASK_SIM(D, true, false); else CASK_SIM(D, false, false);       \
+  }
+    if (kp.d == 64) { CASK_SIM_D(64) } else { CASK_SIM_D(128) }
+#undef CASK_SIM_D
 #undef CASK_SIM
     return hipGetLastError();
   }
-  if (kp.dtype == CASK_F32)
-    return kp.d == 64 ? launch_similarity_fma<float, 64>(kp, b, role, seed_rows, n_seeds, assign_ord, st)
-                      : launch_similarity_fma<float, 128>(kp, b, role, seed_rows, n_seeds, assign_ord, st);
-  return launch_similarity_fma<uint16_t, 64>(kp, b, role, seed_rows, n_seeds, assign_ord, st);
+  return kp.d == 64 ? launch_similarity_fma<float, 64>(kp, b, role, seed_rows, n_seeds, assign_ord, st)
+                    : launch_similarity_fma<float, 128>(kp, b, role, seed_rows, n_seeds, assign_ord, st);
 }
 
 hipError_t launch_gather_merged(const KParams& kp, const Batch& b, const uint8_t* role,

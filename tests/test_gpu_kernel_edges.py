@@ -85,3 +85,38 @@ def test_attention_tiles_splits_and_rows_past_the_end(d, G, stride, n, dtype):
         got = cask.attend(p, Q, Kc, Vc, torch.from_numpy(lens).to(dev), count=None if cnt is None else torch.from_numpy(cnt).to(dev))
         torch.cuda.synchronize()
         _note(dtype, d, G, stride, split, _attend_check(p, rp, got, ref.attend(rp, Qh, Kh, Vh, lens, count=pad), Qh, Kh, Vh, lens, pad))
+
+
+@pytest.mark.parametrize("radius", [0, 70])
+@pytest.mark.parametrize("tau", [0.3, -2.0])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+def test_consolidation_at_the_edges_of_tiles_and_seed_blocks(d, dtype, tau, radius):
+    """cask_consolidate with role arrays of the caller: donor ranges around a 32-row tile and a
+    workgroup's rows, seed counts around a 32-row step and a 128-row block, up to every second row
+    (tau = -2: every donor folds).  A donor may differ only where its two best cosines, or best and
+    threshold, lie within 1e-4 in the oracle (fp32 sums of 64 or 128 products: errors below 2e-5)."""
+    Wn = 16
+    lens = [Wn + 1, Wn + 33, 160, 161, 289, 544, 1057, 2100]
+    pref = [0, 1, 16, 0, 17, 16, 1, 333]
+    seeds = [1, 1, 31, 33, 127, 128, 129, 800]
+    c = _units(lens, pref, head_dim=d, q_per_kv=2, window=Wn, cluster_frac=0.5)
+    if dtype == "f32":
+        c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=2, window=Wn, budget=900,
+                    sim_threshold=tau, merge_radius=radius)
+    row_off, prefix_len, K, V, Q = parity.host_arrays(c)
+    rng = np.random.default_rng(d)
+    total = int(row_off[-1])
+    role = np.full(total, ref.DONOR, dtype=np.uint8)
+    for u, (n, P, M) in enumerate(zip(lens, pref, seeds)):
+        lo = int(row_off[u])
+        role[lo:lo + P] = ref.PREFIX_KEEP
+        role[lo + n - Wn:lo + n] = ref.RECENT
+        role[lo + P + rng.choice(n - Wn - P, size=min(M, n - Wn - P), replace=False)] = ref.SEED
+    s = rng.random(total).astype(np.float32)
+    want, best, second = ref.consolidate(parity.ref_params(p), row_off, prefix_len, K, s, role, want_sims=True)
+    b = parity.to_device(c, p)
+    got = cask.consolidate(b, torch.from_numpy(s).to(b.device), torch.from_numpy(role).to(b.device))
+    torch.cuda.synchronize()
+    assert (want >= 0).sum() > 800
+    _note(d, dtype, tau, radius, "excused", parity.check_assign_excused(got.cpu().numpy(), want, best, second, float(np.float32(tau)), "edges"))
