@@ -56,6 +56,27 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     if (kp.path_flags & CASK_PATH_NARROW_ROWS) w.wide_rows = 0;
   }
   int n_splits = w.wide_rows ? splits_w : splits_n;
+  // Row pitch of the one-launch scoring's partial sums (bf16 only; laid out below).
+  const int len64 = (int)align_up((size_t)(max_unit_len > 0 ? max_unit_len : 1), 64);
+  w.parts_pitch = len64 < 1024 ? len64 : 1024;
+  if (kp.dtype == CASK_F32) {
+    // 128 window rows per workgroup, 32 keys a stage, matrix-bound: the time is that of the fullest
+    // compute unit, its stages plus about two per workgroup.  The splits' row statistics take the
+    // place of the partial sums, 128 keys of whose pitch are worth one split: no more than that, so
+    // that an fp32 batch's workspace is no larger than a bf16 one's.
+    const int most = n_splits + w.parts_pitch / 128;
+    const int64_t pairs = (int64_t)n_units * ((kp.Mq + 127) / 128);
+    double best_cost = 0.0;
+    for (int sp = 1, best = 1; sp <= most && sp <= 64; ++sp) {
+      const int len = (int)align_up((size_t)(max_unit_len + sp - 1) / sp, 64);
+      if (sp > 1 && len < 256) break;
+      const int64_t wgs = pairs * (len > 0 ? (max_unit_len + len - 1) / len : 1);
+      const double cost = (double)((wgs + 255) / 256) * (len / 32 + 2);
+      if (sp == 1 || cost < best_cost) best_cost = cost, best = sp;
+      n_splits = best;
+    }
+    w.parts_pitch = 0;
+  }
   if (kp.score_splits >= 1) n_splits = kp.score_splits;
   int split_len = (int)align_up((size_t)(max_unit_len + n_splits - 1) / n_splits, 64);
   if (split_len < 64) split_len = 64;
@@ -95,10 +116,6 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // one-launch scoring of short units: partial column sums, one row per 64 window rows
   // (reserved whatever the unit length, capped at the longest unit that path takes, so that a
   // workspace sized for longer units also serves a batch of shorter ones)
-  {
-    const size_t len64 = align_up((size_t)(max_unit_len > 0 ? max_unit_len : 1), 64);
-    w.parts_pitch = (int)(len64 < 1024 ? len64 : 1024);
-  }
   w.parts = take(units * (size_t)((kp.Mq + 63) / 64) * (size_t)w.parts_pitch * sizeof(float));
   w.rowstat = take(units * n_splits * w.mq_pad * sizeof(float2));
   w.bias = take(units * w.mq_pad * sizeof(float));

@@ -316,73 +316,235 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   }
 }
 
-// ------------------------------------------------------------------ similarity, plain path
+// ------------------------------------------------------------------ similarity, fp32 caches
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void similarity_fma_kernel(
-    KParams kp, int n_units, int tiles_per_unit, const int64_t* __restrict__ row_off,
-    const int32_t* __restrict__ prefix_len, const T* __restrict__ K,
-    const uint8_t* __restrict__ role, const int32_t* __restrict__ seed_rows,
-    const int32_t* __restrict__ n_seeds, int32_t* __restrict__ assign_ord) {
-  constexpr int SEEDS = 32;
-  __shared__ float sk[SEEDS][D + 1];
-  __shared__ float sinv[SEEDS];
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kF32Slots = 512;  // workgroups aimed at: two per compute unit (three and four measured 5 - 25 % slower)
+
+// Sizes that follow from the head dimension.
+template <int D>
+struct SimF32Geom {
+  static constexpr int kRowBytes = D * 4;
+  static constexpr int kDonorTile = 4 * 16;                // donors of a workgroup's tile: sixteen per wave
+  static constexpr int kSteps = kRowBytes / 64;            // 16-byte pieces of a row per lane
+  static constexpr int kRing = D == 128 ? 2 : 4;           // tiles whose rows are held or in flight
+  static constexpr int kSeeds = 32768 / kRowBytes;         // seeds held in LDS at a time
+  static constexpr int kSeedPitch = kRowBytes + 16;        // sixteen rows' pieces then lie in different banks
+};
+
+__device__ inline float sumsq_f32x4(const f32x4& v) {
+  return __builtin_fmaf(v[3], v[3], __builtin_fmaf(v[2], v[2], __builtin_fmaf(v[1], v[1], v[0] * v[0])));
+}
+
+// Workgroup = `tiles_per_wg` consecutive donor tiles of one unit; wave w owns rows
+// [16 w, 16 (w + 1)) of every tile.
+//
+// The products are 16x16x4 fp32 matrix tiles (seeds x donors^T, fp32 products and sums).  A lane loads the pieces it
+// needs as an operand -- lane (l16, g) pieces g, g + 4, ... of row l16, piece by piece four k-steps --
+// straight into registers, kRing - 1 tiles ahead: no pass through LDS, no barrier.  (A bf16 cache
+// streams faster as whole rows turned round through LDS: 5.3 against 3.9 - 4.7 TB/s; an fp32 batch
+// of 32 units is bound by its products and launch, not by the stream.)  Measured, 32 units of
+// 4096 rows, 52 seeds: 20.8 us; a thread per donor on the vector units took 46.
+//
+// The unit's seeds (kSeeds at a time, with inverse norms) are the A operand, from LDS: a lane
+// owns one donor and sees every fourth group of four seeds in ascending order:
+// cos = (dot * |seed|^-1) * |donor|^-1, first maximum wins.  Places past the last seed
+// carry a NaN as their inverse norm, which no comparison prefers.
+// ONE_BLOCK, RADIUS: as for the bf16 kernel above.
+template <int D, bool ONE_BLOCK, bool RADIUS>
+__global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
+    KParams kp, int n_units, int chunks_per_unit, int tiles_per_wg,
+    const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
+    const float* __restrict__ K, const uint8_t* __restrict__ role,
+    const int32_t* __restrict__ seed_rows, const int32_t* __restrict__ n_seeds,
+    int32_t* __restrict__ assign_ord) {
+  using SG = SimF32Geom<D>;
+  constexpr int kRowBytes = SG::kRowBytes, kDonorTile = SG::kDonorTile;
+  constexpr int KS = SG::kSteps, kRing = SG::kRing, kSeeds = SG::kSeeds, kSeedPitch = SG::kSeedPitch;
+  __shared__ __attribute__((aligned(16))) unsigned char seeds[kSeeds * kSeedPitch];
+  __shared__ __attribute__((aligned(16))) float seed_inv[kSeeds];
+  __shared__ __attribute__((aligned(16))) int seed_pos[kSeeds];  // cache row of each staged seed
   const int bid = blockIdx.x;
-  const int u = bid / tiles_per_unit, tile = bid % tiles_per_unit;
+  const int xcd = bid & 7, kk = bid >> 3;
+  const int u = (kk / chunks_per_unit) * 8 + xcd;
+  const int chunk = kk % chunks_per_unit;
   if (u >= n_units) return;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];
   const UnitPlan pl = make_plan(kp, P, N);
   const int hi = N - pl.r_eff;
-  const int base = P + tile * 256;
-  if (base >= hi) return;
+  const int first = P + chunk * tiles_per_wg * kDonorTile;
+  if (first >= hi) return;
+  const int n_tiles = min(tiles_per_wg, (hi - first + kDonorTile - 1) / kDonorTile);
   const int M = n_seeds[u];
-  const int tid = threadIdx.x;
-  const int i = base + tid;
-  const bool ok = i < hi;
-  const T* Ku = K + (size_t)row0 * D;
-  const int32_t* srow = seed_rows + (size_t)u * kp.B;
-  float k[D];
-  float ss = 0.f;
-#pragma unroll
-  for (int c = 0; c < D; ++c) {
-    k[c] = Elem<T>::load(Ku + (size_t)(ok ? i : P) * D + c);
-    ss = __builtin_fmaf(k[c], k[c], ss);
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (M == 0) {  // no seed to fold into: nothing to read
+    const int end = min(hi, first + n_tiles * kDonorTile);
+    for (int i = first + tid; i < end; i += 256) assign_ord[row0 + i] = -1;
+    return;
   }
-  const float dinv = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
-  float best = kNegInf;
-  int best_ord = -1;
-  for (int s0 = 0; s0 < M; s0 += SEEDS) {
-    __syncthreads();
-    for (int q = tid; q < SEEDS * D; q += 256) {
-      const int sr = q / D, c = q % D;
-      sk[sr][c] = (s0 + sr < M) ? Elem<T>::load(Ku + (size_t)srow[s0 + sr] * D + c) : 0.f;
-    }
-    __syncthreads();
-    if (tid < SEEDS) {
-      float t = 0.f;
-      for (int c = 0; c < D; ++c) t = __builtin_fmaf(sk[tid][c], sk[tid][c], t);
-      sinv[tid] = t > 0.f ? 1.0f / sqrtf(t) : 0.f;
-    }
-    __syncthreads();
-    const int lim = min(SEEDS, M - s0);
-    for (int sr = 0; sr < lim; ++sr) {
-      const int gap = srow[s0 + sr] > i ? srow[s0 + sr] - i : i - srow[s0 + sr];
-      if (kp.radius > 0 && gap > kp.radius) continue;
-      float dot = 0.f;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: feeds scalar load offsets
+  const int l16 = lane & 15, g = lane >> 4;
+  const float* Ku = K + (size_t)row0 * D;
+  const uint8_t* ro = role + row0;
+  const int32_t* srow = seed_rows + (size_t)u * kp.B;
+  // rows past this workgroup's share of the donor range read as zero through the descriptor's
+  // bounds check, without touching memory
+  const int last = min(hi, first + n_tiles * kDonorTile);
+  const __amdgpu_buffer_rsrc_t krsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(Ku), 0, (int)((unsigned)last * (unsigned)kRowBytes), 0x00020000);
+
+  // ---- donor stream (the role of the lane's donor rides along, so that nothing at the end of a
+  // tile has to wait on memory behind the loads already issued for the tiles after it)
+  f32x4 dreg[kRing][KS];
+  int rreg[kRing];
+  const int k_off = l16 * kRowBytes + g * 16;
+  auto fetch_donors = [&](int t, f32x4 (&d)[KS], int& rl) {
+    // Always issued, also for tiles past the end (their rows read as zero and are never
+    // stored): with an unconditional load count the waits for a tile can leave the loads of
+    // the tiles after it in flight.
+    const int r0 = first + t * kDonorTile + wv * 16;
+    rl = (int)ro[min(r0 + l16, N - 1)];
 #pragma unroll
-      for (int c = 0; c < D; ++c) dot = __builtin_fmaf(k[c], sk[sr][c], dot);
-      const float sim = (dot * sinv[sr]) * dinv;
-      if (sim > best) {
-        best = sim;
-        best_ord = s0 + sr;
+    for (int ks = 0; ks < KS; ++ks)
+      d[ks] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+          krsrc, k_off + ks * 64, (int)((unsigned)r0 * (unsigned)kRowBytes), 0));
+  };
+  // ---- seeds [sb, sb + kSeeds) -> LDS (a thread per 16-byte piece) + inverse norms
+  auto stage_seeds = [&](int sb) {
+    constexpr int kPieces = kRowBytes / 16, kPassRows = 256 / kPieces;
+    const int piece = tid % kPieces, prow = tid / kPieces;
+    for (int s0 = 0; s0 < kSeeds && sb + s0 < M; s0 += 4 * kPassRows) {
+      int idx[4];
+      f32x4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int ord = sb + s0 + i * kPassRows + prow;
+        idx[i] = ord < M ? srow[ord] : -1;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (idx[i] >= 0) v[i] = reinterpret_cast<const f32x4*>(Ku + (size_t)idx[i] * D)[piece];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int sr = s0 + i * kPassRows + prow;
+        *reinterpret_cast<f32x4*>(seeds + sr * kSeedPitch + piece * 16) = v[i];
+        float ss = sumsq_f32x4(v[i]);
+#pragma unroll
+        for (int o = kPieces / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+        if (piece == 0) {
+          seed_inv[sr] = idx[i] < 0 ? __builtin_nanf("") : (ss > 0.f ? 1.0f / sqrtf(ss) : 0.f);
+          seed_pos[sr] = idx[i];
+        }
       }
     }
-  }
-  if (ok) {
-    const bool donor = role[row0 + i] == CASK_ROLE_DONOR;
-    assign_ord[row0 + i] = (donor && best_ord >= 0 && best >= kp.tau) ? best_ord : -1;
+  };
+  // merge radius (0 = none): seeds further than this many cache rows from the donor are skipped
+  const int radius = kp.radius > 0 ? kp.radius : 0x7fffffff;
+
+  // inverse norm of the lane's donor (every lane group holds a quarter of its channels)
+  auto inverse_norm = [&](const f32x4 (&d)[KS]) {
+    float ss = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) ss += sumsq_f32x4(d[ks]);
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    return ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+  };
+  // The lane's donor against the staged seeds [sb, sb + m_blk), ascending ordinal: first maximum wins.
+  auto against_block = [&](int sb, int m_blk, const f32x4 (&d)[KS], float dinv, int drow, float& best, int& best_ord) {
+    for (int s0 = 0; s0 < m_blk; s0 += 16) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(seeds + (s0 + l16) * kSeedPitch + (ks * 4 + g) * 16);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], d[ks][e], acc, 0, 0, 0);
+      }
+      const f32x4 si = *reinterpret_cast<const f32x4*>(&seed_inv[s0 + g * 4]);
+      int pos[4] = {0, 0, 0, 0};
+      if (RADIUS) {
+        const int4 sp = *reinterpret_cast<const int4*>(&seed_pos[s0 + g * 4]);
+        pos[0] = sp.x, pos[1] = sp.y, pos[2] = sp.z, pos[3] = sp.w;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float sim = (acc[r] * si[r]) * dinv;
+        bool near = true;
+        if (RADIUS) near = (pos[r] > drow ? pos[r] - drow : drow - pos[r]) <= radius;
+        if (near && sim > best) {
+          best = sim;
+          best_ord = sb + s0 + g * 4 + r;
+        }
+      }
+    }
+  };
+  // the four lane groups hold different seeds of a donor: lowest ordinal wins a tie
+  auto settle = [&](float best, int best_ord, int rl, int drow) {
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const float ob = __shfl_xor(best, o, 64);
+      const int oo = __shfl_xor(best_ord, o, 64);
+      if (oo >= 0 && (best_ord < 0 || better(ob, oo, best, best_ord))) {
+        best = ob;
+        best_ord = oo;
+      }
+    }
+    if (g == 0 && drow < last)  // rows past the workgroup's share belong to another one
+      assign_ord[row0 + drow] = (rl == CASK_ROLE_DONOR && best_ord >= 0 && best >= kp.tau) ? best_ord : -1;
+  };
+
+  if constexpr (ONE_BLOCK) {
+#pragma unroll
+    for (int t = 0; t < kRing; ++t) fetch_donors(t, dreg[t], rreg[t]);
+    stage_seeds(0);
+    __syncthreads();
+    for (int t0 = 0; t0 < n_tiles; t0 += kRing) {
+#pragma unroll
+      for (int b = 0; b < kRing; ++b) {
+        const int drow = first + (t0 + b) * kDonorTile + wv * 16 + l16;
+        float best = kNegInf;
+        int best_ord = -1;
+        against_block(0, M, dreg[b], inverse_norm(dreg[b]), drow, best, best_ord);
+        settle(best, best_ord, rreg[b], drow);
+        fetch_donors(t0 + b + kRing, dreg[b], rreg[b]);  // refill the registers just freed
+      }
+    }
+  } else {
+    // a block of seeds meets every tile of the workgroup (at most kMultiTiles), whose best seeds
+    // so far wait in registers, as in the bf16 kernel
+    float best[kMultiTiles];
+    int best_ord[kMultiTiles], donor[kMultiTiles];
+#pragma unroll
+    for (int t = 0; t < kMultiTiles; ++t) {
+      best[t] = kNegInf;
+      best_ord[t] = -1;
+      donor[t] = CASK_ROLE_PREFIX_DROP;
+    }
+    for (int sb = 0; sb < M; sb += kSeeds) {
+      if (sb > 0) __syncthreads();  // previous block fully consumed
+#pragma unroll
+      for (int t = 0; t < kRing; ++t) fetch_donors(t, dreg[t], rreg[t]);
+      stage_seeds(sb);
+      __syncthreads();
+      const int m_blk = min(kSeeds, M - sb);
+      static_assert(kMultiTiles % kRing == 0, "whole rounds of the register ring");
+#pragma unroll
+      for (int t = 0; t < kMultiTiles; ++t) {
+        if (t < n_tiles) {  // (the same for the whole workgroup)
+          donor[t] = rreg[t % kRing];
+          against_block(sb, m_blk, dreg[t % kRing], inverse_norm(dreg[t % kRing]), first + t * kDonorTile + wv * 16 + l16,
+                        best[t], best_ord[t]);
+          fetch_donors(t + kRing, dreg[t % kRing], rreg[t % kRing]);
+        }
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < kMultiTiles; ++t)
+      if (t < n_tiles) settle(best[t], best_ord[t], donor[t], first + t * kDonorTile + wv * 16 + l16);
   }
 }
 
@@ -1142,15 +1304,26 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
   }
 }
 
-template <typename T, int D>
-hipError_t launch_similarity_fma(const KParams& kp, const Batch& b, const uint8_t* role,
-                                 const int32_t* seed_rows, const int32_t* n_seeds,
-                                 int32_t* assign_ord, hipStream_t st) {
-  const int tiles = (b.max_decode_len + 255) / 256;
+template <int D>
+hipError_t launch_similarity_f32(const KParams& kp, const Batch& b, const uint8_t* role,
+                                 const int32_t* seed_rows, const int32_t* n_seeds, int32_t* assign_ord,
+                                 bool roles_follow_plan, hipStream_t st) {
+  using SG = SimF32Geom<D>;
+  const int tiles = (b.max_decode_len + SG::kDonorTile - 1) / SG::kDonorTile;
   if (tiles == 0) return hipSuccess;
-  similarity_fma_kernel<T, D><<<dim3(b.n_units * tiles), dim3(256), 0, st>>>(
-      kp, b.n_units, tiles, b.row_off, b.prefix_len, static_cast<const T*>(b.K), role, seed_rows,
-      n_seeds, assign_ord);
+  // chunks of a unit as for bf16 caches; beyond kF32Slots units pieces of about 32 tiles
+  int chunks = b.n_units > 0 ? kF32Slots / b.n_units : 1;
+  if (chunks < 1) chunks = (tiles + 31) / 32;
+  if (chunks > tiles) chunks = tiles;
+  const bool one = roles_follow_plan && plan_seed_bound(kp) <= SG::kSeeds;
+  int tiles_per_wg = (tiles + chunks - 1) / chunks;
+  if (!one && tiles_per_wg > kMultiTiles) tiles_per_wg = kMultiTiles;
+  chunks = (tiles + tiles_per_wg - 1) / tiles_per_wg;
+  const int units8 = (b.n_units + 7) / 8 * 8;
+  auto kern = kp.radius > 0 ? (one ? &similarity_f32_kernel<D, true, true> : &similarity_f32_kernel<D, false, true>)
+                            : (one ? &similarity_f32_kernel<D, true, false> : &similarity_f32_kernel<D, false, false>);
+  kern<<<dim3(units8 * chunks), dim3(256), 0, st>>>(kp, b.n_units, chunks, tiles_per_wg, b.row_off, b.prefix_len,
+                                                    static_cast<const float*>(b.K), role, seed_rows, n_seeds, assign_ord);
   return hipGetLastError();
 }
 
@@ -1199,8 +1372,8 @@ hipError_t launch_similarity(const KParams& kp, const Batch& b, const uint8_t* r
 #undef CASK_SIM
     return hipGetLastError();
   }
-  return kp.d == 64 ? launch_similarity_fma<float, 64>(kp, b, role, seed_rows, n_seeds, assign_ord, st)
-                    : launch_similarity_fma<float, 128>(kp, b, role, seed_rows, n_seeds, assign_ord, st);
+  return kp.d == 64 ? launch_similarity_f32<64>(kp, b, role, seed_rows, n_seeds, assign_ord, roles_follow_plan, st)
+                    : launch_similarity_f32<128>(kp, b, role, seed_rows, n_seeds, assign_ord, roles_follow_plan, st);
 }
 
 hipError_t launch_gather_merged(const KParams& kp, const Batch& b, const uint8_t* role,

@@ -9,12 +9,12 @@
 // Logits are never stored: recomputing the contraction on the matrix cores is cheaper than
 // writing and re-reading a W*G x N fp32 matrix through HBM.
 //
-// bf16, d = 128: both sweeps use one MFMA kernel (32x32x16 bf16 tiles, fp32 accumulation).
+// bf16: both sweeps use one MFMA kernel (32x32x16 bf16 tiles, fp32 accumulation).
 // One operand ("resident") stays in registers for the whole loop, the other ("stream") is
 // staged through LDS.  The product tile is stream x resident^T, so each lane owns ONE
 // resident column and 16 stream rows: the reduction over the stream dimension (keys in
 // sweep A, window rows in sweep B) stays inside a lane until the very end.
-// Other dtypes/head sizes take a plain FMA kernel with the same two-sweep structure.
+// fp32 caches take a simpler kernel of the same structure on fp32 matrix tiles.
 #include "cask_common.h"
 
 namespace cask {
@@ -32,24 +32,6 @@ __device__ inline void ml_combine(float& m, float& l, float m2, float l2) {
   const float b = (m2 == kNegInf) ? 0.f : fast_exp2(m2 - M);
   l = l * a + l2 * b;
   m = M;
-}
-
-// -L_row (base-2) of every window row from the per-split partials; -inf for padding rows.
-// Fills negL[0, n_fill); rows >= Mq get -inf.  `pitch` is the row pitch of the partials.
-__device__ inline void fill_neg_lse(const float2* __restrict__ part, int n_splits, int n_fill,
-                                    int Mq, float* negL, int tid, int nthreads, int pitch) {
-  for (int r = tid; r < n_fill; r += nthreads) {
-    float v = kNegInf;
-    if (r < Mq) {
-      float m = kNegInf, l = 0.f;
-      for (int s = 0; s < n_splits; ++s) {
-        const float2 p = part[(size_t)s * pitch + r];
-        ml_combine(m, l, p.x, p.y);
-      }
-      v = -(m + log2f(l));
-    }
-    negL[r] = v;
-  }
 }
 
 // XCD-aware block -> (unit, tile): consecutive workgroups go round-robin over the 8 XCDs, so
@@ -965,107 +947,225 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   }
 }
 
-// ------------------------------------------------------------------ plain FMA path
+// ------------------------------------------------------------------ fp32 caches
 
-// Sweep A: thread = (window row, key sub-range); q row in registers, keys read by the whole
-// wave at the same address (broadcast).
-template <typename T, int D>
-__global__ __launch_bounds__(256) void score_rows_fma_kernel(
+// What the head dimension decides about a ring slot of the fp32 sweeps (32 stream rows).
+template <int D>
+struct F32Geom {
+  static constexpr int kRowBytes = D * 4;
+  static constexpr int kStageRows = 32;
+  static constexpr int kGroupRows = 1024 / kRowBytes;            // rows one load instruction of a wave lands: 2 or 4
+  static constexpr int kGroupPitch = 1024 + kGroupRows * 16;
+  static constexpr int kDataBytes = (kStageRows / kGroupRows) * kGroupPitch;
+  static constexpr int kStageBytes = kDataBytes + 256;           // + -L_row (sweep B; a load instruction's 64 floats)
+  static constexpr int kLoads = kStageRows / kGroupRows / kWaves;  // load instructions per wave and stage
+};
+constexpr int kF32Depth = 3;  // ring slots; three workgroups' rings fit a compute unit
+
+// Both scoring sweeps of an fp32 cache on the fp32 matrix tiles (32x32x2: fp32 products and sums, a
+// chain of D / 2 per tile).  MODE 0 = sweep A (resident: window rows, stream: keys), MODE 1 = sweep B
+// (resident: keys, stream: window rows), as for bf16 above: a wave keeps 32 resident rows as B
+// operands in registers, stream rows arrive 32 at a time through a ring of LDS slots in the same
+// piece-major layout, and a lane owns one resident row and 16 stream rows of a tile.
+//
+// The matrix pipe is the bound: a tile is 64 products of 64 cycles (D = 128) against 16 LDS reads
+// and about 300 cycles of exponentials, so one resident tile per wave is enough and nothing has to be
+// interleaved by hand -- three waves per SIMD from independent workgroups fill the gaps.  The same
+// reason lets sweep A carry a true running maximum.
+// Measured, 32 units of 4096 rows, 256 window rows, d = 128 (@@F32@@); a thread per window row, then
+// per key, on the vector units took 465 + 495 us.
+template <int D, int MODE>
+__global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
     KParams kp, int n_units, int tiles_per_unit, int n_splits, int split_len, int mq_pad,
-    const int64_t* __restrict__ row_off, const T* __restrict__ K, const T* __restrict__ Q,
-    float2* __restrict__ rowstat) {
-  __shared__ float2 xch[256];
+    const int64_t* __restrict__ row_off, const float* __restrict__ K, const float* __restrict__ Q,
+    float2* __restrict__ rowstat, const float* __restrict__ bias, float* __restrict__ bias_out,
+    float* __restrict__ scores) {
+  using SG = F32Geom<D>;
+  constexpr int kRowBytes = SG::kRowBytes, kGroupRows = SG::kGroupRows, kGroupPitch = SG::kGroupPitch;
+  constexpr int kStageRows = SG::kStageRows, kDataBytes = SG::kDataBytes, kStageBytes = SG::kStageBytes;
+  constexpr int kLoads = SG::kLoads;
+  constexpr int kRes = kWaves * 32;  // resident rows per workgroup
+  constexpr int NP = D / 8;          // 16-byte pieces of a row per lane
+  __shared__ __attribute__((aligned(16))) unsigned char ring[kF32Depth * kStageBytes];
   int unit, tile;
   if (!map_block(n_units, tiles_per_unit, unit, tile)) return;
-  const int tid = threadIdx.x, lane = tid & 63, sub = tid >> 6;
-  const int qb = tile / n_splits, split = tile % n_splits;
-  const int row = qb * 64 + lane;
-  const int Mq = kp.Mq;
-  if (qb * 64 >= Mq) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c32 = lane & 31, h = lane >> 5;
   const int64_t row0 = row_off[unit];
   const int N = (int)(row_off[unit + 1] - row0);
-  const bool ok = row < Mq;
-  float q[D];
-  const T* qp = Q + ((size_t)unit * Mq + (ok ? row : 0)) * D;
-#pragma unroll
-  for (int i = 0; i < D; ++i) q[i] = Elem<T>::load(qp + i);
-  int k_begin = split * split_len;
-  int k_end = min(N, k_begin + split_len);
-  const int quarter = (split_len + 3) / 4;
-  k_begin += sub * quarter;
-  k_end = min(k_end, k_begin + quarter);
-  const int last_vis = kp.causal ? N - kp.W + (ok ? row : 0) / kp.G : N - 1;
-  k_end = min(k_end, last_vis + 1);
-  float m = kNegInf, l = 0.f;
-  for (int j = k_begin; j < k_end; ++j) {
-    const T* kr = K + (size_t)(row0 + j) * D;
-    float dot = 0.f;
-#pragma unroll
-    for (int i = 0; i < D; ++i) dot = __builtin_fmaf(q[i], Elem<T>::load(kr + i), dot);
-    const float y = dot * kp.scale_log2;
-    const float m_new = fmaxf(m, y);
-    l = l * fast_exp2(m - m_new) + fast_exp2(y - m_new);
-    m = m_new;
+  const int Mq = kp.Mq, W = kp.W, Gq = kp.G;
+  const float c = kp.scale_log2;
+  const float* Ku = K + (size_t)row0 * D;
+  const float* Qu = Q + (size_t)unit * Mq * D;
+
+  // ---- what this workgroup covers: resident rows [res_base, ..), stream rows [s_begin, s_end)
+  const float *res_ptr, *str_ptr;
+  int res_base, res_limit, s_begin, s_end, split = 0;
+  if (MODE == 0) {
+    res_base = tile / n_splits * kRes;
+    split = tile % n_splits;
+    if (res_base >= Mq) return;
+    res_ptr = Qu;
+    res_limit = Mq;
+    str_ptr = Ku;
+    s_begin = split * split_len;
+    s_end = min(N, s_begin + split_len);
+    if (kp.causal) s_end = min(s_end, N - W + (min(Mq, res_base + kRes) - 1) / Gq + 1);
+  } else {
+    res_base = tile * kRes;
+    if (res_base >= N) return;
+    res_ptr = Ku;
+    res_limit = N;
+    str_ptr = Qu;
+    s_begin = 0;
+    s_end = Mq;
+    if (kp.causal && res_base > N - W) s_begin = ((res_base - (N - W)) * Gq) / kStageRows * kStageRows;
   }
-  xch[tid] = make_float2(m, l);
-  __syncthreads();
-  if (sub == 0) {
-    for (int s = 1; s < 4; ++s) ml_combine(m, l, xch[s * 64 + lane].x, xch[s * 64 + lane].y);
-    if (ok) rowstat[((size_t)unit * n_splits + split) * mq_pad + row] = make_float2(m, l);
+  const int n_stages = s_end > s_begin ? (s_end - s_begin + kStageRows - 1) / kStageRows : 0;
+  const int res_row = res_base + wv * 32 + c32;  // the lane's resident row
+  const bool wave_live = res_base + wv * 32 < res_limit;
+
+  // rows past the end read as zero through the descriptors
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(str_ptr), 0, (int)((unsigned)max(s_end, 0) * (unsigned)kRowBytes), 0x00020000);
+  const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(bias + (size_t)unit * mq_pad), 0, mq_pad * 4, 0x00020000);
+  const int ld_voff = (wv * kGroupRows + lane % kGroupRows) * kRowBytes + (lane / kGroupRows) * 16;
+  auto issue_stage = [&](int stage) {  // (also past the last stage: the load count stays the same)
+    unsigned char* slot = ring + (stage % kF32Depth) * kStageBytes;
+    const unsigned soff = (unsigned)(s_begin + stage * kStageRows) * (unsigned)kRowBytes;
+    if (MODE == 1 && (stage & (kWaves - 1)) == wv)  // one wave in turn: first of the stage's loads, so it is waited for with them
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(brsrc, (__attribute__((address_space(3))) void*)(slot + kDataBytes), 4,
+                                               lane * 4, (s_begin + stage * kStageRows) * 4, 0, 0);
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc, (__attribute__((address_space(3))) void*)(slot + (wv + kWaves * j) * kGroupPitch), 16, ld_voff,
+          (int)(soff + j * (kWaves * 1024u)), 0, 0);
+  };
+  float res[NP * 4];
+  if (n_stages > 0) {
+#pragma unroll
+    for (int st = 0; st < kF32Depth - 1; ++st) issue_stage(st);
+  }
+  {
+    const float* rp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;  // a row past the end is not stored
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(rp + p * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) res[p * 4 + e] = v[e];
+    }
+  }
+  // take the wait for them here: inside the loop it would drain the ring
+#pragma unroll
+  for (int i = 0; i < NP * 4; ++i) asm volatile("" : "+v"(res[i]));
+
+  // stages [0, sk) show the wave nothing, [sk, f0) and [f1, n_stages) are partly masked
+  int sk = 0, f0 = 0, f1 = n_stages;
+  int lim = 0, first_row = 0;
+  if (MODE == 0) {
+    lim = min(s_end - 1, kp.causal ? N - W + res_row / Gq : N - 1);  // last key the lane's row sees
+    const int clean_rows = min((kp.causal ? N - W : N) + 1, s_end) - s_begin;
+    f1 = clean_rows > 0 ? min(n_stages, clean_rows / kStageRows) : 0;
+  } else if (kp.causal) {
+    const int k0 = res_base + wv * 32 - (N - W);  // the wave's oldest key, relative to the window
+    first_row = max(0, (res_row - (N - W)) * Gq);  // first window row that sees the lane's key
+    sk = max(0, min(n_stages, (max(0, k0 * Gq) - s_begin) / kStageRows));
+    f0 = max(sk, min(n_stages, (max(0, (k0 + 31) * Gq) - s_begin + kStageRows - 1) / kStageRows));
+  }
+  if (!wave_live) sk = n_stages;  // only loads and barriers
+
+  float m_ref = kNegInf, l_run = 0.f, colsum = 0.f;
+  const int a_off = (c32 / kGroupRows) * kGroupPitch + (c32 % kGroupRows) * 16 + h * (kGroupRows * 16);
+  for (int it = 0; it < n_stages; ++it) {
+    // this thread's loads of stage `it` have landed when only those of the next stage are in
+    // flight; the barrier extends that to the workgroup and frees the slot consumed before
+    __builtin_amdgcn_s_waitcnt(0x0F70 | kLoads);
+    __builtin_amdgcn_s_barrier();
+    issue_stage(it + kF32Depth - 1);
+    if (it < sk) continue;
+    const unsigned char* slot = ring + (it % kF32Depth) * kStageBytes;
+    f32x16 acc = {0};
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      // (read with the bf16 sweeps' operand type: LDS reads of other types are taken to alias the
+      // ring's loads in flight and would wait for all of them)
+      const f32x4 v = __builtin_bit_cast(f32x4, *reinterpret_cast<const bf16x8*>(slot + a_off + p * (2 * kGroupRows * 16)));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], res[p * 4 + e], acc, 0, 0, 0);
+    }
+    const int trow = s_begin + it * kStageRows + h * 4;  // first stream row of the lane
+    if (MODE == 0) {
+      if (it >= f1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (trow + (r >> 2) * 8 + (r & 3) > lim) acc[r] = kNegInf;
+      }
+      float xm = acc[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) xm = fmaxf(xm, acc[r]);
+      const float m_new = fmaxf(m_ref, xm * c);
+      const float nm = (m_new == kNegInf) ? 0.f : -m_new;
+      float sum = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum += fast_exp2(__builtin_fmaf(acc[r], c, nm));
+      l_run = l_run * fast_exp2(m_ref + nm) + sum;
+      m_ref = m_new;
+    } else {
+      float nl[16];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 v = __builtin_bit_cast(f32x4, *reinterpret_cast<const bf16x8*>(slot + kDataBytes + (g * 8 + h * 4) * 4));
+        nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
+      }
+      float sum = 0.f;
+      if (it < f0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float y = __builtin_fmaf(acc[r], c, nl[r]);
+          sum += fast_exp2(trow + (r >> 2) * 8 + (r & 3) < first_row ? kNegInf : y);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum += fast_exp2(__builtin_fmaf(acc[r], c, nl[r]));
+      }
+      colsum += sum;
+    }
+  }
+  // loads issued past the last stage may still be landing in LDS
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+
+  if (MODE == 0) {
+    const float m2 = __shfl_xor(m_ref, 32, 64), l2 = __shfl_xor(l_run, 32, 64);
+    ml_combine(m_ref, l_run, m2, l2);
+    if (h == 0 && res_row < Mq)
+      rowstat[((size_t)unit * n_splits + split) * mq_pad + res_row] = make_float2(m_ref, l_run);
+    if (n_splits == 1 && h == 0 && res_row < mq_pad)  // a single split is the whole row
+      bias_out[(size_t)unit * mq_pad + res_row] = res_row < Mq ? -(m_ref + log2f(l_run)) : kPadNegL;
+  } else {
+    const float tot = colsum + __shfl_xor(colsum, 32, 64);
+    if (h == 0 && res_row < N) scores[row0 + res_row] = tot * (1.0f / (float)Mq);
   }
 }
 
-// Sweep B: thread = key; key row in registers, window rows read at a wave-uniform address.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void score_cols_fma_kernel(
-    KParams kp, int n_units, int tiles_per_unit, int n_splits, int mq_pad,
-    const int64_t* __restrict__ row_off, const T* __restrict__ K, const T* __restrict__ Q,
-    const float2* __restrict__ rowstat, float* __restrict__ scores) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* negL = reinterpret_cast<float*>(smem);
-  int unit, tile;
-  if (!map_block(n_units, tiles_per_unit, unit, tile)) return;
-  const int tid = threadIdx.x;
-  const int64_t row0 = row_off[unit];
-  const int N = (int)(row_off[unit + 1] - row0);
-  if (tile * 256 >= N) return;
-  const int Mq = kp.Mq;
-  fill_neg_lse(rowstat + (size_t)unit * n_splits * mq_pad, n_splits, mq_pad, Mq, negL, tid, 256, mq_pad);
-  __syncthreads();
-  const int j = tile * 256 + tid;
-  const bool ok = j < N;
-  float k[D];
-  const T* kr = K + (size_t)(row0 + (ok ? j : 0)) * D;
-#pragma unroll
-  for (int i = 0; i < D; ++i) k[i] = Elem<T>::load(kr + i);
-  float sum = 0.f;
-  for (int r = 0; r < Mq; ++r) {
-    const int tw = kp.causal ? N - kp.W + r / kp.G : N - 1;
-    if (j > tw) continue;
-    const T* qp = Q + ((size_t)unit * Mq + r) * D;
-    float dot = 0.f;
-#pragma unroll
-    for (int i = 0; i < D; ++i) dot = __builtin_fmaf(k[i], Elem<T>::load(qp + i), dot);
-    sum += fast_exp2(__builtin_fmaf(dot, kp.scale_log2, negL[r]));
-  }
-  if (ok) scores[row0 + j] = sum * (1.0f / (float)Mq);
-}
-
-template <typename T, int D>
-hipError_t launch_fma(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
-                      float* scores, hipStream_t st, hipEvent_t between) {
+template <int D>
+hipError_t launch_score_f32(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
+                            float* scores, hipStream_t st, hipEvent_t between) {
   float2* rowstat = reinterpret_cast<float2*>(ws + wl.rowstat);
+  float* bias = reinterpret_cast<float*>(ws + wl.bias);
+  const float *K = static_cast<const float*>(b.K), *Q = static_cast<const float*>(b.Q);
   const int units8 = (b.n_units + 7) / 8 * 8;
-  const int qblocks = (kp.Mq + 63) / 64;
-  const int tilesA = qblocks * wl.n_splits;
-  score_rows_fma_kernel<T, D><<<dim3(units8 * tilesA), dim3(256), 0, st>>>(
-      kp, b.n_units, tilesA, wl.n_splits, wl.split_len, wl.mq_pad, b.row_off,
-      static_cast<const T*>(b.K), static_cast<const T*>(b.Q), rowstat);
+  const int tilesA = (kp.Mq + kWaves * 32 - 1) / (kWaves * 32) * wl.n_splits;
+  score_f32_kernel<D, 0><<<dim3(units8 * tilesA), dim3(kThreads), 0, st>>>(
+      kp, b.n_units, tilesA, wl.n_splits, wl.split_len, wl.mq_pad, b.row_off, K, Q, rowstat, nullptr, bias, scores);
   if (between) (void)hipEventRecord(between, st);
-  const int tilesB = (b.max_unit_len + 255) / 256;
-  score_cols_fma_kernel<T, D><<<dim3(units8 * tilesB), dim3(256), wl.mq_pad * sizeof(float), st>>>(
-      kp, b.n_units, tilesB, wl.n_splits, wl.mq_pad, b.row_off, static_cast<const T*>(b.K),
-      static_cast<const T*>(b.Q), rowstat, scores);
+  if (wl.n_splits > 1)
+    score_bias_kernel<<<dim3(b.n_units), dim3(kBiasThreads), 0, st>>>(kp, wl.n_splits, wl.mq_pad, rowstat, bias);
+  const int tilesB = (b.max_unit_len + kWaves * 32 - 1) / (kWaves * 32);
+  score_f32_kernel<D, 1><<<dim3(units8 * tilesB), dim3(kThreads), 0, st>>>(
+      kp, b.n_units, tilesB, wl.n_splits, wl.split_len, wl.mq_pad, b.row_off, K, Q, rowstat, bias, nullptr, scores);
   return hipGetLastError();
 }
 
@@ -1128,8 +1228,8 @@ hipError_t launch_score_mfma(const KParams& kp, const Batch& b, const Workspace&
 hipError_t launch_score(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
                         float* scores, hipStream_t st, hipEvent_t between) {
   if (kp.dtype == CASK_F32)
-    return kp.d == 64 ? launch_fma<float, 64>(kp, b, wl, ws, scores, st, between)
-                      : launch_fma<float, 128>(kp, b, wl, ws, scores, st, between);
+    return kp.d == 64 ? launch_score_f32<64>(kp, b, wl, ws, scores, st, between)
+                      : launch_score_f32<128>(kp, b, wl, ws, scores, st, between);
   return kp.d == 64 ? launch_score_mfma<64>(kp, b, wl, ws, scores, st, between)
                     : launch_score_mfma<128>(kp, b, wl, ws, scores, st, between);
 }

@@ -52,6 +52,28 @@ def test_scores_with_64_channels(G, Wn, causal, splits, form):
     _note(form, G, Wn, causal, "score error / max", parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,Wn,causal,splits", [(4, 64, 1, 0), (7, 100, 1, 3), (1, 17, 1, 0), (4, 128, 0, 64), (1, 33, 0, 1)])
+def test_fp32_scores_on_the_matrix_tiles(G, Wn, causal, splits, d):
+    """fp32 scores: units of a window, a 32-row tile, a workgroup's 128 rows and one more.  Bar: 1e-5 of
+    the unit's largest score (logits of up to 128 products and sums of at most a few thousand terms
+    in fp32, relative errors below 3e-6 in all)."""
+    lens = [Wn, Wn + 1, 129, 128, 160, 257, 1025, 1599, 4097]
+    pref = [0, 1, 0, 0, 40, 100, 0, 333, 50]
+    c = _units(lens, pref, head_dim=d, q_per_kv=G, window=Wn)
+    noise = torch.Generator().manual_seed(d)
+    c = {k: (v.float() * (1 + 1e-3 * torch.randn(v.shape, generator=noise)) if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    p = cask.Params(dtype=cask.F32, head_dim=d, q_per_kv=G, window=Wn, causal=causal, budget=Wn + 60, score_splits=splits)
+    row_off, _, K, _, Q = parity.host_arrays(c)
+    b = parity.to_device(c, p)
+    s = cask.score(b)
+    s2 = cask.score(b, torch.full_like(s, 7.0))
+    torch.cuda.synchronize()
+    assert torch.equal(s, s2)
+    _note(d, G, Wn, causal, "score error / max",
+          parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off, rel=1e-5))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d,G,stride,n", [(128, 7, 1025, 12), (64, 16, 530, 12), (128, 17, 97, 12), (64, 1, 2000, 3), (128, 5, 9001, 3)])
 def test_attention_tiles_splits_and_rows_past_the_end(d, G, stride, n, dtype):
