@@ -22,14 +22,14 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // Measured on this kernel, a launch takes about (rounds of 512 workgroups, rounded up to a
   // half) x (stages per workgroup + 4), a stage of the wide form counting 1.85 narrow ones (twice
   // the products, less LDS traffic per product); take the split count that minimises it.
-  auto best_splits = [&](bool wide, double* cost_out) {
+  auto best_splits = [&](bool wide, int shortest, int most, double* cost_out) {
     const int block_rows = wide ? 512 : 256;
     const int64_t pairs = (int64_t)n_units * ((kp.Mq + block_rows - 1) / block_rows);
     int best = 1;
     double best_cost = 0.0;
-    for (int sp = 1; sp <= 64; ++sp) {
+    for (int sp = 1; sp <= most; ++sp) {
       const int len = (int)align_up((size_t)(max_unit_len + sp - 1) / sp, 64);
-      if (sp > 1 && len < 1024) break;
+      if (sp > 1 && len < shortest) break;
       const int eff = len > 0 ? (max_unit_len + len - 1) / len : 1;
       const int64_t wgs = pairs * eff;
       const double rounds = 0.5 * (double)((wgs + 255) / 256);
@@ -46,28 +46,41 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // read from LDS serves four products) when that leaves no more waves idle than 64 per wave
   // (256 per workgroup) does (W*G = 896, 1024, 512, 384: yes; 640, 768: no) and the model above
   // does not prefer the narrow form (small batches: twice as many workgroups fill more of the chip).
-  double cost_n = 0.0, cost_w = 0.0;
-  const int splits_n = best_splits(false, &cost_n), splits_w = best_splits(true, &cost_w);
-  {
+  int sized;  // key splits the layout has room for on their own
+  auto choose = [&](int shortest, int most) {
+    double cost_n = 0.0, cost_w = 0.0;
+    const int splits_n = best_splits(false, shortest, most, &cost_n), splits_w = best_splits(true, shortest, most, &cost_w);
     const int live_w = (kp.Mq + 127) / 128, all_w = (kp.Mq + 511) / 512 * 4;
     const int live_n = (kp.Mq + 63) / 64, all_n = (kp.Mq + 255) / 256 * 4;
     w.wide_rows = (kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) w.wide_rows = 1;
     if (kp.path_flags & CASK_PATH_NARROW_ROWS) w.wide_rows = 0;
-  }
-  int n_splits = w.wide_rows ? splits_w : splits_n;
+    return w.wide_rows ? splits_w : splits_n;
+  };
+  auto whole_stages = [&](int n, int* len_out) {  // splits of whole stages that cover the longest unit
+    int len = (int)align_up((size_t)(max_unit_len + n - 1) / n, 64);
+    if (len < 64) len = 64;
+    *len_out = len;
+    const int k = (max_unit_len + len - 1) / len;
+    return k < 1 ? 1 : k;
+  };
+  int n_splits = choose(1024, 64), split_len;
+  if (kp.score_splits >= 1) n_splits = kp.score_splits;
+  sized = n_splits = whole_stages(n_splits, &split_len);
   // Row pitch of the one-launch scoring's partial sums (bf16 only; laid out below).
   const int len64 = (int)align_up((size_t)(max_unit_len > 0 ? max_unit_len : 1), 64);
   w.parts_pitch = len64 < 1024 ? len64 : 1024;
-  if (kp.dtype == CASK_F32) {
+  // Small batches are cut finer than the 1024 keys above: the statistics of the additional splits
+  // lie over those partial sums, which no batch with more than one split uses (128 keys of their
+  // pitch give the space of one split), so that the workspace does not grow.
+  const int most = sized + w.parts_pitch / 128 < 64 ? sized + w.parts_pitch / 128 : 64;
+  if (kp.score_splits < 1 && kp.dtype == CASK_F32) {
     // 128 window rows per workgroup, 32 keys a stage, matrix-bound: the time is that of the fullest
-    // compute unit, its stages plus about two per workgroup.  The splits' row statistics take the
-    // place of the partial sums, 128 keys of whose pitch are worth one split: no more than that, so
-    // that an fp32 batch's workspace is no larger than a bf16 one's.
-    const int most = n_splits + w.parts_pitch / 128;
+    // compute unit, its stages plus about two per workgroup (measured within 5 % of the best of
+    // 2 - 16 splits on 32 x 4096, 8 x 15129 and 5 x 3129 rows).
     const int64_t pairs = (int64_t)n_units * ((kp.Mq + 127) / 128);
     double best_cost = 0.0;
-    for (int sp = 1, best = 1; sp <= most && sp <= 64; ++sp) {
+    for (int sp = 1, best = 1; sp <= most; ++sp) {
       const int len = (int)align_up((size_t)(max_unit_len + sp - 1) / sp, 64);
       if (sp > 1 && len < 256) break;
       const int64_t wgs = pairs * (len > 0 ? (max_unit_len + len - 1) / len : 1);
@@ -75,13 +88,10 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
       if (sp == 1 || cost < best_cost) best_cost = cost, best = sp;
       n_splits = best;
     }
-    w.parts_pitch = 0;
+    n_splits = whole_stages(n_splits, &split_len);
+  } else if (kp.score_splits < 1 && max_unit_len > 1024) {
+    n_splits = whole_stages(choose(512, most), &split_len);
   }
-  if (kp.score_splits >= 1) n_splits = kp.score_splits;
-  int split_len = (int)align_up((size_t)(max_unit_len + n_splits - 1) / n_splits, 64);
-  if (split_len < 64) split_len = 64;
-  n_splits = (max_unit_len + split_len - 1) / split_len;
-  if (n_splits < 1) n_splits = 1;
   w.n_splits = n_splits;
   // Sweep B of a batch of short units has few workgroups (one per 256 keys), each paying its
   // fixed cost for all W*G window rows: two workgroups then share a key tile, one half of the
@@ -89,14 +99,14 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // change the result).
   w.q_splits = 1;
   {
-    const int64_t wgsB = (int64_t)((n_units + 7) / 8 * 8) * ((max_unit_len + 255) / 256);
+    const int64_t wgsB = (int64_t)n_units * ((max_unit_len + 255) / 256);
     if (wgsB <= 384 && kp.Mq >= 512) w.q_splits = 2;  // measured: helps up to about 1.5 rounds of the 512 slots
     if (kp.score_qsplit >= 1) w.q_splits = kp.score_qsplit;
   }
   // Sweep B with 128 resident keys per wave (512 per workgroup) when that still leaves at least
   // two rounds of workgroups
   {
-    const int64_t wgs_wide = (int64_t)((n_units + 7) / 8 * 8) * ((max_unit_len + 511) / 512);
+    const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
     w.wide_cols = (w.q_splits == 1 && wgs_wide >= 1024) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) {
       w.wide_cols = 1;
@@ -117,7 +127,8 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // (reserved whatever the unit length, capped at the longest unit that path takes, so that a
   // workspace sized for longer units also serves a batch of shorter ones)
   w.parts = take(units * (size_t)((kp.Mq + 63) / 64) * (size_t)w.parts_pitch * sizeof(float));
-  w.rowstat = take(units * n_splits * w.mq_pad * sizeof(float2));
+  w.rowstat = take(units * sized * w.mq_pad * sizeof(float2));
+  if (n_splits > sized) w.rowstat = w.parts;  // (then the partial sums are not used)
   w.bias = take(units * w.mq_pad * sizeof(float));
   w.scores = take(rows * sizeof(float));
   w.role = take(rows);

@@ -155,6 +155,32 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
+// XCD-aware block -> (unit, tile): consecutive workgroups go round-robin over the 8 XCDs.  Of the
+// units that make up whole groups of eight, unit u is pinned to XCD (u % 8) and its tiles are
+// consecutive on that XCD: what the tiles of a unit share (keys or queries) stays in one L2 while
+// they run, and units of different length even out.  The tiles of the one to seven units left
+// over are dealt to the XCDs in eight equal runs (pinned like the others they left up to seven XCDs
+// idle: an event on four units of 8448 rows 96 -> 80 us, finer key splits included).
+__device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int& tile) {
+  const int xcd = blockIdx.x & 7;
+  int k = blockIdx.x >> 3;
+  const int whole = (n_units >> 3) * tiles_per_unit;
+  if (k < whole) {
+    unit = (k / tiles_per_unit) * 8 + xcd;
+    tile = k % tiles_per_unit;
+    return true;
+  }
+  const int items = (n_units & 7) * tiles_per_unit, run = (items + 7) >> 3;
+  k -= whole;
+  const int item = xcd * run + k;
+  unit = (n_units & ~7) + item / tiles_per_unit;
+  tile = item % tiles_per_unit;
+  return k < run && item < items;
+}
+inline int mapped_blocks(int n_units, int tiles_per_unit) {
+  return (n_units >> 3) * tiles_per_unit * 8 + ((n_units & 7) * tiles_per_unit + 7) / 8 * 8;
+}
+
 // Raises a kernel's dynamic-LDS limit the first time the kernel is launched on a device (a
 // function attribute, not a stream operation).  One instance per kernel; safe to call from
 // several threads.

@@ -91,11 +91,8 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   __shared__ __attribute__((aligned(16))) unsigned char turn[4][kGroups * kGroupPitch];
   __shared__ __attribute__((aligned(16))) float seed_inv[kSeedBlock];
   __shared__ __attribute__((aligned(16))) int seed_pos[kSeedBlock];  // cache row of each staged seed
-  const int bid = blockIdx.x;
-  const int xcd = bid & 7, kk = bid >> 3;
-  const int u = (kk / chunks_per_unit) * 8 + xcd;
-  const int chunk = kk % chunks_per_unit;
-  if (u >= n_units) return;
+  int u, chunk;
+  if (!map_block(n_units, chunks_per_unit, u, chunk)) return;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];
@@ -364,11 +361,8 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
   __shared__ __attribute__((aligned(16))) unsigned char seeds[kSeeds * kSeedPitch];
   __shared__ __attribute__((aligned(16))) float seed_inv[kSeeds];
   __shared__ __attribute__((aligned(16))) int seed_pos[kSeeds];  // cache row of each staged seed
-  const int bid = blockIdx.x;
-  const int xcd = bid & 7, kk = bid >> 3;
-  const int u = (kk / chunks_per_unit) * 8 + xcd;
-  const int chunk = kk % chunks_per_unit;
-  if (u >= n_units) return;
+  int u, chunk;
+  if (!map_block(n_units, chunks_per_unit, u, chunk)) return;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];
@@ -1319,10 +1313,9 @@ hipError_t launch_similarity_f32(const KParams& kp, const Batch& b, const uint8_
   int tiles_per_wg = (tiles + chunks - 1) / chunks;
   if (!one && tiles_per_wg > kMultiTiles) tiles_per_wg = kMultiTiles;
   chunks = (tiles + tiles_per_wg - 1) / tiles_per_wg;
-  const int units8 = (b.n_units + 7) / 8 * 8;
   auto kern = kp.radius > 0 ? (one ? &similarity_f32_kernel<D, true, true> : &similarity_f32_kernel<D, false, true>)
                             : (one ? &similarity_f32_kernel<D, true, false> : &similarity_f32_kernel<D, false, false>);
-  kern<<<dim3(units8 * chunks), dim3(256), 0, st>>>(kp, b.n_units, chunks, tiles_per_wg, b.row_off, b.prefix_len,
+  kern<<<dim3(mapped_blocks(b.n_units, chunks)), dim3(256), 0, st>>>(kp, b.n_units, chunks, tiles_per_wg, b.row_off, b.prefix_len,
                                                     static_cast<const float*>(b.K), role, seed_rows, n_seeds, assign_ord);
   return hipGetLastError();
 }
@@ -1356,9 +1349,8 @@ hipError_t launch_similarity(const KParams& kp, const Batch& b, const uint8_t* r
     int tiles_per_wg = (tiles + chunks - 1) / chunks;
     if (!one && tiles_per_wg > kMultiTiles) tiles_per_wg = kMultiTiles;  // its tiles' results wait in registers
     chunks = (tiles + tiles_per_wg - 1) / tiles_per_wg;
-    const int units8 = (b.n_units + 7) / 8 * 8;
 #define CASK_SIM(D, ONE, RAD)                                                          \
-  similarity_mfma_kernel<D, ONE, RAD><<<dim3(units8 * chunks), dim3(256), 0, st>>>(    \
+  similarity_mfma_kernel<D, ONE, RAD><<<dim3(mapped_blocks(b.n_units, chunks)), dim3(256), 0, st>>>(    \
       kp, b.n_units, chunks, tiles_per_wg, b.row_off, b.prefix_len,                    \
       static_cast<const uint16_t*>(b.K), role, seed_rows, n_seeds, assign_ord)
 #define CASK_SIM_D(D)                                                        \

@@ -34,18 +34,6 @@ __device__ inline void ml_combine(float& m, float& l, float m2, float l2) {
   m = M;
 }
 
-// XCD-aware block -> (unit, tile): consecutive workgroups go round-robin over the 8 XCDs, so
-// unit u is pinned to XCD (u % 8) and its tiles are consecutive on that XCD: the unit's K
-// (sweep A) or Q (sweep B) stays in one L2 while its tiles run.
-__device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int& tile) {
-  const int bid = blockIdx.x;
-  const int xcd = bid & 7;
-  const int k = bid >> 3;
-  unit = (k / tiles_per_unit) * 8 + xcd;
-  tile = k % tiles_per_unit;
-  return unit < n_units;
-}
-
 // ------------------------------------------------------------------ MFMA path (bf16)
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -972,8 +960,8 @@ constexpr int kF32Depth = 3;  // ring slots; three workgroups' rings fit a compu
 // and about 300 cycles of exponentials, so one resident tile per wave is enough and nothing has to be
 // interleaved by hand -- three waves per SIMD from independent workgroups fill the gaps.  The same
 // reason lets sweep A carry a true running maximum.
-// Measured, 32 units of 4096 rows, 256 window rows, d = 128 (@@F32@@); a thread per window row, then
-// per key, on the vector units took 465 + 495 us.
+// Measured, 32 units of 4096 rows, 256 window rows, d = 128: 81 + 94 us (55 + 55 at the rate
+// of the fp32 matrix tiles); a thread per window row, then per key, on the vector units took 465 + 495.
 template <int D, int MODE>
 __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
     KParams kp, int n_units, int tiles_per_unit, int n_splits, int split_len, int mq_pad,
@@ -1156,15 +1144,14 @@ hipError_t launch_score_f32(const KParams& kp, const Batch& b, const Workspace& 
   float2* rowstat = reinterpret_cast<float2*>(ws + wl.rowstat);
   float* bias = reinterpret_cast<float*>(ws + wl.bias);
   const float *K = static_cast<const float*>(b.K), *Q = static_cast<const float*>(b.Q);
-  const int units8 = (b.n_units + 7) / 8 * 8;
   const int tilesA = (kp.Mq + kWaves * 32 - 1) / (kWaves * 32) * wl.n_splits;
-  score_f32_kernel<D, 0><<<dim3(units8 * tilesA), dim3(kThreads), 0, st>>>(
+  score_f32_kernel<D, 0><<<dim3(mapped_blocks(b.n_units, tilesA)), dim3(kThreads), 0, st>>>(
       kp, b.n_units, tilesA, wl.n_splits, wl.split_len, wl.mq_pad, b.row_off, K, Q, rowstat, nullptr, bias, scores);
   if (between) (void)hipEventRecord(between, st);
   if (wl.n_splits > 1)
     score_bias_kernel<<<dim3(b.n_units), dim3(kBiasThreads), 0, st>>>(kp, wl.n_splits, wl.mq_pad, rowstat, bias);
   const int tilesB = (b.max_unit_len + kWaves * 32 - 1) / (kWaves * 32);
-  score_f32_kernel<D, 1><<<dim3(units8 * tilesB), dim3(kThreads), 0, st>>>(
+  score_f32_kernel<D, 1><<<dim3(mapped_blocks(b.n_units, tilesB)), dim3(kThreads), 0, st>>>(
       kp, b.n_units, tilesB, wl.n_splits, wl.split_len, wl.mq_pad, b.row_off, K, Q, rowstat, bias, nullptr, scores);
   return hipGetLastError();
 }
@@ -1194,7 +1181,6 @@ hipError_t launch_score_mfma(const KParams& kp, const Batch& b, const Workspace&
                              hipStream_t st, hipEvent_t between) {
   float2* rowstat = reinterpret_cast<float2*>(ws + wl.rowstat);
   float* bias = reinterpret_cast<float*>(ws + wl.bias);
-  const int units8 = (b.n_units + 7) / 8 * 8;
   const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes;
   // W*G <= 512 (one wide row block per unit, eight stream stages per workgroup of sweep B): the
   // resident rows come through the ring (measured: both sweeps 3 - 4 % faster on the Llama-shaped
@@ -1202,12 +1188,12 @@ hipError_t launch_score_mfma(const KParams& kp, const Batch& b, const Workspace&
   const bool ring_res = kp.Mq <= 2 * kResRows;
   auto sweep_a = [&](auto kern, int block_rows) {
     const int tiles = (kp.Mq + block_rows - 1) / block_rows * wl.n_splits;
-    return kern(units8 * tiles, lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
+    return kern(mapped_blocks(b.n_units, tiles), lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
                 b.row_off, b.K, b.Q, rowstat, nullptr, bias, scores, nullptr, 0);
   };
   auto sweep_b = [&](auto kern, int block_rows) {
     const int tiles = (b.max_unit_len + block_rows - 1) / block_rows * wl.q_splits;
-    return kern(units8 * tiles, lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
+    return kern(mapped_blocks(b.n_units, tiles), lds, st, kp, b.n_units, tiles, wl.n_splits, wl.split_len, wl.q_splits, wl.mq_pad,
                 b.row_off, b.K, b.Q, rowstat, bias, nullptr, scores, nullptr, 0);
   };
   hipError_t e;
@@ -1267,7 +1253,7 @@ hipError_t launch_fused_sweeps(const KParams& kp, const Batch& b, const Workspac
   const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes + kResRows * sizeof(float) + 4 * kWaves * 64 * sizeof(float);
   const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
   const int whole = (b.max_unit_len + kStageRows - 1) / kStageRows * kStageRows;
-  return launch_sweep<D, 3, 2, false>((b.n_units + 7) / 8 * 8 * qblocks, lds, st, kp, b.n_units, qblocks, 1, whole, 1,
+  return launch_sweep<D, 3, 2, false>(mapped_blocks(b.n_units, qblocks), lds, st, kp, b.n_units, qblocks, 1, whole, 1,
                                       wl.mq_pad, b.row_off, b.K, b.Q, nullptr, nullptr, nullptr, scores, nullptr, 0);
 }
 
@@ -1275,7 +1261,7 @@ template <int D>
 hipError_t launch_sweeps_to_parts(const KParams& kp, const Batch& b, const Workspace& wl, float* parts, hipStream_t st) {
   const size_t lds = (size_t)kDepth * StageGeom<D>::kStageBytes + kResRows * sizeof(float);
   const int qblocks = (kp.Mq + kResRows - 1) / kResRows;
-  return launch_sweep<D, 2, 2, false>((b.n_units + 7) / 8 * 8 * qblocks, lds, st, kp, b.n_units, qblocks, 1, wl.split_len,
+  return launch_sweep<D, 2, 2, false>(mapped_blocks(b.n_units, qblocks), lds, st, kp, b.n_units, qblocks, 1, wl.split_len,
                                       1, wl.mq_pad, b.row_off, b.K, b.Q, nullptr, nullptr, nullptr, nullptr, parts,
                                       wl.parts_pitch);
 }
