@@ -486,7 +486,7 @@ int cask_compress_step(const cask_params* params, const cask_batch* batch, const
   StageRecorder rec(st);
   rec.mark();  // start
   const bool fused_tail = tail_small_fits(kp, b) && kp.dedup == 0 && !(kp.path_flags & CASK_PATH_NO_FUSED_TAIL);
-  // short units: both sweeps are one launch as well, handing partial sums to the tail kernel
+  // short units: the scoring is one launch as well, handing partial sums to the tail kernel
   // (reported as the first scoring stage; the second reads as an empty bracket)
   const bool fused_score = fused_tail && !given && score_parts_fits(kp, b, wl) &&
                            !(kp.path_flags & CASK_PATH_NO_FUSED_SCORE);

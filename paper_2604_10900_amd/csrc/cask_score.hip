@@ -935,6 +935,265 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   }
 }
 
+// ------------------------------------------------------------------ short units, one sweep
+
+// Scores of units of at most 1024 rows with the contraction and the exponentials done once: a
+// workgroup takes 64 window rows of a unit and ALL its keys, and the logits stay in registers (fp32)
+// between the row statistics and the column sums.  It leaves one partial column sum per key,
+// `parts[unit][block of 64 rows][key]`; whoever reads the scores adds them in order (no atomics: the
+// same bits every run).
+//
+// Wave w of NW holds the key tiles w, w + NW, ... (KT of 32 keys) against both 32-row tiles: KT x 2
+// accumulators of 16 registers, 64 more for the window rows' operands (read from LDS once), so two
+// waves per SIMD at KT <= 5.  Keys reach LDS by direct loads into two slots of the wave's own: no
+// barrier in the loop.  A lane owns one key of a tile and 16 rows of each row tile, so column sums
+// stay in the lane; a row's maximum and sum cross the 32 lanes once per wave (reduce32), and the
+// waves exchange (maximum, sum) pairs through LDS: the one barrier behind the window rows'.
+//
+// Operand rows lie in LDS in groups of 1 KB (four rows of 256 bytes, eight of 128): piece p of
+// row r of group g at ((p ^ g) x rows + r) x 16, which spreads any 16 lanes of an operand read over
+// all banks without padding (two workgroups take exactly the 160 KB of a compute unit).
+//
+// Bound: a workgroup's chain (window rows and first keys 3 us, loop, exponentials, exchange, column
+// sums: 8 - 13 us); in a full chip the loop runs at the keys' rate from L2 (14 TB/s over all
+// compute units) and the rest at the vector pipes', one after the other, where the two sweeps below
+// overlap them.  So it is for batches that leave the sweeps' 256-row workgroups too few (rule at
+// launch_score_parts).  4 units x 512 rows, 896 window rows: 22.4 -> 10.1 us; 112 x 640 rows: 48.4 ->
+// 47.  Several blocks per workgroup, walking the tiles back and forth so that two need not be read
+// again, took 51 - 62 us there.
+template <typename Op>
+__device__ __forceinline__ float reduce32(float (&v)[32], int c32, Op op) {
+  // v[i] of the 32 lanes of a half wave combined over the lanes; lane c32 gets value c32
+  float a[16], b[8], c[4], d[2];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {  // (swaps the odd rows of 16 lanes of the first with the even ones of the second)
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[j]), __float_as_uint(v[j + 16]), false, false);
+    a[j] = op(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  }
+  auto halve = [&](bool up, float lo, float hi, auto ctrl) {
+    const float keep = up ? hi : lo, send = up ? lo : hi;
+    const int got = __builtin_amdgcn_update_dpp(0, __float_as_int(send), decltype(ctrl)::value, 0xF, 0xF, true);
+    return op(keep, __int_as_float(got));
+  };
+#pragma unroll
+  for (int j = 0; j < 8; ++j) b[j] = halve(c32 & 8, a[j], a[j + 8], std::integral_constant<int, 0x128>());  // row_ror:8
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c[j] = halve(c32 & 4, b[j], b[j + 4], std::integral_constant<int, 0x141>());  // row_half_mirror
+#pragma unroll
+  for (int j = 0; j < 2; ++j) d[j] = halve(c32 & 2, c[j], c[j + 2], std::integral_constant<int, 0x4E>());   // lanes ^ 2
+  return halve(c32 & 1, d[0], d[1], std::integral_constant<int, 0xB1>());                                    // lanes ^ 1
+}
+
+template <int D, int KT, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void score_short_kernel(
+    KParams kp, int n_units, int blocks, const int64_t* __restrict__ row_off, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ Q, float* __restrict__ parts, int part_pitch) {
+  constexpr int RB = D * 2, GR = 1024 / RB, NK = D / 16;
+  constexpr int TL = 32 / GR;               // loads (groups) of a 32-row tile
+  constexpr int kTile = 32 * RB;
+  constexpr int kStep = 2 * GR * 16;        // two pieces of a group
+  static_assert(KT >= 2 && (2 * TL) % NW == 0, "two slots are filled ahead; the waves share the window rows' loads");
+  static_assert(NW * 768 <= 2 * kTile, "the exchange lies over the window rows");
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * kTile + NW * 2 * kTile];
+  int unit, blk;
+  if (!map_block(n_units, blocks, unit, blk)) return;
+  const int lane = threadIdx.x & 63, c32 = lane & 31, h = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t row0 = row_off[unit];
+  const int N = (int)(row_off[unit + 1] - row0);  // <= KT * NW * 32: the host checked
+  const int Mq = kp.Mq, Gq = kp.G, row_base = blk * 64;
+  const int tail = kp.causal ? N - kp.W : N - 1;  // keys beyond are hidden from some row
+  const float c = kp.scale_log2;
+  unsigned char* const own = smem + 2 * kTile + wv * (2 * kTile);
+
+  const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(K + (size_t)row0 * D), 0, N * RB, 0x00020000);
+  const __amdgpu_buffer_rsrc_t qrsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(Q + (size_t)unit * Mq * D), 0, Mq * RB, 0x00020000);
+  const int ld_voff = (lane % GR) * RB + (lane / GR) * 16;  // group 0; group g takes piece ^ g
+  auto load_group = [&](const __amdgpu_buffer_rsrc_t& rsrc, unsigned char* dst, int g, int row) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(dst + g * 1024), 16,
+                                             ld_voff ^ (g * 16), row * RB, 0, 0);
+  };
+  auto load_keys = [&](int kt) {  // rows past the unit's end read as zero
+#pragma unroll
+    for (int g = 0; g < TL; ++g) load_group(krsrc, own + (kt & 1) * kTile, g, (kt * NW + wv) * 32 + g * GR);
+  };
+#pragma unroll
+  for (int j = 0; j < 2 * TL / NW; ++j) {  // rows past W*G read as zero
+    const int g = wv * (2 * TL / NW) + j;
+    load_group(qrsrc, smem, g, row_base + g * GR);
+  }
+  load_keys(0);
+  load_keys(1);
+  // operand of lane (c32, h), k-step ks: piece 2 ks + h of row c32
+  const int rd = (c32 / GR) * 1024 + (c32 % GR) * 16 + ((h ^ (c32 / GR)) * (GR * 16));
+  const int my_row = (c32 >> 4) * 32 + ((c32 >> 2) & 3) * 8 + h * 4 + (c32 & 3);  // where reduce32 leaves value c32
+  float* const bcast = reinterpret_cast<float*>(smem + wv * 768);  // one value per row, for the wave itself
+  auto stat_of = [&](int w) { return reinterpret_cast<float2*>(smem + w * 768 + 256); };  // (maximum, sum) per row, for all
+  // (one instruction; fmaxf, which this becomes if the bound is a known constant, would first quiet
+  // a NaN in either operand: one more each)
+  float bound = __builtin_inff();
+  asm("" : "+s"(bound));
+  auto larger = [&](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, bound); };
+
+  __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * TL) & 0xF) | (((2 * TL) >> 4) << 14));  // the window rows are here
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  bf16x8 q[2][NK];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {
+    // (the second tile's groups are TL .. 2 TL - 1: their number reaches into the piece as well)
+    const int rq = rd ^ (rt * TL * (GR * 16));
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks)
+      q[rt][ks] = *reinterpret_cast<const bf16x8*>(smem + rt * kTile + (rq ^ (ks * kStep)));
+  }
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks) asm volatile("" ::"v"(q[rt][ks]));
+  // every wave has its operands: the exchange below may overwrite the window rows
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+
+  // ---- logits; a tile that no row of the block sees is left out, here and below
+  const int last_row = min(Mq, row_base + 64) - 1;
+  const int last_key = kp.causal ? N - kp.W + last_row / Gq : N - 1;  // < N
+  auto tile0 = [&](int kt) { return (kt * NW + wv) * 32; };  // first key
+  auto seen = [&](int kt) { return tile0(kt) <= last_key; };
+  auto masked = [&](int kt) { return tile0(kt) + 31 > tail; };
+  // Bit r: the lane's key of tile kt is hidden from row r of the 16 the lane holds in row tile rt.
+  // (Bit fields, not compares: a compare and its select wait for each other.)
+  auto hidden_bits = [&](int kt, int rt) {
+    const int key = tile0(kt) + c32;
+    const int first = key < N ? (kp.causal ? (key - (N - kp.W)) * Gq : 0) : 0x40000000;  // first row that sees the key
+    const int d = min(max(first - row_base - rt * 32 - h * 4, 0), 32);                    // hidden: row offset < d
+    const unsigned below = (unsigned)((1ull << d) - 1ull);                                // offsets 0 .. 31; the lane's are 8 g + 0 .. 3
+    return (below & 0xFu) | ((below >> 4) & 0xF0u) | ((below >> 8) & 0xF00u) | ((below >> 12) & 0xF000u);
+  };
+  auto where_hidden = [&](unsigned bits, int r, unsigned then, float x) {  // x, or the bit pattern `then` where hidden
+    unsigned t;  // (written out: the compiler makes a shift, a compare and a select of it)
+    asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(t) : "v"(bits), "n"(r));
+    return __uint_as_float((t & then) | (~t & __float_as_uint(x)));
+  };
+  f32x16 acc[KT][2];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) {
+    if (kt + 1 < KT) __builtin_amdgcn_s_waitcnt(0x0F70 | TL);  // the next tile may still be in flight
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    asm volatile("" ::: "memory");
+    if (seen(kt)) {
+      const unsigned char* slot = own + (kt & 1) * kTile;
+#pragma unroll
+      for (int ks = 0; ks < NK; ++ks) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(slot + (rd ^ (ks * kStep)));
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt)
+          acc[kt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q[rt][ks], b, ks == 0 ? f32x16{0} : acc[kt][rt], 0, 0, 0);
+      }
+      if (masked(kt)) {
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+          const unsigned bits = hidden_bits(kt, rt);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[kt][rt][r] = where_hidden(bits, r, 0xFF800000u, acc[kt][rt][r]);
+        }
+      }
+    }
+    if (kt + 2 < KT) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // the slot's operands are in registers
+      asm volatile("" ::: "memory");
+      load_keys(kt + 2);
+    }
+  }
+
+  // ---- row statistics of the wave's keys
+  auto publish = [&](float x) {
+    asm volatile("" ::: "memory");  // (the wave's LDS accesses stay in order; the compiler's of other types must too)
+    bcast[my_row] = x;
+    asm volatile("" ::: "memory");
+  };
+  auto published = [&](int rt, float (&v)[16]) {  // v[r] <- x of the lane that holds row r of the lane's 16 in row tile rt
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 t = *reinterpret_cast<const f32x4*>(bcast + rt * 32 + g * 8 + h * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[g * 4 + e] = t[e];
+    }
+  };
+  float v[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) v[i] = kNegInf;
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+    if (seen(kt)) {
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = larger(v[i], acc[kt][i >> 4][i & 15]);
+    }
+  const float m = reduce32(v, c32, larger) * c;
+  publish(m == kNegInf ? 0.f : -m);
+  float sum[32];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt) {  // (a row tile at a time: fewer registers)
+    float nm[16];
+    published(rt, nm);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum[rt * 16 + r] = 0.f;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+      if (seen(kt)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float e = fast_exp2(__builtin_fmaf(acc[kt][rt][r], c, nm[r]));
+          acc[kt][rt][r] = e;
+          sum[rt * 16 + r] += e;
+        }
+      }
+  }
+  const float l = reduce32(sum, c32, [](float x, float y) { return x + y; });
+  stat_of(wv)[my_row] = make_float2(m, l);
+  __syncthreads();
+
+  // ---- the rows' weights 2^(m - L) of this wave's terms, then the column sums
+  {
+    float M = kNegInf, l_all = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float2 o = stat_of(w)[my_row];
+      ml_combine(M, l_all, o.x, o.y);
+    }
+    publish(row_base + my_row < Mq ? fast_exp2(m - (M + log2f(l_all))) : 0.f);
+  }
+  float w[2][16];
+  published(0, w[0]);
+  published(1, w[1]);
+  float* const out = parts + ((size_t)unit * blocks + blk) * part_pitch;
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) {
+    float s[2] = {0.f, 0.f};
+    if (seen(kt)) {
+      if (masked(kt)) {  // (a hidden term is 0 whatever the row's weight, a NaN included)
+        const unsigned bits[2] = {hidden_bits(kt, 0), hidden_bits(kt, 1)};
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt)
+            s[rt] = __builtin_fmaf(acc[kt][rt][r], where_hidden(bits[rt], r, 0u, w[rt][r]), s[rt]);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+          for (int rt = 0; rt < 2; ++rt) s[rt] = __builtin_fmaf(acc[kt][rt][r], w[rt][r], s[rt]);
+      }
+    }
+    const float mine = s[0] + s[1], tot = mine + __shfl_xor(mine, 32, 64);
+    const int key = tile0(kt) + c32;
+    if (h == 0 && key < N) out[key] = tot;
+  }
+}
+
 // ------------------------------------------------------------------ fp32 caches
 
 // What the head dimension decides about a ring slot of the fp32 sweeps (32 stream rows).
@@ -1265,6 +1524,31 @@ hipError_t launch_sweeps_to_parts(const KParams& kp, const Batch& b, const Works
                                       1, wl.mq_pad, b.row_off, b.K, b.Q, nullptr, nullptr, nullptr, nullptr, parts,
                                       wl.parts_pitch);
 }
+
+template <int D>
+hipError_t launch_short(const KParams& kp, const Batch& b, float* parts, int pitch, hipStream_t st) {
+  const int blocks = (kp.Mq + 63) / 64, grid = mapped_blocks(b.n_units, blocks);
+  auto go = [&](auto kt, auto nw) {
+    score_short_kernel<D, decltype(kt)::value, decltype(nw)::value><<<dim3(grid), dim3(decltype(nw)::value * 64), 0, st>>>(
+        kp, b.n_units, blocks, b.row_off, static_cast<const uint16_t*>(b.K), static_cast<const uint16_t*>(b.Q), parts, pitch);
+    return hipGetLastError();
+  };
+  using std::integral_constant;
+  const integral_constant<int, 4> four;
+  const integral_constant<int, 8> eight;
+  const int tiles = (b.max_unit_len + 31) / 32;
+  // Two workgroups of four waves share a compute unit up to 640 rows.  Where a workgroup has the
+  // compute unit to itself anyway, and beyond 640 rows, it takes eight waves.
+  if (grid > 256 && tiles <= 20) {
+    if (tiles <= 8) return go(integral_constant<int, 2>(), four);
+    if (tiles <= 12) return go(integral_constant<int, 3>(), four);
+    if (tiles <= 16) return go(four, four);
+    return go(integral_constant<int, 5>(), four);
+  }
+  if (tiles <= 16) return go(integral_constant<int, 2>(), eight);
+  if (tiles <= 24) return go(integral_constant<int, 3>(), eight);
+  return go(four, eight);
+}
 }  // namespace
 
 hipError_t launch_score_fused(const KParams& kp, const Batch& b, const Workspace& wl, float* scores,
@@ -1290,13 +1574,20 @@ bool score_parts_fits(const KParams& kp, const Batch& b, const Workspace& wl) {
   return score_uses_mfma(kp) && wl.n_splits == 1 && wl.parts_pitch > 0 && b.max_unit_len <= wl.parts_pitch;
 }
 
-// Both scoring sweeps in one launch (short units, one key split): writes, for every unit,
-// ceil(W*G / 64) partial column sums per key, `parts[unit][part][key]` with row pitch
-// wl.parts_pitch; score[key] = (sum of the parts in order) / (W*G).
+// Scores of short units in one launch: writes, for every unit, ceil(W*G / 64) partial column
+// sums per key, `parts[unit][part][key]` with row pitch wl.parts_pitch; score[key] = (sum of the
+// parts in order) / (W*G).
+// Two sweeps with 256 window rows to a workgroup overlap matrix and vector work and are the better
+// form once they fill the chip; one sweep is, with its 64 rows to a workgroup, while all of its
+// workgroups run at once.  Events, two sweeps against one: 56 workgroups of 64 rows (4 units of 512)
+// 40 / 28 us, 112 (8 of 1024) 89 / 66, 392 (28 of 768) 65 / 57, 448 (112 of 640) 59 / 49; 896 (64 of
+// 512) 44 / 45, 896 (64 of 1024) 100 / 112, 1568 (112 of 1024) 138 / 163, 8192 (512 of 900) 380 / 531.
 hipError_t launch_score_parts(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
                               hipStream_t st) {
   if (!score_parts_fits(kp, b, wl)) return hipErrorInvalidValue;
   float* parts = reinterpret_cast<float*>(ws + wl.parts);
+  if ((int64_t)b.n_units * ((kp.Mq + 63) / 64) <= 512)
+    return kp.d == 64 ? launch_short<64>(kp, b, parts, wl.parts_pitch, st) : launch_short<128>(kp, b, parts, wl.parts_pitch, st);
   const hipError_t e = kp.d == 64 ? launch_sweeps_to_parts<64>(kp, b, wl, parts, st)
                                   : launch_sweeps_to_parts<128>(kp, b, wl, parts, st);
   return e != hipSuccess ? e : hipGetLastError();

@@ -142,3 +142,41 @@ def test_consolidation_at_the_edges_of_tiles_and_seed_blocks(d, dtype, tau, radi
     torch.cuda.synchronize()
     assert (want >= 0).sum() > 800
     _note(d, dtype, tau, radius, "excused", parity.check_assign_excused(got.cpu().numpy(), want, best, second, float(np.float32(tau)), "edges"))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("longest,units,G,Wn,causal", [
+    (256, 40, 7, 64, 1), (384, 40, 7, 64, 0), (511, 40, 7, 65, 1), (640, 40, 8, 57, 1), (641, 40, 7, 64, 1), (600, 140, 5, 60, 1),
+    (96, 2, 1, 17, 1), (512, 3, 7, 128, 1), (768, 3, 5, 100, 0), (769, 2, 7, 33, 1), (1024, 3, 4, 64, 1)])
+def test_scores_of_short_units_in_one_sweep(longest, units, G, Wn, causal, d):
+    """Units of at most 1024 rows, whose event scores them in one launch: four waves (more than 256
+    workgroups) or eight, every number of key tiles per wave, lengths around a tile and down to the
+    window, a last block of window rows that is not full, and a batch that takes two sweeps; the scores of the event against the oracle
+    (bar as above: 1e-4 of the unit's largest score)."""
+    cand = [longest, Wn, Wn + 1, longest - 1, longest // 2 + 1, (longest + Wn) // 2, max(Wn, longest - 32), max(Wn, 129)]
+    lens = [min(longest, cand[i % len(cand)]) for i in range(units)]
+    c = _units(lens, [i % 3 * 5 if n > Wn + 10 else 0 for i, n in enumerate(lens)], head_dim=d, q_per_kv=G, window=Wn)
+    p = cask.Params(dtype=cask.BF16, head_dim=d, q_per_kv=G, window=Wn, causal=causal, budget=max(Wn + 5, longest // 2))
+    row_off, _, K, _, Q = parity.host_arrays(c)
+    b = parity.to_device(c, p)
+    s = cask.compress(b).scores.clone()
+    s2 = cask.compress(b).scores
+    torch.cuda.synchronize()
+    assert torch.equal(s, s2)
+    err = parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off)
+    _note(d, longest, units, "score error / max", err)
+    assert err < 5e-6   # fp32 sums of at most 1024 terms, two levels of exponentials: relative errors of a few 2^-20
+
+
+def test_hidden_keys_keep_their_scores_when_a_window_row_is_nan():
+    """A window row that holds NaN spoils the keys it sees and no others."""
+    Wn, G, n = 40, 2, 300
+    c = _units([n, n], [0, 0], head_dim=128, q_per_kv=G, window=Wn)
+    p = cask.Params(dtype=cask.BF16, head_dim=128, q_per_kv=G, window=Wn, budget=n)
+    clean = cask.compress(parity.to_device(c, p)).scores.clone()
+    c["Q"][0, 9, 1] = float("nan")
+    got = cask.compress(parity.to_device(c, p)).scores
+    torch.cuda.synchronize()
+    last = n - Wn + 9                      # the last key that window row sees
+    assert torch.isnan(got[:last + 1]).all()
+    assert torch.equal(got[last + 1:], clean[last + 1:])
