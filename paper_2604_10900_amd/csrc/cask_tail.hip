@@ -5,6 +5,8 @@
 // between them.  bf16 caches, cosine geometry (Sections 2.1 - 2.4).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "cask.h"
 #include "cask_common.h"
 
@@ -19,6 +21,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kTailThreads = 1024;
 constexpr int kTailWaves = kTailThreads / 64;
 constexpr int kTailRows = kTailThreads;  // longest unit: a row per thread
+constexpr int kRankPad = 64;             // rows of a piece of the rank count
 constexpr int kTailSeedBlock = 128;      // seeds staged in LDS at a time
 constexpr float kNegInf = -__builtin_inff();
 constexpr int kRepFlag = 0x4000;         // in src_s: the slot holds a representative (rows are < 1024)
@@ -35,10 +38,12 @@ __device__ inline float sumsq8(const uint4& v) {
 }
 
 // Thread i owns row i of the unit.
-//  1. rank: the order (score descending, index ascending) becomes one 64-bit key per row
-//     (score key, then inverted index), and a row's rank inside its range (prefix, or decode
-//     trace without the recent tail) is the number of larger keys: a counting loop over LDS,
-//     split over the idle threads when the unit is shorter than the workgroup.
+//  1. rank: a row's rank inside its range (prefix, or decode trace without the recent tail) is the
+//     number of rows with a larger score key, or an equal one and a lower index: a counting loop
+//     over the range's keys in LDS, four to a read.  The work is dealt to the waves in pieces of 64
+//     rows x an eighth of the range, so all sixteen have the same share whatever the range (a
+//     thread per row and a share of the range with 64-bit keys took 6.3 us of a workgroup's 26 at
+//     640 rows, 3.5 of 15 at 512).  A piece compares with >= before its rows' block, > behind it, and by index inside it.
 //  2. roles from the plan's ranks; output slots and seed ordinals from one block scan.
 //  3. cosine of every decode row against every seed on the matrix cores: seeds are the A
 //     operand (staged in LDS kTailSeedBlock at a time, with inverse norms), 32 decode rows a
@@ -46,13 +51,18 @@ __device__ inline float sumsq8(const uint4& v) {
 //     in ascending order: first maximum wins, folded if >= tau.
 //  4. kept rows are copied 16 bytes a thread; a wave per seed with donors folds its group in
 //     ascending row order in fp32 (score-weighted; count-weighted when the group has no mass).
+// `copiers`: a second workgroup per unit (blocks n_units ..) repeats steps 1 and 2 and copies the
+// rows that are kept and no seeds while the first one is in step 3; the first is left with the
+// seeds' own rows.  (The copy was 5 us of the chain at 512 kept rows, and the chip has compute units
+// to spare as long as both workgroups of every unit run at once.  With the rank count above and the
+// seeds' norms read four at a time: 112 units x 640 rows 31.1 -> 24.8 us, 4 x 512 rows 18.1 -> 16.5.)
 template <int D>
 __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
     KParams kp, const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
     float* scores, const float* __restrict__ parts, int n_parts, int parts_pitch,
     const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ in_count,
-    uint16_t* __restrict__ K_out, uint16_t* __restrict__ V_out, int out_stride,
+    uint16_t* __restrict__ K_out, uint16_t* __restrict__ V_out, int out_stride, int n_units, int copiers,
     int32_t* __restrict__ out_len, int32_t* __restrict__ out_src, float* __restrict__ out_mass,
     int32_t* __restrict__ out_count, int32_t* __restrict__ assign, int32_t* __restrict__ status) {
   constexpr int ROWB = D * 2;      // bytes per row
@@ -60,18 +70,21 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   constexpr int KS = D / 16;       // MFMA k-steps
   constexpr int PPR = ROWB / 16;   // 16-byte pieces per row
   __shared__ __attribute__((aligned(16))) unsigned char seedk[kTailSeedBlock * PITCH];
-  __shared__ unsigned long long ckey[kTailRows];  // step 1; afterwards its memory holds bsim
-  __shared__ int rank_s[kTailRows];               // step 1; afterwards the donors per seed (seg_cnt)
+  __shared__ __attribute__((aligned(16))) uint32_t ckey[kTailRows + 2 * kRankPad];  // step 1; afterwards its memory holds bsim
+  __shared__ int rank_s[kTailRows + 2 * kRankPad];  // step 1, by place in ckey; afterwards the donors per seed (seg_cnt)
   __shared__ short slot_s[kTailRows];             // output slot of a row, -1 if it is not kept
   __shared__ short fold_s[kTailRows];             // seed ordinal a row belongs to (seeds: their own), -1 if none
   __shared__ short seed_row_s[kTailRows];         // row of every seed ordinal
   __shared__ short src_s[kTailRows];              // row of every output slot
-  __shared__ float seed_inv[kTailSeedBlock];
+  __shared__ __attribute__((aligned(16))) float seed_inv[kTailSeedBlock];
   __shared__ int wsum[kTailWaves];
   float* bsim_s = reinterpret_cast<float*>(ckey);
   int* seg_cnt = rank_s;
 
-  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const bool copier = (int)blockIdx.x >= n_units;
+  const int u = copier ? (int)blockIdx.x - n_units : (int)blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);  // <= kTailRows: the host checked
   const int P = prefix_len[u];
@@ -99,38 +112,57 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
           if (q0 + e < n_parts) tot += v[e];
       }
       my_s = tot * (1.0f / (float)kp.Mq);
-      scores[row0 + i] = my_s;  // read again below by other threads, behind barriers
+      if (!copier) scores[row0 + i] = my_s;  // read again below by other threads, behind barriers
     } else {
       my_s = s[i];
     }
   }
-  ckey[i] = i < N ? (((unsigned long long)score_key(my_s)) << 32) | (unsigned)(~i) : 0ull;
-  rank_s[i] = 0;
+  // a range that is kept or dropped as a whole needs no ranks
+  const bool pre_ranks = pl.p_keep > 0 && pl.p_keep < P, dec_ranks = pl.core < hi - P;
+  // the decode range's keys from 0, the prefix's behind them, both padded to whole blocks of 64
+  const int n_dec = hi - P, pre_at = (n_dec + kRankPad - 1) / kRankPad * kRankPad;
+  const int place = i < P ? pre_at + i : i - P;
+  if (i < hi) ckey[place] = score_key(my_s);
+  {  // (a padding key stands behind every row of its range and counts for none)
+    if (tid < pre_at - n_dec) ckey[n_dec + tid] = 0u;
+    const int pre_end = pre_at + (P + kRankPad - 1) / kRankPad * kRankPad;
+    if (tid < pre_end - pre_at - P) ckey[pre_at + P + tid] = 0u;
+    for (int q = tid; q < pre_end; q += kTailThreads) rank_s[q] = 0;
+  }
   __syncthreads();
   {
-    int shift = 10;  // rows_per = 1 << shift threads cover the rows once; the rest split the loop
-    if (N <= 256) shift = 8;
-    else if (N <= 512) shift = 9;
-    const int parts = kTailThreads >> shift;
-    const int r = tid & ((1 << shift) - 1), part = tid >> shift;
-    const bool prefix_row = r < P;
-    // a range that is kept or dropped as a whole needs no ranks
-    const bool need = prefix_row ? (pl.p_keep > 0 && pl.p_keep < P) : (r < hi && pl.core < hi - P);
-    if (need) {
-      const int lo_r = prefix_row ? 0 : P, hi_r = prefix_row ? P : hi;
-      const int per = (hi_r - lo_r + parts - 1) / parts;
-      const int j0 = lo_r + part * per, j1 = min(hi_r, j0 + per);
-      const unsigned long long me = ckey[r];
-      int cnt = 0, j = j0;
-      for (; j + 8 <= j1; j += 8) {  // eight independent LDS reads in flight
-        unsigned long long kj[8];
+    constexpr int kParts = 8;
+    const int dec_blocks = dec_ranks ? pre_at / kRankPad : 0;
+    const int blocks = dec_blocks + (pre_ranks ? (P + kRankPad - 1) / kRankPad : 0);
+    for (int task = wv; task < blocks * kParts; task += kTailWaves) {
+      const int blk = task / kParts, part = task % kParts;
+      const bool dec = blk < dec_blocks;
+      const uint32_t* keys = ckey + (dec ? 0 : pre_at);
+      const int n = dec ? n_dec : P, base = (dec ? blk : blk - dec_blocks) * kRankPad;
+      const int per = (n + 4 * kParts - 1) / (4 * kParts) * 4;
+      const int j0 = part * per, j1 = min((n + 3) & ~3, j0 + per);  // multiples of four
+      const uint32_t me = keys[base + lane];
+      int cnt = 0;
+      auto count = [&](int from, int to, auto ahead) {  // keys [from, to) of the part; ahead(key, place)
+        int j = from;
+        for (; j + 16 <= to; j += 16) {  // four reads in flight
+          uint4 k[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) kj[e] = ckey[j + e];
+          for (int e = 0; e < 4; ++e) k[e] = *reinterpret_cast<const uint4*>(keys + j + 4 * e);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) cnt += kj[e] > me ? 1 : 0;
-      }
-      for (; j < j1; ++j) cnt += ckey[j] > me ? 1 : 0;
-      if (cnt) atomicAdd(&rank_s[r], cnt);
+          for (int e = 0; e < 4; ++e)
+            cnt += (ahead(k[e].x, j + 4 * e) ? 1 : 0) + (ahead(k[e].y, j + 4 * e + 1) ? 1 : 0) +
+                   (ahead(k[e].z, j + 4 * e + 2) ? 1 : 0) + (ahead(k[e].w, j + 4 * e + 3) ? 1 : 0);
+        }
+        for (; j < to; j += 4) {
+          const uint4 k = *reinterpret_cast<const uint4*>(keys + j);
+          cnt += (ahead(k.x, j) ? 1 : 0) + (ahead(k.y, j + 1) ? 1 : 0) + (ahead(k.z, j + 2) ? 1 : 0) + (ahead(k.w, j + 3) ? 1 : 0);
+        }
+      };
+      count(j0, min(j1, base), [&](uint32_t k, int) { return k >= me; });
+      count(max(j0, base), min(j1, base + kRankPad), [&](uint32_t k, int at) { return k > me || (k == me && at < base + lane); });
+      count(max(j0, base + kRankPad), j1, [&](uint32_t k, int) { return k > me; });
+      if (cnt) atomicAdd(&rank_s[(dec ? 0 : pre_at) + base + lane], cnt);
     }
   }
   __syncthreads();
@@ -138,7 +170,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   // ---- 2. roles, slots, seed ordinals
   bool kept = false, seed = false, donor = false;
   if (i < N) {
-    const int rk = rank_s[i];
+    const int rk = i < hi ? rank_s[place] : 0;
     if (i < P) {
       kept = rk < pl.p_keep;  // ranks are zero when the whole prefix stays or goes
     } else if (i >= hi) {
@@ -166,12 +198,54 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   if (slot >= B) slot = -1;
   const int ord = seed ? (base >> 16) + __popcll(bs & below) : -1;
   slot_s[i] = (short)slot;
-  if (slot >= 0) src_s[slot] = (short)i;
+  if (slot >= 0) src_s[slot] = (short)(copier && seed ? i | kRepFlag : i);  // (a copier leaves the seeds' slots alone)
   if (seed) seed_row_s[ord] = (short)i;
   fold_s[i] = -1;
   bsim_s[i] = kNegInf;
   seg_cnt[i] = 0;
   __syncthreads();
+  // Copy of `n` slots, K and V, 16 bytes a thread; slots flagged in src_s are left alone.
+  auto copy_slots = [&](int n, auto slot_at) {
+    constexpr int PER_SLOT = 2 * PPR;  // K pieces, then V pieces
+    constexpr int NB = 12;             // loads in flight per thread
+    const int pieces = n * PER_SLOT;
+    uint16_t* Ko = K_out + (size_t)u * out_stride * D;
+    uint16_t* Vo = V_out + (size_t)u * out_stride * D;
+    for (int p0 = tid; p0 < pieces; p0 += NB * kTailThreads) {
+      // every load is issued, without a branch around it (past the end the last piece is
+      // read again, a representative's own row is read in vain): only the stores are
+      // conditional, so all NB loads are in flight together
+      uint4 v[NB];
+      int dst[NB];  // element offset in the unit's output, V flagged by bit 30; -1: no store
+#pragma unroll
+      for (int e = 0; e < NB; ++e) {
+        const int p = p0 + e * kTailThreads;
+        const int pc = p < pieces ? p : pieces - 1;
+        const int t = slot_at(pc / PER_SLOT), w = pc % PER_SLOT;
+        const bool is_v = w >= PPR;
+        const int piece = is_v ? w - PPR : w;
+        const int src = t >= 0 ? src_s[t] : kRepFlag;
+        v[e] = *reinterpret_cast<const uint4*>((is_v ? Vu : Ku) + (size_t)(src & (kRepFlag - 1)) * D + piece * 8);
+        dst[e] = (p < pieces && !(src & kRepFlag)) ? ((t * D + piece * 8) | (is_v ? (1 << 30) : 0)) : -1;
+      }
+      // (keeps the compiler from sinking each load into the branch of its store)
+#pragma unroll
+      for (int e = 0; e < NB; e += 4)
+        asm volatile("" : "+v"(v[e].x), "+v"(v[e].y), "+v"(v[e].z), "+v"(v[e].w),
+                          "+v"(v[e + 1].x), "+v"(v[e + 1].y), "+v"(v[e + 1].z), "+v"(v[e + 1].w),
+                          "+v"(v[e + 2].x), "+v"(v[e + 2].y), "+v"(v[e + 2].z), "+v"(v[e + 2].w),
+                          "+v"(v[e + 3].x), "+v"(v[e + 3].y), "+v"(v[e + 3].z), "+v"(v[e + 3].w));
+#pragma unroll
+      for (int e = 0; e < NB; ++e)
+        if (dst[e] >= 0)
+          *reinterpret_cast<uint4*>(((dst[e] >> 30) ? Vo : Ko) + (dst[e] & ((1 << 30) - 1))) = v[e];
+    }
+  };
+  auto any_slot = [](int t) { return t; };
+  if (copier) {
+    copy_slots(L, any_slot);
+    return;
+  }
 
   // ---- 3. cosine against the seeds
   const int n = hi - P;
@@ -245,22 +319,30 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
             const bf16x8 a = *reinterpret_cast<const bf16x8*>(seedk + (s0 + c32) * PITCH + (2 * ks + h) * 16);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bres[ks], acc, 0, 0, 0);
           }
+          auto pick = [&](auto plain_tag) {  // plain: no merge radius and all 32 seeds of this step exist
+            constexpr bool kPlain = decltype(plain_tag)::value;
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {  // ascending seed ordinal within the lane
+            for (int g = 0; g < 4; ++g) {  // ascending seed ordinal within the lane
+              const float4 si = *reinterpret_cast<const float4*>(&seed_inv[s0 + g * 8 + h * 4]);
+              const float inv[4] = {si.x, si.y, si.z, si.w};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int sr = s0 + g * 8 + h * 4 + q;
-              if (sr < m_blk) {
-                const float sim = (acc[g * 4 + q] * seed_inv[sr]) * dinv;
-                const int pos = seed_row_s[sb + sr];
-                const int gap = pos > drow ? pos - drow : drow - pos;
-                if (gap <= radius && sim > best) {
+              for (int q = 0; q < 4; ++q) {
+                const int sr = s0 + g * 8 + h * 4 + q;
+                bool near = true;
+                if (!kPlain && sr < m_blk) {
+                  const int pos = seed_row_s[sb + sr];
+                  near = (pos > drow ? pos - drow : drow - pos) <= radius;
+                }
+                const float sim = (acc[g * 4 + q] * inv[q]) * dinv;
+                if ((kPlain || (sr < m_blk && near)) && sim > best) {
                   best = sim;
                   best_ord = sb + sr;
                 }
               }
             }
-          }
+          };
+          if (kp.radius <= 0 && s0 + 32 <= m_blk) pick(std::true_type{});
+          else pick(std::false_type{});
         }
         const float ob = __shfl_xor(best, 32, 64);
         const int oo = __shfl_xor(best_ord, 32, 64);
@@ -300,42 +382,8 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
     }
   }
   __syncthreads();
-  {
-    constexpr int PER_SLOT = 2 * PPR;  // K pieces, then V pieces
-    constexpr int NB = 12;             // loads in flight per thread
-    const int pieces = L * PER_SLOT;
-    uint16_t* Ko = K_out + (size_t)u * out_stride * D;
-    uint16_t* Vo = V_out + (size_t)u * out_stride * D;
-    for (int p0 = tid; p0 < pieces; p0 += NB * kTailThreads) {
-      // every load is issued, without a branch around it (past the end the last piece is
-      // read again, a representative's own row is read in vain): only the stores are
-      // conditional, so all NB loads are in flight together
-      uint4 v[NB];
-      int dst[NB];  // element offset in the unit's output, V flagged by bit 30; -1: no store
-#pragma unroll
-      for (int e = 0; e < NB; ++e) {
-        const int p = p0 + e * kTailThreads;
-        const int pc = p < pieces ? p : pieces - 1;
-        const int t = pc / PER_SLOT, w = pc % PER_SLOT;
-        const bool is_v = w >= PPR;
-        const int piece = is_v ? w - PPR : w;
-        const int src = src_s[t];
-        v[e] = *reinterpret_cast<const uint4*>((is_v ? Vu : Ku) + (size_t)(src & (kRepFlag - 1)) * D + piece * 8);
-        dst[e] = (p < pieces && !(src & kRepFlag)) ? ((t * D + piece * 8) | (is_v ? (1 << 30) : 0)) : -1;
-      }
-      // (keeps the compiler from sinking each load into the branch of its store)
-#pragma unroll
-      for (int e = 0; e < NB; e += 4)
-        asm volatile("" : "+v"(v[e].x), "+v"(v[e].y), "+v"(v[e].z), "+v"(v[e].w),
-                          "+v"(v[e + 1].x), "+v"(v[e + 1].y), "+v"(v[e + 1].z), "+v"(v[e + 1].w),
-                          "+v"(v[e + 2].x), "+v"(v[e + 2].y), "+v"(v[e + 2].z), "+v"(v[e + 2].w),
-                          "+v"(v[e + 3].x), "+v"(v[e + 3].y), "+v"(v[e + 3].z), "+v"(v[e + 3].w));
-#pragma unroll
-      for (int e = 0; e < NB; ++e)
-        if (dst[e] >= 0)
-          *reinterpret_cast<uint4*>(((dst[e] >> 30) ? Vo : Ko) + (dst[e] & ((1 << 30) - 1))) = v[e];
-    }
-  }
+  if (copiers) copy_slots(M, [&](int g) { return (int)slot_s[seed_row_s[g]]; });
+  else copy_slots(L, any_slot);
   if (n_fold > 0) {
     const bool active = lane < D / 2;  // two elements a lane
     for (int g = wv; g < M; g += kTailWaves) {
@@ -427,12 +475,13 @@ hipError_t launch_tail_small(const KParams& kp, const Batch& b, float* scores, c
                              int32_t* out_count, int32_t* assign, int32_t* status,
                              hipStream_t st) {
   if (!tail_small_fits(kp, b)) return hipErrorInvalidValue;
+  const int copiers = b.n_units <= 128 ? 1 : 0;  // a workgroup fills a compute unit; there are 256
 #define CASK_TAIL(D)                                                                             \
-  tail_small_kernel<D><<<dim3(b.n_units), dim3(kTailThreads), 0, st>>>(                          \
+  tail_small_kernel<D><<<dim3(b.n_units * (1 + copiers)), dim3(kTailThreads), 0, st>>>(          \
       kp, b.row_off, b.prefix_len, scores, parts, n_parts, parts_pitch,                          \
       static_cast<const uint16_t*>(b.K),                                                         \
       static_cast<const uint16_t*>(b.V), in_count, static_cast<uint16_t*>(K_out),                \
-      static_cast<uint16_t*>(V_out), out_stride, out_len, out_src, out_mass, out_count, assign,  \
+      static_cast<uint16_t*>(V_out), out_stride, b.n_units, copiers, out_len, out_src, out_mass, out_count, assign,  \
       status)
   if (kp.d == 64) CASK_TAIL(64); else CASK_TAIL(128);
 #undef CASK_TAIL

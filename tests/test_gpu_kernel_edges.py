@@ -180,3 +180,19 @@ def test_hidden_keys_keep_their_scores_when_a_window_row_is_nan():
     last = n - Wn + 9                      # the last key that window row sees
     assert torch.isnan(got[:last + 1]).all()
     assert torch.equal(got[last + 1:], clean[last + 1:])
+
+
+@pytest.mark.parametrize("units", [3, 131])
+@pytest.mark.parametrize("d,R,budget,core,prefix_budget", [(128, -1, 300, -1, 100), (64, 40, 257, 64, 65), (128, 33, 129, 0, 64)])
+def test_tail_of_short_units_at_the_edges_of_rank_pieces(d, R, budget, core, prefix_budget, units):
+    """Whole events on units of at most 1024 rows: prefix and decode ranges of 63, 64, 65, ... rows
+    (pieces of the rank count), ranks asked for in both, with the copying workgroups (few units) and
+    without; rows, roles, folds and statuses element by element against the oracle."""
+    Wn = 32
+    cand = [(200, 0), (64 + Wn, 1), (Wn + 129, 64), (Wn + 128, 63), (320, 65), (512, 128), (1024, 129), (1000, 300), (577, 449), (Wn, 0)]
+    lens, pref = zip(*[cand[(i * 3 + units) % len(cand)] for i in range(units)])
+    if units > 10:   # (the oracle's time: mostly the shorter ones)
+        lens, pref = zip(*[(n, q) if i % 10 == 0 else (min(n, 330), min(q, 66)) for i, (n, q) in enumerate(zip(lens, pref))])
+    c = _units(list(lens), list(pref), head_dim=d, q_per_kv=2, window=Wn, cluster_frac=0.6)
+    p = cask.Params(dtype=cask.BF16, head_dim=d, q_per_kv=2, window=Wn, recent=R, budget=budget, core=core, prefix_budget=prefix_budget)
+    _note(d, budget, units, parity.full_check(c, p))
