@@ -196,3 +196,30 @@ def test_tail_of_short_units_at_the_edges_of_rank_pieces(d, R, budget, core, pre
     c = _units(list(lens), list(pref), head_dim=d, q_per_kv=2, window=Wn, cluster_frac=0.6)
     p = cask.Params(dtype=cask.BF16, head_dim=d, q_per_kv=2, window=Wn, recent=R, budget=budget, core=core, prefix_budget=prefix_budget)
     _note(d, budget, units, parity.full_check(c, p))
+
+
+@pytest.mark.parametrize("merged", [0.02, 0.9])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
+def test_group_diagnostics_around_a_round_of_rows(d, dtype, merged):
+    """Dispersion and lost mass of units around a wave's 64 rows, a workgroup's 1024 and its 8192 in
+    flight, with few and with nearly all rows assigned to a slot.  Bar 2e-5: distances of fp32 terms
+    (64 bands, relative error below 1e-5 in all), summed in double."""
+    Wn, B_ = 16, 40
+    lens = [Wn, 63, 64, 65, 1023, 1025, 8191, 8193, 9300]
+    c = _units(lens, [0] * len(lens), head_dim=d, q_per_kv=1, window=Wn)
+    f32 = dtype == "f32"
+    if f32:
+        c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    p = cask.Params(dtype=cask.F32 if f32 else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=B_)
+    row_off, _, K, _, _ = parity.host_arrays(c)
+    rng = np.random.default_rng(d)
+    total = int(row_off[-1])
+    s = rng.random(total).astype(np.float32)
+    a = np.where(rng.random(total) < merged, rng.integers(0, B_, total), -1).astype(np.int32)
+    Ko = torch.randn(len(lens), B_, d, generator=torch.Generator().manual_seed(d)).to(torch.float32 if f32 else torch.bfloat16)
+    want_d, want_l = ref.group_diagnostics(parity.ref_params(p), row_off, K, s, a, caches.host_bits(Ko))
+    b = parity.to_device(c, p)
+    got_d, got_l = cask.group_diagnostics(b, torch.from_numpy(s).to(b.device), torch.from_numpy(a).to(b.device), Ko.to(b.device))
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(got_d.cpu().numpy(), want_d, rtol=2e-5, atol=1e-6)
+    np.testing.assert_allclose(got_l.cpu().numpy(), want_l, rtol=1e-6, atol=1e-6)
