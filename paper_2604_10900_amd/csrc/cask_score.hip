@@ -15,6 +15,7 @@
 // resident column and 16 stream rows: the reduction over the stream dimension (keys in
 // sweep A, window rows in sweep B) stays inside a lane until the very end.
 // fp32 caches take a simpler kernel of the same structure on fp32 matrix tiles.
+// Few short bf16 units take one sweep that keeps its logits in registers (score_short_kernel).
 #include "cask_common.h"
 
 namespace cask {
