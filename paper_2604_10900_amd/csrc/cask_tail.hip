@@ -40,10 +40,12 @@ __device__ inline float sumsq8(const uint4& v) {
 // Thread i owns row i of the unit.
 //  1. rank: a row's rank inside its range (prefix, or decode trace without the recent tail) is the
 //     number of rows with a larger score key, or an equal one and a lower index: a counting loop
-//     over the range's keys in LDS, four to a read.  The work is dealt to the waves in pieces of 64
-//     rows x an eighth of the range, so all sixteen have the same share whatever the range (a
-//     thread per row and a share of the range with 64-bit keys took 6.3 us of a workgroup's 26 at
-//     640 rows, 3.5 of 15 at 512).  A piece compares with >= before its rows' block, > behind it, and by index inside it.
+//     over the range's keys in LDS.  The work is dealt to the sixteen waves in pieces of 64 rows x
+//     32 keys, a piece's keys read in eight 16-byte loads together.  A piece compares with >= before
+//     its rows' block, > behind it, and by index inside it.  (Pieces of an eighth of the range, with
+//     loops over what is left of 16 and 4 keys and compares whose masks spilled scalar registers,
+//     lost to a thread per row and 64-bit keys below 400 rows: 256 units x 300 rows 20.4 against
+//     19.2 us for the kernel and its launch, now 19.2; 576 x 384 63.7 / 62.2, now 61.5.)
 //  2. roles from the plan's ranks; output slots and seed ordinals from one block scan.
 //  3. cosine of every decode row against every seed on the matrix cores: seeds are the A
 //     operand (staged in LDS kTailSeedBlock at a time, with inverse norms), 32 decode rows a
@@ -51,18 +53,19 @@ __device__ inline float sumsq8(const uint4& v) {
 //     in ascending order: first maximum wins, folded if >= tau.
 //  4. kept rows are copied 16 bytes a thread; a wave per seed with donors folds its group in
 //     ascending row order in fp32 (score-weighted; count-weighted when the group has no mass).
-// `copiers`: a second workgroup per unit (blocks n_units ..) repeats steps 1 and 2 and copies the
+// COPIERS: a second workgroup per unit (blocks n_units ..) repeats steps 1 and 2 and copies the
 // rows that are kept and no seeds while the first one is in step 3; the first is left with the
 // seeds' own rows.  (The copy was 5 us of the chain at 512 kept rows, and the chip has compute units
 // to spare as long as both workgroups of every unit run at once.  With the rank count above and the
-// seeds' norms read four at a time: 112 units x 640 rows 31.1 -> 24.8 us, 4 x 512 rows 18.1 -> 16.5.)
-template <int D>
+// seeds' norms read four at a time, against one workgroup and 64-bit rank keys: 112 units x 640 rows
+// 30.0 -> 23.0 us, 112 x 250 16.3 -> 15.9, 4 x 512 17.5 -> 15.7.)
+template <int D, bool COPIERS>
 __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
     KParams kp, const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
     float* scores, const float* __restrict__ parts, int n_parts, int parts_pitch,
     const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, const int32_t* __restrict__ in_count,
-    uint16_t* __restrict__ K_out, uint16_t* __restrict__ V_out, int out_stride, int n_units, int copiers,
+    uint16_t* __restrict__ K_out, uint16_t* __restrict__ V_out, int out_stride, int n_units,
     int32_t* __restrict__ out_len, int32_t* __restrict__ out_src, float* __restrict__ out_mass,
     int32_t* __restrict__ out_count, int32_t* __restrict__ assign, int32_t* __restrict__ status) {
   constexpr int ROWB = D * 2;      // bytes per row
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   float* bsim_s = reinterpret_cast<float*>(ckey);
   int* seg_cnt = rank_s;
 
-  const bool copier = (int)blockIdx.x >= n_units;
+  const bool copier = COPIERS && (int)blockIdx.x >= n_units;
   const int u = copier ? (int)blockIdx.x - n_units : (int)blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -120,49 +123,53 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   // a range that is kept or dropped as a whole needs no ranks
   const bool pre_ranks = pl.p_keep > 0 && pl.p_keep < P, dec_ranks = pl.core < hi - P;
   // the decode range's keys from 0, the prefix's behind them, both padded to whole blocks of 64
-  const int n_dec = hi - P, pre_at = (n_dec + kRankPad - 1) / kRankPad * kRankPad;
+  const int n_dec = hi - P, pre_at = (n_dec + kRankPad - 1) & -kRankPad;
   const int place = i < P ? pre_at + i : i - P;
+  // a padding key stands behind every row of its range and counts for none
+  if (tid < pre_at - n_dec) ckey[n_dec + tid] = 0u;
+  if (tid < ((P + kRankPad - 1) & -kRankPad) - P) ckey[pre_at + P + tid] = 0u;
+  rank_s[tid] = 0;
+  if (tid < 2 * kRankPad) rank_s[kTailRows + tid] = 0;
   if (i < hi) ckey[place] = score_key(my_s);
-  {  // (a padding key stands behind every row of its range and counts for none)
-    if (tid < pre_at - n_dec) ckey[n_dec + tid] = 0u;
-    const int pre_end = pre_at + (P + kRankPad - 1) / kRankPad * kRankPad;
-    if (tid < pre_end - pre_at - P) ckey[pre_at + P + tid] = 0u;
-    for (int q = tid; q < pre_end; q += kTailThreads) rank_s[q] = 0;
-  }
   __syncthreads();
   {
-    constexpr int kParts = 8;
-    const int dec_blocks = dec_ranks ? pre_at / kRankPad : 0;
-    const int blocks = dec_blocks + (pre_ranks ? (P + kRankPad - 1) / kRankPad : 0);
-    for (int task = wv; task < blocks * kParts; task += kTailWaves) {
-      const int blk = task / kParts, part = task % kParts;
-      const bool dec = blk < dec_blocks;
-      const uint32_t* keys = ckey + (dec ? 0 : pre_at);
-      const int n = dec ? n_dec : P, base = (dec ? blk : blk - dec_blocks) * kRankPad;
-      const int per = (n + 4 * kParts - 1) / (4 * kParts) * 4;
-      const int j0 = part * per, j1 = min((n + 3) & ~3, j0 + per);  // multiples of four
+    constexpr int kKeys = 32;  // of a piece (half a padded block: the last piece stays inside the padding)
+    const int dec_blocks = dec_ranks ? pre_at / kRankPad : 0, pre_blocks = pre_ranks ? (P + kRankPad - 1) / kRankPad : 0;
+    const int dec_parts = (n_dec + kKeys - 1) / kKeys, pre_parts = (P + kKeys - 1) / kKeys;
+    const int dec_tasks = dec_blocks * dec_parts;
+    for (int task = wv; task < dec_tasks + pre_blocks * pre_parts; task += kTailWaves) {
+      const bool dec = task < dec_tasks;
+      const int from = dec ? 0 : pre_at, parts_n = dec ? dec_parts : pre_parts, t = dec ? task : task - dec_tasks;
+      const int blk = t / parts_n, at = (t % parts_n) * kKeys, base = blk * kRankPad;
+      const uint32_t* keys = ckey + from;
       const uint32_t me = keys[base + lane];
-      int cnt = 0;
-      auto count = [&](int from, int to, auto ahead) {  // keys [from, to) of the part; ahead(key, place)
-        int j = from;
-        for (; j + 16 <= to; j += 16) {  // four reads in flight
-          uint4 k[4];
+      uint4 k[kKeys / 4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) k[e] = *reinterpret_cast<const uint4*>(keys + j + 4 * e);
+      for (int e = 0; e < kKeys / 4; ++e) k[e] = *reinterpret_cast<const uint4*>(keys + at + 4 * e);
+      // (differences that stop at zero: a compare's mask would take two scalar registers per key)
+      auto above = [](uint32_t x, uint32_t y) { return min(__builtin_elementwise_sub_sat(x, y), 1u); };  // x > y
+      unsigned cnt = 0;
+      auto count = [&](auto term) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            cnt += (ahead(k[e].x, j + 4 * e) ? 1 : 0) + (ahead(k[e].y, j + 4 * e + 1) ? 1 : 0) +
-                   (ahead(k[e].z, j + 4 * e + 2) ? 1 : 0) + (ahead(k[e].w, j + 4 * e + 3) ? 1 : 0);
-        }
-        for (; j < to; j += 4) {
-          const uint4 k = *reinterpret_cast<const uint4*>(keys + j);
-          cnt += (ahead(k.x, j) ? 1 : 0) + (ahead(k.y, j + 1) ? 1 : 0) + (ahead(k.z, j + 2) ? 1 : 0) + (ahead(k.w, j + 3) ? 1 : 0);
+        for (int e = 0; e < kKeys / 4; ++e) {
+          cnt += term(k[e].x, 4 * e) + term(k[e].y, 4 * e + 1);
+          cnt += term(k[e].z, 4 * e + 2) + term(k[e].w, 4 * e + 3);
         }
       };
-      count(j0, min(j1, base), [&](uint32_t k, int) { return k >= me; });
-      count(max(j0, base), min(j1, base + kRankPad), [&](uint32_t k, int at) { return k > me || (k == me && at < base + lane); });
-      count(max(j0, base + kRankPad), j1, [&](uint32_t k, int) { return k > me; });
-      if (cnt) atomicAdd(&rank_s[(dec ? 0 : pre_at) + base + lane], cnt);
+      if (at < base) {  // x >= me where me is not above x
+        count([&](uint32_t x, int) { return above(me, x); });
+        cnt = kKeys - cnt;
+      } else if (at >= base + kRankPad) {
+        count([&](uint32_t x, int) { return above(x, me); });
+      } else {
+        const int mine = base + lane - at;
+        const unsigned lower = mine >= 32 ? ~0u : mine > 0 ? (1u << mine) - 1u : 0u;  // bit p: key p has a lower index
+        count([&](uint32_t x, int p) {
+          const unsigned up = above(x, me);
+          return up | (~(up | above(me, x)) & (lower >> p) & 1u);
+        });
+      }
+      if (cnt) atomicAdd(&rank_s[from + base + lane], cnt);
     }
   }
   __syncthreads();
@@ -205,7 +212,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   seg_cnt[i] = 0;
   __syncthreads();
   // Copy of `n` slots, K and V, 16 bytes a thread; slots flagged in src_s are left alone.
-  auto copy_slots = [&](int n, auto slot_at) {
+  auto copy_slots = [&](int n, auto slot_at, auto src_at) {
     constexpr int PER_SLOT = 2 * PPR;  // K pieces, then V pieces
     constexpr int NB = 12;             // loads in flight per thread
     const int pieces = n * PER_SLOT;
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
         const int t = slot_at(pc / PER_SLOT), w = pc % PER_SLOT;
         const bool is_v = w >= PPR;
         const int piece = is_v ? w - PPR : w;
-        const int src = t >= 0 ? src_s[t] : kRepFlag;
+        const int src = src_at(t);
         v[e] = *reinterpret_cast<const uint4*>((is_v ? Vu : Ku) + (size_t)(src & (kRepFlag - 1)) * D + piece * 8);
         dst[e] = (p < pieces && !(src & kRepFlag)) ? ((t * D + piece * 8) | (is_v ? (1 << 30) : 0)) : -1;
       }
@@ -241,9 +248,9 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
           *reinterpret_cast<uint4*>(((dst[e] >> 30) ? Vo : Ko) + (dst[e] & ((1 << 30) - 1))) = v[e];
     }
   };
-  auto any_slot = [](int t) { return t; };
+  auto copy_all = [&] { copy_slots(L, [](int t) { return t; }, [&](int t) { return (int)src_s[t]; }); };
   if (copier) {
-    copy_slots(L, any_slot);
+    copy_all();
     return;
   }
 
@@ -382,8 +389,12 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
     }
   }
   __syncthreads();
-  if (copiers) copy_slots(M, [&](int g) { return (int)slot_s[seed_row_s[g]]; });
-  else copy_slots(L, any_slot);
+  if constexpr (COPIERS)  // (no branch around the LDS reads either: the loads would wait for one another)
+    copy_slots(M, [&](int g) { return (int)slot_s[seed_row_s[g]]; }, [&](int t) {
+      const int src = src_s[t > 0 ? t : 0];
+      return t < 0 ? kRepFlag : src;
+    });
+  else copy_all();
   if (n_fold > 0) {
     const bool active = lane < D / 2;  // two elements a lane
     for (int g = wv; g < M; g += kTailWaves) {
@@ -475,16 +486,15 @@ hipError_t launch_tail_small(const KParams& kp, const Batch& b, float* scores, c
                              int32_t* out_count, int32_t* assign, int32_t* status,
                              hipStream_t st) {
   if (!tail_small_fits(kp, b)) return hipErrorInvalidValue;
-  const int copiers = b.n_units <= 128 ? 1 : 0;  // a workgroup fills a compute unit; there are 256
-#define CASK_TAIL(D)                                                                             \
-  tail_small_kernel<D><<<dim3(b.n_units * (1 + copiers)), dim3(kTailThreads), 0, st>>>(          \
-      kp, b.row_off, b.prefix_len, scores, parts, n_parts, parts_pitch,                          \
-      static_cast<const uint16_t*>(b.K),                                                         \
-      static_cast<const uint16_t*>(b.V), in_count, static_cast<uint16_t*>(K_out),                \
-      static_cast<uint16_t*>(V_out), out_stride, b.n_units, copiers, out_len, out_src, out_mass, out_count, assign,  \
-      status)
-  if (kp.d == 64) CASK_TAIL(64); else CASK_TAIL(128);
-#undef CASK_TAIL
+  const bool copiers = b.n_units <= 128;  // a workgroup fills a compute unit; there are 256
+  auto go = [&](auto kern) {
+    kern<<<dim3(b.n_units * (copiers ? 2 : 1)), dim3(kTailThreads), 0, st>>>(
+        kp, b.row_off, b.prefix_len, scores, parts, n_parts, parts_pitch, static_cast<const uint16_t*>(b.K),
+        static_cast<const uint16_t*>(b.V), in_count, static_cast<uint16_t*>(K_out), static_cast<uint16_t*>(V_out), out_stride,
+        b.n_units, out_len, out_src, out_mass, out_count, assign, status);
+  };
+  if (kp.d == 64) go(copiers ? &tail_small_kernel<64, true> : &tail_small_kernel<64, false>);
+  else go(copiers ? &tail_small_kernel<128, true> : &tail_small_kernel<128, false>);
   return hipGetLastError();
 }
 
