@@ -109,6 +109,33 @@ def test_attention_tiles_splits_and_rows_past_the_end(d, G, stride, n, dtype):
         _note(dtype, d, G, stride, split, _attend_check(p, rp, got, ref.attend(rp, Qh, Kh, Vh, lens, count=pad), Qh, Kh, Vh, lens, pad))
 
 
+@pytest.mark.parametrize("d,G,n,units", [(128, 7, 2000, 12), (128, 4, 300, 24), (64, 3, 1000, 24), (64, 8, 4097, 6)])
+def test_fp32_attention_keeps_the_precision_of_short_sums(d, G, n, units):
+    """fp32 cask_attend against 64-bit sums: 2-norm of the error over 2-norm of the result.  A weight is
+    off by ln 2 times its base-2 logit's error, and the logits that count are about 10 here.  A logit
+    of d products in chains of eight, the chains added in pairs, passes about 8 / 2 + log2(d / 8) = 8
+    roundings of 2^-25 x 10 / sqrt(3) at full size, most of them smaller: below ln 2 x 4.8e-7 = 3.4e-7;
+    the value sums add less than 2e-7, in squares: 4e-7.  (One chain of d products: 4.5e-7 to 8.5e-7.)"""
+    dev = torch.device("cuda:0")
+    g = torch.Generator().manual_seed(n + d)
+    Q = 1.2 * torch.randn(units, G, d, generator=g)
+    K = torch.randn(units, n, d, generator=g)
+    Q += 0.35 * K[:, n // 2][:, None] + 0.35 * K[:, n // 3][:, None]     # two rows that hold much of the weight
+    V = torch.randn(units, n, d, generator=g)
+    count = torch.randint(1, 4, (units, n), generator=g, dtype=torch.int32)
+    p = cask.Params(dtype=cask.F32, head_dim=d, q_per_kv=G, window=1, budget=n)
+    for cnt in (None, count):
+        x = Q.double() @ K.double().transpose(1, 2) / d ** 0.5
+        if cnt is not None:
+            x = x + cnt.double().log()[:, None, :]
+        want = torch.softmax(x, dim=2) @ V.double()
+        got = cask.attend(p, Q.to(dev), K.to(dev), V.to(dev), torch.full((units,), n, dtype=torch.int32, device=dev),
+                          count=None if cnt is None else cnt.to(dev)).cpu().double()
+        err = float((got - want).norm() / want.norm())
+        _note(d, G, n, cnt is not None, "largest logit", round(float(x.max()) * 1.4427, 1), "error", err)
+        assert err < 4e-7
+
+
 @pytest.mark.parametrize("radius", [0, 70])
 @pytest.mark.parametrize("tau", [0.3, -2.0])
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
