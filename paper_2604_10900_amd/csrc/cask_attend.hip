@@ -372,7 +372,9 @@ hipError_t launch_attend_as(const KParams& kp, int n_units, const void* Q, const
 }
 
 // Waves per workgroup.  Few units: eight (more rows of a unit in flight); many: four, so that
-// several workgroups share a compute unit and one's merge overlaps the others' loads.
+// several workgroups share a compute unit and one's merge overlaps the others' loads.  Long fp32
+// units of 64 channels take eight whatever their number (600 units, four against eight: 3000 rows 174 / 166 us,
+// 1000 rows 62 / 58; 4000 units x 1000 rows 320 / 309; but 2000 of 250 rows 46 / 48).
 // Non-temporal loads where the caches of the call exceed the 256 MB last-level cache, so that no
 // call can find them there (554 MB: 102 -> 91 us; 1 GB of fp32: 185 -> 169 us); below that a
 // call that repeats finds its rows there and the hint costs up to a quarter.
@@ -381,7 +383,8 @@ hipError_t launch_attend_t(const KParams& kp, int n_units, const void* Q, const 
                            const int32_t* len, const int32_t* count, int count_pitch, void* out, int splits,
                            float* part, hipStream_t st) {
   const bool nt = (int64_t)n_units * stride * (2 * D * (int)sizeof(T)) > (256ll << 20);
-  const bool four = (int64_t)n_units * splits >= 512;
+  const bool long_f32 = sizeof(T) == 4 && D == 64 && stride > 6 * 8 * AttGeom<T, D>::kTileRows;  // six rounds of eight waves
+  const bool four = (int64_t)n_units * splits >= 512 && !long_f32;
   auto go = [&](auto f) { return f(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, splits, part, st); };
   if (four) return nt ? go(&launch_attend_as<T, D, 4, true>) : go(&launch_attend_as<T, D, 4, false>);
   return nt ? go(&launch_attend_as<T, D, 8, true>) : go(&launch_attend_as<T, D, 8, false>);
