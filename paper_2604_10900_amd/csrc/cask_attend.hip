@@ -392,18 +392,29 @@ hipError_t launch_attend_t(const KParams& kp, int n_units, const void* Q, const 
 
 }  // namespace
 
-// Workgroups that share a unit.  Without a workspace one; with it enough to fill the chip, as long
-// as each still has two rounds of tiles and the unit at least six (the combining launch behind them
-// costs about 4 us, a round of eight waves about 2.5 us).  Measured, one workgroup per unit -> split:
-// 8 units x 16 000 rows 159 -> 21 us, 16 x 4000 45 -> 13.7, 45 x 15 648 218 -> 73, 4 x 1500 21.7 ->
-// 13; 256 x 2000 (two each) 43 -> 47, so not beyond 128 units.
+// Workgroups that share a unit.  Without a workspace one; with it enough to fill the chip's compute
+// units, of which a workgroup of eight waves takes one (the row loads in flight need the registers),
+// as long as each still has two rounds of tiles and the unit at least six (the combining launch behind
+// them costs about 4 us, a round of eight waves about 2.5 us).  A few workgroups more than compute
+// units make a second turn of the chip that is nearly empty, so it is as many as fit at once; twice
+// as many (the form with four waves) only where that fills the chip exactly and they stay long enough,
+// or where one turn would leave a fifth of the chip idle and the units are long.
+// Measured, one workgroup per unit -> split (bf16, d = 128): 8 units x 16 000 rows 159 -> 21 us,
+// 16 x 4000 45 -> 14, 4 x 1500 21 -> 12, 100 x 2000 34 -> 25, 128 x 2000 36 -> 30; with 384 and
+// 400 workgroups the last two took 37 and 29.  Two workgroups a unit and six rounds: 128 x 1281 19.6 ->
+// 20.6, so a bf16 unit has to have seven then (seven: 29.7 -> 24.5; fp32, whose rounds are longer, six: 27.2 ->
+// 22.9).  256 x 2000 (two each) 43 -> 47, so not beyond 128 units.
 int attend_splits(const KParams& kp, int n_units, int stride) {
   if (n_units <= 0 || n_units > 128) return 1;
   const int tile = kp.dtype == CASK_BF16 ? 32 : 16;
   const int rounds = (stride + tile * 8 - 1) / (tile * 8);  // of eight waves, all rows used
   if (rounds < 6) return 1;
-  int s = 512 / n_units;
+  int s = 256 / n_units;
+  const int twice = 512 / n_units;
+  // (96 units: 6000 rows, two and five workgroups each 59.6 / 58.7 us; 16 000 rows 141 / 132)
+  if ((twice * n_units == 512 && rounds >= 2 * twice) || (10 * twice > 23 * s && rounds >= 4 * twice)) s = twice;
   if (s > rounds / 2) s = rounds / 2;
+  if (s == 2 && rounds < 7 && kp.dtype == CASK_BF16) return 1;
   return s > 64 ? 64 : s;
 }
 

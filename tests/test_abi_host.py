@@ -336,6 +336,30 @@ def test_attend_validates_on_the_host(cask):
     assert rc(params=cask.Params(head_dim=100).c()) == cask.binding.EINVAL
 
 
+def _attend_splits(cask, p, units, stride):
+    """Workgroups a unit's rows are shared by, from the size of the partial results."""
+    n = cask.load().cask_attend_workspace_bytes(C.byref(p.c()), units, stride)
+    per = units * p.q_per_kv * (p.head_dim + 2) * 4
+    assert n % per == 0
+    return n // per or 1
+
+
+@pytest.mark.parametrize("dtype,tile", [(1, 32), (0, 16)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_attend_splits_leave_no_nearly_empty_turn_of_the_chip(cask, dtype, tile, d):
+    """The split of cask_attend_ws: at most one workgroup per compute unit (256), or two each where that
+    fills the chip to four fifths; two rounds of tiles or more for every workgroup."""
+    p = cask.Params(dtype=dtype, head_dim=d, q_per_kv=4, window=1, budget=1)
+    for units in list(range(1, 131)) + [255, 256, 512]:
+        for stride in (1, 16, 500, 641, 1280, 1281, 1540, 2000, 2600, 4000, 9000, 16384, 100000):
+            s = _attend_splits(cask, p, units, stride)
+            rounds = -(-stride // (8 * tile))
+            assert 1 <= s <= 64
+            if s > 1:
+                assert units <= 128 and rounds >= 6 and 2 * s <= rounds
+                assert units * s <= 256 or 410 <= units * s <= 512, (units, stride, s)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is what this build measures: `bench.py --gpus 2` says so and exits before it
     touches a device."""
