@@ -408,7 +408,7 @@ int attend_splits(const KParams& kp, int n_units, int stride) {
   if (n_units <= 0 || n_units > 128) return 1;
   const int tile = kp.dtype == CASK_BF16 ? 32 : 16;
   const int rounds = (stride + tile * 8 - 1) / (tile * 8);  // of eight waves, all rows used
-  if (rounds < 6) return 1;
+  if (rounds < 6 || (int64_t)n_units * kp.G * kp.d > (1 << 30)) return 1;  // (the combining launch counts elements in 32 bits)
   int s = 256 / n_units;
   const int twice = 512 / n_units;
   // (96 units: 6000 rows, two and five workgroups each 59.6 / 58.7 us; 16 000 rows 141 / 132)

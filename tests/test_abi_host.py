@@ -360,6 +360,16 @@ def test_attend_splits_leave_no_nearly_empty_turn_of_the_chip(cask, dtype, tile,
                 assert units * s <= 256 or 410 <= units * s <= 512, (units, stride, s)
 
 
+def test_attend_does_not_split_more_elements_than_the_combining_launch_counts(cask):
+    """units x heads x channels beyond 32 bits: no split (its launch would be refused or write elsewhere)."""
+    for heads, units in ((1 << 17, 128), (1 << 20, 16), (1 << 18, 64)):
+        p = cask.Params(dtype=1, head_dim=128, q_per_kv=heads, window=1, budget=1)
+        assert units * heads * 128 >= 1 << 31
+        assert _attend_splits(cask, p, units, 8192) == 1
+    p = cask.Params(dtype=1, head_dim=128, q_per_kv=512, window=1, budget=1)
+    assert _attend_splits(cask, p, 16, 8192) > 1
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is what this build measures: `bench.py --gpus 2` says so and exits before it
     touches a device."""
