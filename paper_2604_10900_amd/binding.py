@@ -8,6 +8,7 @@ compression event is computed here, and there is no CPU fallback: a missing libr
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -65,8 +66,14 @@ class _Plan(C.Structure):
                 ("core", C.c_int32), ("seeds", C.c_int32), ("status", C.c_int32)]
 
 
+class _ImageSlot:
+    """Where Params keeps its C image: outside the instance's dict, so that vars(), copies and pickles
+    hold the fields alone."""
+    __slots__ = ("_image",)
+
+
 @dataclass
-class Params:
+class Params(_ImageSlot):
     dtype: int = BF16
     head_dim: int = 128
     q_per_kv: int = 1
@@ -87,20 +94,22 @@ class Params:
     score_splits: int = 0          # forced key splits of the first scoring sweep (0: the library's choice)
     score_qsplit: int = 0          # forced sharing of a key tile in the second sweep (0: the library's choice)
 
-    def __setattr__(self, name, value):
-        object.__setattr__(self, name, value)
-        object.__setattr__(self, "_packed", None)   # the C image of the fields is stale
+    def __getstate__(self):
+        return dict(self.__dict__)
 
     def c(self, scores_given: int = 0) -> _Params:
-        """The C struct of one call: the fields (packed when they last changed), the environment's
-        switches, and the band weights' present address."""
-        packed = self._packed
-        if packed is None:
-            packed = bytes(_Params(self.dtype, self.head_dim, self.q_per_kv, self.window, self.recent, self.budget, self.core,
-                                   self.prefix_budget, self.sim_threshold, self.softmax_scale, self.causal, 0,
-                                   self.merge_radius, self.merge_geometry, self.dist_threshold, None, self.seed_dedup,
-                                   self.path_flags, self.score_splits, self.score_qsplit))
-            object.__setattr__(self, "_packed", packed)
+        """The C struct of one call: the fields, the environment's switches, and the band weights'
+        present address.  (The packed fields are kept beside the values they were packed from and
+        used again while the fields hold these values, however they were set: 1.0 us a call, 2 us
+        packed each time.)"""
+        values = _packed_values(self)
+        try:
+            packed_from, packed = self._image
+        except AttributeError:   # not packed yet
+            packed_from = None
+        if packed_from != values:
+            packed = bytes(_Params(*values[:11], 0, *values[11:14], None, *values[14:]))
+            self._image = (values, packed)   # one assignment: another thread sees both parts or neither
         out = _Params.from_buffer_copy(packed)
         if scores_given:
             out.scores_given = scores_given
@@ -115,10 +124,13 @@ class Params:
         return out
 
 
+_packed_values = operator.attrgetter(*(f for f, _ in _Params._fields_ if f not in ("scores_given", "band_weight")))
+
 _ENV_NAMES = ("CASK_FUSED_TAIL", "CASK_FUSED_SCORE", "CASK_FUSED_SWEEPS", "CASK_DEDUP_VECTOR", "CASK_NARROW_ROWS",
               "CASK_WIDE_ROWS", "CASK_SPLITS", "CASK_QSPLIT")
 # os.environ's own dict, looked up without its per-access encoding (eight lookups 0.4 us, through the
 # mapping 5 us): an event of a short unit takes 40 us in all
+_env_object = os.environ
 _env_raw = getattr(os.environ, "_data", None)
 _env_keys = tuple(os.environ.encodekey(n) for n in _ENV_NAMES) if _env_raw is not None else _ENV_NAMES
 _env_lookup = _env_raw.get if _env_raw is not None else os.environ.get
@@ -126,6 +138,8 @@ _env_lookup = _env_raw.get if _env_raw is not None else os.environ.get
 
 def _env_any() -> bool:
     """Whether any of the measurement switches is set."""
+    if os.environ is not _env_object:
+        return any(map(os.environ.get, _ENV_NAMES))
     return any(map(_env_lookup, _env_keys))
 
 

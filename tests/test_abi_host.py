@@ -370,6 +370,66 @@ def test_attend_does_not_split_more_elements_than_the_combining_launch_counts(ca
     assert _attend_splits(cask, p, 16, 8192) > 1
 
 
+def test_params_struct_follows_the_fields_however_they_are_set(cask):
+    """The C struct of a call holds the fields' present values, also where they were not set by plain
+    assignment, and the instance shows its fields and nothing else."""
+    import copy
+    import dataclasses
+    import pickle
+    Params = cask.Params
+    p = Params(budget=300, sim_threshold=0.5)
+    assert p.c().budget == 300
+    vars(p)["budget"] = 301
+    assert p.c().budget == 301
+    p.__dict__.update(window=64, q_per_kv=2)
+    assert (p.c().window, p.c().q_per_kv) == (64, 2)
+    object.__setattr__(p, "core", 7)
+    assert p.c().core == 7
+    p.sim_threshold = 0.25
+    assert p.c().sim_threshold == 0.25
+    assert p.c(1).scores_given == 1 and p.c().scores_given == 0
+    names = [f.name for f in dataclasses.fields(Params)]
+    assert sorted(vars(p)) == sorted(names)
+    for q in (Params(**vars(p)), copy.copy(p), copy.deepcopy(p), pickle.loads(pickle.dumps(p)), dataclasses.replace(p)):
+        assert q == p and bytes(q.c()) == bytes(p.c())
+        q.budget = 999
+        assert q.c().budget == 999 and p.c().budget == 301
+    old = Params.__new__(Params)          # an instance restored from its fields alone
+    old.__dict__.update(vars(p))
+    assert bytes(old.c()) == bytes(p.c())
+    p.budget = 384.0
+    with pytest.raises(TypeError):
+        p.c()
+
+
+def test_params_field_set_while_another_thread_packs(cask, monkeypatch):
+    """A field set between the reading of the fields and the end of the packing shows in the next call."""
+    b = cask.binding
+    p = cask.Params(budget=300)
+    plain = b._Params
+
+    def packing(*a):
+        out = plain(*a)
+        p.budget = 400            # what another thread does meanwhile
+        return out
+    packing.from_buffer_copy = plain.from_buffer_copy
+    monkeypatch.setattr(b, "_Params", packing)
+    first = p.c().budget
+    monkeypatch.setattr(b, "_Params", plain)
+    assert first in (300, 400) and p.c().budget == 400
+
+
+def test_environment_switches_are_read_at_the_call(cask, monkeypatch):
+    p = cask.Params()
+    assert p.c().score_splits == 0
+    monkeypatch.setenv("CASK_SPLITS", "3")
+    assert p.c().score_splits == 3
+    monkeypatch.delenv("CASK_SPLITS")
+    assert p.c().score_splits == 0
+    monkeypatch.setattr(os, "environ", {"CASK_SPLITS": "5", "CASK_NARROW_ROWS": "1"})
+    assert p.c().score_splits == 5 and p.c().path_flags == cask.binding.PATH_NARROW_ROWS
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU is what this build measures: `bench.py --gpus 2` says so and exits before it
     touches a device."""
