@@ -52,6 +52,26 @@ def test_scores_with_64_channels(G, Wn, causal, splits, form):
     _note(form, G, Wn, causal, "score error / max", parity.check_scores(s.cpu().numpy(), ref.score(parity.ref_params(p), row_off, K, Q), row_off))
 
 
+@pytest.mark.parametrize("G,Wn,n,units", [(1, 128, 2000, 8), (2, 32, 3000, 12), (4, 64, 5378, 6), (5, 100, 1500, 12)])
+def test_scores_with_64_channels_keep_the_precision_of_the_vector_kernel(G, Wn, n, units):
+    """bf16 scores with d = 64 against 64-bit sums: 2-norm of the error over 2-norm of the result.  Two
+    roundings count: that of a row's log-sum-exp (8 to 32 in base 2: half an ulp of it, uniform, 2.7e-7 to
+    5.5e-7 x ln 2) and that of a term's distance from the row's reference, as much again if the reference
+    lies as far off; a score is the mean over rows, so both shrink with the rows that see the key.
+    Reference near the largest logit: 1.7e-7 to 2.6e-7; at the row's first: 3.3e-7 to 4.2e-7."""
+    c = _units([n] * units, [n // 8] * units, head_dim=64, q_per_kv=G, window=Wn)
+    K, Q = c["K"].double().reshape(units, n, 64), c["Q"].double().reshape(units, Wn * G, 64)
+    x = Q @ K.transpose(1, 2).contiguous() / 8.0
+    sees = n - Wn + torch.arange(Wn * G) // G
+    x.masked_fill_(torch.arange(n)[None, None] > sees[None, :, None], float("-inf"))
+    want = torch.softmax(x, dim=2).mean(dim=1).reshape(-1)
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=G, window=Wn, budget=Wn + 60)
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    err = float((got - want).norm() / want.norm())
+    _note(G, Wn, n, units, "error", err)
+    assert err < 3e-7
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("G,Wn,causal,splits", [(4, 64, 1, 0), (7, 100, 1, 3), (1, 17, 1, 0), (4, 128, 0, 64), (1, 33, 0, 1)])
 def test_fp32_scores_on_the_matrix_tiles(G, Wn, causal, splits, d):
