@@ -260,6 +260,20 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           brsrc, (__attribute__((address_space(3))) void*)(slot + kDataBytes), 4, lane * 4,
           (s_begin + sstage * kStageRows) * 4, 0, 0);
+    // Sweep B's last stage, 64 channels: its places past the last window row hold that row again (their
+    // bias makes nothing of it).  A zero row times a key with an infinity would be a NaN.
+    const int past = s_begin + (src_stage + 1) * kStageRows - s_end;
+    if (MODE == 1 && D == 64 && past > 0 && past < kStageRows) {
+#pragma unroll
+      for (int j = 0; j < kLoadsPerThread; ++j) {
+        const int grp = wv + kWaves * j;
+        const int over = max(0, grp * kGroupRows + lane % kGroupRows - (kStageRows - 1 - past));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc, (__attribute__((address_space(3))) void*)(slot + grp * kGroupPitch),
+            16, ld_voff + (j * kWaves * kGroupRows - over) * kRowBytes, soff, 0, 0);
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < kLoadsPerThread; ++j) {
       const int grp = wv + kWaves * j;
@@ -309,7 +323,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     // zero), after the ring's first loads are on their way so that the two latencies overlap
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      const int r = res_row_of(ct);
+      // (one launch for both sweeps: places past the last window row hold that row again, see issue_stage)
+      const int r = kTwoPass ? min(res_row_of(ct), res_limit - 1) : res_row_of(ct);
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks) {
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(res_rsrc, r * kRowBytes + h * 16, ks * 32, 0);
@@ -1079,14 +1094,16 @@ __global__ __launch_bounds__(NW * 64, 2) void score_short_kernel(
   const int last_key = kp.causal ? N - kp.W + last_row / Gq : N - 1;  // < N
   auto tile0 = [&](int kt) { return (kt * NW + wv) * 32; };  // first key
   auto seen = [&](int kt) { return tile0(kt) <= last_key; };
-  auto masked = [&](int kt) { return tile0(kt) + 31 > tail; };
+  const bool ragged = row_base + 64 > Mq;  // (a zero row past the last times a key with an infinity: a NaN)
+  auto masked = [&](int kt) { return tile0(kt) + 31 > tail || ragged; };
   // Bit r: the lane's key of tile kt is hidden from row r of the 16 the lane holds in row tile rt.
   // (Bit fields, not compares: a compare and its select wait for each other.)
   auto hidden_bits = [&](int kt, int rt) {
     const int key = tile0(kt) + c32;
     const int first = key < N ? (kp.causal ? (key - (N - kp.W)) * Gq : 0) : 0x40000000;  // first row that sees the key
     const int d = min(max(first - row_base - rt * 32 - h * 4, 0), 32);                    // hidden: row offset < d
-    const unsigned below = (unsigned)((1ull << d) - 1ull);                                // offsets 0 .. 31; the lane's are 8 g + 0 .. 3
+    const int rows = min(max(Mq - row_base - rt * 32 - h * 4, 0), 32);                    // hidden: row offset >= rows
+    const unsigned below = (unsigned)((1ull << d) - 1ull) | ~(unsigned)((1ull << rows) - 1ull);  // offsets 0 .. 31; the lane's are 8 g + 0 .. 3
     return (below & 0xFu) | ((below >> 4) & 0xF0u) | ((below >> 8) & 0xF00u) | ((below >> 12) & 0xF000u);
   };
   auto where_hidden = [&](unsigned bits, int r, unsigned then, float x) {  // x, or the bit pattern `then` where hidden
@@ -1384,11 +1401,12 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
         nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
       }
       float sum = 0.f;
-      if (it < f0) {
+      if (it < f0 || s_begin + (it + 1) * kStageRows > s_end) {  // (rows past the last: zero times an infinite key is a NaN)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+          const int row = trow + (r >> 2) * 8 + (r & 3);
           const float y = __builtin_fmaf(acc[r], c, nl[r]);
-          sum += fast_exp2(trow + (r >> 2) * 8 + (r & 3) < first_row ? kNegInf : y);
+          sum += fast_exp2(row < first_row || row >= s_end ? kNegInf : y);
         }
       } else {
 #pragma unroll

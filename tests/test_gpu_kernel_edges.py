@@ -229,6 +229,35 @@ def test_hidden_keys_keep_their_scores_when_a_window_row_is_nan():
     assert torch.equal(got[last + 1:], clean[last + 1:])
 
 
+@pytest.mark.parametrize("dtype,d,form", [("bf16", 64, f) for f in sorted(SCORE_FORMS)] + [("f32", 64, "chosen"), ("f32", 128, "chosen"),
+                                                                                         ("bf16", 64, "short"), ("bf16", 128, "short")])
+@pytest.mark.parametrize("G,Wn", [(1, 17), (2, 33), (7, 100), (4, 64)])
+def test_a_key_at_minus_infinity_scores_zero(G, Wn, dtype, d, form):
+    """Keys whose logit is -inf for every window row that sees them get the score 0 and leave the others
+    theirs, also where W * G does not fill the last tile of window rows (the tile's spare places must
+    not multiply zeros with the infinity)."""
+    lens = [300, 449] if form == "short" else [257, 1500, 700]
+    c = _units(lens, [0] * len(lens), head_dim=d, q_per_kv=G, window=Wn)
+    if dtype == "f32":
+        c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    c["Q"][..., 0] = c["Q"][..., 0].abs() + 0.125
+    spots = [int(c["row_off"][u]) + r for u, n in enumerate(lens) for r in (5, n // 2, n - 1)]
+    c["K"][spots, 0] = float("-inf")
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60,
+                    path_flags=SCORE_FORMS.get(form, 0))
+    b = parity.to_device(c, p)
+    got = (cask.compress(b).scores if form == "short" else cask.score(b)).cpu()
+    want = torch.empty(got.shape, dtype=torch.float64)
+    for u, n in enumerate(lens):
+        lo = int(c["row_off"][u])
+        x = c["Q"][u].double().reshape(-1, d) @ c["K"][lo:lo + n].double().t().contiguous() / d ** 0.5
+        x.masked_fill_(torch.arange(n)[None] > n - Wn + torch.arange(Wn * G)[:, None] // G, float("-inf"))
+        want[lo:lo + n] = torch.softmax(x, dim=1).mean(dim=0)
+    assert not torch.isnan(want).any()
+    assert (got[spots] == 0).all()
+    assert float((got.double() - want).abs().max()) <= 1e-4 * float(want.max())
+
+
 @pytest.mark.parametrize("units", [3, 131])
 @pytest.mark.parametrize("d,R,budget,core,prefix_budget", [(128, -1, 300, -1, 100), (64, 40, 257, 64, 65), (128, 33, 129, 0, 64)])
 def test_tail_of_short_units_at_the_edges_of_rank_pieces(d, R, budget, core, prefix_budget, units):
