@@ -41,7 +41,7 @@ __device__ inline float sumsq8(const uint4& v) {
 //  1. rank: a row's rank inside its range (prefix, or decode trace without the recent tail) is the
 //     number of rows with a larger score key, or an equal one and a lower index: a counting loop
 //     over the range's keys in LDS.  The work is dealt to the sixteen waves in pieces of 64 rows x
-//     32 keys, a piece's keys read in eight 16-byte loads together.  A piece compares with >= before
+//     32 keys (LONG: 128), read in eight 16-byte loads together.  A piece compares with >= before
 //     its rows' block, > behind it, and by index inside it.  (Pieces of an eighth of the range, with
 //     loops over what is left of 16 and 4 keys and compares whose masks spilled scalar registers,
 //     lost to a thread per row and 64-bit keys below 400 rows: 256 units x 300 rows 20.4 against
@@ -59,7 +59,7 @@ __device__ inline float sumsq8(const uint4& v) {
 // to spare as long as both workgroups of every unit run at once.  With the rank count above and the
 // seeds' norms read four at a time, against one workgroup and 64-bit rank keys: 112 units x 640 rows
 // 30.0 -> 23.0 us, 112 x 250 16.3 -> 15.9, 4 x 512 17.5 -> 15.7.)
-template <int D, bool COPIERS>
+template <int D, bool COPIERS, bool LONG>
 __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
     KParams kp, const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
     float* scores, const float* __restrict__ parts, int n_parts, int parts_pitch,
@@ -133,43 +133,51 @@ __global__ __launch_bounds__(kTailThreads) void tail_small_kernel(
   if (i < hi) ckey[place] = score_key(my_s);
   __syncthreads();
   {
-    constexpr int kKeys = 32;  // of a piece (half a padded block: the last piece stays inside the padding)
+    constexpr int kKeys = 32;              // keys read together (half a padded block: the last ones stay inside the padding)
+    constexpr int kPiece = LONG ? 128 : kKeys;  // keys of a piece
     const int dec_blocks = dec_ranks ? pre_at / kRankPad : 0, pre_blocks = pre_ranks ? (P + kRankPad - 1) / kRankPad : 0;
-    const int dec_parts = (n_dec + kKeys - 1) / kKeys, pre_parts = (P + kKeys - 1) / kKeys;
+    const int dec_parts = (n_dec + kPiece - 1) / kPiece, pre_parts = (P + kPiece - 1) / kPiece;
     const int dec_tasks = dec_blocks * dec_parts;
     for (int task = wv; task < dec_tasks + pre_blocks * pre_parts; task += kTailWaves) {
       const bool dec = task < dec_tasks;
       const int from = dec ? 0 : pre_at, parts_n = dec ? dec_parts : pre_parts, t = dec ? task : task - dec_tasks;
-      const int blk = t / parts_n, at = (t % parts_n) * kKeys, base = blk * kRankPad;
+      const int blk = t / parts_n, base = blk * kRankPad;
+      int at = (t % parts_n) * kPiece;
+      const int end = min(at + kPiece, dec ? n_dec : P);
       const uint32_t* keys = ckey + from;
       const uint32_t me = keys[base + lane];
-      uint4 k[kKeys / 4];
-#pragma unroll
-      for (int e = 0; e < kKeys / 4; ++e) k[e] = *reinterpret_cast<const uint4*>(keys + at + 4 * e);
       // (differences that stop at zero: a compare's mask would take two scalar registers per key)
       auto above = [](uint32_t x, uint32_t y) { return min(__builtin_elementwise_sub_sat(x, y), 1u); };  // x > y
-      unsigned cnt = 0;
-      auto count = [&](auto term) {
+      int rank = 0;
+      do {
+        uint4 k[kKeys / 4];
 #pragma unroll
-        for (int e = 0; e < kKeys / 4; ++e) {
-          cnt += term(k[e].x, 4 * e) + term(k[e].y, 4 * e + 1);
-          cnt += term(k[e].z, 4 * e + 2) + term(k[e].w, 4 * e + 3);
+        for (int e = 0; e < kKeys / 4; ++e) k[e] = *reinterpret_cast<const uint4*>(keys + at + 4 * e);
+        unsigned cnt = 0;
+        auto count = [&](auto term) {
+#pragma unroll
+          for (int e = 0; e < kKeys / 4; ++e) {
+            cnt += term(k[e].x, 4 * e) + term(k[e].y, 4 * e + 1);
+            cnt += term(k[e].z, 4 * e + 2) + term(k[e].w, 4 * e + 3);
+          }
+        };
+        if (at < base) {  // x >= me where me is not above x
+          count([&](uint32_t x, int) { return above(me, x); });
+          cnt = kKeys - cnt;
+        } else if (at >= base + kRankPad) {
+          count([&](uint32_t x, int) { return above(x, me); });
+        } else {
+          const int mine = base + lane - at;
+          const unsigned lower = mine >= 32 ? ~0u : mine > 0 ? (1u << mine) - 1u : 0u;  // bit p: key p has a lower index
+          count([&](uint32_t x, int p) {
+            const unsigned up = above(x, me);
+            return up | (~(up | above(me, x)) & (lower >> p) & 1u);
+          });
         }
-      };
-      if (at < base) {  // x >= me where me is not above x
-        count([&](uint32_t x, int) { return above(me, x); });
-        cnt = kKeys - cnt;
-      } else if (at >= base + kRankPad) {
-        count([&](uint32_t x, int) { return above(x, me); });
-      } else {
-        const int mine = base + lane - at;
-        const unsigned lower = mine >= 32 ? ~0u : mine > 0 ? (1u << mine) - 1u : 0u;  // bit p: key p has a lower index
-        count([&](uint32_t x, int p) {
-          const unsigned up = above(x, me);
-          return up | (~(up | above(me, x)) & (lower >> p) & 1u);
-        });
-      }
-      if (cnt) atomicAdd(&rank_s[from + base + lane], cnt);
+        rank += (int)cnt;
+        at += kKeys;
+      } while (LONG && at < end);
+      if (rank) atomicAdd(&rank_s[from + base + lane], rank);
     }
   }
   __syncthreads();
@@ -493,8 +501,17 @@ hipError_t launch_tail_small(const KParams& kp, const Batch& b, float* scores, c
         static_cast<const uint16_t*>(b.V), in_count, static_cast<uint16_t*>(K_out), static_cast<uint16_t*>(V_out), out_stride,
         b.n_units, out_len, out_src, out_mass, out_count, assign, status);
   };
-  if (kp.d == 64) go(copiers ? &tail_small_kernel<64, true> : &tail_small_kernel<64, false>);
-  else go(copiers ? &tail_small_kernel<128, true> : &tail_small_kernel<128, false>);
+  using std::integral_constant;
+  const bool longer = b.max_unit_len > 640;  // (700 to 1024 rows in pieces of 32 keys: 1 - 4 % slower)
+  auto pick = [&](auto d, auto c) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool C = decltype(c)::value;
+    go(longer ? &tail_small_kernel<D, C, true> : &tail_small_kernel<D, C, false>);
+  };
+  const integral_constant<int, 64> d64;
+  const integral_constant<int, 128> d128;
+  if (kp.d == 64) copiers ? pick(d64, std::true_type()) : pick(d64, std::false_type());
+  else copiers ? pick(d128, std::true_type()) : pick(d128, std::false_type());
   return hipGetLastError();
 }
 

@@ -274,6 +274,19 @@ def test_tail_of_short_units_at_the_edges_of_rank_pieces(d, R, budget, core, pre
     _note(d, budget, units, parity.full_check(c, p))
 
 
+@pytest.mark.parametrize("longest", [640, 641])
+@pytest.mark.parametrize("units", [4, 130])
+def test_rank_pieces_of_batches_up_to_and_beyond_640_rows(units, longest):
+    """The rank count's two piece sizes (the batch's longest unit decides), with and without the copying
+    workgroups: prefix-only units, prefixes and traces of a piece, a block and one row more or less."""
+    Wn = 32
+    cand = [(longest, 300), (64 + Wn, 64 + Wn), (longest, longest), (Wn + 33, 31), (Wn + 257, 129), (Wn + 160, 32), (400, 255)]
+    lens, pref = zip(*[cand[i % len(cand)] for i in range(units)])
+    c = _units(list(lens), list(pref), head_dim=128, q_per_kv=2, window=Wn, cluster_frac=0.6)
+    p = cask.Params(dtype=cask.BF16, head_dim=128, q_per_kv=2, window=Wn, budget=90, prefix_budget=40)
+    _note(units, longest, parity.full_check(c, p))
+
+
 @pytest.mark.parametrize("merged", [0.02, 0.9])
 @pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "f32"), (128, "f32")])
 def test_group_diagnostics_around_a_round_of_rows(d, dtype, merged):
