@@ -129,6 +129,80 @@ def test_attention_tiles_splits_and_rows_past_the_end(d, G, stride, n, dtype):
         _note(dtype, d, G, stride, split, _attend_check(p, rp, got, ref.attend(rp, Qh, Kh, Vh, lens, count=pad), Qh, Kh, Vh, lens, pad))
 
 
+def _attend_inputs(dtype, d, G, stride, n, seed):
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(seed)
+    Q, K, V = ((s * torch.randn(*shape, generator=g, device="cuda:0")).to(dt)
+               for s, shape in ((1.5, (n, G, d)), (1.0, (n, stride, d)), (1.0, (n, stride, d))))
+    rng = np.random.default_rng(seed)
+    lens = np.where(rng.random(n) < 0.3, rng.integers(1, stride + 1, n), stride - rng.integers(0, min(stride, 40), n)).astype(np.int32)
+    lens[0] = stride
+    count = rng.integers(1, 20, (n, stride)).astype(np.int32)
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=1, budget=stride)
+    return p, Q, K, V, lens, count
+
+
+def _attend_some(p, got, Q, K, V, lens, count, units):
+    """Units `units` of a result against the oracle."""
+    rp = parity.ref_params(p)
+    Qh, Kh, Vh = (caches.host_bits(x[units]) for x in (Q, K, V))
+    cnt = None if count is None else count[units]
+    return _attend_check(p, rp, got[units], ref.attend(rp, Qh, Kh, Vh, lens[units], count=cnt), Qh, Kh, Vh, lens[units], cnt)
+
+
+@pytest.mark.parametrize("dtype,d,G,stride,n", [
+    # four waves per workgroup (512 workgroups or more)
+    ("bf16", 128, 7, 97, 513), ("bf16", 64, 3, 161, 600), ("f32", 128, 17, 33, 520), ("f32", 64, 2, 300, 512), ("bf16", 128, 4, 2050, 128),
+    # long fp32 units of 64 channels: eight waves however many units
+    ("f32", 64, 2, 769, 512),
+    # caches beyond 256 MB: non-temporal loads, four and eight waves
+    ("bf16", 128, 4, 1101, 512), ("bf16", 128, 2, 1801, 300), ("bf16", 64, 4, 1001, 1100), ("bf16", 64, 1, 2201, 500),
+    ("f32", 128, 3, 551, 512), ("f32", 128, 4, 1001, 300), ("f32", 64, 4, 601, 1024), ("f32", 64, 2, 1101, 512)])
+def test_attention_forms_of_many_units_and_large_caches(dtype, d, G, stride, n):
+    """Every wave count and load policy of cask_attend; a tenth of a large call's units is compared (all of a
+    small one's).  Rows behind a unit's length hold NaN.  Tolerance: derived at _attend_check."""
+    p, Q, K, V, lens, count = _attend_inputs(dtype, d, G, stride, n, seed=stride)
+    past = torch.arange(stride, device=K.device)[None] >= torch.from_numpy(lens).to(K.device)[:, None]
+    clean = K.clone(), V.clone()
+    K[past] = float("nan")
+    V[past] = float("nan")
+    large = n * stride * d * K.element_size() * 2 > 256 << 20
+    units = list(range(0, n, n // 12 if large or n * stride > 60000 else 1)) + [n - 1]
+    for cnt in (None, count):
+        got = cask.attend(p, Q, K, V, torch.from_numpy(lens).to(K.device), count=None if cnt is None else torch.from_numpy(cnt).to(K.device))
+        torch.cuda.synchronize()
+        assert torch.isfinite(got).all()
+        _note(dtype, d, G, stride, n, "large" if large else "", _attend_some(p, got, Q, *clean, lens, cnt, units))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,G,stride,n", [(128, 5, 9001, 3), (64, 16, 2000, 7), (64, 17, 1800, 100)])
+def test_attention_of_long_units_with_and_without_a_workspace(d, G, stride, n, dtype):
+    """Few long units through cask_attend, and through cask_attend_ws with no workspace and with one a byte
+    short: one launch each, the same bits, against the oracle and within its bar of the split result."""
+    p, Q, K, V, lens, count = _attend_inputs(dtype, d, G, stride, n, seed=7)
+    lib, dev = B.load(), K.device
+    cp = p.c()
+    need = lib.cask_attend_workspace_bytes(B.C.byref(cp), n, stride)
+    assert need > 0
+    ln, cn = torch.from_numpy(lens).to(dev), torch.from_numpy(count).to(dev)
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    st = torch.cuda.current_stream().cuda_stream
+    args = [B.C.byref(cp), n, Q.data_ptr(), K.data_ptr(), V.data_ptr(), stride, ln.data_ptr(), cn.data_ptr(), stride]
+    outs = [torch.full_like(Q, 7.0) for _ in range(4)]
+    assert lib.cask_attend(*args, outs[0].data_ptr(), st) == 0
+    assert lib.cask_attend_ws(*args, outs[1].data_ptr(), None, 0, st) == 0
+    assert lib.cask_attend_ws(*args, outs[2].data_ptr(), ws.data_ptr(), need - 1, st) == 0
+    assert lib.cask_attend_ws(*args, outs[3].data_ptr(), ws.data_ptr(), need, st) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    units = list(range(min(n, 8)))
+    for o in (outs[0], outs[3]):
+        _note(dtype, d, G, stride, n, _attend_some(p, o, Q, K, V, lens, count, units))
+    assert torch.equal(outs[3], cask.attend(p, Q, K, V, ln, count=cn))
+
+
 @pytest.mark.parametrize("d,G,n,units", [(128, 7, 2000, 12), (128, 4, 300, 24), (64, 3, 1000, 24), (64, 8, 4097, 6)])
 def test_fp32_attention_keeps_the_precision_of_short_sums(d, G, n, units):
     """fp32 cask_attend against 64-bit sums: 2-norm of the error over 2-norm of the result.  A weight is
