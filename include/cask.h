@@ -28,9 +28,9 @@
  *     mirrored on the host (the host copy sizes the launches).
  *   - Calls that share a workspace on different streams race; one workspace per stream.
  *   - The first launch of a kernel on a device raises that kernel's LDS limit (a function
- *     attribute, not a stream operation; the scoring sweeps, the one-launch scoring and
- *     cask_attend's matrix-core kernels need more than the default 64 KB): make one call of an
- *     entry point with the shapes in question before capturing the stream into a HIP graph.
+ *     attribute, not a stream operation; the scoring sweeps, the one-launch scoring of larger
+ *     batches and cask_attend): make one call of an entry point with the shapes in question
+ *     before capturing the stream into a HIP graph.
  *   - Entry points may be called from several host threads (each on its own stream and
  *     workspace); the timing aid at the end of this header records one stream at a time.
  */
@@ -119,7 +119,7 @@ enum {
   CASK_PATH_NO_FUSED_TAIL = 1,  /* short units: the general kernels instead of the one-launch tail */
   CASK_PATH_NO_FUSED_SCORE = 2, /* short units: two scoring launches instead of one */
   CASK_PATH_DEDUP_VECTOR = 4,   /* bf16 de-duplicated seeding on the vector kernel fp32 caches use */
-  CASK_PATH_ATTEND_VECTOR = 8,  /* accepted, no effect (cask_attend has one kernel for every dtype) */
+  CASK_PATH_ATTEND_VECTOR = 8,  /* obsolete: accepted, no effect (cask_attend has one kernel for every dtype) */
   CASK_PATH_NO_FUSED_SWEEPS = 16, /* many long units with W*G <= 512: two scoring launches instead of one */
   CASK_PATH_FORCE_FUSED_SWEEPS = 32, /* W*G <= 512: one scoring launch whatever the number of units */
   CASK_PATH_NARROW_ROWS = 64, /* both scoring sweeps: 64 resident rows per wave (256 per workgroup) whatever the shape */
@@ -184,9 +184,9 @@ int cask_consolidate(const cask_params* params, const cask_batch* batch, const f
 
 /* The whole event (Sections 2.1-2.4).  (A batch whose units all have at most 1024 rows, with
  * B <= 1024, bf16 and the cosine geometry, takes a one-launch path after scoring; results and
- * tie rules are the same; with d = 128 the two scoring sweeps of such a batch are one launch
- * as well; CASK_PATH_NO_FUSED_TAIL and CASK_PATH_NO_FUSED_SCORE in path_flags switch these
- * paths off.)
+ * tie rules are the same; the scoring of such a batch is one launch as well -- both sweeps over
+ * the keys, or one where the batch is small enough to keep its logits in registers;
+ * CASK_PATH_NO_FUSED_TAIL and CASK_PATH_NO_FUSED_SCORE in path_flags switch these paths off.)
  *   K_out, V_out [n_units, B, d]  rows [0, out_len[u]) in ascending source order; a
  *                                 representative sits at its seed's position; kept tokens
  *                                 are bit-identical copies; rows >= out_len[u] untouched
@@ -315,8 +315,8 @@ size_t cask_attend_workspace_bytes(const cask_params* params, int32_t n_units, i
  * 4 similarity, 5 gather merged donors (grouping by seed; the same launch copies the kept rows
  * to the output), 6 emit (folds the seeds that have donors).  A batch of short units (every unit at most
  * 1024 rows, B <= 1024, bf16, cosine geometry) runs stages 2-6 as one kernel: its time is
- * reported as stage 2 and stages 3-6 read as the cost of an empty event pair; with d = 128
- * stages 0 and 1 are one kernel too, reported as stage 0.
+ * reported as stage 2 and stages 3-6 read as the cost of an empty event pair; stages 0 and 1 are
+ * one kernel too, reported as stage 0.
  * cask_timing_enable(n > 0) creates events for the next n compress calls (n <= 4096) and
  * switches recording on; n <= 0 switches it off and destroys them.  Calls beyond n are not
  * recorded.  cask_timing_read waits for the recorded calls, writes the summed milliseconds

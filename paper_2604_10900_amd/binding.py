@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libcask.so")
 F32, BF16 = 0, 1
 OK, EINVAL, ENOMEM, EDEVICE = 0, -1, -2, -3
 ST_ACTIVE, ST_IDENTITY, ST_PREFIX_BUDGET_EXHAUSTED, ST_MERGE_INACTIVE = 0, 1, 2, 4
-PATH_NO_FUSED_TAIL, PATH_NO_FUSED_SCORE, PATH_DEDUP_VECTOR, PATH_ATTEND_VECTOR, PATH_NO_FUSED_SWEEPS = 1, 2, 4, 8, 16
+PATH_NO_FUSED_TAIL, PATH_NO_FUSED_SCORE, PATH_DEDUP_VECTOR, PATH_ATTEND_VECTOR, PATH_NO_FUSED_SWEEPS = 1, 2, 4, 8, 16   # (PATH_ATTEND_VECTOR: obsolete, no effect)
 PATH_FORCE_FUSED_SWEEPS = 32
 PATH_NARROW_ROWS = 64
 PATH_WIDE_ROWS = 128

@@ -1612,10 +1612,14 @@ bool score_parts_fits(const KParams& kp, const Batch& b, const Workspace& wl) {
 // sums per key, `parts[unit][part][key]` with row pitch wl.parts_pitch; score[key] = (sum of the
 // parts in order) / (W*G).
 // Two sweeps with 256 window rows to a workgroup overlap matrix and vector work and are the better
-// form once they fill the chip; one sweep is, with its 64 rows to a workgroup, while all of its
-// workgroups run at once.  Events, two sweeps against one: 56 workgroups of 64 rows (4 units of 512)
-// 40 / 28 us, 112 (8 of 1024) 89 / 66, 392 (28 of 768) 65 / 57, 448 (112 of 640) 59 / 49; 896 (64 of
-// 512) 44 / 45, 896 (64 of 1024) 100 / 112, 1568 (112 of 1024) 138 / 163, 8192 (512 of 900) 380 / 531.
+// form once they fill the chip several times; one sweep, with its 64 rows to a workgroup, is before
+// that.  The line is where it was measured: up to 512 workgroups of 64 rows one sweep wins at every
+// length, also where its eight-wave form (one workgroup to a compute unit) needs a second turn of the
+// chip, and at 896 it no longer does.  Events, two sweeps against one, d = 128: 56 workgroups (4 units
+// of 512) 40 / 28 us, 112 (8 of 1024) 89 / 66, 280 (20 of 1024) 75 / 64, 504 (36 of 1024) 77 / 66, 504 (36
+// of 700) 55 / 48, 512 (64 of 1024) 76 / 65, 512 (128 of 500) 45 / 37, 512 (512 of 1024) 192 / 179; 896 (64 of 512)
+// 44 / 45, 896 (64 of 1024) 100 / 112, 1568 (112 of 1024) 138 / 163, 8192 (512 of 900) 380 / 531.
+// d = 64: 504 (36 of 1024) 68 / 56, 504 (36 of 700) 50 / 43, 512 (512 of 1024) 133 / 124.
 hipError_t launch_score_parts(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
                               hipStream_t st) {
   if (!score_parts_fits(kp, b, wl)) return hipErrorInvalidValue;
