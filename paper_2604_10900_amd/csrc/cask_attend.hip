@@ -371,10 +371,12 @@ hipError_t launch_attend_as(const KParams& kp, int n_units, const void* Q, const
   return hipSuccess;
 }
 
-// Waves per workgroup.  Few units: eight (more rows of a unit in flight); many: four, so that
-// several workgroups share a compute unit and one's merge overlaps the others' loads.  Long fp32
-// units of 64 channels take eight whatever their number (600 units, four against eight: 3000 rows 174 / 166 us,
-// 1000 rows 62 / 58; 4000 units x 1000 rows 320 / 309; but 2000 of 250 rows 46 / 48).
+// Waves per workgroup.  As long as every workgroup has a compute unit to itself: eight (more rows of a
+// unit in flight); with more workgroups than compute units four, so that several share one and
+// one's merge overlaps the others' loads (eight / four: 300 units x 500 rows bf16, d = 128 21.4 / 19.2 us, d = 64 x 2000
+// 40.8 / 35.7; 294 units of 3800 - 4750 rows 74.3 / 73.0).  Long fp32 units are the exception where it was
+// measured: 64 channels from 512 workgroups on (600 x 3000 four 174, eight 166; 600 x 1000 62 / 58; 4000 x
+// 1000 320 / 309; but 2000 x 250 46 / 48 and 400 x 2000 77 / 82), 128 channels up to 511 (400 x 4000 298 / 284).
 // Non-temporal loads where the caches of the call exceed the 256 MB last-level cache, so that no
 // call can find them there (554 MB: 102 -> 91 us; 1 GB of fp32: 185 -> 169 us); below that a
 // call that repeats finds its rows there and the hint costs up to a quarter.
@@ -383,8 +385,10 @@ hipError_t launch_attend_t(const KParams& kp, int n_units, const void* Q, const 
                            const int32_t* len, const int32_t* count, int count_pitch, void* out, int splits,
                            float* part, hipStream_t st) {
   const bool nt = (int64_t)n_units * stride * (2 * D * (int)sizeof(T)) > (256ll << 20);
-  const bool long_f32 = sizeof(T) == 4 && D == 64 && stride > 6 * 8 * AttGeom<T, D>::kTileRows;  // six rounds of eight waves
-  const bool four = (int64_t)n_units * splits >= 512 && !long_f32;
+  const int64_t groups = (int64_t)n_units * splits;
+  const int rounds = (stride - 1) / (8 * AttGeom<T, D>::kTileRows) + 1;  // of eight waves
+  const bool eight_f32 = sizeof(T) == 4 && (D == 64 ? groups >= 512 && rounds > 6 : groups < 512 && rounds > 24);
+  const bool four = groups > 256 && !eight_f32;
   auto go = [&](auto f) { return f(kp, n_units, Q, Kc, Vc, stride, len, count, count_pitch, out, splits, part, st); };
   if (four) return nt ? go(&launch_attend_as<T, D, 4, true>) : go(&launch_attend_as<T, D, 4, false>);
   return nt ? go(&launch_attend_as<T, D, 8, true>) : go(&launch_attend_as<T, D, 8, false>);
