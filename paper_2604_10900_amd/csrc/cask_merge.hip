@@ -1241,9 +1241,11 @@ hipError_t launch_emit_t(const KParams& kp, const Batch& b, const float* scores,
 // second, so a band's two channels sit eight lanes apart).  The sums are kept in double; the 64
 // group sums are added in order by one thread.
 // Bound: round trips to memory.  A thread takes the assignment and score of kDiagRows rows at once
-// (1024 apart), and a wave hands the few of its 64 rows that went to a slot to its four groups, two
-// each in flight.  With a group per row, one row at a time, the walk was a chain of N / 64 x 2 trips:
-// 46 us on 56 units of 6256 rows; four rows at a time 40 us, now 26.6 us.
+// (1024 apart); the rows that went to a slot are listed in LDS in ascending order, and the 64 groups take
+// the list in turn, several rows in flight each.  With a group per row, one row at a time, the walk
+// was a chain of N / 64 x 2 trips: 46 us on 56 units of 6256 rows, 12.6 on 27 of 735; with every
+// wave handing its own 64 rows to its four groups, whose longest chain is the always-kept tail's, 26.6 and
+// 17.0; with the list 13.8 and 12.0.
 constexpr int kDiagRows = 8;
 template <typename T, int D>
 __global__ __launch_bounds__(1024) void group_diag_kernel(
@@ -1254,7 +1256,11 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
   constexpr int EPL = D / 16;
   constexpr int WORDS = EPL * sizeof(T) / 4;
   struct alignas(WORDS * 4 > 16 ? 16 : WORDS * 4) Raw { uint32_t w[WORDS]; };
+  constexpr int kAhead = sizeof(T) == 2 ? 4 : 2;  // rows of a group in flight
   __shared__ double part_d[64], part_l[64];
+  __shared__ int slot_l[1024 * kDiagRows];         // the listed rows' slots
+  __shared__ uint16_t row_l[1024 * kDiagRows];     // their rows, from the round's first
+  __shared__ int count_l[16 * kDiagRows];          // rows listed per 64 of the round
   const int u = blockIdx.x, tid = threadIdx.x, grp = tid >> 4, gl = tid & 15;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
@@ -1262,7 +1268,7 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
 #pragma unroll
   for (int e = 0; e < EPL; ++e) w[e] = kp.band_w ? kp.band_w[(gl & 7) * EPL + e] : 1.f;
   double disp = 0.0, lost = 0.0;
-  const int lane = tid & 63, wv = tid >> 6, sub = (tid >> 4) & 3;
+  const int lane = tid & 63, wv = tid >> 6;
   for (int c0 = 0; c0 < N; c0 += 1024 * kDiagRows) {
     int t[kDiagRows];
     float a[kDiagRows];
@@ -1272,49 +1278,62 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
       t[q] = i < N ? assign[row0 + i] : kp.B;
       a[q] = i < N ? scores[row0 + i] : 0.f;
     }
+    unsigned long long listed[kDiagRows];
 #pragma unroll
     for (int q = 0; q < kDiagRows; ++q) {
       if (t[q] < 0) lost += (double)a[q];
-      unsigned long long mask = __ballot(t[q] >= 0 && t[q] < kp.B);
-      while (mask != 0ull) {  // up to eight of the wave's rows: two per group
-        int at[2] = {-1, -1};
+      listed[q] = __ballot(t[q] >= 0 && t[q] < kp.B);
+      if (lane == 0) count_l[q * 16 + wv] = __popcll(listed[q]);
+    }
+    __syncthreads();  // (also: the list of the round before has been read)
+    static_assert(kDiagRows == 8, "two counts per lane");
+    int c_lo = count_l[lane], c_hi = count_l[64 + lane];
+    const int own_lo = c_lo, own_hi = c_hi;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int bit = mask != 0ull ? __ffsll((long long)mask) - 1 : -1;
-          mask &= mask - 1ull;  // (0 stays 0)
-          if (sub == (k & 3)) at[k >> 2] = bit;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(c_lo, o, 64), y = __shfl_up(c_hi, o, 64);
+      if (lane >= o) c_lo += x, c_hi += y;
+    }
+    const int half = __shfl(c_lo, 63, 64), total = half + __shfl(c_hi, 63, 64);
+    c_lo -= own_lo;
+    c_hi += half - own_hi;
+#pragma unroll
+    for (int q = 0; q < kDiagRows; ++q) {
+      const int first = __shfl(q < 4 ? c_lo : c_hi, (q & 3) * 16 + wv, 64);
+      if ((listed[q] >> lane) & 1ull) {
+        const int at = first + __popcll(listed[q] & ((1ull << lane) - 1ull));
+        slot_l[at] = t[q];
+        row_l[at] = (uint16_t)(q * 1024 + tid);
+      }
+    }
+    __syncthreads();
+    for (int e0 = grp; e0 < total; e0 += 64 * kAhead) {
+      Raw kr[kAhead], rr[kAhead];
+      float ar[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {  // (past the end the last row is read again)
+        const int e = min(e0 + k * 64, total - 1);
+        const int64_t row = row0 + c0 + row_l[e];
+        kr[k] = *reinterpret_cast<const Raw*>(K + (size_t)row * D + gl * EPL);
+        rr[k] = *reinterpret_cast<const Raw*>(K_out + ((size_t)u * out_stride + slot_l[e]) * D + gl * EPL);
+        ar[k] = scores[row];
+      }
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const T* kp_ = reinterpret_cast<const T*>(&kr[k]);
+        const T* rp_ = reinterpret_cast<const T*>(&rr[k]);
+        float r = 0.f;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+          const float x = Elem<T>::load(kp_ + e) - Elem<T>::load(rp_ + e);
+          const float sq = x * x;
+          const float other = __shfl_xor(sq, 8, 64);  // the band's other channel
+          r = __builtin_fmaf(w[e], __builtin_amdgcn_sqrtf(sq + other), r);
         }
-        Raw kr[2], rr[2];
-        float ar[2];
+        if (gl >= 8) r = 0.f;  // both halves computed the same bands
 #pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const int from = at[k] >= 0 ? at[k] : lane;
-          const int slot = __shfl(t[q], from, 64);
-          ar[k] = __shfl(a[q], from, 64);
-          if (at[k] >= 0) {
-            kr[k] = *reinterpret_cast<const Raw*>(K + (size_t)(row0 + c0 + q * 1024 + wv * 64 + at[k]) * D + gl * EPL);
-            rr[k] = *reinterpret_cast<const Raw*>(K_out + ((size_t)u * out_stride + slot) * D + gl * EPL);
-          } else {
-            kr[k] = rr[k] = Raw{};
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const T* kp_ = reinterpret_cast<const T*>(&kr[k]);
-          const T* rp_ = reinterpret_cast<const T*>(&rr[k]);
-          float r = 0.f;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            const float x = Elem<T>::load(kp_ + e) - Elem<T>::load(rp_ + e);
-            const float sq = x * x;
-            const float other = __shfl_xor(sq, 8, 64);  // the band's other channel
-            r = __builtin_fmaf(w[e], __builtin_amdgcn_sqrtf(sq + other), r);
-          }
-          if (gl >= 8) r = 0.f;  // both halves computed the same bands
-#pragma unroll
-          for (int o = 4; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
-          if (at[k] >= 0) disp += (double)ar[k] * (double)r;
-        }
+        for (int o = 4; o > 0; o >>= 1) r += __shfl_xor(r, o, 64);
+        if (e0 + k * 64 < total) disp += (double)ar[k] * (double)r;
       }
     }
   }
