@@ -407,12 +407,16 @@ hipError_t launch_attend_t(const KParams& kp, int n_units, const void* Q, const 
 // 16 x 4000 45 -> 14, 4 x 1500 21 -> 12, 100 x 2000 34 -> 25, 128 x 2000 36 -> 30; with 384 and
 // 400 workgroups the last two took 37 and 29.  Two workgroups a unit and six rounds: 128 x 1281 19.6 ->
 // 20.6, so a bf16 unit has to have seven then (seven: 29.7 -> 24.5; fp32, whose rounds are longer, six: 27.2 ->
-// 22.9).  256 x 2000 (two each) 43 -> 47, so not beyond 128 units.
+// 22.9).  256 x 2000 (two each) 43 -> 47, so not beyond 128 units, but for one case: fp32 with 128 channels,
+// two workgroups of four waves to a compute unit, where a few units more than compute units leave most
+// of the chip half empty (300 x 1500 109 -> 87 us, 260 x 3000 200 -> 152, 350 x 1500 115 -> 105; 300 x 600 47.8 ->
+// 46.5; 400 x 600 52 -> 60).
 int attend_splits(const KParams& kp, int n_units, int stride) {
-  if (n_units <= 0 || n_units > 128) return 1;
+  if (n_units <= 0 || n_units > 380) return 1;
   const int tile = kp.dtype == CASK_BF16 ? 32 : 16;
   const int rounds = (stride + tile * 8 - 1) / (tile * 8);  // of eight waves, all rows used
   if (rounds < 6 || (int64_t)n_units * kp.G * kp.d > (1 << 30)) return 1;  // (the combining launch counts elements in 32 bits)
+  if (n_units > 128) return n_units > 256 && rounds >= 9 && kp.dtype == CASK_F32 && kp.d == 128 ? 3 : 1;
   int s = 256 / n_units;
   const int twice = 512 / n_units;
   // (96 units: 6000 rows, two and five workgroups each 59.6 / 58.7 us; 16 000 rows 141 / 132)

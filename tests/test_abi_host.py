@@ -350,12 +350,14 @@ def test_attend_splits_leave_no_nearly_empty_turn_of_the_chip(cask, dtype, tile,
     """The split of cask_attend_ws: at most one workgroup per compute unit (256), or two each where that
     fills the chip to four fifths; two rounds of tiles or more for every workgroup."""
     p = cask.Params(dtype=dtype, head_dim=d, q_per_kv=4, window=1, budget=1)
-    for units in list(range(1, 131)) + [255, 256, 512]:
+    for units in list(range(1, 131)) + [255, 256, 257, 300, 380, 381, 512]:
         for stride in (1, 16, 500, 641, 1280, 1281, 1540, 2000, 2600, 4000, 9000, 16384, 100000):
             s = _attend_splits(cask, p, units, stride)
             rounds = -(-stride // (8 * tile))
             assert 1 <= s <= 64
-            if s > 1:
+            if units > 128:   # three each where units of 128 fp32 channels just exceed the compute units
+                assert s == (3 if dtype == 0 and d == 128 and 256 < units <= 380 and rounds >= 9 else 1)
+            elif s > 1:
                 assert units <= 128 and rounds >= 6 and 2 * s <= rounds
                 assert units * s <= 256 or 410 <= units * s <= 512, (units, stride, s)
 

@@ -156,9 +156,11 @@ def _attend_some(p, got, Q, K, V, lens, count, units):
     ("bf16", 128, 7, 97, 513), ("bf16", 64, 3, 161, 600), ("f32", 128, 17, 33, 520), ("f32", 64, 2, 300, 512), ("bf16", 128, 4, 2050, 128),
     # long fp32 units of 64 channels: eight waves however many units
     ("f32", 64, 2, 769, 512),
+    # long fp32 units of 128 channels: eight waves between 257 and 511 workgroups
+    ("f32", 128, 1, 3201, 390),
     # caches beyond 256 MB: non-temporal loads, four and eight waves
     ("bf16", 128, 4, 1101, 512), ("bf16", 128, 2, 1801, 300), ("bf16", 64, 4, 1001, 1100), ("bf16", 64, 1, 2201, 500),
-    ("f32", 128, 3, 551, 512), ("f32", 128, 4, 1001, 300), ("f32", 64, 4, 601, 1024), ("f32", 64, 2, 1101, 512)])
+    ("f32", 128, 3, 551, 512), ("f32", 128, 4, 1001, 300), ("f32", 128, 2, 1101, 257), ("f32", 64, 4, 601, 1024), ("f32", 64, 2, 1101, 512)])
 def test_attention_forms_of_many_units_and_large_caches(dtype, d, G, stride, n):
     """Every wave count and load policy of cask_attend; a tenth of a large call's units is compared (all of a
     small one's).  Rows behind a unit's length hold NaN.  Tolerance: derived at _attend_check."""
