@@ -1318,6 +1318,20 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
     if (MODE == 1 && (stage & (kWaves - 1)) == wv)  // one wave in turn: first of the stage's loads, so it is waited for with them
       __builtin_amdgcn_raw_ptr_buffer_load_lds(brsrc, (__attribute__((address_space(3))) void*)(slot + kDataBytes), 4,
                                                lane * 4, (s_begin + stage * kStageRows) * 4, 0, 0);
+    // Sweep B's last stage: places past the last window row hold that row again (their bias makes nothing of
+    // it; a zero row times a key with an infinity would be a NaN).
+    const int past = s_begin + (stage + 1) * kStageRows - s_end;
+    if (MODE == 1 && past > 0 && past < kStageRows) {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int grp = wv + kWaves * j;
+        const int over = max(0, grp * kGroupRows + lane % kGroupRows - (kStageRows - 1 - past));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc, (__attribute__((address_space(3))) void*)(slot + grp * kGroupPitch), 16,
+            ld_voff + (j * kWaves * kGroupRows - over) * kRowBytes, (int)soff, 0, 0);
+      }
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < kLoads; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -1401,12 +1415,11 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
         nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
       }
       float sum = 0.f;
-      if (it < f0 || s_begin + (it + 1) * kStageRows > s_end) {  // (rows past the last: zero times an infinite key is a NaN)
+      if (it < f0) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = trow + (r >> 2) * 8 + (r & 3);
           const float y = __builtin_fmaf(acc[r], c, nl[r]);
-          sum += fast_exp2(row < first_row || row >= s_end ? kNegInf : y);
+          sum += fast_exp2(trow + (r >> 2) * 8 + (r & 3) < first_row ? kNegInf : y);
         }
       } else {
 #pragma unroll
