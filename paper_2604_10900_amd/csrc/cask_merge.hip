@@ -1269,15 +1269,18 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
   for (int e = 0; e < EPL; ++e) w[e] = kp.band_w ? kp.band_w[(gl & 7) * EPL + e] : 1.f;
   double disp = 0.0, lost = 0.0;
   const int lane = tid & 63, wv = tid >> 6;
-  for (int c0 = 0; c0 < N; c0 += 1024 * kDiagRows) {
-    int t[kDiagRows];
-    float a[kDiagRows];
+  int t[kDiagRows];
+  float a[kDiagRows];
+  auto fetch = [&](int c0) {
 #pragma unroll
     for (int q = 0; q < kDiagRows; ++q) {
       const int i = c0 + q * 1024 + tid;
       t[q] = i < N ? assign[row0 + i] : kp.B;
       a[q] = i < N ? scores[row0 + i] : 0.f;
     }
+  };
+  fetch(0);
+  for (int c0 = 0; c0 < N; c0 += 1024 * kDiagRows) {
     unsigned long long listed[kDiagRows];
 #pragma unroll
     for (int q = 0; q < kDiagRows; ++q) {
@@ -1306,6 +1309,7 @@ __global__ __launch_bounds__(1024) void group_diag_kernel(
         row_l[at] = (uint16_t)(q * 1024 + tid);
       }
     }
+    if (c0 + 1024 * kDiagRows < N) fetch(c0 + 1024 * kDiagRows);  // on its way while the list is taken
     __syncthreads();
     for (int e0 = grp; e0 < total; e0 += 64 * kAhead) {
       Raw kr[kAhead], rr[kAhead];
