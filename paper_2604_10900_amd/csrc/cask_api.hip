@@ -321,7 +321,7 @@ int cask_prefix_evict(const cask_params* params, const cask_batch* batch, const 
   if (rc) return rc;
   if (b.n_units == 0) return CASK_OK;
   if (!scores || !role) return CASK_EINVAL;
-  return dev_rc(launch_select(kp, b, scores, role, status, true, false, static_cast<hipStream_t>(hip_stream)));
+  return dev_rc(launch_select(kp, b, scores, role, status, true, false, nullptr, static_cast<hipStream_t>(hip_stream)));
 }
 
 int cask_partition(const cask_params* params, const cask_batch* batch, const float* scores,
@@ -336,7 +336,7 @@ int cask_partition(const cask_params* params, const cask_batch* batch, const flo
   if (rc) return rc;
   if (b.n_units == 0) return CASK_OK;
   if (!scores || !role) return CASK_EINVAL;
-  hipError_t e = launch_select(kp, b, scores, role, status, false, true, static_cast<hipStream_t>(hip_stream));
+  hipError_t e = launch_select(kp, b, scores, role, status, false, true, nullptr, static_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return CASK_EDEVICE;
   return dev_rc(launch_dedup_seeds(kp, b, scores, role, static_cast<hipStream_t>(hip_stream)));
 }
@@ -361,11 +361,16 @@ int cask_consolidate(const cask_params* params, const cask_batch* batch, const f
   int32_t* seed_rows = reinterpret_cast<int32_t*>(w + wl.seed_rows);
   int32_t* n_seeds = reinterpret_cast<int32_t*>(w + wl.n_seeds);
   int32_t* assign_ord = reinterpret_cast<int32_t*>(w + wl.assign_ord);
-  hipError_t e = launch_index_roles(kp, b, role, nullptr, nullptr, nullptr, seed_rows, n_seeds, st);
+  WalkArrays walk{};
+  walk.assign = assign;
+  walk.assign_mode = 2;
+  walk.seed_rows = seed_rows;
+  walk.n_seeds = n_seeds;
+  hipError_t e = launch_index_roles(kp, b, role, walk, st);
   if (e != hipSuccess) return CASK_EDEVICE;
   e = launch_similarity(kp, b, role, seed_rows, n_seeds, assign_ord, false, st);
   if (e != hipSuccess) return CASK_EDEVICE;
-  e = launch_gather_merged(kp, b, role, assign_ord, nullptr, seed_rows,
+  e = launch_gather_merged(kp, b, assign_ord, nullptr, seed_rows,
                            reinterpret_cast<int32_t*>(w + wl.merged_row),
                            reinterpret_cast<int32_t*>(w + wl.merged_ord), nullptr, assign, 2,
                            nullptr, n_seeds, nullptr, nullptr, nullptr, st);
@@ -516,18 +521,25 @@ int cask_compress_step(const cask_params* params, const cask_batch* batch, const
     for (int k = 0; k < 5; ++k) rec.mark();
     return dev_rc(e);
   }
+  WalkArrays walk{};
+  walk.slot_of = slot_of;
+  walk.assign = assign;
+  walk.assign_mode = 1;
+  walk.out_src = out_src;
+  walk.out_len = out_len;
+  walk.seed_rows = seed_rows;
+  walk.n_seeds = n_seeds;
   if (kp.dedup > 0) {
     // de-duplicated seeding sits between the selection and the ordered walk: three launches
-    e = launch_select(kp, b, s, role, status, true, true, st);
+    e = launch_select(kp, b, s, role, status, true, true, nullptr, st);
     if (e == hipSuccess) e = launch_dedup_seeds(kp, b, s, role, st);
     if (e != hipSuccess) return CASK_EDEVICE;
     rec.mark();
-    e = launch_index_roles(kp, b, role, slot_of, out_src, out_len, seed_rows, n_seeds, st);
+    e = launch_index_roles(kp, b, role, walk, st);
     if (e != hipSuccess) return CASK_EDEVICE;
     rec.mark();
   } else {
-    e = launch_select_index(kp, b, s, role, status, slot_of, out_src, out_len, seed_rows, n_seeds,
-                            st);
+    e = launch_select(kp, b, s, role, status, true, true, &walk, st);
     if (e != hipSuccess) return CASK_EDEVICE;
     rec.mark();
     rec.mark();  // the ordered walk runs inside the select kernel here: its own stage reads as zero
@@ -548,7 +560,7 @@ int cask_compress_step(const cask_params* params, const cask_batch* batch, const
   cj.out_mass = out_mass;
   cj.out_count = out_count;
   cj.out_stride = out_stride_rows;
-  e = launch_gather_merged(kp, b, role, assign_ord, slot_of, seed_rows, merged_row, merged_ord,
+  e = launch_gather_merged(kp, b, assign_ord, slot_of, seed_rows, merged_row, merged_ord,
                            n_merged, assign, assign ? 1 : 0, status, n_seeds, seg_row, seg_start,
                            &cj, st);
   if (e != hipSuccess) return CASK_EDEVICE;

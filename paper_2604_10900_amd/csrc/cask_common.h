@@ -213,7 +213,7 @@ struct Workspace {
   size_t bias;       // float  [n_units][mq_pad]: -L_row of every window row (base-2 log-sum-exp over all keys)
   size_t scores;     // float  [total_rows] (used when the caller passes no score buffer)
   size_t role;       // uint8  [total_rows]
-  size_t slot_of;    // int32  [total_rows] output slot of kept rows, -1 otherwise
+  size_t slot_of;    // int32  [total_rows] output slot of kept rows (written for those alone)
   size_t assign_ord; // int32  [total_rows] seed ordinal a donor folds into, -1 otherwise
   size_t merged_row; // int32  [total_rows] per unit: rows of merged donors, ascending
   size_t merged_ord; // int32  [total_rows] their seed ordinals
@@ -262,19 +262,26 @@ hipError_t launch_score_fused(const KParams& kp, const Batch& b, const Workspace
 bool score_parts_fits(const KParams& kp, const Batch& b, const Workspace& wl);
 hipError_t launch_score_parts(const KParams& kp, const Batch& b, const Workspace& wl, char* ws,
                               hipStream_t st);
-hipError_t launch_select(const KParams& kp, const Batch& b, const float* scores, uint8_t* role,
-                         int32_t* status, bool do_prefix, bool do_decode, hipStream_t st);
+// Where the ordered walk of a batch leaves its results (any but seed_rows, n_seeds may be null):
+// assign gets the slot (assign_mode 1) or the unit-local row (2) of every row that is kept and -1 for
+// the rest; the donors that fold are entered later (launch_gather_merged).
+struct WalkArrays {
+  int32_t* slot_of;  // kept rows only
+  int32_t* assign;
+  int assign_mode;
+  int32_t* out_src;
+  int32_t* out_len;
+  int32_t* seed_rows;
+  int32_t* n_seeds;
+};
+// the stages of the selection that are asked for and, with `walk`, the ordered walk in the same launch
+hipError_t launch_select(const KParams& kp, const Batch& b, const float* scores, uint8_t* role, int32_t* status,
+                         bool do_prefix, bool do_decode, const WalkArrays* walk, hipStream_t st);
 // de-duplicated seeding: turns the provisional seeds launch_select marked into seeds and donors
 hipError_t launch_dedup_seeds(const KParams& kp, const Batch& b, const float* scores, uint8_t* role,
                               hipStream_t st);
-// both stages of the selection and the ordered walk in one launch (whole-event path)
-hipError_t launch_select_index(const KParams& kp, const Batch& b, const float* scores,
-                               uint8_t* role, int32_t* status, int32_t* slot_of, int32_t* out_src,
-                               int32_t* out_len, int32_t* seed_rows, int32_t* n_seeds,
-                               hipStream_t st);
-hipError_t launch_index_roles(const KParams& kp, const Batch& b, const uint8_t* role,
-                              int32_t* slot_of, int32_t* out_src, int32_t* out_len,
-                              int32_t* seed_rows, int32_t* n_seeds, hipStream_t st);
+hipError_t launch_index_roles(const KParams& kp, const Batch& b, const uint8_t* role, const WalkArrays& walk,
+                              hipStream_t st);
 hipError_t launch_mass_diag(const KParams& kp, const Batch& b, const float* scores,
                             const uint8_t* role, const float* out_mass, const int32_t* out_len,
                             float* rho, hipStream_t st);
@@ -300,7 +307,7 @@ struct CopyJob {
   int n_units;
   int lane_bytes;
 };
-hipError_t launch_gather_merged(const KParams& kp, const Batch& b, const uint8_t* role,
+hipError_t launch_gather_merged(const KParams& kp, const Batch& b,
                                 const int32_t* assign_ord, const int32_t* slot_of,
                                 const int32_t* seed_rows, int32_t* merged_row, int32_t* merged_ord,
                                 int32_t* n_merged, int32_t* assign_out, int assign_mode,

@@ -777,7 +777,7 @@ template <int PER>
 __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
     KParams kp, int n_gather, CopyJob cj,
     const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
-    const uint8_t* __restrict__ role, const int32_t* __restrict__ assign_ord,
+    const int32_t* __restrict__ assign_ord,
     const int32_t* __restrict__ slot_of, const int32_t* __restrict__ seed_rows,
     int32_t* __restrict__ merged_row, int32_t* __restrict__ merged_ord,
     int32_t* __restrict__ n_merged, int32_t* __restrict__ assign_out, int assign_mode,
@@ -799,16 +799,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
   const UnitPlan pl = make_plan(kp, P, N);
   const int hi = N - pl.r_eff;
   const int32_t* srow = seed_rows + (size_t)u * kp.B;
-  // rows outside the donor range: kept rows map to themselves, the rest is dropped
-  if (assign_mode != 0) {
-    for (int i = tid; i < N; i += kGatherThreads) {
-      if (i >= P && i < hi) continue;
-      const int r = role[row0 + i];
-      const bool kept = r == CASK_ROLE_PREFIX_KEEP || r == CASK_ROLE_RECENT || r == CASK_ROLE_CORE ||
-                        r == CASK_ROLE_SEED;
-      assign_out[row0 + i] = !kept ? -1 : (assign_mode == 1 ? slot_of[row0 + i] : i);
-    }
-  }
   // A wave owns PER * 64 consecutive rows of a chunk, touched 64 consecutive rows at a time
   // (coalesced); positions inside the wave come from ballots with a running carry, and one
   // exchange of the wave totals per chunk orders the waves.
@@ -816,17 +806,12 @@ __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
   int count = 0;
   for (int cb = P; cb < hi; cb += kGatherThreads * PER) {
     const int i0 = cb + wv * (64 * PER) + lane;
-    int r[PER], ord[PER], pos[PER];
+    int ord[PER], pos[PER];
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const bool in = i0 + e * 64 < hi;
-      r[e] = in ? (int)role[row0 + i0 + e * 64] : (int)CASK_ROLE_PREFIX_DROP;
-      ord[e] = in ? assign_ord[row0 + i0 + e * 64] : -1;
-    }
+    for (int e = 0; e < PER; ++e) ord[e] = i0 + e * 64 < hi ? assign_ord[row0 + i0 + e * 64] : -1;  // (>= 0: a donor that folds)
     int run = 0;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-      if (r[e] != CASK_ROLE_DONOR) ord[e] = -1;
       const unsigned long long b = __ballot(ord[e] >= 0);
       pos[e] = run + __popcll(b & below);
       run += __popcll(b);
@@ -854,25 +839,20 @@ __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
       }
     }
     if (assign_mode != 0) {
-      // What a row maps to: a folding donor to its seed, a kept row to itself, anything else to
-      // nothing.  The two dependent lookups (seed's row, then its slot) are taken for all of the
-      // thread's rows at a time: one after the other, every row would wait for its own round trip.
+      // A folding donor maps to its seed (all other rows were entered by the ordered walk).  The two
+      // dependent lookups (seed's row, then its slot) are taken for all of the thread's rows at a
+      // time: one after the other, every row would wait for its own round trip.
       int tgt[PER];
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int i = i0 + e * 64;
-        const bool kept = r[e] == CASK_ROLE_CORE || r[e] == CASK_ROLE_SEED;
-        tgt[e] = (i < hi && ord[e] >= 0) ? srow[ord[e]] : ((i < hi && kept) ? i : -1);  // (ord >= 0 only for donors)
-      }
+      for (int e = 0; e < PER; ++e) tgt[e] = ord[e] >= 0 ? srow[ord[e]] : -1;
       if (assign_mode == 1) {
 #pragma unroll
-        for (int e = 0; e < PER; ++e) tgt[e] = tgt[e] >= 0 ? slot_of[row0 + tgt[e]] : -1;
+        for (int e = 0; e < PER; ++e)
+          if (ord[e] >= 0) tgt[e] = slot_of[row0 + tgt[e]];
       }
 #pragma unroll
-      for (int e = 0; e < PER; ++e) {
-        const int i = i0 + e * 64;
-        if (i < hi) assign_out[row0 + i] = tgt[e];
-      }
+      for (int e = 0; e < PER; ++e)
+        if (ord[e] >= 0) assign_out[row0 + i0 + e * 64] = tgt[e];
     }
     count += tot;
   }
@@ -1430,7 +1410,7 @@ hipError_t launch_similarity(const KParams& kp, const Batch& b, const uint8_t* r
                     : launch_similarity_f32<128>(kp, b, role, seed_rows, n_seeds, assign_ord, roles_follow_plan, st);
 }
 
-hipError_t launch_gather_merged(const KParams& kp, const Batch& b, const uint8_t* role,
+hipError_t launch_gather_merged(const KParams& kp, const Batch& b,
                                 const int32_t* assign_ord, const int32_t* slot_of,
                                 const int32_t* seed_rows, int32_t* merged_row, int32_t* merged_ord,
                                 int32_t* n_merged, int32_t* assign_out, int assign_mode,
@@ -1453,7 +1433,7 @@ hipError_t launch_gather_merged(const KParams& kp, const Batch& b, const uint8_t
   auto kern = per_need <= 4 ? &gather_merged_kernel<4>
                             : (per_need <= 8 ? &gather_merged_kernel<8> : &gather_merged_kernel<kGatherPer>);
   kern<<<dim3((unsigned)(b.n_units + copy_blocks)), dim3(kGatherThreads), 0, st>>>(
-      kp, b.n_units, cj, b.row_off, b.prefix_len, role, assign_ord, slot_of, seed_rows, merged_row, merged_ord,
+      kp, b.n_units, cj, b.row_off, b.prefix_len, assign_ord, slot_of, seed_rows, merged_row, merged_ord,
       n_merged, assign_out, assign_mode, status, n_seeds, seg_row, seg_start);
   return hipGetLastError();
 }

@@ -388,3 +388,47 @@ def test_group_diagnostics_around_a_round_of_rows(d, dtype, merged):
     torch.cuda.synchronize()
     np.testing.assert_allclose(got_d.cpu().numpy(), want_d, rtol=2e-5, atol=1e-6)
     np.testing.assert_allclose(got_l.cpu().numpy(), want_l, rtol=1e-6, atol=1e-6)
+
+
+@pytest.mark.parametrize("spread", ["outlier", "binades", "clusters"])
+@pytest.mark.parametrize("N,P", [(6144, 100), (6145, 6000), (18432, 16384), (18433, 9000), (25601, 40), (36864, 20000), (36865, 300), (40000, 37000)])
+def test_ranks_where_the_bins_are_uneven(N, P, spread):
+    """Roles and kept rows on injected scores at the edges of the selection's instances (6, 12, 18, 25, 36
+    keys a thread, then a chunk of keys at a time): two outliers that leave everything else in one
+    bin of the first histogram, sixty binades, and clusters a few ulps wide with ties in them."""
+    rng = np.random.default_rng(N + len(spread))
+    lens, pref = [N, 1200], [P, 200]
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    total = int(row_off[-1])
+    if spread == "outlier":
+        sc = (1.0 + rng.permutation(total) / total).astype(np.float32)
+        sc[[5, N + 5]], sc[[9, N + 9]] = 3e38, -3e38
+    elif spread == "binades":
+        sc = (2.0 ** rng.uniform(-60, 0, total)).astype(np.float32)
+    else:
+        sc = (2.0 ** rng.integers(-3, 3, total)).astype(np.float32)
+        sc = (sc.view(np.uint32) + rng.integers(0, 200, total).astype(np.uint32)).view(np.float32)
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=64, budget=900, sim_threshold=2.0)
+    rp, prefix = parity.ref_params(p), np.array(pref, dtype=np.int32)
+    role_w, _ = ref.prefix_evict(rp, row_off, prefix, sc)
+    role_w, _ = ref.partition(rp, row_off, prefix, sc, role_w)
+    K = torch.from_numpy(rng.standard_normal((total, 64)).astype(np.float32)).to(torch.bfloat16).cuda()
+    b = cask.Batch(p, torch.from_numpy(row_off), torch.from_numpy(prefix), K, K, torch.zeros(2, 64, 1, 64, dtype=torch.bfloat16, device="cuda"))
+    sd = torch.from_numpy(sc).cuda()
+    role, _ = cask.prefix_evict(b, sd)
+    role, _ = cask.partition(b, sd, role)
+    out = cask.compress(b, scores=sd)
+    rho = cask.mass_diagnostics(b, sd, role, out.out_mass, out.out_len)
+    torch.cuda.synchronize()
+    assert np.array_equal(role.cpu().numpy(), role_w)
+    kept = np.isin(role_w, [1, 2, 3, 5])
+    for u in range(2):
+        rows = np.nonzero(kept[row_off[u]: row_off[u + 1]])[0]
+        assert int(out.out_len[u]) == len(rows) == 900
+        assert np.array_equal(out.out_src[u].cpu().numpy(), rows)
+        want = np.full(lens[u], -1)
+        want[rows] = np.arange(len(rows))
+        assert np.array_equal(out.assign[row_off[u]: row_off[u + 1]].cpu().numpy(), want)
+    if spread != "outlier":
+        want_rho = ref.mass_diagnostics(rp, row_off, sc, role_w, out.out_mass.cpu().numpy(), out.out_len.cpu().numpy())
+        np.testing.assert_allclose(rho.cpu().numpy(), want_rho, rtol=2e-6)
