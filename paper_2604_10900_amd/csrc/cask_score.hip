@@ -14,11 +14,13 @@
 // staged through LDS.  The product tile is stream x resident^T, so each lane owns ONE
 // resident column and 16 stream rows: the reduction over the stream dimension (keys in
 // sweep A, window rows in sweep B) stays inside a lane until the very end.
-// fp32 caches take a simpler kernel of the same structure on fp32 matrix tiles.
+// fp32 caches take a simpler kernel of the same structure, their values split into three bf16 terms.
 // Few short bf16 units take one sweep that keeps its logits in registers (score_short_kernel).
 #include "cask_common.h"
 
 namespace cask {
+
+#define CASK_INLINE __attribute__((always_inline))
 
 namespace {
 
@@ -1229,44 +1231,78 @@ __global__ __launch_bounds__(NW * 64, 2) void score_short_kernel(
 
 // ------------------------------------------------------------------ fp32 caches
 
-// What the head dimension decides about a ring slot of the fp32 sweeps (32 stream rows).
+// What the head dimension decides about a stage (32 stream rows) of the fp32 sweeps.
 template <int D>
 struct F32Geom {
-  static constexpr int kRowBytes = D * 4;
   static constexpr int kStageRows = 32;
-  static constexpr int kGroupRows = 1024 / kRowBytes;            // rows one load instruction of a wave lands: 2 or 4
-  static constexpr int kGroupPitch = 1024 + kGroupRows * 16;
-  static constexpr int kDataBytes = (kStageRows / kGroupRows) * kGroupPitch;
-  static constexpr int kStageBytes = kDataBytes + 256;           // + -L_row (sweep B; a load instruction's 64 floats)
-  static constexpr int kLoads = kStageRows / kGroupRows / kWaves;  // load instructions per wave and stage
+  static constexpr int kPieces = D / 8;                      // 16-byte pieces (eight terms) of a row of a plane
+  static constexpr int kPlaneBytes = kStageRows * D * 2;
+  static constexpr int kStageBytes = 3 * kPlaneBytes;
+  static constexpr int kItems = kStageRows * kPieces / kThreads;  // pieces a thread splits per stage
 };
-constexpr int kF32Depth = 3;  // ring slots; three workgroups' rings fit a compute unit
 
-// Both scoring sweeps of an fp32 cache on the fp32 matrix tiles (32x32x2: fp32 products and sums, a
-// chain of D / 2 per tile).  MODE 0 = sweep A (resident: window rows, stream: keys), MODE 1 = sweep B
-// (resident: keys, stream: window rows), as for bf16 above: a wave keeps 32 resident rows as B
-// operands in registers, stream rows arrive 32 at a time through a ring of LDS slots in the same
-// piece-major layout, and a lane owns one resident row and 16 stream rows of a tile.
+// x = hi + mid + lo, each rounded to bf16: 24 bits, so the three terms are x itself up to 2^-25 of it
+// (a value that rounds past the bf16 range gives an infinity and a NaN, like an infinity itself).
+struct Split3 {
+  bf16x8 hi, mid, lo;
+};
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void split_pair(float x0, float x1, Split3& o, int q) {  // terms 2 q and 2 q + 1
+  auto round2 = [](float a, float b) { return __builtin_convertvector(f32x2{a, b}, bf16x2); };
+  auto first = [](bf16x2 v) { return __uint_as_float(__builtin_bit_cast(uint32_t, v) << 16); };
+  auto second = [](bf16x2 v) { return __uint_as_float(__builtin_bit_cast(uint32_t, v) & 0xffff0000u); };
+  const bf16x2 hi = round2(x0, x1);
+  const float r0 = x0 - first(hi), r1 = x1 - second(hi);
+  const bf16x2 mid = round2(r0, r1), lo = round2(r0 - first(mid), r1 - second(mid));
+  o.hi[2 * q] = hi[0], o.hi[2 * q + 1] = hi[1];
+  o.mid[2 * q] = mid[0], o.mid[2 * q + 1] = mid[1];
+  o.lo[2 * q] = lo[0], o.lo[2 * q + 1] = lo[1];
+}
+__device__ __forceinline__ Split3 split3(const f32x4& a, const f32x4& b) {
+  Split3 o;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) split_pair(q < 2 ? a[2 * q] : b[2 * q - 4], q < 2 ? a[2 * q + 1] : b[2 * q - 3], o, q);
+  return o;
+}
+
+// Both scoring sweeps of an fp32 cache.  MODE 0 = sweep A (resident: window rows, stream: keys),
+// MODE 1 = sweep B (resident: keys, stream: window rows), as for bf16 above: a wave keeps 32 resident
+// rows as B operands in registers, and a lane owns one resident row and 16 stream rows of a tile.
 //
-// The matrix pipe is the bound: a tile is 64 products of 64 cycles (D = 128) against 16 LDS reads
-// and about 300 cycles of exponentials, so one resident tile per wave is enough and nothing has to be
-// interleaved by hand -- three waves per SIMD from independent workgroups fill the gaps.  The same
-// reason lets sweep A carry a true running maximum.
-// Measured, 32 units of 4096 rows, 256 window rows, d = 128: 81 + 94 us (55 + 55 at the rate
-// of the fp32 matrix tiles); a thread per window row, then per key, on the vector units took 465 + 495.
+// The products are bf16 matrix tiles over terms of the operands: with x = hi + mid + lo the product of
+// two values is hi hi + (hi mid + mid hi) + (mid mid + hi lo + lo hi) up to 2^-24 of it, products of
+// bf16 terms are exact in fp32, and six of them take 6 x 32 cycles for sixteen channels where the
+// fp32 tiles (32x32x2) take 8 x 64.  The five small ones have an accumulator of their own, so that the
+// large one is rounded once per sixteen channels, not once per two: the result is closer to 64-bit sums
+// than the fp32 tiles' was.  A term that is not finite (an infinity or NaN in the cache, a value past
+// the bf16 range) makes the wave's sums NaN; the wave then takes its share again on the fp32 tiles,
+// operands straight from memory (rare, slow, exact).
+//
+// Stream rows are split once per workgroup: a thread loads eight channels three stages ahead, splits them
+// and leaves the terms in LDS as three planes, one stage ahead; one barrier a stage.  The 16-byte piece p
+// of row r lies at slot p ^ r of its row (d = 64: p ^ r / 2, two rows to 256 bytes), which spreads any
+// 16 lanes of an operand read, and of a store, over all banks.
+//
+// Bound: the matrix pipe (1536 cycles a tile of d = 128).  The clean stages are software-pipelined: the six products
+// of a k-step carry two logits of the tile before (fma, exp2, add: the reference is taken once, as in
+// the bf16 sweeps, and a sum out of range goes the way of a NaN) and two channels of the split of the
+// stage after.  32 units of 4096 rows, 256 window rows, d = 128: 50 + 53 us, 1.0 PFLOP/s of bf16 products, which
+// is what the bf16 sweeps reach (the clock under matrix load is 1.8 GHz); the fp32 tiles took 81 + 94.  Norm
+// of the scores' error against 64-bit sums over nine shapes: 1.7e-7 - 3.1e-7, with fp32 products 2.2e-7 - 6.8e-7.
+// The resident rows a lane per row from memory, the stream one stage ahead: 64 + 55 us.
 template <int D, int MODE>
-__global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
     KParams kp, int n_units, int tiles_per_unit, int n_splits, int split_len, int mq_pad,
     const int64_t* __restrict__ row_off, const float* __restrict__ K, const float* __restrict__ Q,
     float2* __restrict__ rowstat, const float* __restrict__ bias, float* __restrict__ bias_out,
     float* __restrict__ scores) {
   using SG = F32Geom<D>;
-  constexpr int kRowBytes = SG::kRowBytes, kGroupRows = SG::kGroupRows, kGroupPitch = SG::kGroupPitch;
-  constexpr int kStageRows = SG::kStageRows, kDataBytes = SG::kDataBytes, kStageBytes = SG::kStageBytes;
-  constexpr int kLoads = SG::kLoads;
+  constexpr int kStageRows = SG::kStageRows, kPieces = SG::kPieces, kPlane = SG::kPlaneBytes, kItems = SG::kItems;
   constexpr int kRes = kWaves * 32;  // resident rows per workgroup
-  constexpr int NP = D / 8;          // 16-byte pieces of a row per lane
-  __shared__ __attribute__((aligned(16))) unsigned char ring[kF32Depth * kStageBytes];
+  constexpr int NK = D / 16;
+  __shared__ __attribute__((aligned(16))) unsigned char stage_mem[2 * SG::kStageBytes];
+  __shared__ __attribute__((aligned(16))) float negl[4][kStageRows];  // sweep B: -L of the rows of four stages
   int unit, tile;
   if (!map_block(n_units, tiles_per_unit, unit, tile)) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1306,55 +1342,88 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
   const int res_row = res_base + wv * 32 + c32;  // the lane's resident row
   const bool wave_live = res_base + wv * 32 < res_limit;
 
-  // rows past the end read as zero through the descriptors
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(str_ptr), 0, (int)((unsigned)max(s_end, 0) * (unsigned)kRowBytes), 0x00020000);
-  const __amdgpu_buffer_rsrc_t brsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<float*>(bias + (size_t)unit * mq_pad), 0, mq_pad * 4, 0x00020000);
-  const int ld_voff = (wv * kGroupRows + lane % kGroupRows) * kRowBytes + (lane / kGroupRows) * 16;
-  auto issue_stage = [&](int stage) {  // (also past the last stage: the load count stays the same)
-    unsigned char* slot = ring + (stage % kF32Depth) * kStageBytes;
-    const unsigned soff = (unsigned)(s_begin + stage * kStageRows) * (unsigned)kRowBytes;
-    if (MODE == 1 && (stage & (kWaves - 1)) == wv)  // one wave in turn: first of the stage's loads, so it is waited for with them
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(brsrc, (__attribute__((address_space(3))) void*)(slot + kDataBytes), 4,
-                                               lane * 4, (s_begin + stage * kStageRows) * 4, 0, 0);
-    // Sweep B's last stage: places past the last window row hold that row again (their bias makes nothing of
-    // it; a zero row times a key with an infinity would be a NaN).
-    const int past = s_begin + (stage + 1) * kStageRows - s_end;
-    if (MODE == 1 && past > 0 && past < kStageRows) {
-#pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        const int grp = wv + kWaves * j;
-        const int over = max(0, grp * kGroupRows + lane % kGroupRows - (kStageRows - 1 - past));
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            rsrc, (__attribute__((address_space(3))) void*)(slot + grp * kGroupPitch), 16,
-            ld_voff + (j * kWaves * kGroupRows - over) * kRowBytes, (int)soff, 0, 0);
-      }
-      return;
-    }
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rsrc, (__attribute__((address_space(3))) void*)(slot + (wv + kWaves * j) * kGroupPitch), 16, ld_voff,
-          (int)(soff + j * (kWaves * 1024u)), 0, 0);
+  // ---- rows on their way: 32 at a time, a thread taking eight channels of one (two rows of d = 128) as they
+  // lie in memory.  Places past the last row hold that row again: of the stream, sweep A masks them and
+  // sweep B's bias makes nothing of them (a zero row times an infinity would be a NaN); resident ones
+  // are not stored.
+  struct Raw {
+    f32x4 v[kItems][2];
+    float nl;
   };
-  float res[NP * 4];
-  if (n_stages > 0) {
+  const __amdgpu_buffer_rsrc_t str_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(str_ptr), 0, (int)((unsigned)max(s_end, 0) * (unsigned)(D * 4)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t res_rsrc = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(res_ptr), 0, (int)((unsigned)res_limit * (unsigned)(D * 4)), 0x00020000);
+  auto load_rows = [&](Raw& raw, const __amdgpu_buffer_rsrc_t& rsrc, int first, int last) CASK_INLINE {
 #pragma unroll
-    for (int st = 0; st < kF32Depth - 1; ++st) issue_stage(st);
-  }
-  {
-    const float* rp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;  // a row past the end is not stored
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(rp + p * 8);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) res[p * 4 + e] = v[e];
+    for (int j = 0; j < kItems; ++j) {
+      const int item = tid + j * kThreads;
+      const unsigned at = (unsigned)min(first + item / kPieces, last) * (unsigned)(D * 4) + (item % kPieces) * 32;
+      raw.v[j][0] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 0, 0));
+      raw.v[j][1] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)at, 16, 0));
     }
-  }
-  // take the wait for them here: inside the loop it would drain the ring
+  };
+  auto load_stage = [&](Raw& raw, int st) CASK_INLINE {  // (past the last stage: its last row again)
+    load_rows(raw, str_rsrc, s_begin + st * kStageRows, s_end - 1);
+    if (MODE == 1 && tid < kStageRows) raw.nl = bias[(size_t)unit * mq_pad + min(s_begin + st * kStageRows + tid, mq_pad - 1)];
+  };
+  auto swizzle = [](int row, int piece) CASK_INLINE { return row * (D * 2) + ((piece ^ (D == 128 ? row & 15 : (row >> 1) & 7)) * 16); };
+  auto slot_of = [&](int st) -> unsigned char* { return stage_mem + (st & 1) * SG::kStageBytes; };
+  auto store_item = [&](int st, int j, const Split3& t) CASK_INLINE {
+    const int item = tid + j * kThreads;
+    unsigned char* p = slot_of(st) + swizzle(item / kPieces, item % kPieces);
+    *reinterpret_cast<bf16x8*>(p) = t.hi;
+    *reinterpret_cast<bf16x8*>(p + kPlane) = t.mid;
+    *reinterpret_cast<bf16x8*>(p + 2 * kPlane) = t.lo;
+  };
+  auto store_negl = [&](const Raw& raw, int st) CASK_INLINE {
+    if (MODE == 1 && tid < kStageRows) negl[st & 3][tid] = raw.nl;
+  };
+  auto store_rows = [&](const Raw& raw, int st) CASK_INLINE {
 #pragma unroll
-  for (int i = 0; i < NP * 4; ++i) asm volatile("" : "+v"(res[i]));
+    for (int j = 0; j < kItems; ++j) store_item(st, j, split3(raw.v[j][0], raw.v[j][1]));
+  };
+  const int rd = swizzle(c32, h);  // the lane's piece of k-step 0; k-step ks: 32 ks further in the row's order
+  auto read_terms = [&](int st, int ks) CASK_INLINE {
+    const unsigned char* p = slot_of(st) + (rd ^ (ks * 32));
+    Split3 t;
+    t.hi = *reinterpret_cast<const bf16x8*>(p);
+    t.mid = *reinterpret_cast<const bf16x8*>(p + kPlane);
+    t.lo = *reinterpret_cast<const bf16x8*>(p + 2 * kPlane);
+    return t;
+  };
+  auto stage_barrier = [&]() CASK_INLINE {  // this wave's LDS accesses are done; its loads stay in flight
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  // Stream stage st waits in even or odd (st & 1) until it is split, loaded three stages ahead of its use.
+  // The resident rows come the same way, whole rows at a time (a lane per row, each load would touch
+  // 32 rows at 32 bytes each), two waves' at a time.
+  Split3 res[NK];
+  Raw even, odd;
+  if (n_stages > 0) {
+    Raw mine[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) load_rows(mine[w], res_rsrc, res_base + w * 32, res_limit - 1);
+    load_stage(even, 0);
+    load_stage(odd, 1);
+#pragma unroll
+    for (int w = 0; w < kWaves; w += 2) {
+      store_rows(mine[w], 0);
+      store_rows(mine[w + 1], 1);
+      stage_barrier();
+      if ((wv & 2) == w) {
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) res[ks] = read_terms(wv, ks);
+      }
+      stage_barrier();
+    }
+    store_rows(even, 0);
+    store_negl(even, 0);
+    load_stage(even, 2);
+  }
 
   // stages [0, sk) show the wave nothing, [sk, f0) and [f1, n_stages) are partly masked
   int sk = 0, f0 = 0, f1 = n_stages;
@@ -1369,27 +1438,11 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
     sk = max(0, min(n_stages, (max(0, k0 * Gq) - s_begin) / kStageRows));
     f0 = max(sk, min(n_stages, (max(0, (k0 + 31) * Gq) - s_begin + kStageRows - 1) / kStageRows));
   }
-  if (!wave_live) sk = n_stages;  // only loads and barriers
+  if (!wave_live) sk = n_stages;  // only loads, splits and barriers
 
   float m_ref = kNegInf, l_run = 0.f, colsum = 0.f;
-  const int a_off = (c32 / kGroupRows) * kGroupPitch + (c32 % kGroupRows) * 16 + h * (kGroupRows * 16);
-  for (int it = 0; it < n_stages; ++it) {
-    // this thread's loads of stage `it` have landed when only those of the next stage are in
-    // flight; the barrier extends that to the workgroup and frees the slot consumed before
-    __builtin_amdgcn_s_waitcnt(0x0F70 | kLoads);
-    __builtin_amdgcn_s_barrier();
-    issue_stage(it + kF32Depth - 1);
-    if (it < sk) continue;
-    const unsigned char* slot = ring + (it % kF32Depth) * kStageBytes;
-    f32x16 acc = {0};
-#pragma unroll
-    for (int p = 0; p < NP; ++p) {
-      // (read with the bf16 sweeps' operand type: LDS reads of other types are taken to alias the
-      // ring's loads in flight and would wait for all of them)
-      const f32x4 v = __builtin_bit_cast(f32x4, *reinterpret_cast<const bf16x8*>(slot + a_off + p * (2 * kGroupRows * 16)));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(v[e], res[p * 4 + e], acc, 0, 0, 0);
-    }
+  // a finished tile of stage `it` into the sums; nl: -L of the lane's sixteen rows (sweep B)
+  auto tally = [&](f32x16& acc, const float (&nl)[16], int it) {
     const int trow = s_begin + it * kStageRows + h * 4;  // first stream row of the lane
     if (MODE == 0) {
       if (it >= f1) {
@@ -1408,12 +1461,6 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
       l_run = l_run * fast_exp2(m_ref + nm) + sum;
       m_ref = m_new;
     } else {
-      float nl[16];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = __builtin_bit_cast(f32x4, *reinterpret_cast<const bf16x8*>(slot + kDataBytes + (g * 8 + h * 4) * 4));
-        nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
-      }
       float sum = 0.f;
       if (it < f0) {
 #pragma unroll
@@ -1427,9 +1474,160 @@ __global__ __launch_bounds__(kThreads, 3) void score_f32_kernel(
       }
       colsum += sum;
     }
+  };
+  f32x16 acc, small;
+  auto products = [&](const Split3& a, int ks) CASK_INLINE {
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.lo, res[ks].hi, ks == 0 ? f32x16{0} : small, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, res[ks].hi, ks == 0 ? f32x16{0} : acc, 0, 0, 0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, res[ks].lo, small, 0, 0, 0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, res[ks].mid, small, 0, 0, 0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.mid, res[ks].hi, small, 0, 0, 0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.hi, res[ks].mid, small, 0, 0, 0);
+  };
+  auto load_nl = [&](float (&nl)[16], int it) {
+    if (MODE == 1) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&negl[it & 3][g * 8 + h * 4]);
+        nl[g * 4 + 0] = v[0]; nl[g * 4 + 1] = v[1]; nl[g * 4 + 2] = v[2]; nl[g * 4 + 3] = v[3];
+      }
+    }
+  };
+  // one stage, nothing overlapped; leaves the tile's logits in acc
+  auto plain_chain = [&](int it) CASK_INLINE {
+    Split3 a = read_terms(it, 0);
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks) {
+      products(a, ks);
+      if (ks + 1 < NK) a = read_terms(it, ks + 1);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] += small[r];
+  };
+  // Stage `it` is whole behind the barrier, and stage it - 1 has been read by everyone.  `raw` holds stage
+  // it + 1: even behind an odd stage.  (Named at every call, and the loops run two stages at a time: chosen
+  // by a branch, the loads go to other registers, and the copy waits for them.)
+  auto next_stage = [&](int it, Raw& raw) CASK_INLINE {
+    stage_barrier();
+    store_rows(raw, it + 1);
+    store_negl(raw, it + 1);
+    load_stage(raw, it + 3);
+  };
+  auto plain_stage = [&](int it, Raw& raw) CASK_INLINE {
+    next_stage(it, raw);
+    if (it < sk) return;
+    plain_chain(it);
+    float nl[16];
+    load_nl(nl, it);
+    tally(acc, nl, it);
+  };
+  auto plain = [&](int from, int to) CASK_INLINE {
+    if ((from & 1) && from < to) plain_stage(from++, even);
+    for (; from + 1 < to; from += 2) {
+      plain_stage(from, odd);
+      plain_stage(from + 1, even);
+    }
+    if (from < to) plain_stage(from, odd);
+  };
+  auto pipelined = [&](int from, int to) CASK_INLINE {  // clean stages, to > from, from even
+    next_stage(from, odd);
+    plain_chain(from);
+    if (MODE == 0) {  // (always the first stages of the workgroup) at most 16 above the row's largest logit so far
+      float top = acc[0], low = acc[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) {
+        top = fmaxf(top, acc[r]);
+        low = fminf(low, acc[r]);
+      }
+      m_ref = __builtin_fmaf(top, c, fminf(0.3f * c * (top - low), 16.f));
+    }
+    f32x16 old = acc;
+    float sum = 0.f;
+    auto bank = [&]() CASK_INLINE {
+      if (MODE == 0) l_run += sum;
+      else colsum += sum;
+      sum = 0.f;
+    };
+    auto body = [&](int it, Raw& raw) CASK_INLINE {
+      stage_barrier();
+      Split3 a = read_terms(it, 0);
+      Split3 t;
+      store_negl(raw, it + 1);
+#pragma unroll
+      for (int ks = 0; ks < NK; ++ks) {
+        constexpr int kTerms = 16 / NK;  // 2 or 4 logits of the old tile
+        float nl[4];
+        if (MODE == 1) {
+          const int r0 = ks * kTerms;
+          const f32x4 v = *reinterpret_cast<const f32x4*>(&negl[(it - 1) & 3][(r0 >> 2) * 8 + h * 4]);
+#pragma unroll
+          for (int e = 0; e < kTerms; ++e) nl[e] = v[(r0 & 3) + e];
+        }
+        Split3 next = a;
+        if (ks + 1 < NK) next = read_terms(it, ks + 1);
+        products(a, ks);
+#pragma unroll
+        for (int e = 0; e < kTerms; ++e) sum += fast_exp2(__builtin_fmaf(old[ks * kTerms + e], c, MODE == 0 ? -m_ref : nl[e]));
+        const int j = ks / 4, q = ks % 4;
+        split_pair(raw.v[j][q >> 1][(q & 1) * 2], raw.v[j][q >> 1][(q & 1) * 2 + 1], t, q);
+        if (q == 3) store_item(it + 1, j, t);
+        // (pinned: the optimiser would sink the sum out of the products it is meant to overlap with)
+        asm volatile("" : "+v"(sum));
+        __builtin_amdgcn_sched_barrier(0);
+        a = next;
+      }
+      bank();
+      load_stage(raw, it + 3);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) old[r] = acc[r] + small[r];
+    };
+    int it = from + 1;
+    for (; it + 1 < to; it += 2) {
+      body(it, even);
+      body(it + 1, odd);
+    }
+    if (it < to) body(it, even);
+    float nl[16];
+    load_nl(nl, to - 1);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sum += fast_exp2(__builtin_fmaf(old[r], c, MODE == 0 ? -m_ref : nl[r]));
+    bank();
+  };
+  if (!wave_live || MODE == 1) {
+    const int from = (f0 + 1) & ~1;
+    plain(0, wave_live ? min(from, n_stages) : n_stages);
+    if (wave_live && from < n_stages) pipelined(from, n_stages);
+  } else {
+    int first = 0;
+    asm volatile("" : "+s"(first));
+    if (f1 > 0) pipelined(first, f1);
+    plain(f1, n_stages);
   }
-  // loads issued past the last stage may still be landing in LDS
-  __builtin_amdgcn_s_waitcnt(0x0F70);
+
+  // ---- not finite somewhere: the wave's share again with fp32 products
+  const float total = MODE == 0 ? l_run : colsum;
+  if (__builtin_amdgcn_ballot_w64(wave_live && !(total < __builtin_inff())) != 0ull) {
+    m_ref = kNegInf;
+    l_run = colsum = 0.f;
+    const float* bp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;
+    for (int it = sk; it < n_stages; ++it) {
+      const int srow = s_begin + it * kStageRows;
+      const float* ap = str_ptr + (size_t)min(srow + c32, s_end - 1) * D + h * 4;
+      f32x16 acc = {0};
+      for (int p = 0; p < D / 8; ++p) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(ap + p * 8), y = *reinterpret_cast<const f32x4*>(bp + p * 8);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+      }
+      float nl[16];
+      if (MODE == 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          nl[r] = bias[(size_t)unit * mq_pad + min(srow + (r >> 2) * 8 + h * 4 + (r & 3), mq_pad - 1)];
+      }
+      tally(acc, nl, it);
+    }
+  }
 
   if (MODE == 0) {
     const float m2 = __shfl_xor(m_ref, 32, 64), l2 = __shfl_xor(l_run, 32, 64);

@@ -432,3 +432,39 @@ def test_ranks_where_the_bins_are_uneven(N, P, spread):
     if spread != "outlier":
         want_rho = ref.mass_diagnostics(rp, row_off, sc, role_w, out.out_mass.cpu().numpy(), out.out_len.cpu().numpy())
         np.testing.assert_allclose(rho.cpu().numpy(), want_rho, rtol=2e-6)
+
+
+def _scores64(c, units, n, d, G, Wn):
+    """Scores in 64 bits, on the CPU."""
+    K, Q = c["K"].double().reshape(units, n, d), c["Q"].double().reshape(units, Wn * G, d)
+    x = Q @ K.transpose(1, 2).contiguous() / d ** 0.5
+    x.masked_fill_(torch.arange(n)[None, None] > (n - Wn + torch.arange(Wn * G) // G)[None, :, None], float("-inf"))
+    return torch.softmax(x, dim=2).mean(dim=1).reshape(-1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,Wn,n,units,kind", [(4, 64, 4096, 4, "plain"), (2, 32, 1000, 6, "plain"), (7, 100, 1531, 3, "plain"),
+                                               (4, 64, 1000, 4, "small_keys"), (4, 64, 1000, 4, "past_bf16")])
+def test_fp32_scores_from_bf16_terms(G, Wn, n, units, kind, d):
+    """fp32 scores against 64-bit sums, 2-norm of the error over 2-norm of the result.  The products of three
+    bf16 terms leave 2^-24 of a product; what counts are the roundings of a logit (two large partial sums
+    of sixteen channels at a time) and of the log-sum-exp (half an ulp at 8 to 16 in base 2: 3.4e-7 to
+    6.9e-7 x ln 2, uniform, shrinking with the rows that see a key): measured 1.2e-7 to 3.1e-7.  small_keys:
+    keys 2^-100 of the queries' inverse (their third terms stay normal numbers); past_bf16: finite keys that
+    round to infinity in bf16 take the wave's share to the fp32 tiles."""
+    c = _units([n] * units, [n // 8] * units, head_dim=d, q_per_kv=G, window=Wn)
+    noise = torch.Generator().manual_seed(d + n)
+    c = {k: (v.float() * (1 + 1e-3 * torch.randn(v.shape, generator=noise)) if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    if kind == "small_keys":
+        c["K"], c["Q"] = c["K"] * 2.0 ** -100, c["Q"] * 2.0 ** 100
+    elif kind == "past_bf16":
+        c["Q"][..., 5] *= 2.0 ** -126
+        c["K"][:, 5] *= 2.0 ** 20
+        c["K"][[3, 40, n - Wn - 2, 2 * n - Wn + 1], 5] = torch.tensor([3.4e38, -3.4e38, 3.4e38, 3.4e38])
+    want = _scores64(c, units, n, d, G, Wn)
+    assert bool(torch.isfinite(want).all())
+    p = cask.Params(dtype=cask.F32, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60)
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    err = float((got - want).norm() / want.norm())
+    _note(G, Wn, n, units, kind, d, "error", err)
+    assert err < 4e-7
