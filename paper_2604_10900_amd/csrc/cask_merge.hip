@@ -55,6 +55,20 @@ __device__ inline float sumsq_bf16x8(const uint4& v) {
   return s;
 }
 
+// What the two lanes l and l + 32 hold, the same pair in both: {lower half's, upper half's}.
+struct Halves { float lower, upper; };
+__device__ __forceinline__ Halves both_halves(float x) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return {__uint_as_float(s[0]), __uint_as_float(s[1])};
+}
+__device__ __forceinline__ float inverse_norm(float ss) { return ss > 0.f ? 1.0f / sqrtf(ss) : 0.f; }
+
+// Whether a cosine x |donor|^-1 can reach tau, from the squared norm alone: the hardware's reciprocal root
+// is within an ulp for normal numbers, so the slack is generous; what passes is compared exactly later.
+__device__ __forceinline__ bool may_reach(float x, float ss, float tau) {
+  return ss < 1e-30f || !(x * __builtin_amdgcn_rsqf(ss) < tau - 1e-5f * __builtin_fabsf(tau));
+}
+
 // Workgroup = `tiles_per_wg` consecutive donor tiles of one unit; wave w owns rows
 // [32 w, 32 w + 32) of every tile.
 //
@@ -70,11 +84,17 @@ __device__ inline float sumsq_bf16x8(const uint4& v) {
 //
 // Compute side: the unit's seeds (kSeedBlock at a time, same layout, with inverse norms) are
 // the A operand, so a lane owns one donor and sees its seeds in ascending order:
-// cos = (dot * |seed|^-1) * |donor|^-1 in fp32, first maximum wins.
+// cos = (dot * |seed|^-1) * |donor|^-1 in fp32, first maximum wins.  Of 32 seeds only the largest
+// product is formed (16 multiplications and 8 maxima a lane); which seed it was, and the donor's exact
+// inverse norm, are found where some lane's cosine may reach tau, which most tiles' do not: an argmax
+// carried along cost six dependent instructions a seed, and the vector pipes, not the stream, were the
+// bound with 64 channels and with many seeds.  Places past the last seed carry a NaN as inverse norm,
+// which no maximum prefers.
 // ONE_BLOCK: every unit has at most kSeedBlock seeds, so they are staged once per workgroup and
 // the tile loop contains nothing but the donor stream (the host knows the bound).
-// Measured, d = 64 (128 units of 5378 rows, 84 MB of keys): 30 us; a thread per donor on the
-// vector units, its key in registers, took 105 us.
+// Measured, an argmax per seed and the exact norm per tile before: d = 64, 128 units of 5378 rows 28.1 -> 20.0 us
+// (84 MB of keys), 20 of 4000 13.6 -> 8.2; d = 128, 282 seeds, 62.6 -> 50; 30 units of 6000 rows 16.0 -> 12.2,
+// 112 of 33 024 179 -> 164 (5.8 TB/s).
 // RADIUS: a merge radius is set (the epilogue then looks up every seed's cache row).
 template <int D, bool ONE_BLOCK, bool RADIUS>
 __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
@@ -163,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
 #pragma unroll
         for (int o = kPieces / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
         if (piece == 0) {
-          seed_inv[sr] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+          seed_inv[sr] = idx[i] < 0 ? __builtin_nanf("") : inverse_norm(ss);
           seed_pos[sr] = idx[i];
         }
       }
@@ -186,7 +206,7 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   auto turn_at = [&](int ks) { return turn_ld[ks % kAddr] + (ks / kAddr) * (kAddr * 32); };
 
   // registers -> private LDS region -> B operand of this lane's donor; refills the registers
-  // with tile t + kPrefetch; returns the donor's inverse norm
+  // with tile t + kPrefetch; returns the donor's squared norm
   auto turn_donors = [&](int t, uint4 (&d)[kGroups], int& rl, bf16x8 (&bres)[NK]) -> float {
 #pragma unroll
     for (int j = 0; j < kGroups; ++j)
@@ -199,60 +219,73 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
       ss += sumsq_bf16x8(v);
       bres[ks] = __builtin_bit_cast(bf16x8, v);
     }
-    ss += __shfl_xor(ss, 32, 64);
-    return ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+    const Halves n = both_halves(ss);
+    return n.lower + n.upper;
   };
   // The lane's donor against the staged seeds [sb, sb + m_blk), ascending ordinal: first maximum
   // wins.  `best` is the cosine without the donor's own inverse norm: a positive factor common
-  // to all of a donor's seeds, applied once when the winner is settled.
-  auto against_block = [&](int sb, int m_blk, const bf16x8 (&bres)[NK], int drow, float& best, int& best_ord) {
-    for (int s0 = 0; s0 < m_blk; s0 += 32) {
-      bf16x8 a[NK];
+  // to all of a donor's seeds, applied once when the winner is settled.  `best_ord` is kept only where
+  // the cosine may reach tau: a larger one that may not leaves none that does behind.
+  auto against_block = [&](int sb, int m_blk, const bf16x8 (&bres)[NK], int drow, float ss, float& best, int& best_ord) {
+    auto chain = [&](int s0) {
       const unsigned char* ap = seeds + (s0 / kGroupRows) * kGroupPitch;
-#pragma unroll
-      for (int ks = 0; ks < NK; ++ks) a[ks] = *reinterpret_cast<const bf16x8*>(ap + turn_at(ks));
       f32x16 acc = {0};
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks], bres[ks], acc, 0, 0, 0);
-      auto pick = [&](auto whole_tag) {  // whole: all 32 seeds of this step exist
-        constexpr bool kWhole = decltype(whole_tag)::value;
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(ap + turn_at(ks)), bres[ks], acc, 0, 0, 0);
+      return acc;
+    };
+    auto pick = [&](const f32x16& acc, int s0) {
+      float v[16], top = 0.f;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {  // ascending seed ordinal within the lane
-          const float4 si = *reinterpret_cast<const float4*>(&seed_inv[s0 + g * 8 + h * 4]);
-          const float sv[4] = {si.x, si.y, si.z, si.w};
-          int pv[4] = {0, 0, 0, 0};
-          if (RADIUS) {
-            const int4 sp = *reinterpret_cast<const int4*>(&seed_pos[s0 + g * 8 + h * 4]);
-            pv[0] = sp.x, pv[1] = sp.y, pv[2] = sp.z, pv[3] = sp.w;
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int sr = s0 + g * 8 + h * 4 + q;
-            const float sim = acc[g * 4 + q] * sv[q];
-            bool near = true;
-            if (RADIUS) near = (pv[q] > drow ? pv[q] - drow : drow - pv[q]) <= radius;
-            if ((kWhole || sr < m_blk) && near && sim > best) {
-              best = sim;
-              best_ord = sb + sr;
-            }
-          }
+      for (int g = 0; g < 4; ++g) {  // ascending seed ordinal within the lane
+        const float4 si = *reinterpret_cast<const float4*>(&seed_inv[s0 + g * 8 + h * 4]);
+        const float sv[4] = {si.x, si.y, si.z, si.w};
+        int pv[4] = {0, 0, 0, 0};
+        if (RADIUS) {
+          const int4 sp = *reinterpret_cast<const int4*>(&seed_pos[s0 + g * 8 + h * 4]);
+          pv[0] = sp.x, pv[1] = sp.y, pv[2] = sp.z, pv[3] = sp.w;
         }
-      };
-      if (s0 + 32 <= m_blk) pick(std::true_type{});
-      else pick(std::false_type{});
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float x = acc[g * 4 + q] * sv[q];
+          if (RADIUS && (pv[q] > drow ? pv[q] - drow : drow - pv[q]) > radius) x = __builtin_nanf("");
+          v[g * 4 + q] = x;
+          top = g == 0 && q == 0 ? x : fmaxf(top, x);
+        }
+      }
+      const bool wins = top > best && may_reach(top, ss, kp.tau);
+      if (__builtin_amdgcn_ballot_w64(wins) != 0ull) {
+        int at = 0;
+#pragma unroll
+        for (int i = 15; i > 0; --i) at = v[i] == top ? (i >> 2) * 8 + (i & 3) : at;
+        if (v[0] == top) at = 0;
+        if (wins) best_ord = sb + s0 + h * 4 + at;
+      }
+      best = fmaxf(best, top);
+    };
+    for (int s0 = 0; s0 < m_blk; s0 += 64) {  // (two chains in flight: a pick waits for its own to end)
+      const f32x16 lo = chain(s0);
+      if (s0 + 32 < m_blk) {
+        const f32x16 up = chain(s0 + 32);
+        pick(lo, s0);
+        pick(up, s0 + 32);
+      } else {
+        pick(lo, s0);
+      }
     }
   };
   // the two half-waves hold the even and the odd groups of four seeds: lowest ordinal wins a tie
-  auto settle = [&](float best, int best_ord, float dinv, bool donor, int drow) {
-    const float ob = __shfl_xor(best, 32, 64);
-    const int oo = __shfl_xor(best_ord, 32, 64);
-    if (oo >= 0 && (best_ord < 0 || better(ob, oo, best, best_ord))) {
-      best = ob;
-      best_ord = oo;
+  auto settle = [&](float best, int best_ord, float ss, bool donor, int drow) {
+    int ord = -1;
+    if (__builtin_amdgcn_ballot_w64(best_ord >= 0) != 0ull) {
+      const Halves b = both_halves(best), o = both_halves(__int_as_float(best_ord));
+      const int o0 = __float_as_int(o.lower), o1 = __float_as_int(o.upper);
+      const bool second = o1 >= 0 && (o0 < 0 || better(b.upper, o1, b.lower, o0));
+      ord = second ? o1 : o0;
+      if (!(donor && ord >= 0 && (second ? b.upper : b.lower) * inverse_norm(ss) >= kp.tau)) ord = -1;
     }
-    if (h == 0 && drow < last)  // rows past the workgroup's share belong to another one
-      assign_ord[row0 + drow] = (donor && best_ord >= 0 && best * dinv >= kp.tau) ? best_ord : -1;
+    if (h == 0 && drow < last) assign_ord[row0 + drow] = ord;  // rows past the workgroup's share belong to another one
   };
 
   if constexpr (ONE_BLOCK) {
@@ -263,29 +296,32 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
     auto tile_body = [&](int t, uint4 (&d)[kGroups], int& rl) {
       const bool donor = rl == CASK_ROLE_DONOR;
       bf16x8 bres[NK];
-      const float dinv = turn_donors(t, d, rl, bres);
+      const float ss = turn_donors(t, d, rl, bres);
       const int drow = first + t * kDonorTile + wv * 32 + c32;
       float best = kNegInf;
       int best_ord = -1;
-      against_block(0, M, bres, drow, best, best_ord);
-      settle(best, best_ord, dinv, donor, drow);
+      against_block(0, M, bres, drow, ss, best, best_ord);
+      settle(best, best_ord, ss, donor, drow);
     };
     for (int t = 0; t < n_tiles; t += kPrefetch) {
 #pragma unroll
-      for (int b = 0; b < kPrefetch; ++b) tile_body(t + b, dreg[b], rreg[b]);
+      for (int b = 0; b < kPrefetch; ++b) {
+        if (t + b >= n_tiles) return;
+        tile_body(t + b, dreg[b], rreg[b]);
+      }
     }
   } else {
     // More seeds than LDS holds at a time: a block of seeds is staged once and meets every tile
     // of the workgroup (at most kMultiTiles; the donors stream again per block, from L2) while
     // each tile's best seed so far waits in registers.  Staging per tile instead made a unit
     // with 282 seeds and four tiles a chain of twelve stagings and twenty-four barriers.
-    float best[kMultiTiles], dinv[kMultiTiles];
+    float best[kMultiTiles], ss[kMultiTiles];
     int best_ord[kMultiTiles];
     bool donor[kMultiTiles];
 #pragma unroll
     for (int t = 0; t < kMultiTiles; ++t) {
       best[t] = kNegInf;
-      dinv[t] = 0.f;
+      ss[t] = 0.f;
       best_ord[t] = -1;
       donor[t] = false;
     }
@@ -302,14 +338,14 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
         if (t < n_tiles) {  // (the same for the whole workgroup)
           donor[t] = rreg[t % kPrefetch] == CASK_ROLE_DONOR;
           bf16x8 bres[NK];
-          dinv[t] = turn_donors(t, dreg[t % kPrefetch], rreg[t % kPrefetch], bres);
-          against_block(sb, m_blk, bres, first + t * kDonorTile + wv * 32 + c32, best[t], best_ord[t]);
+          ss[t] = turn_donors(t, dreg[t % kPrefetch], rreg[t % kPrefetch], bres);
+          against_block(sb, m_blk, bres, first + t * kDonorTile + wv * 32 + c32, ss[t], best[t], best_ord[t]);
         }
       }
     }
 #pragma unroll
     for (int t = 0; t < kMultiTiles; ++t)
-      if (t < n_tiles) settle(best[t], best_ord[t], dinv[t], donor[t], first + t * kDonorTile + wv * 32 + c32);
+      if (t < n_tiles) settle(best[t], best_ord[t], ss[t], donor[t], first + t * kDonorTile + wv * 32 + c32);
   }
 }
 
