@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "cask.h"
 #include "cask_common.h"
@@ -198,7 +199,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// The same walk for bf16 caches with every cosine a 32x32x16 MFMA product, and with the order
+// The same walk for bf16 caches that walk more rows than dedup_seed_all_kernel (below) holds, with every
+// cosine a 32x32x16 MFMA product, and with the order
 // of the work turned round so that a row is staged in LDS once: the walk takes its sorted rows
 // 64 at a time; the block's rows are staged (padded pitch: operand reads are conflict-free),
 // four waves form the block's own 64 x 64 cosines (a row's mask of earlier block mates it
@@ -388,6 +390,200 @@ __global__ __launch_bounds__(kDdThreads) void dedup_seed_mfma_kernel(
     if (is_seed[k]) ro[row_of(k)] = CASK_ROLE_SEED;
 }
 
+// ------------------------------------------------------------------ bf16, every walked row in LDS
+
+// The walk where the parameters bound it to kDdAllRows rows a unit (a budget of 512 at h = 4): all rows are
+// staged in LDS once, with their inverse norms; the sixteen waves form every cosine of an earlier with a
+// later row (32 x 32 MFMA tiles of the lower triangle) and leave one bit per pair; one wave then walks
+// the ranks on those bits alone, 64 a step.  Rows are ranked by counting larger keys, in pieces shared
+// by all threads.
+// Bound: a chain of latencies per unit (roles and scores of the unit, rows, tiles, walk).  The general kernel
+// above scans roles a row at a time twice, sorts in 28 - 45 barrier steps and goes to memory for every
+// block of 64: 56 units of 6256 rows, 128 of them walked, 24.7 -> 10.8 us; 20 of 4000, 280 walked, 40 -> 19.
+constexpr int kDaThreads = 1024;
+constexpr int kDaWaves = kDaThreads / 64;
+constexpr int kDdAllRows = 448;  // rows, bits and keys of as many fill the 160 KB of a compute unit
+template <int D>
+struct DedupAll {
+  static constexpr int kPitch = D * 2 + 16;  // 16-byte reads of eight consecutive rows hit different banks
+  static size_t lds_bytes(int cap, int width) { return (size_t)cap * (kPitch + cap / 8 + 8 + 4 + 4) + (size_t)width * 8; }
+};
+
+template <int D>
+__global__ __launch_bounds__(kDaThreads) void dedup_seed_all_kernel(
+    KParams kp, int cap, int width, const int64_t* __restrict__ row_off, const int32_t* __restrict__ prefix_len,
+    const uint16_t* __restrict__ K, const float* __restrict__ scores, uint8_t* __restrict__ role) {
+  constexpr int kPitch = DedupAll<D>::kPitch, KS = D / 16, PPR = D / 8;
+  extern __shared__ __attribute__((aligned(16))) unsigned char dd_mem[];
+  // cap (a multiple of 64) of each: rows, keys by rank, words of pair bits (row i, bit j: the earlier row j
+  // resembles it), ranks, inverse norms; in front of the keys by rank, `width` (cap or more, a power of two) as they come
+  unsigned char* const rows_s = dd_mem;
+  uint64_t* const keys = reinterpret_cast<uint64_t*>(rows_s + (size_t)cap * kPitch);
+  uint64_t* const sorted = keys + width;
+  const int words = cap / 32;
+  uint32_t* const like = reinterpret_cast<uint32_t*>(sorted + cap);
+  int* const rank_s = reinterpret_cast<int*>(like + cap * words);
+  float* const inv_s = reinterpret_cast<float*>(rank_s + cap);
+  __shared__ uint32_t kept_s[kDdAllRows / 32];
+  __shared__ int n_cand;
+  const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, h = lane >> 5;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t row0 = row_off[u];
+  const int N = (int)(row_off[u + 1] - row0);
+  const int P = prefix_len[u];
+  const UnitPlan pl = make_plan(kp, P, N);
+  const int hi = N - pl.r_eff, n = hi - P, C = pl.core, M = pl.seeds;
+  // the same condition under which the selection widened its seed range
+  if ((pl.status & CASK_ST_PREFIX_BUDGET_EXHAUSTED) || M <= 0 || n <= C + M) return;
+  const float* s = scores + row0;
+  uint8_t* ro = role + row0;
+  const uint16_t* Ku = K + row0 * D;
+
+  // ---- the provisional seeds (their order of arrival does not matter)
+  if (tid == 0) n_cand = 0;
+  if (tid < cap) rank_s[tid] = 0;
+  if (tid < kDdAllRows / 32) kept_s[tid] = 0u;
+  __syncthreads();
+  constexpr int kAhead = 8;
+  for (int base = P; base < hi; base += kDaThreads * kAhead) {
+    int r[kAhead];
+    float v[kAhead];
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) {
+      const int i = min(base + e * kDaThreads + tid, hi - 1);
+      r[e] = ro[i];
+      v[e] = s[i];
+    }
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) {
+      const int i = base + e * kDaThreads + tid;
+      const bool mine = i < hi && r[e] == CASK_ROLE_SEED;
+      const unsigned long long all = __ballot(mine);
+      if (all == 0ull) continue;
+      int at = 0;
+      if (lane == 0) at = atomicAdd(&n_cand, __popcll(all));
+      at = __builtin_amdgcn_readfirstlane(at) + __popcll(all & ((1ull << lane) - 1ull));
+      if (mine && at < cap) keys[at] = ((uint64_t)score_key(v[e]) << 32) | (uint32_t)~(uint32_t)i;
+    }
+  }
+  __syncthreads();
+  const int Tn = min(n_cand, cap);
+
+  // ---- ranks: `share` threads a row, each counting the larger ones among its part of the keys
+  {
+    int part_of = 64;
+    while (part_of < Tn) part_of <<= 1;  // <= width
+    if (tid >= Tn && tid < part_of) keys[tid] = 0ull;  // below every real key
+    __syncthreads();
+    const int share = kDaThreads / part_of, me = tid & (part_of - 1), part = tid / part_of;
+    const int per = ((Tn + share - 1) / share + 3) & ~3;  // (up to four past the end of the last part: still zeros)
+    const uint64_t mine = keys[me];
+    int larger = 0;
+    for (int k = part * per; me < Tn && k < min((part + 1) * per, Tn); k += 4) {
+      ulonglong2 v[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) v[e] = *reinterpret_cast<const ulonglong2*>(keys + k + 2 * e);
+#pragma unroll
+      for (int e = 0; e < 2; ++e) larger += (v[e].x > mine ? 1 : 0) + (v[e].y > mine ? 1 : 0);
+    }
+    if (me < Tn && larger) atomicAdd(&rank_s[me], larger);
+  }
+  __syncthreads();
+  if (tid < Tn) sorted[rank_s[tid]] = keys[tid];
+  __syncthreads();
+  auto row_of = [&](int rank) { return (int)(~(uint32_t)sorted[rank]); };
+
+  // ---- rows and inverse norms (places past the last row hold it again: their bits are not looked at)
+  const int padded = (Tn + 31) & ~31;
+  {
+    constexpr int kPass = kDaThreads / PPR;  // rows a pass: 64 or 128
+    const int piece = tid % PPR;
+    for (int j0 = tid / PPR; j0 < padded; j0 += 4 * kPass) {
+      u32x4 v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[e] = *reinterpret_cast<const u32x4*>(Ku + (size_t)row_of(min(j0 + e * kPass, Tn - 1)) * D + piece * 8);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e * kPass;
+        float nn = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const float a = __uint_as_float(v[e][w] << 16), b = __uint_as_float(v[e][w] & 0xffff0000u);
+          nn = __builtin_fmaf(a, a, nn);
+          nn = __builtin_fmaf(b, b, nn);
+        }
+#pragma unroll
+        for (int o = PPR / 2; o > 0; o >>= 1) nn += __shfl_xor(nn, o, 64);
+        if (j < padded) {
+          *reinterpret_cast<u32x4*>(rows_s + j * kPitch + piece * 16) = v[e];
+          if (piece == 0) inv_s[j] = nn > 0.f ? 1.f / sqrtf(nn) : 0.f;
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- pair bits: tile (rt, ct), ct <= rt, of rows 32 rt .. against the earlier rows 32 ct ..
+  {
+    auto operand = [&](int row, int ks) {
+      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(rows_s + row * kPitch + (2 * ks + h) * 16));
+    };
+    const int tiles = padded / 32;
+    int rt = 0, first = 0;  // tiles of the rows before: rt (rt + 1) / 2
+    for (int t = wv; t < tiles * (tiles + 1) / 2; t += kDaWaves) {
+      while (t >= first + rt + 1) first += ++rt;
+      const int ct = t - first;
+      f32x16 acc = {0};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(rt * 32 + c32, ks), operand(ct * 32 + c32, ks), acc, 0, 0, 0);
+      const int j = ct * 32 + c32;
+      const float inv_j = inv_s[j];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int i = rt * 32 + (r >> 2) * 8 + h * 4 + (r & 3);
+        const unsigned long long b = __ballot(j < i && acc[r] * inv_s[i] * inv_j >= kp.tau);
+        if (c32 == 0) like[i * words + ct] = h ? (uint32_t)(b >> 32) : (uint32_t)b;
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- the walk
+  if (wv == 0) {
+    int chosen = 0;
+    for (int b0 = 0; b0 < Tn && chosen < M; b0 += 64) {
+      const int me = min(b0 + lane, Tn - 1);
+      const uint32_t* mine = like + me * words;
+      uint32_t hit = 0u;
+#pragma unroll 4
+      for (int w = 0; w < b0 / 32; ++w) hit |= mine[w] & kept_s[w];
+      const bool free_ = b0 + lane < Tn && hit == 0u;
+      // (the second word of the last rows' block may not exist: no row has a mate there)
+      const uint32_t lo = mine[b0 / 32], up = b0 + 32 < padded && lane >= 32 ? mine[b0 / 32 + 1] : 0u;
+      uint64_t kept = __ballot(free_ && (lo | up) == 0u);
+      uint64_t open = __ballot(free_ && (lo | up) != 0u);
+      while (open != 0ull) {  // in rank order: a row's mates all come before it
+        const int i = __ffsll((long long)open) - 1;
+        open &= open - 1ull;
+        const uint64_t mates = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)up, i) << 32) |
+                               (uint32_t)__builtin_amdgcn_readlane((int)lo, i);
+        if ((mates & kept) == 0ull) kept |= 1ull << i;
+      }
+      // the first M - chosen of them
+      kept = __ballot(((kept >> lane) & 1ull) && __popcll(kept & ((1ull << lane) - 1ull)) < M - chosen);
+      chosen += __popcll(kept);
+      if (lane == 0) kept_s[b0 / 32] = (uint32_t)kept;
+      if (lane == 0 && b0 / 32 + 1 < kDdAllRows / 32) kept_s[b0 / 32 + 1] = (uint32_t)(kept >> 32);
+      asm volatile("" ::: "memory");  // (the wave's own LDS accesses stay in order)
+    }
+  }
+  __syncthreads();
+  // every other provisional seed becomes a donor
+  if (tid < Tn && !((kept_s[tid >> 5] >> (tid & 31)) & 1u)) ro[row_of(tid)] = CASK_ROLE_DONOR;
+}
+
 }  // namespace
 
 hipError_t launch_dedup_seeds(const KParams& kp, const Batch& b, const float* scores, uint8_t* role,
@@ -396,6 +592,22 @@ hipError_t launch_dedup_seeds(const KParams& kp, const Batch& b, const float* sc
 #define CASK_DD(T, D)                                                              \
   dedup_seed_kernel<T, D><<<dim3(b.n_units), dim3(kDdThreads), 0, st>>>(           \
       kp, b.row_off, b.prefix_len, static_cast<const T*>(b.K), scores, role)
+  const int64_t most = (int64_t)kp.dedup * plan_seed_bound(kp);  // rows a walk covers
+  if (kp.dtype == CASK_BF16 && most <= kDdAllRows && !(kp.path_flags & CASK_PATH_DEDUP_VECTOR)) {
+    const int cap = (int)(most + 63) / 64 * 64;
+    int width = 64;
+    while (width < cap) width <<= 1;
+    auto go = [&](auto d) {
+      constexpr int D = decltype(d)::value;
+      static LdsLimitOnce lim;
+      const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&dedup_seed_all_kernel<D>), 160 * 1024 - 256);  // (beside the static LDS)
+      if (e != hipSuccess) return e;
+      dedup_seed_all_kernel<D><<<dim3(b.n_units), dim3(kDaThreads), DedupAll<D>::lds_bytes(cap, width), st>>>(
+          kp, cap, width, b.row_off, b.prefix_len, static_cast<const uint16_t*>(b.K), scores, role);
+      return hipGetLastError();
+    };
+    return kp.d == 64 ? go(std::integral_constant<int, 64>()) : go(std::integral_constant<int, 128>());
+  }
   if (kp.dtype == CASK_F32) {
     if (kp.d == 64) CASK_DD(float, 64); else CASK_DD(float, 128);
   } else if (kp.path_flags & CASK_PATH_DEDUP_VECTOR) {  // the vector-ALU kernel, for comparisons

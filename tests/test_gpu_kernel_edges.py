@@ -468,3 +468,24 @@ def test_fp32_scores_from_bf16_terms(G, Wn, n, units, kind, d):
     err = float((got - want).norm() / want.norm())
     _note(G, Wn, n, units, kind, d, "error", err)
     assert err < 4e-7
+
+
+@pytest.mark.parametrize("budget,h,d,prefix,rows", [(320, 7, 128, 0, 1500), (321, 7, 128, 0, 1500), (320, 7, 64, 40, 900), (256, 1, 128, 30, 1200),
+                                                    (192, 2, 64, 0, 700), (300, 7, 128, 20, 330)])
+def test_dedup_walk_with_every_row_in_lds(budget, h, d, prefix, rows):
+    """De-duplicated seeding of bf16 units where the walk covers at most 448 rows (budget 320, h = 7: exactly;
+    321: the general kernel), a few blocks of 64 and one, and a scratch shorter than the walk; roles and
+    events against the oracle, at a threshold that no decision of the walk comes close to."""
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=3, prefix=prefix, decode=rows, budget=budget, head_dim=d, window=32, cluster_frac=0.6)
+    c = caches.make(w, seed=5 + budget)
+    row_off, prefix_len, K, V, Q = parity.host_arrays(c)
+    for dt in (0.0, 0.013, -0.017, 0.031, -0.029, 0.047):
+        p = parity.params_of(w, sim_threshold=0.8 + dt, seed_dedup=h)
+        rp = parity.ref_params(p)
+        scores = ref.score(rp, row_off, K, Q)
+        role0, _ = ref.prefix_evict(rp, row_off, prefix_len, scores)
+        if ref.partition_keys(rp, row_off, prefix_len, K, scores, role0)[2].min() >= 1e-3:
+            break
+    else:
+        pytest.fail("no clear threshold for this cache")
+    _note(budget, h, d, parity.full_check(c, p))
