@@ -560,13 +560,20 @@ int cask_compress_step(const cask_params* params, const cask_batch* batch, const
   cj.out_mass = out_mass;
   cj.out_count = out_count;
   cj.out_stride = out_stride_rows;
+  if (group_fold_fits(kp, b)) {  // (reported as the grouping stage; the fold reads as an empty bracket)
+    e = launch_group_fold(kp, b, role, assign_ord, slot_of, seed_rows, n_seeds, merged_row, merged_ord, seg_row, assign, status,
+                          cj, st);
+    if (e != hipSuccess) return CASK_EDEVICE;
+    rec.mark();
+    rec.mark();
+    return CASK_OK;
+  }
   e = launch_gather_merged(kp, b, assign_ord, slot_of, seed_rows, merged_row, merged_ord,
                            n_merged, assign, assign ? 1 : 0, status, n_seeds, seg_row, seg_start,
                            &cj, st);
   if (e != hipSuccess) return CASK_EDEVICE;
   rec.mark();
-  e = launch_emit(kp, b, s, seed_rows, n_seeds, slot_of, seg_row, seg_start, n_merged, K_out,
-                  V_out, out_mass, in_count, out_count, out_stride_rows, st);
+  e = launch_emit(kp, b, seed_rows, n_seeds, slot_of, seg_row, seg_start, n_merged, cj, st);
   rec.mark();
   return dev_rc(e);
 }

@@ -163,9 +163,9 @@ __device__ inline float wave_sum(float v) {
 // idle: an event on four units of 8448 rows 96 -> 80 us, finer key splits included.  Events on 7 to 140
 // units that are no multiple of eight, 1500 to 6000 rows, 16 to 896 window rows: 27 shapes, 0 to 18 %
 // faster, none slower).
-__device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int& tile) {
-  const int xcd = blockIdx.x & 7;
-  int k = blockIdx.x >> 3;
+__device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int& tile, int block) {
+  const int xcd = block & 7;
+  int k = block >> 3;
   const int whole = (n_units >> 3) * tiles_per_unit;
   if (k < whole) {
     unit = (k / tiles_per_unit) * 8 + xcd;
@@ -178,6 +178,9 @@ __device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int
   unit = (n_units & ~7) + item / tiles_per_unit;
   tile = item % tiles_per_unit;
   return k < run && item < items;
+}
+__device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int& tile) {
+  return map_block(n_units, tiles_per_unit, unit, tile, (int)blockIdx.x);
 }
 inline int mapped_blocks(int n_units, int tiles_per_unit) {
   return (n_units >> 3) * tiles_per_unit * 8 + ((n_units & 7) * tiles_per_unit + 7) / 8 * 8;
@@ -306,6 +309,7 @@ struct CopyJob {
   int out_stride;
   int n_units;
   int lane_bytes;
+  const uint8_t* role;  // (launch_group_fold: rows that are seeds are left to the launch's other workgroups)
 };
 hipError_t launch_gather_merged(const KParams& kp, const Batch& b,
                                 const int32_t* assign_ord, const int32_t* slot_of,
@@ -335,11 +339,14 @@ hipError_t launch_group_diag(const KParams& kp, const Batch& b, const float* sco
                              float* dispersion, float* lost_mass, hipStream_t st);
 // Folds every seed that has donors into its output slot; the kept rows (the seeds' own among
 // them) were copied by the launch that grouped the donors (`launch_gather_merged` with a copy).
-hipError_t launch_emit(const KParams& kp, const Batch& b, const float* scores,
-                       const int32_t* seed_rows, const int32_t* n_seeds, const int32_t* slot_of,
-                       const int32_t* seg_row, const int32_t* seg_start,
-                       const int32_t* n_merged, void* K_out, void* V_out, float* out_mass,
-                       const int32_t* in_count, int32_t* out_count, int out_stride,
-                       hipStream_t st);
+hipError_t launch_emit(const KParams& kp, const Batch& b, const int32_t* seed_rows, const int32_t* n_seeds,
+                       const int32_t* slot_of, const int32_t* seg_row, const int32_t* seg_start,
+                       const int32_t* n_merged, const CopyJob& cj, hipStream_t st);
+// Grouping, fold and copy in one launch, for budgets whose seeds fit a workgroup's LDS.
+bool group_fold_fits(const KParams& kp, const Batch& b);
+hipError_t launch_group_fold(const KParams& kp, const Batch& b, const uint8_t* role, const int32_t* assign_ord,
+                             const int32_t* slot_of, const int32_t* seed_rows, const int32_t* n_seeds, int32_t* merged_row,
+                             int32_t* merged_ord, int32_t* seg_row, int32_t* assign_out, int32_t* status, const CopyJob& copy,
+                             hipStream_t st);
 
 }  // namespace cask

@@ -2,6 +2,7 @@
 //   similarity   every donor against every seed of its unit by key cosine; best seed kept
 //                when the cosine reaches tau (bf16: MFMA contraction seeds x donors^T,
 //                each lane owns one donor and scans its seeds in ascending order);
+//   group + fold the two steps below in one launch, for units of at most 8192 decode rows;
 //   gather       ordered list of the donors that merge (ascending row), per unit, then the
 //                same list grouped by seed; spare workgroups of the launch copy the kept
 //                tokens to the output bit for bit, sixteen lanes per row;
@@ -741,30 +742,27 @@ constexpr int kSmallList = 64;  // donor lists up to this length are split by a 
 // row groups (of four rows) a copy wave handles one after the other; measured: two beat four
 // and one (a long prefix-heavy copy, B = 2048: 64 us against 76 and 74)
 constexpr int kCopyRounds = 2;
+constexpr int kCopySlots = 4 * kCopyRounds;  // output slots of a copy wave
 
 // Copy of the rows an event keeps as they are (Sections 2.1, 2.4: protected tokens and the kept
 // part of the scratch stay untouched; only a seed with donors becomes a folded representative).
 // A wave owns 8 consecutive output slots of one unit, sixteen lanes a row (a sixteenth of the
 // row each); it puts the loads of its rows of K and V in flight before it touches any of them
-// and writes every slot, the seeds' too: the fold that follows in the stream overwrites the
-// seeds whose group has donors.  The copy needs nothing but the ordered walk's output, so it
+// and writes every slot but the seeds' (LEAVE_SEEDS), which the workgroups that fold
+// them write beside it; without, the seeds' too: a fold that follows in the stream overwrites
+// those whose group has donors.  The copy needs nothing but the ordered walk's output, so it
 // shares a launch with the grouping of the donors, whose workgroups leave most of the chip
 // idle.  The row pieces are native vectors: with HIP's vector classes the staging arrays end up
 // in scratch memory.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-template <typename Vec, int PIECES>
+template <typename Vec, int PIECES, bool LEAVE_SEEDS>
 __device__ __forceinline__ void copy_kept_rows(const CopyJob& cj, int B,
                                                const int64_t* __restrict__ row_off,
-                                               long long wave, int lane) {
-  constexpr int kSlotsPerWave = 4 * kCopyRounds;
+                                               int u, int t_base, int lane) {
   constexpr int BPL = (int)sizeof(Vec) * PIECES;  // a lane's share of a row: a sixteenth of it
   const int grp = lane >> 4, gl = lane & 15;
-  const int waves_per_unit = (B + kSlotsPerWave - 1) / kSlotsPerWave;
-  const int u = (int)(wave / waves_per_unit);
-  const int t_base = (int)(wave % waves_per_unit) * kSlotsPerWave;
-  if (u >= cj.n_units) return;
-  int slot[kCopyRounds], src[kCopyRounds], c0[kCopyRounds];
+  int slot[kCopyRounds], src[kCopyRounds], c0[kCopyRounds], rl[kCopyRounds];
   float a0[kCopyRounds];
   Vec kraw[kCopyRounds][PIECES], vraw[kCopyRounds][PIECES];
   // the slots' sources are read along with the unit's length, which says how many of them mean
@@ -791,10 +789,11 @@ __device__ __forceinline__ void copy_kept_rows(const CopyJob& cj, int B,
     }
     a0[j] = cj.scores[row];
     c0[j] = cj.in_count ? cj.in_count[row] : 1;
+    if (LEAVE_SEEDS) rl[j] = cj.role[row];
   }
 #pragma unroll
   for (int j = 0; j < kCopyRounds; ++j) {
-    if (src[j] < 0) continue;
+    if (src[j] < 0 || (LEAVE_SEEDS && rl[j] == CASK_ROLE_SEED)) continue;
     const size_t at = ((size_t)u * cj.out_stride + slot[j]) * pitch + (size_t)gl * BPL;
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
@@ -824,9 +823,11 @@ __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   if (u >= n_gather) {
     const long long wave = (long long)(u - n_gather) * (kGatherThreads / 64) + wv;
-    if (cj.lane_bytes == 16) copy_kept_rows<u32x4, 1>(cj, kp.B, row_off, wave, lane);
-    else if (cj.lane_bytes == 32) copy_kept_rows<u32x4, 2>(cj, kp.B, row_off, wave, lane);
-    else copy_kept_rows<u32x2, 1>(cj, kp.B, row_off, wave, lane);
+    const int per_unit = (kp.B + kCopySlots - 1) / kCopySlots, cu = (int)(wave / per_unit), first = (int)(wave % per_unit) * kCopySlots;
+    if (cu >= cj.n_units) return;
+    if (cj.lane_bytes == 16) copy_kept_rows<u32x4, 1, false>(cj, kp.B, row_off, cu, first, lane);
+    else if (cj.lane_bytes == 32) copy_kept_rows<u32x4, 2, false>(cj, kp.B, row_off, cu, first, lane);
+    else copy_kept_rows<u32x2, 1, false>(cj, kp.B, row_off, cu, first, lane);
     return;
   }
   const int64_t row0 = row_off[u];
@@ -1029,156 +1030,186 @@ __global__ __launch_bounds__(kGatherThreads) void gather_merged_kernel(
 // included, and overwrites the slots of the seeds that have donors.
 constexpr int kWaveFoldMax = 64;  // donors of one seed that a single wave folds (four rounds of its four groups)
 
+template <typename T>
+struct FoldIo {
+  const T* K;
+  const T* V;
+  const float* scores;
+  const int32_t* in_count;
+  T* K_out;
+  T* V_out;
+  float* out_mass;
+  int32_t* out_count;
+  int out_stride, B;
+};
+// (kernels take the pointers one by one, as ones that do not alias: from a struct of them the loads of a group
+// would be kept behind the stores of the one before)
+#define CASK_FOLD_ARGS(T)                                                                                              \
+  const T *__restrict__ K, const T *__restrict__ V, const float *__restrict__ scores, const int32_t *__restrict__ in_count, \
+      T *__restrict__ K_out, T *__restrict__ V_out, float *__restrict__ out_mass, int32_t *__restrict__ out_count, int out_stride, int B
 template <typename T, int D>
-__global__ __launch_bounds__(256) void emit_kernel(
-    KParams kp, int n_units, int fold_per_unit,
-    const int64_t* __restrict__ row_off, const T* __restrict__ K, const T* __restrict__ V,
-    const float* __restrict__ scores, const int32_t* __restrict__ seed_rows,
-    const int32_t* __restrict__ n_seeds, const int32_t* __restrict__ slot_of,
-    const int32_t* __restrict__ seg_row, const int32_t* __restrict__ seg_start,
-    const int32_t* __restrict__ n_merged, T* __restrict__ K_out, T* __restrict__ V_out,
-    float* __restrict__ out_mass, const int32_t* __restrict__ in_count,
-    int32_t* __restrict__ out_count, int out_stride) {
-  constexpr int EPL = D / 16;                    // elements per lane
-  constexpr int WORDS = EPL * sizeof(T) / 4;     // 32-bit words per lane
+struct FoldLane {
+  static constexpr int EPL = D / 16;                    // elements per lane
+  static constexpr int WORDS = EPL * sizeof(T) / 4;     // 32-bit words per lane
   struct alignas(WORDS * 4 > 16 ? 16 : WORDS * 4) Raw { uint32_t w[WORDS]; };
-  __shared__ int long_item[256][4];              // (unit, ordinal, segment bounds) of the long groups of a round
-  __shared__ int n_long;
-  __shared__ float part[4][4 * EPL][16];         // the waves' sums of a group folded by all four
-  __shared__ float part_mass[4];
-  __shared__ int part_count[4];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4, gl = lane & 15;
-  const int B = kp.B;
+  typedef uint32_t Words __attribute__((ext_vector_type(WORDS), aligned(WORDS * 4 > 16 ? 16 : WORDS * 4)));
+  struct Share {                                        // four waves' sums of a group that they fold together
+    float part[4][4 * EPL][16];
+    float mass[4];
+    int count[4];
+  };
+};
 
-  // Folds the donors [s0, s1) of one seed.  `ng` 16-lane groups share them round-robin and this
-  // one is number `g`; with `all_waves` the groups are the workgroup's sixteen and the waves'
-  // sums are added through LDS as (w0 + w1) + (w2 + w3), else they are the wave's four.
-  auto fold_group = [&](int u, int ord, int s0, int s1, int g, auto ng_c, auto all_c) {
-    constexpr int ng = decltype(ng_c)::value;
-    constexpr bool all_waves = decltype(all_c)::value;
-    const int64_t row0 = row_off[u];
-    const int32_t* seg = seg_row + row0;
-    const int srow = seed_rows[(size_t)u * B + ord];
-    const int slot = slot_of[row0 + srow];
-    float ka[EPL], va[EPL], ku[EPL], vu[EPL];  // score-weighted and count-weighted sums
-    float mass = 0.f;
-    int count = 0;
+// Folds donors [s0, s1) of one seed (row `srow` of the unit at row0) into output slot `slot`; donor k is row
+// row_at(k).  `NG` 16-lane groups share them round-robin and this one is number `g`: a wave's four, or
+// the sixteen of four waves (`all`: wave w4 of four; every thread of the workgroup then has to call it,
+// with s0 == s1 and `live` false where there is nothing to fold), whose sums are added through LDS as
+// (w0 + w1) + (w2 + w3).
+template <typename T, int D, int NG, bool ALL, typename RowAt>
+__device__ __forceinline__ void fold_group(const FoldIo<T>& io, int u, int64_t row0, int srow, int slot, int s0, int s1, int g, int w4,
+                                           bool live, RowAt row_at, typename FoldLane<T, D>::Share* share) {
+  using FL = FoldLane<T, D>;
+  constexpr int EPL = FL::EPL;
+  typedef typename FL::Raw Raw;
+  const int lane = threadIdx.x & 63, grp = lane >> 4, gl = lane & 15;
+  float ka[EPL], va[EPL], ku[EPL], vu[EPL];  // score-weighted and count-weighted sums
+  float mass = 0.f;
+  int count = 0;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) ka[e] = va[e] = ku[e] = vu[e] = 0.f;
-    if (g == 0) {  // the seed's own row opens the first group's sum
-      const float a = scores[row0 + srow];
-      const int c = in_count ? in_count[row0 + srow] : 1;
-      const Raw sk = *reinterpret_cast<const Raw*>(K + (size_t)(row0 + srow) * D + gl * EPL);
-      const Raw sv = *reinterpret_cast<const Raw*>(V + (size_t)(row0 + srow) * D + gl * EPL);
-      const T* skp = reinterpret_cast<const T*>(&sk);
-      const T* svp = reinterpret_cast<const T*>(&sv);
+  for (int e = 0; e < EPL; ++e) ka[e] = va[e] = ku[e] = vu[e] = 0.f;
+  if (live && g == 0) {  // the seed's own row opens the first group's sum
+    const float a = io.scores[row0 + srow];
+    const int c = io.in_count ? io.in_count[row0 + srow] : 1;
+    const Raw sk = *reinterpret_cast<const Raw*>(io.K + (size_t)(row0 + srow) * D + gl * EPL);
+    const Raw sv = *reinterpret_cast<const Raw*>(io.V + (size_t)(row0 + srow) * D + gl * EPL);
+    const T* skp = reinterpret_cast<const T*>(&sk);
+    const T* svp = reinterpret_cast<const T*>(&sv);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        const float kf = Elem<T>::load(skp + e), vf = Elem<T>::load(svp + e);
-        ka[e] = a * kf; va[e] = a * vf; ku[e] = (float)c * kf; vu[e] = (float)c * vf;
-      }
-      mass = a;
-      count = c;
+    for (int e = 0; e < EPL; ++e) {
+      const float kf = Elem<T>::load(skp + e), vf = Elem<T>::load(svp + e);
+      ka[e] = a * kf; va[e] = a * vf; ku[e] = (float)c * kf; vu[e] = (float)c * vf;
     }
-    for (int idx = s0 + g; idx < s1; idx += 4 * ng) {
-      int drow[4], dc[4];
-      float a[4];
-      Raw dk[4], dv[4];
+    mass = a;
+    count = c;
+  }
+  for (int idx = s0 + g; idx < s1; idx += 4 * NG) {
+    int drow[4], dc[4];
+    float a[4];
+    Raw dk[4], dv[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) drow[q] = seg[min(idx + ng * q, s1 - 1)];
+    for (int q = 0; q < 4; ++q) drow[q] = row_at(min(idx + NG * q, s1 - 1));
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = scores[row0 + drow[q]];
-        dc[q] = in_count ? in_count[row0 + drow[q]] : 1;
-        dk[q] = *reinterpret_cast<const Raw*>(K + (size_t)(row0 + drow[q]) * D + gl * EPL);
-        dv[q] = *reinterpret_cast<const Raw*>(V + (size_t)(row0 + drow[q]) * D + gl * EPL);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (idx + ng * q < s1) {
-          const float dcf = (float)dc[q];
-          const T* dkp = reinterpret_cast<const T*>(&dk[q]);
-          const T* dvp = reinterpret_cast<const T*>(&dv[q]);
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            const float kf = Elem<T>::load(dkp + e), vf = Elem<T>::load(dvp + e);
-            ka[e] = __builtin_fmaf(a[q], kf, ka[e]);
-            va[e] = __builtin_fmaf(a[q], vf, va[e]);
-            ku[e] = __builtin_fmaf(dcf, kf, ku[e]);
-            vu[e] = __builtin_fmaf(dcf, vf, vu[e]);
-          }
-          mass += a[q];
-          count += dc[q];
-        }
-      }
+    for (int q = 0; q < 4; ++q) {
+      a[q] = io.scores[row0 + drow[q]];
+      dc[q] = io.in_count ? io.in_count[row0 + drow[q]] : 1;
+      dk[q] = *reinterpret_cast<const Raw*>(io.K + (size_t)(row0 + drow[q]) * D + gl * EPL);
+      dv[q] = *reinterpret_cast<const Raw*>(io.V + (size_t)(row0 + drow[q]) * D + gl * EPL);
     }
-    // (g0 + g1) + (g2 + g3): addition commutes, so every lane ends with the same bits
 #pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        ka[e] += __shfl_xor(ka[e], o, 64);
-        va[e] += __shfl_xor(va[e], o, 64);
-        ku[e] += __shfl_xor(ku[e], o, 64);
-        vu[e] += __shfl_xor(vu[e], o, 64);
-      }
-      mass += __shfl_xor(mass, o, 64);
-      count += __shfl_xor(count, o, 64);
-    }
-    if constexpr (all_waves) {
-      // The waves' sums meet in LDS.  Wave 0 adds them as (w0 + w1) + (w2 + w3), its 16-lane group
-      // q taking one of the four sums (score-weighted K, V, count-weighted K, V), and the two
-      // groups whose sums the result is made of write it.
-      if (grp == 0) {
+    for (int q = 0; q < 4; ++q) {
+      if (idx + NG * q < s1) {
+        const float dcf = (float)dc[q];
+        const T* dkp = reinterpret_cast<const T*>(&dk[q]);
+        const T* dvp = reinterpret_cast<const T*>(&dv[q]);
 #pragma unroll
         for (int e = 0; e < EPL; ++e) {
-          part[wv][e][gl] = ka[e];
-          part[wv][EPL + e][gl] = va[e];
-          part[wv][2 * EPL + e][gl] = ku[e];
-          part[wv][3 * EPL + e][gl] = vu[e];
+          const float kf = Elem<T>::load(dkp + e), vf = Elem<T>::load(dvp + e);
+          ka[e] = __builtin_fmaf(a[q], kf, ka[e]);
+          va[e] = __builtin_fmaf(a[q], vf, va[e]);
+          ku[e] = __builtin_fmaf(dcf, kf, ku[e]);
+          vu[e] = __builtin_fmaf(dcf, vf, vu[e]);
         }
-        if (gl == 0) {
-          part_mass[wv] = mass;
-          part_count[wv] = count;
-        }
+        mass += a[q];
+        count += dc[q];
       }
-      __syncthreads();
-      if (wv == 0) {
-        const float m = (part_mass[0] + part_mass[1]) + (part_mass[2] + part_mass[3]);
-        const int c = (part_count[0] + part_count[1]) + (part_count[2] + part_count[3]);
-        const bool uniform = m == 0.f;  // no score mass: average over the original tokens
-        const float denom = uniform ? (float)c : m;
-        if ((grp >= 2) == uniform) {
-          Raw o_;
-          T* op = reinterpret_cast<T*>(&o_);
+    }
+  }
+  // (g0 + g1) + (g2 + g3): addition commutes, so every lane ends with the same bits
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) {
-            const int k = grp * EPL + e;
-            Elem<T>::store(op + e, ((part[0][k][gl] + part[1][k][gl]) + (part[2][k][gl] + part[3][k][gl])) / denom);
-          }
-          T* dst = (grp & 1) ? V_out : K_out;
-          *reinterpret_cast<Raw*>(dst + ((size_t)u * out_stride + slot) * D + gl * EPL) = o_;
-        }
-        if (out_mass && lane == 0) out_mass[(size_t)u * B + slot] = m;
-        if (out_count && lane == 0) out_count[(size_t)u * B + slot] = c;
-      }
-      __syncthreads();  // the next group's sums go to the same place
-    } else if (grp == 0) {
-      const bool uniform = mass == 0.f;  // no score mass: average over the original tokens
-      const float denom = uniform ? (float)count : mass;
-      Raw ok_, ov_;
-      T* okp = reinterpret_cast<T*>(&ok_);
-      T* ovp = reinterpret_cast<T*>(&ov_);
+  for (int o = 16; o <= 32; o <<= 1) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      ka[e] += __shfl_xor(ka[e], o, 64);
+      va[e] += __shfl_xor(va[e], o, 64);
+      ku[e] += __shfl_xor(ku[e], o, 64);
+      vu[e] += __shfl_xor(vu[e], o, 64);
+    }
+    mass += __shfl_xor(mass, o, 64);
+    count += __shfl_xor(count, o, 64);
+  }
+  if constexpr (ALL) {
+    // The waves' sums meet in LDS.  The first of the four adds them as (w0 + w1) + (w2 + w3), its 16-lane
+    // group q taking one of the four sums (score-weighted K, V, count-weighted K, V), and the two
+    // groups whose sums the result is made of write it.
+    if (grp == 0) {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
-        Elem<T>::store(okp + e, (uniform ? ku[e] : ka[e]) / denom);
-        Elem<T>::store(ovp + e, (uniform ? vu[e] : va[e]) / denom);
+        share->part[w4][e][gl] = ka[e];
+        share->part[w4][EPL + e][gl] = va[e];
+        share->part[w4][2 * EPL + e][gl] = ku[e];
+        share->part[w4][3 * EPL + e][gl] = vu[e];
       }
-      *reinterpret_cast<Raw*>(K_out + ((size_t)u * out_stride + slot) * D + gl * EPL) = ok_;
-      *reinterpret_cast<Raw*>(V_out + ((size_t)u * out_stride + slot) * D + gl * EPL) = ov_;
-      if (out_mass && gl == 0) out_mass[(size_t)u * B + slot] = mass;
-      if (out_count && gl == 0) out_count[(size_t)u * B + slot] = count;
+      if (gl == 0) {
+        share->mass[w4] = mass;
+        share->count[w4] = count;
+      }
     }
+    __syncthreads();
+    if (live && w4 == 0) {
+      const float m = (share->mass[0] + share->mass[1]) + (share->mass[2] + share->mass[3]);
+      const int c = (share->count[0] + share->count[1]) + (share->count[2] + share->count[3]);
+      const bool uniform = m == 0.f;  // no score mass: average over the original tokens
+      const float denom = uniform ? (float)c : m;
+      if ((grp >= 2) == uniform) {
+        Raw o_;
+        T* op = reinterpret_cast<T*>(&o_);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+          const int k = grp * EPL + e;
+          Elem<T>::store(op + e, ((share->part[0][k][gl] + share->part[1][k][gl]) + (share->part[2][k][gl] + share->part[3][k][gl])) / denom);
+        }
+        T* dst = (grp & 1) ? io.V_out : io.K_out;
+        *reinterpret_cast<Raw*>(dst + ((size_t)u * io.out_stride + slot) * D + gl * EPL) = o_;
+      }
+      if (io.out_mass && lane == 0) io.out_mass[(size_t)u * io.B + slot] = m;
+      if (io.out_count && lane == 0) io.out_count[(size_t)u * io.B + slot] = c;
+    }
+    __syncthreads();  // the next group's sums go to the same place
+  } else if (grp == 0) {
+    const bool uniform = mass == 0.f;  // no score mass: average over the original tokens
+    const float denom = uniform ? (float)count : mass;
+    Raw ok_, ov_;
+    T* okp = reinterpret_cast<T*>(&ok_);
+    T* ovp = reinterpret_cast<T*>(&ov_);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+      Elem<T>::store(okp + e, (uniform ? ku[e] : ka[e]) / denom);
+      Elem<T>::store(ovp + e, (uniform ? vu[e] : va[e]) / denom);
+    }
+    *reinterpret_cast<Raw*>(io.K_out + ((size_t)u * io.out_stride + slot) * D + gl * EPL) = ok_;
+    *reinterpret_cast<Raw*>(io.V_out + ((size_t)u * io.out_stride + slot) * D + gl * EPL) = ov_;
+    if (io.out_mass && gl == 0) io.out_mass[(size_t)u * io.B + slot] = mass;
+    if (io.out_count && gl == 0) io.out_count[(size_t)u * io.B + slot] = count;
+  }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void emit_kernel(
+    int n_units, int fold_per_unit, CASK_FOLD_ARGS(T), const int64_t* __restrict__ row_off, const int32_t* __restrict__ seed_rows,
+    const int32_t* __restrict__ n_seeds, const int32_t* __restrict__ slot_of,
+    const int32_t* __restrict__ seg_row, const int32_t* __restrict__ seg_start, const int32_t* __restrict__ n_merged) {
+  const FoldIo<T> io = {K, V, scores, in_count, K_out, V_out, out_mass, out_count, out_stride, B};
+  __shared__ int long_item[256][4];              // (unit, ordinal, segment bounds) of the long groups of a round
+  __shared__ int n_long;
+  __shared__ typename FoldLane<T, D>::Share share;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, grp = lane >> 4;
+  auto fold = [&](int u, int ord, int s0, int s1, auto all_c) {
+    constexpr bool kAll = decltype(all_c)::value;
+    const int64_t row0 = row_off[u];
+    const int32_t* seg = seg_row + row0;
+    const int srow = seed_rows[(size_t)u * B + ord], slot = slot_of[row0 + srow];
+    fold_group<T, D, kAll ? 16 : 4, kAll>(io, u, row0, srow, slot, s0, s1, kAll ? wv * 4 + grp : grp, wv, true,
+                                          [&](int k) { return seg[k]; }, &share);
   };
 
   // Work items are (unit, seed ordinal) pairs; each lane tests one item of a round
@@ -1217,25 +1248,24 @@ __global__ __launch_bounds__(256) void emit_kernel(
     while (todo != 0ull) {
       const int src_lane = __ffsll((long long)todo) - 1;
       todo &= todo - 1ull;
-      fold_group(__shfl(my_u, src_lane, 64), __shfl(my_ord, src_lane, 64), __shfl(my_s0, src_lane, 64),
-                 __shfl(my_s1, src_lane, 64), grp, std::integral_constant<int, 4>{}, std::false_type{});
+      fold(__shfl(my_u, src_lane, 64), __shfl(my_ord, src_lane, 64), __shfl(my_s0, src_lane, 64),
+           __shfl(my_s1, src_lane, 64), std::false_type{});
     }
     __syncthreads();
     const int nl = n_long;
     for (int i = 0; i < nl; ++i)
-      fold_group(long_item[i][0], long_item[i][1], long_item[i][2], long_item[i][3], wv * 4 + grp,
-                 std::integral_constant<int, 16>{}, std::true_type{});
+      fold(long_item[i][0], long_item[i][1], long_item[i][2], long_item[i][3], std::true_type{});
     __syncthreads();  // everyone has read the list's length before it is cleared
   }
 }
 
+#define CASK_FOLD_PASS(T)                                                                                            \
+  static_cast<const T*>(b.K), static_cast<const T*>(b.V), cj.scores, cj.in_count, reinterpret_cast<T*>(cj.K_out),     \
+      reinterpret_cast<T*>(cj.V_out), cj.out_mass, cj.out_count, cj.out_stride, kp.B
+
 template <typename T, int D>
-hipError_t launch_emit_t(const KParams& kp, const Batch& b, const float* scores,
-                         const int32_t* seed_rows, const int32_t* n_seeds,
-                         const int32_t* slot_of, const int32_t* seg_row,
-                         const int32_t* seg_start, const int32_t* n_merged, void* K_out,
-                         void* V_out, float* out_mass, const int32_t* in_count,
-                         int32_t* out_count, int out_stride, hipStream_t st) {
+hipError_t launch_emit_t(const KParams& kp, const Batch& b, const int32_t* seed_rows, const int32_t* n_seeds, const int32_t* slot_of,
+                         const int32_t* seg_row, const int32_t* seg_start, const int32_t* n_merged, const CopyJob& cj, hipStream_t st) {
   // (unit, seed ordinal) work items; a fold wave tests 64 of them per round
   const int fold_per_unit = plan_seed_bound(kp);
   const long long items = (long long)b.n_units * fold_per_unit;
@@ -1243,11 +1273,287 @@ hipError_t launch_emit_t(const KParams& kp, const Batch& b, const float* scores,
   if (fold_blocks > 2048) fold_blocks = 2048;  // ... up to 8192 waves
   if (fold_blocks == 0) return hipSuccess;
   emit_kernel<T, D><<<dim3((unsigned)fold_blocks), dim3(256), 0, st>>>(
-      kp, b.n_units, fold_per_unit, b.row_off, static_cast<const T*>(b.K),
-      static_cast<const T*>(b.V), scores, seed_rows, n_seeds, slot_of, seg_row, seg_start,
-      n_merged, static_cast<T*>(K_out), static_cast<T*>(V_out), out_mass, in_count, out_count,
-      out_stride);
+      b.n_units, fold_per_unit, CASK_FOLD_PASS(T), b.row_off, seed_rows, n_seeds, slot_of, seg_row, seg_start, n_merged);
   return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ grouping and fold in one launch
+
+constexpr int kFoldThreads = 512;
+constexpr int kFoldWaves = kFoldThreads / 64;
+constexpr int kFoldTeams = kFoldWaves / 4;   // four waves fold a long group together
+constexpr int kFoldSeeds = 1024;             // most seeds of a unit (rule at launch_group_fold)
+constexpr int kFoldList = 1024;              // donors that wait in LDS
+constexpr int kFoldAhead = 16;               // rows of a thread in flight
+
+// Grouping, fold and copy of an event in one launch.  `shares` workgroups (a power of two) take a unit
+// together without a word between them: each reads the donors' assignments of the whole unit and keeps
+// those of its own seeds, ordinals congruent to its number.  What is read several times comes from L2;
+// what is saved is a launch and the trips through memory that carried the groups to it.
+// A workgroup's donors usually fit a list in LDS (ascending rows, seeds of at most kWaveFoldMax donors):
+// a wave takes a seed, picks its rows out of the list by ballots and folds them.  Otherwise the list goes to
+// memory and is split by seed there, stably: a histogram per wave gives every (wave, seed) pair its
+// first place, and a wave walks its run 64 entries at a time; four waves together fold a long group.
+// Either way a seed's donors are summed in the order and the tree of fold_group: the same bits.
+// A seed without donors is copied as it is; the copying workgroups leave the seeds out.
+// Bound: a chain of about five trips to memory.  Against the two launches (grouping and copy, fold): 112 units of
+// 8448 rows 23.2 -> 18.5 us, 8 of 3000 11.8 -> 8.8, 128 of 5378 (d = 64) 15.8 -> 13.6; every donor folding, the
+// event on 8 x 3000 rows 79.8 -> 72.6 us.  With the workgroups anywhere on the chip: 19.9, 10.1, 14.7.
+template <typename T, int D>
+__global__ __launch_bounds__(kFoldThreads, 2) void group_fold_kernel(
+    KParams kp, CASK_FOLD_ARGS(T), int n_units, int n_fold, int shares, int seeds, CopyJob cj, const int64_t* __restrict__ row_off,
+    const int32_t* __restrict__ prefix_len, const int32_t* __restrict__ assign_ord, const int32_t* __restrict__ slot_of,
+    const int32_t* __restrict__ seed_rows, const int32_t* __restrict__ n_seeds, int32_t* merged_row, int32_t* merged_ord,
+    int32_t* seg_row, int32_t* __restrict__ assign_out, int32_t* __restrict__ status) {
+  using FL = FoldLane<T, D>;
+  const FoldIo<T> io = {K, V, scores, in_count, K_out, V_out, out_mass, out_count, out_stride, B};
+  // [seeds]: rows, slots, donors per seed, where a group starts, seeds with long groups; behind them
+  // kFoldWaves cursors a seed, or the list in LDS
+  extern __shared__ __attribute__((aligned(16))) int fold_mem[];
+  __shared__ int wave_tot[3][kFoldWaves];
+  __shared__ int n_long, longest;
+  __shared__ union {
+    typename FL::Share share[kFoldTeams];
+    int rows[kFoldWaves][kWaveFoldMax];                    // the rows of the seed a wave folds
+  } sh;
+  int *const seed_row_l = fold_mem, *const slot_l = fold_mem + seeds, *const cnt_l = slot_l + seeds, *const start_l = cnt_l + seeds;
+  int *const long_l = start_l + seeds, *const cursor = long_l + seeds;
+  int* const list_row = cursor;
+  int* const list_ord = cursor + kFoldList;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // (both kinds of workgroup run where their unit's selection and similarity did: what those wrote is in that L2)
+  int u, f;
+  if ((int)blockIdx.x >= n_fold) {
+    const int wgs = (kp.B + kFoldWaves * kCopySlots - 1) / (kFoldWaves * kCopySlots);
+    if (!map_block(n_units, wgs, u, f, (int)blockIdx.x - n_fold)) return;
+    const int first = (f * kFoldWaves + wv) * kCopySlots;
+    if (cj.lane_bytes == 16) copy_kept_rows<u32x4, 1, true>(cj, kp.B, row_off, u, first, lane);
+    else if (cj.lane_bytes == 32) copy_kept_rows<u32x4, 2, true>(cj, kp.B, row_off, u, first, lane);
+    else copy_kept_rows<u32x2, 1, true>(cj, kp.B, row_off, u, first, lane);
+    return;
+  }
+  if (!map_block(n_units, shares, u, f)) return;
+  const int lg = 31 - __clz(shares);
+  const int64_t row0 = row_off[u];
+  const int N = (int)(row_off[u + 1] - row0);
+  const int P = prefix_len[u];
+  const UnitPlan pl = make_plan(kp, P, N);
+  const int hi = N - pl.r_eff;
+  const int M = n_seeds[u], mine_n = M > f ? (M - f + shares - 1) >> lg : 0;  // own seeds: ordinals f, f + shares, ...
+  const int32_t* ord_u = assign_ord + row0;
+
+  const int first_row = P + wv * (64 * kFoldAhead) + lane;  // the thread's rows: 64 apart (the host checked that they cover the unit)
+  int ord[kFoldAhead];
+#pragma unroll
+  for (int e = 0; e < kFoldAhead; ++e) ord[e] = first_row + e * 64 < hi ? ord_u[first_row + e * 64] : -1;  // (>= 0: a donor that folds)
+  for (int l = tid; l < mine_n; l += kFoldThreads) {
+    const int r = seed_rows[(size_t)u * kp.B + (l << lg) + f];
+    seed_row_l[l] = r;
+    slot_l[l] = slot_of[row0 + r];
+    cnt_l[l] = 0;
+  }
+  if (tid == 0) n_long = longest = 0;
+
+  // ---- the unit's donors: all that fold, those of the shares before this one (their entries come first in
+  // the lists in memory), and this share's own
+  const unsigned long long below = (1ull << lane) - 1ull;
+  auto is_own = [&](int o) { return o >= 0 && (o & (shares - 1)) == f; };
+  int all = 0, before = 0, own = 0, own_before = 0;
+  int pos[kFoldAhead];
+  {
+    int a = 0, b = 0, c = 0;
+#pragma unroll
+    for (int e = 0; e < kFoldAhead; ++e) {
+      const unsigned long long m = __ballot(is_own(ord[e]));
+      pos[e] = c + __popcll(m & below);
+      c += __popcll(m);
+      a += __popcll(__ballot(ord[e] >= 0));
+      b += __popcll(__ballot(ord[e] >= 0 && (ord[e] & (shares - 1)) < f));
+      asm volatile("" : "+v"(pos[e]), "+v"(ord[e]));  // (final here: no ballots held across the barrier)
+    }
+    if (lane == 0) {
+      wave_tot[0][wv] = a;
+      wave_tot[1][wv] = b;
+      wave_tot[2][wv] = c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kFoldWaves; ++w) {
+      all += wave_tot[0][w];
+      before += wave_tot[1][w];
+      own_before += w < wv ? wave_tot[2][w] : 0;
+      own += wave_tot[2][w];
+    }
+  }
+  if (f == 0 && tid == 0 && status && all == 0 && !(pl.status & (CASK_ST_IDENTITY | CASK_ST_PREFIX_BUDGET_EXHAUSTED)))
+    status[u] = pl.status | CASK_ST_MERGE_INACTIVE;
+  if (mine_n == 0) return;  // (the same in every thread)
+
+  // ---- the share's list, ascending rows
+  int32_t* const mrow = merged_row + row0 + before;
+  int32_t* const mord = merged_ord + row0 + before;
+  const bool in_lds = own <= kFoldList;
+#pragma unroll
+  for (int e = 0; e < kFoldAhead; ++e) {
+    asm volatile("" : "+v"(ord[e]));
+    if (!is_own(ord[e])) continue;
+    const int i = first_row + e * 64, at = own_before + pos[e], l = ord[e] >> lg;
+    if (in_lds) {
+      list_row[at] = i;
+      list_ord[at] = l;
+    } else {
+      mrow[at] = i;
+      mord[at] = l;
+    }
+    atomicAdd(&cnt_l[l], 1);
+  }
+  __syncthreads();
+  if (own > kWaveFoldMax) {
+    for (int l = tid; l < mine_n; l += kFoldThreads)
+      if (cnt_l[l] > kWaveFoldMax) atomicMax(&longest, cnt_l[l]);
+    __syncthreads();
+  }
+  // What is left to do behind the folds (its stores would be waited for at their barriers): the donors'
+  // assignments, and the seeds without donors, which pass through, sixteen lanes a row.
+  auto rest = [&]() {
+#pragma unroll
+    for (int e = 0; e < kFoldAhead; ++e) {
+      asm volatile("" : "+v"(ord[e]));
+      if (assign_out && is_own(ord[e])) assign_out[row0 + first_row + e * 64] = slot_l[ord[e] >> lg];
+    }
+    const int gl = lane & 15;
+    for (int l = tid >> 4; l < mine_n; l += kFoldThreads / 16) {
+      if (cnt_l[l] != 0) continue;
+      const int64_t row = row0 + seed_row_l[l];
+      const int slot = slot_l[l];
+      const size_t from = (size_t)row * D + gl * FL::EPL, to = ((size_t)u * io.out_stride + slot) * D + gl * FL::EPL;
+      const typename FL::Words k = *reinterpret_cast<const typename FL::Words*>(io.K + from);
+      const typename FL::Words v = *reinterpret_cast<const typename FL::Words*>(io.V + from);
+      *reinterpret_cast<typename FL::Words*>(io.K_out + to) = k;
+      *reinterpret_cast<typename FL::Words*>(io.V_out + to) = v;
+      if (gl == 0 && io.out_mass) io.out_mass[(size_t)u * io.B + slot] = io.scores[row];
+      if (gl == 0 && io.out_count) io.out_count[(size_t)u * io.B + slot] = io.in_count ? io.in_count[row] : 1;
+    }
+  };
+  if (own == 0) {
+    rest();
+    return;
+  }
+  auto fold_by_wave = [&](int l, int s0, int s1, auto row_at) {
+    fold_group<T, D, 4, false>(io, u, row0, seed_row_l[l], slot_l[l], s0, s1, lane >> 4, 0, true, row_at, nullptr);
+  };
+  if (in_lds && longest == 0) {
+    for (int l = wv; l < mine_n; l += kFoldWaves) {
+      const int n = cnt_l[l];
+      if (n == 0) continue;
+      int have = 0;
+      for (int k = 0; k < own && have < n; k += 64) {
+        const bool m = k + lane < own && list_ord[k + lane] == l;
+        const unsigned long long b = __ballot(m);
+        if (m) sh.rows[wv][have + __popcll(b & ((1ull << lane) - 1ull))] = list_row[k + lane];
+        have += __popcll(b);
+      }
+      asm volatile("" ::: "memory");  // (the wave's own LDS accesses stay in order)
+      fold_by_wave(l, 0, n, [&](int k) { return sh.rows[wv][k]; });
+      asm volatile("" ::: "memory");
+    }
+    rest();
+    return;
+  }
+
+  // ---- a long list, or a seed with many donors: split by seed in memory
+  int32_t* const seg = seg_row + row0 + before;
+  if (in_lds) {  // (the cursors take the list's place)
+    int r[kFoldList / kFoldThreads], o[kFoldList / kFoldThreads];
+#pragma unroll
+    for (int q = 0; q < kFoldList / kFoldThreads; ++q) {
+      const int k = q * kFoldThreads + tid;
+      r[q] = k < own ? list_row[k] : 0;
+      o[q] = k < own ? list_ord[k] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kFoldList / kFoldThreads; ++q) {
+      const int k = q * kFoldThreads + tid;
+      if (k < own) {
+        mrow[k] = r[q];
+        mord[k] = o[q];
+      }
+    }
+    __syncthreads();
+  }
+  for (int k = tid; k < kFoldWaves * seeds; k += kFoldThreads) cursor[k] = 0;
+  __syncthreads();  // (also: the list in memory is read by other threads below)
+  const int run = (own + kFoldThreads - 1) / kFoldThreads * 64;
+  const int c0 = min(own, wv * run), c1 = min(own, c0 + run);
+  int* const my_cursor = cursor + wv * seeds;
+  for (int k = c0 + lane; k < c1; k += 64) atomicAdd(&my_cursor[mord[k]], 1);
+  if (wv == 0) {  // starts of the groups
+    int carry = 0;
+    for (int l0 = 0; l0 < mine_n; l0 += 64) {
+      const int v = l0 + lane < mine_n ? cnt_l[l0 + lane] : 0;
+      int incl = v;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+      }
+      if (l0 + lane < mine_n) start_l[l0 + lane] = carry + incl - v;
+      carry += __shfl(incl, 63, 64);
+    }
+  }
+  __syncthreads();
+  for (int l = tid; l < mine_n; l += kFoldThreads) {
+    int at = start_l[l];
+    for (int w = 0; w < kFoldWaves; ++w) {
+      const int t = cursor[w * seeds + l];
+      cursor[w * seeds + l] = at;
+      at += t;
+    }
+    if (cnt_l[l] > kWaveFoldMax) long_l[atomicAdd(&n_long, 1)] = l;  // (their order does not reach the results)
+  }
+  __syncthreads();
+  int nbits = 1;
+  while ((1 << nbits) < mine_n) ++nbits;
+  constexpr int kAhead = 4;  // 64-entry steps whose loads are in flight together
+  for (int i0 = c0; i0 < c1; i0 += 64 * kAhead) {
+    int os[kAhead], rs[kAhead];
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) {
+      const int idx = min(i0 + e * 64 + lane, c1 - 1);  // clamped: no branch around the loads
+      os[e] = mord[idx];
+      rs[e] = mrow[idx];
+    }
+#pragma unroll
+    for (int e = 0; e < kAhead; ++e) {
+      const bool valid = i0 + e * 64 + lane < c1;
+      unsigned long long same = __ballot(valid);
+      for (int bit = 0; bit < nbits; ++bit) {
+        const bool one = ((os[e] >> bit) & 1) != 0;
+        const unsigned long long ones = __ballot(valid && one);
+        same &= one ? ones : ~ones;
+      }
+      if (valid) {  // `same`: the valid lanes with this lane's seed
+        const int rank = __popcll(same & ((1ull << lane) - 1ull));
+        const int cur = my_cursor[os[e]];
+        seg[cur + rank] = rs[e];
+        if (rank == __popcll(same) - 1) my_cursor[os[e]] = cur + rank + 1;  // (after every lane's read)
+      }
+    }
+  }
+  __syncthreads();  // the groups in memory are read by other threads below
+  for (int l = wv; l < mine_n; l += kFoldWaves)
+    if (cnt_l[l] > 0 && cnt_l[l] <= kWaveFoldMax) fold_by_wave(l, start_l[l], start_l[l] + cnt_l[l], [&](int k) { return seg[k]; });
+  __syncthreads();
+  const int nl = n_long, team = wv >> 2, w4 = wv & 3;
+  for (int k0 = 0; k0 < nl; k0 += kFoldTeams) {
+    const bool live = k0 + team < nl;
+    const int l = long_l[live ? k0 + team : k0];
+    const int s0 = start_l[l], s1 = live ? s0 + cnt_l[l] : s0;
+    fold_group<T, D, 16, true>(io, u, row0, seed_row_l[l], slot_l[l], s0, s1, w4 * 4 + (lane >> 4), w4, live,
+                               [&](int k) { return seg[k]; }, &sh.share[team]);
+  }
+  rest();
 }
 
 // ------------------------------------------------------------------ dispersion and lost mass
@@ -1459,7 +1765,7 @@ hipError_t launch_gather_merged(const KParams& kp, const Batch& b,
     cj = *copy;
     cj.n_units = b.n_units;
     cj.lane_bytes = kp.d * (kp.dtype == CASK_F32 ? 4 : 2) / 16;
-    const long long waves = (long long)b.n_units * ((kp.B + 4 * kCopyRounds - 1) / (4 * kCopyRounds));
+    const long long waves = (long long)b.n_units * ((kp.B + kCopySlots - 1) / kCopySlots);
     copy_blocks = (waves + kGatherThreads / 64 - 1) / (kGatherThreads / 64);
     if (b.n_units + copy_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
   }
@@ -1490,18 +1796,52 @@ hipError_t launch_group_diag(const KParams& kp, const Batch& b, const float* sco
   return hipGetLastError();
 }
 
-hipError_t launch_emit(const KParams& kp, const Batch& b, const float* scores,
-                       const int32_t* seed_rows, const int32_t* n_seeds, const int32_t* slot_of,
-                       const int32_t* seg_row, const int32_t* seg_start,
-                       const int32_t* n_merged, void* K_out, void* V_out, float* out_mass,
-                       const int32_t* in_count, int32_t* out_count, int out_stride,
-                       hipStream_t st) {
-#define CASK_EMIT(T, D)                                                                     \
-  launch_emit_t<T, D>(kp, b, scores, seed_rows, n_seeds, slot_of, seg_row, seg_start, n_merged, \
-                      K_out, V_out, out_mass, in_count, out_count, out_stride, st)
+hipError_t launch_emit(const KParams& kp, const Batch& b, const int32_t* seed_rows, const int32_t* n_seeds,
+                       const int32_t* slot_of, const int32_t* seg_row, const int32_t* seg_start,
+                       const int32_t* n_merged, const CopyJob& cj, hipStream_t st) {
+#define CASK_EMIT(T, D) launch_emit_t<T, D>(kp, b, seed_rows, n_seeds, slot_of, seg_row, seg_start, n_merged, cj, st)
   if (kp.dtype == CASK_F32) return kp.d == 64 ? CASK_EMIT(float, 64) : CASK_EMIT(float, 128);
   return kp.d == 64 ? CASK_EMIT(uint16_t, 64) : CASK_EMIT(uint16_t, 128);
 #undef CASK_EMIT
+}
+
+// A workgroup reads a whole unit's assignments: one chunk of them (8192 rows) is one trip to memory, two
+// would be four, counted and then listed (event on 112 units of 33 024 rows 0.5 % slower than in two launches).
+// Beyond 256 units the two launches fill the chip by themselves: one share a unit is 2 % faster on 600 units of
+// 2000 rows but 3 % slower where every donor folds, two shares are up to 3 % slower.
+bool group_fold_fits(const KParams& kp, const Batch& b) {
+  return b.n_units <= 256 && plan_seed_bound(kp) <= kFoldSeeds && b.max_decode_len <= kFoldThreads * kFoldAhead;
+}
+
+hipError_t launch_group_fold(const KParams& kp, const Batch& b, const uint8_t* role, const int32_t* assign_ord,
+                             const int32_t* slot_of, const int32_t* seed_rows, const int32_t* n_seeds, int32_t* merged_row,
+                             int32_t* merged_ord, int32_t* seg_row, int32_t* assign_out, int32_t* status, const CopyJob& copy,
+                             hipStream_t st) {
+  if (!group_fold_fits(kp, b)) return hipErrorInvalidValue;
+  int shares = 2;  // of a unit: about two workgroups to a compute unit in all, two to eight
+  while (shares < 8 && (long long)b.n_units * shares * 2 <= 512) shares *= 2;
+  CopyJob cj = copy;
+  cj.role = role;
+  cj.lane_bytes = kp.d * (kp.dtype == CASK_F32 ? 4 : 2) / 16;
+  const int wgs = (kp.B + kFoldWaves * kCopySlots - 1) / (kFoldWaves * kCopySlots);  // a unit's copying workgroups
+  if ((long long)b.n_units * (wgs + shares) + 16 > 0x7fffffffLL) return hipErrorInvalidValue;
+  const int folds = mapped_blocks(b.n_units, shares), blocks = folds + mapped_blocks(b.n_units, wgs);
+  const int seeds = (plan_seed_bound(kp) + shares - 1) / shares;  // of a share
+  const size_t lds = ((size_t)5 * seeds + (kFoldWaves * seeds > 2 * kFoldList ? kFoldWaves * seeds : 2 * kFoldList)) * sizeof(int);
+  auto go = [&](auto t, auto d) {
+    using T = decltype(t);
+    static LdsLimitOnce lim;
+    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&group_fold_kernel<T, decltype(d)::value>), 80 * 1024);
+    if (e != hipSuccess) return e;
+    group_fold_kernel<T, decltype(d)::value><<<dim3((unsigned)blocks), dim3(kFoldThreads), lds, st>>>(
+        kp, CASK_FOLD_PASS(T), b.n_units, (int)folds, shares, seeds, cj, b.row_off, b.prefix_len, assign_ord, slot_of, seed_rows, n_seeds,
+        merged_row, merged_ord, seg_row, assign_out, status);
+    return hipGetLastError();
+  };
+  const std::integral_constant<int, 64> d64;
+  const std::integral_constant<int, 128> d128;
+  if (kp.dtype == CASK_F32) return kp.d == 64 ? go(float(), d64) : go(float(), d128);
+  return kp.d == 64 ? go(uint16_t(), d64) : go(uint16_t(), d128);
 }
 
 }  // namespace cask

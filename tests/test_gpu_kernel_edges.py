@@ -489,3 +489,20 @@ def test_dedup_walk_with_every_row_in_lds(budget, h, d, prefix, rows):
     else:
         pytest.fail("no clear threshold for this cache")
     _note(budget, h, d, parity.full_check(c, p))
+
+
+@pytest.mark.parametrize("units,N,P,budget,tau,dtype,d", [(3, 8292, 100, 160, -1.0, "bf16", 128), (3, 8293, 100, 160, -1.0, "bf16", 128),
+                                                          (131, 1200, 0, 90, 0.2, "bf16", 64), (70, 1100, 60, 130, -1.0, "f32", 64),
+                                                          (2, 3000, 2000, 700, -1.0, "f32", 128), (5, 1500, 0, 65, -1.0, "bf16", 128)])
+def test_grouping_and_fold_in_one_launch(units, N, P, budget, tau, dtype, d):
+    """Whole events where every donor, or most, fold: two to eight workgroups a unit, lists in LDS and in memory
+    (a share's 1024 donors), groups folded by one wave and by four, a decode trace that just fills a
+    workgroup's rows (8192) and one row more (two launches), a single seed; against the oracle."""
+    Wn = 32
+    kw = dict(head_dim=d, q_per_kv=1, window=Wn, cluster_frac=0.5)
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=units, prefix=P, decode=N - P, budget=budget, **kw)
+    c = caches.make(w, seed=units + N)
+    if dtype == "f32":
+        c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=budget, sim_threshold=tau)
+    _note(units, N, budget, parity.full_check(c, p, expect_folds=True))
