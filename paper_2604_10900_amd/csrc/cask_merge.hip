@@ -592,6 +592,18 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
 // chunk (by summed weight) first, and a wave leaves a seed as soon as no lane's partial sum can
 // still win (<= theta and < its best so far).  Lanes that finish hold the full sum in the same
 // order as without the early exit, so the result does not depend on it.
+//
+// The vector pipes bound that: seven issue slots a band, at least eight bands for every seed and wave.
+// Few pairs can win, and most of the others are told by the matrix cores first: a sum of non-negative
+// terms is at least their Euclidean norm, d >= |W (k_i - k_j)|_2 (W: each channel times its band's
+// weight), whose square is |W k_i|^2 + |W k_j|^2 - 2 <W k_i, W k_j>.  The product comes from W k rounded
+// to bf16: off by at most 2^-8 + 2^-18 of |W k_i| |W k_j|, twice that is at most 2^-8 + 2^-18 of the sum of
+// the squares, and kScreen covers it with the fp32 roundings.  A seed is left out for a donor only
+// where the bound is above theta; what is not finite, or out of the range where that holds, is never
+// left out.  The distances that remain are the ones above, seeds in ascending order: the same bits.
+// (112 units x 4352 rows, 128 channels, a threshold at the planted near-duplicates: 69 -> 48 us;
+// 112 x 8448 with 333 seeds 1120 -> 415.  Where every pair survives the screen costs 0 - 12 %.)
+constexpr float kScreen = 0.0042f;
 template <typename T>
 __device__ inline void load8(const T* p, float* out);
 template <>
@@ -613,7 +625,7 @@ __device__ inline void load8<uint16_t>(const uint16_t* p, float* out) {
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(256) void similarity_kappa_kernel(
+__global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
     KParams kp, int n_units, int tiles_per_unit, const int64_t* __restrict__ row_off,
     const int32_t* __restrict__ prefix_len, const T* __restrict__ K,
     const uint8_t* __restrict__ role, const int32_t* __restrict__ seed_rows,
@@ -621,13 +633,18 @@ __global__ __launch_bounds__(256) void similarity_kappa_kernel(
   constexpr int SEEDS = 32;
   constexpr int H = D / 2;
   constexpr int NCH = H / 8;  // chunks of eight bands
-  __shared__ __attribute__((aligned(16))) float sk[SEEDS][D];
+  constexpr int NK = D / 16;  // k-steps of a product tile
+  constexpr int PIECES = D / 8;
+  __shared__ __attribute__((aligned(16))) float sk[SEEDS][D + 4];  // (lanes read different rows: on other banks)
+  __shared__ bf16x8 sw[PIECES * SEEDS];  // W k of the seeds: piece p of seed s at p * SEEDS + s
+  __shared__ __attribute__((aligned(16))) float sc[SEEDS];  // the seeds' half of the screen's bar
   __shared__ __attribute__((aligned(16))) float wband[H];
   __shared__ int spos[SEEDS];
   __shared__ uint32_t chunk_order;  // four bits per position: which chunk is summed there
-  const int bid = blockIdx.x;
-  const int u = bid / tiles_per_unit, tile = bid % tiles_per_unit;
-  if (u >= n_units) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const float band = kp.band_w[tid % H];  // (this load and those below without a branch: all under way at once)
+  int u, tile;
+  if (!map_block(n_units, tiles_per_unit, u, tile)) return;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];
@@ -636,51 +653,136 @@ __global__ __launch_bounds__(256) void similarity_kappa_kernel(
   const int base = P + tile * 256;
   if (base >= hi) return;
   const int M = n_seeds[u];
-  const int tid = threadIdx.x;
+  const int c32 = lane & 31, h = lane >> 5;
   const int i = base + tid;
   const bool ok = i < hi;
   const T* Ku = K + (size_t)row0 * D;
   const int32_t* srow = seed_rows + (size_t)u * kp.B;
-  if (tid < H) wband[tid] = kp.band_w[tid];
+  const uint8_t own_role = role[row0 + min(i, hi - 1)];
+  if (tid < H) wband[tid] = band;
   __syncthreads();
-  if (tid == 0) {
-    float cw[NCH];
-    for (int c = 0; c < NCH; ++c) {
-      cw[c] = 0.f;
-      for (int f = 0; f < 8; ++f) cw[c] += wband[c * 8 + f];
+  if (tid < 64) {
+    float cw = 0.f;
+    for (int f = 0; f < 8; ++f) cw += wband[(lane % NCH) * 8 + f];
+    int r = 0;  // rank = chunks that come before this lane's
+    for (int e = 0; e < NCH; ++e) {
+      const float ce = __shfl(cw, e, 64);
+      r += (int)(ce > cw) | ((int)(ce == cw) & (int)(e < lane % NCH));
     }
-    uint32_t packed = 0;
-    for (int c = 0; c < NCH; ++c) {  // rank = chunks that come before c
-      int r = 0;
-      for (int e = 0; e < NCH; ++e) r += (cw[e] > cw[c]) || (cw[e] == cw[c] && e < c);
-      packed |= (uint32_t)c << (4 * r);
-    }
-    chunk_order = packed;
-  }
-  __syncthreads();
-  const uint32_t order = __builtin_amdgcn_readfirstlane(chunk_order);
-  const bool donor = ok && role[row0 + i] == CASK_ROLE_DONOR;
-  float k[D];
+    uint32_t packed = (uint32_t)(lane % NCH) << (4 * r);
 #pragma unroll
-  for (int c = 0; c < D; c += 8) load8<T>(Ku + (size_t)(ok ? i : P) * D + c, k + c);
+    for (int m = 1; m < NCH; m *= 2) packed |= (uint32_t)__shfl_xor((int)packed, m, 64);
+    if (tid == 0) chunk_order = packed;
+  }
+  const bool donor = ok && own_role == CASK_ROLE_DONOR;
+  const uint64_t donors = __builtin_amdgcn_ballot_w64(donor);
+
+  const float bar = kp.theta * kp.theta * 1.002f;
+  auto usable = [](float n2) { return n2 > 1e-26f && n2 < 1e36f; };  // (false for NaN)
   float best = __builtin_inff();
   int best_ord = -1;
   for (int s0 = 0; s0 < M; s0 += SEEDS) {
-    __syncthreads();
-    for (int q = tid; q < SEEDS * D / 8; q += 256) {
-      const int sr = q / (D / 8), c = (q % (D / 8)) * 8;
-      float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      if (s0 + sr < M) load8<T>(Ku + (size_t)srow[s0 + sr] * D + c, v);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) sk[sr][c + e] = v[e];
-    }
-    if (tid < SEEDS) spos[tid] = (s0 + tid < M) ? srow[s0 + tid] : 0;
-    __syncthreads();
     const int lim = min(SEEDS, M - s0);
-    for (int sr = 0; sr < lim; ++sr) {
-      const int gap = spos[sr] > i ? spos[sr] - i : i - spos[sr];
-      const bool in_reach = donor && (kp.radius <= 0 || gap <= kp.radius);
-      if (__builtin_amdgcn_ballot_w64(in_reach) == 0) continue;
+    float seed[SEEDS * PIECES / 256][8];  // this thread's pieces of the seeds: under way while the rows come in
+#pragma unroll
+    for (int j = 0; j < SEEDS * PIECES / 256; ++j) {
+      const int q = j * 256 + tid, sr = q / PIECES, c = (q % PIECES) * 8;
+      load8<T>(Ku + (size_t)srow[s0 + min(sr, lim - 1)] * D + c, seed[j]);  // (places past the last seed: masked below)
+    }
+    const int seed_at = srow[s0 + min(tid, lim - 1)];
+    // W k of the wave's 64 rows as two operand tiles (lane (c32, h): row c32, channels 16 ks + 8 h ...), and
+    // each row's half of the bar: a pair is left out where its product < kc + sc.  (Again for each block
+    // of seeds: kept beside the rows below they do not fit the registers of two waves.)
+    bf16x8 wk[2][NK];
+    float kc[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      int at = min(base + (tid & ~63) + t * 32 + c32, hi - 1);
+      asm volatile("" : "+v"(at));  // (else all of this is taken out of the loop)
+      const T* row = Ku + (size_t)at * D;
+      float n2 = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < NK; ++ks) {
+        float v[8];
+        load8<T>(row + ks * 16 + h * 8, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = v[e] * wband[(ks * 16 + h * 8) % H + e];
+          n2 = __builtin_fmaf(x, x, n2);
+          wk[t][ks][e] = (__bf16)x;
+        }
+      }
+      n2 += __shfl_xor(n2, 32, 64);
+      kc[t] = usable(n2) ? 0.5f * (n2 * (1.f - kScreen) - bar) : kNegInf;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < SEEDS * PIECES / 256; ++j) {
+      const int q = j * 256 + tid, sr = q / PIECES, c = (q % PIECES) * 8;
+      const float(&v)[8] = seed[j];
+      float n2 = 0.f;
+      bf16x8 x8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        sk[sr][c + e] = v[e];
+        const float x = v[e] * wband[c % H + e];
+        n2 = __builtin_fmaf(x, x, n2);
+        x8[e] = (__bf16)x;
+      }
+      sw[(q % PIECES) * SEEDS + sr] = x8;
+#pragma unroll
+      for (int m = 1; m < PIECES; m *= 2) n2 += __shfl_xor(n2, m, 64);  // a row's pieces: neighbouring lanes
+      if (c == 0) sc[sr] = usable(n2) ? 0.5f * n2 * (1.f - kScreen) : kNegInf;
+    }
+    if (tid < SEEDS) spos[tid] = seed_at;
+    __syncthreads();
+    if (donors == 0) continue;
+
+    // ---- screen: 32 seeds against the wave's 64 rows.  A lane owns one row of a tile and the seeds
+    // 8 (r / 4) + 4 h + r % 4: the ballot of register r holds seed s of 32 rows in its lower half and
+    // seed s + 4 in its upper.
+    f32x16 acc0 = f32x16{0}, acc1 = f32x16{0};
+#pragma unroll
+    for (int ks = 0; ks < NK; ++ks) {
+      const bf16x8 a = sw[(2 * ks + h) * SEEDS + c32];
+      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[0][ks], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[1][ks], acc1, 0, 0, 0);
+    }
+    const uint64_t d0 = (donors & 0xffffffffull) * 0x100000001ull, d1 = (donors >> 32) * 0x100000001ull;
+    uint32_t mine = 0;  // seeds left for this lane's row
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int s = (r >> 2) * 8 + (r & 3);
+      const float bs = sc[s + h * 4];
+      const uint64_t m0 = __builtin_amdgcn_ballot_w64(!(acc0[r] < kc[0] + bs)) & d0;
+      const uint64_t m1 = __builtin_amdgcn_ballot_w64(!(acc1[r] < kc[1] + bs)) & d1;
+      if ((m0 | m1) != 0) {
+        const uint64_t own = (h ? m1 : m0) >> c32;
+        mine |= (uint32_t)(own & 1u) << s | (uint32_t)((own >> 32) & 1u) << (s + 4);
+      }
+    }
+    if (lim < SEEDS) mine &= (1u << lim) - 1u;
+    auto skip_far = [&]() {  // to the lane's next seed within the radius
+      if (kp.radius <= 0) return;
+      while (mine != 0) {
+        const int at = spos[__builtin_ctz(mine)];
+        if ((at > i ? at - i : i - at) <= kp.radius) break;
+        mine &= mine - 1;
+      }
+    };
+    skip_far();
+    if (__builtin_amdgcn_ballot_w64(mine != 0) == 0) continue;
+
+    // ---- the pairs that are left: every lane takes its own next seed, in ascending order
+    int from = mine != 0 ? i : P;  // (a row costs its cache lines again with every piece: lanes without a pair share one)
+    asm volatile("" : "+v"(from));  // (else the loads are taken out of the loop and spilled)
+    float k[D];
+#pragma unroll
+    for (int c = 0; c < D; c += 8) load8<T>(Ku + (size_t)from * D + c, k + c);
+    for (; __builtin_amdgcn_ballot_w64(mine != 0) != 0; mine &= mine - 1, skip_far()) {
+      const bool in_reach = mine != 0;
+      const int sr = in_reach ? __builtin_ctz(mine) : 0;
+      const uint32_t order = __builtin_amdgcn_readfirstlane(chunk_order);
       float dist = 0.f;
       bool finished = true;
       for (int ci = 0; ci < NCH; ++ci) {
@@ -726,7 +828,7 @@ hipError_t launch_similarity_kappa(const KParams& kp, const Batch& b, const uint
                                    int32_t* assign_ord, hipStream_t st) {
   const int tiles = (b.max_decode_len + 255) / 256;
   if (tiles == 0) return hipSuccess;
-  similarity_kappa_kernel<T, D><<<dim3(b.n_units * tiles), dim3(256), 0, st>>>(
+  similarity_kappa_kernel<T, D><<<dim3(mapped_blocks(b.n_units, tiles)), dim3(256), 0, st>>>(
       kp, b.n_units, tiles, b.row_off, b.prefix_len, static_cast<const T*>(b.K), role, seed_rows,
       n_seeds, assign_ord);
   return hipGetLastError();

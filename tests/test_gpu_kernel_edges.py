@@ -506,3 +506,32 @@ def test_grouping_and_fold_in_one_launch(units, N, P, budget, tau, dtype, d):
         c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
     p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=budget, sim_threshold=tau)
     _note(units, N, budget, parity.full_check(c, p, expect_folds=True))
+
+
+@pytest.mark.parametrize("units,N,P,budget,dtype,d,radius,scale", [(3, 700, 40, 230, "bf16", 128, 0, 1.0), (2, 289, 1, 120, "bf16", 128, 90, 1.0),
+                                                                    (9, 1100, 300, 380, "bf16", 64, 0, 1.0), (2, 600, 20, 320, "f32", 128, 100, 1.0),
+                                                                    (2, 500, 0, 200, "f32", 64, 0, 1e16), (2, 500, 0, 200, "f32", 128, 0, 1e-14),
+                                                                    (1, 500, 0, 200, "bf16", 128, 0, 1e17)])
+def test_band_distance_screen(units, N, P, budget, dtype, d, radius, scale):
+    """Kappa geometry with thresholds among the nearest distances (no donor folds, some, most, all), so that
+    the screen decides on pairs near the bar: blocks of 32 seeds and remainders, last tiles of rows, keys
+    whose squares are at either end of the range where the screen holds; against the oracle."""
+    Wn = 32
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=units, prefix=P, decode=N - P, budget=budget, head_dim=d, q_per_kv=1, window=Wn,
+                      cluster_frac=0.5)
+    c = caches.make(w, seed=units + N)
+    c["K"] = (c["K"].float() * scale).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    c["Q"] = (c["Q"].float() / scale).to(c["K"].dtype)
+    c["V"] = c["V"].to(c["K"].dtype)
+    band = torch.rand(d // 2, generator=torch.Generator().manual_seed(d)) ** 2
+    band[5] = 0.0
+    kw = dict(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=budget, merge_geometry=1,
+              band_weight=band.cuda(), merge_radius=radius)
+    row_off, prefix_len, K, V, Q = parity.host_arrays(c)
+    rp = parity.ref_params(cask.Params(dist_threshold=1e30, **kw))
+    want = ref.compress(rp, row_off, prefix_len, K, V, Q)
+    near = -ref.consolidate(rp, row_off, prefix_len, K, want["scores"], want["role"], want_sims=True)[1][want["role"] == 4]
+    near = np.sort(near[np.isfinite(near)])
+    for share in (0.0, 0.05, 0.5, 0.95, 1.0):
+        theta = float(near[int(share * (len(near) - 1))]) * (0.5 if share == 0.0 else 1.001)
+        _note(units, N, dtype, d, scale, "theta", theta, parity.full_check(c, cask.Params(dist_threshold=theta, **kw)))
