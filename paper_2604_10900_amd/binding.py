@@ -328,7 +328,7 @@ def score(b: Batch, scores: Optional[torch.Tensor] = None) -> torch.Tensor:
 def prefix_evict(b: Batch, scores: torch.Tensor, role: Optional[torch.Tensor] = None):
     if role is None:
         role = torch.full((b.total_rows,), 255, dtype=torch.uint8, device=b.device)
-    status = torch.zeros(b.n_units, dtype=torch.int32, device=b.device)
+    status = torch.empty(b.n_units, dtype=torch.int32, device=b.device)   # (the kernel writes every unit's)
     cp, cb, ws = b.params.c(), b.c(), b.workspace()
     rc = load().cask_prefix_evict(C.byref(cp), C.byref(cb), _dptr(scores), _dptr(role),
                                   _dptr(status), _dptr(ws), ws.numel(), _stream())
@@ -340,7 +340,7 @@ def prefix_evict(b: Batch, scores: torch.Tensor, role: Optional[torch.Tensor] = 
 def partition(b: Batch, scores: torch.Tensor, role: Optional[torch.Tensor] = None):
     if role is None:
         role = torch.full((b.total_rows,), 255, dtype=torch.uint8, device=b.device)
-    status = torch.zeros(b.n_units, dtype=torch.int32, device=b.device)
+    status = torch.empty(b.n_units, dtype=torch.int32, device=b.device)   # (the kernel writes every unit's)
     cp, cb, ws = b.params.c(), b.c(), b.workspace()
     rc = load().cask_partition(C.byref(cp), C.byref(cb), _dptr(scores), _dptr(role),
                                _dptr(status), _dptr(ws), ws.numel(), _stream())
@@ -381,7 +381,7 @@ def compress_step(b: Batch, K_out: torch.Tensor, V_out: torch.Tensor, out: "Outp
 def mass_diagnostics(b: Batch, scores: torch.Tensor, role: torch.Tensor, out_mass: torch.Tensor,
                      out_len: torch.Tensor) -> torch.Tensor:
     """[n_units, 2] float: (rho_core, rho_rep) of every unit (cask_mass_diagnostics)."""
-    rho = torch.zeros(b.n_units, 2, dtype=torch.float32, device=b.device)
+    rho = torch.empty(b.n_units, 2, dtype=torch.float32, device=b.device)   # (the kernel writes every unit's)
     cp, cb = b.params.c(), b.c()
     rc = load().cask_mass_diagnostics(C.byref(cp), C.byref(cb), _dptr(scores), _dptr(role),
                                       _dptr(out_mass), _dptr(out_len), _dptr(rho), _stream())
@@ -394,8 +394,7 @@ def group_diagnostics(b: Batch, scores: torch.Tensor, assign: torch.Tensor, K_ou
     """(dispersion, lost_mass), each [n_units] float (cask_group_diagnostics).  K_out
     [n_units, stride, d] in the cache dtype, stride >= budget."""
     assert K_out.is_contiguous() and K_out.dim() == 3 and K_out.shape[0] == b.n_units
-    disp = torch.zeros(b.n_units, dtype=torch.float32, device=b.device)
-    lost = torch.zeros(b.n_units, dtype=torch.float32, device=b.device)
+    disp, lost = torch.empty(2, b.n_units, dtype=torch.float32, device=b.device).unbind()   # (the kernel writes every unit's)
     cp, cb = b.params.c(), b.c()
     rc = load().cask_group_diagnostics(C.byref(cp), C.byref(cb), _dptr(scores), _dptr(assign),
                                        _dptr(K_out), C.c_int32(K_out.shape[1]), _dptr(disp),
