@@ -114,6 +114,7 @@ __global__ __launch_bounds__(256, 2) void similarity_mfma_kernel(
   __shared__ __attribute__((aligned(16))) int seed_pos[kSeedBlock];  // cache row of each staged seed
   int u, chunk;
   if (!map_block(n_units, chunks_per_unit, u, chunk)) return;
+  chunk = turned(u, chunk, chunks_per_unit);
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];
@@ -400,6 +401,7 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
   __shared__ __attribute__((aligned(16))) int seed_pos[kSeeds];  // cache row of each staged seed
   int u, chunk;
   if (!map_block(n_units, chunks_per_unit, u, chunk)) return;
+  chunk = turned(u, chunk, chunks_per_unit);
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
   const int P = prefix_len[u];

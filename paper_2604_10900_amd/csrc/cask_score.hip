@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
   int split = 0;
   if (kRowPass) {
     const int qb = tile / n_splits;
-    split = tile % n_splits;
+    split = turned(unit, tile % n_splits, n_splits);
     res_base = qb * kResRowsT;
     if (res_base >= Mq) return;
     res_ptr = Qu;

@@ -535,3 +535,24 @@ def test_band_distance_screen(units, N, P, budget, dtype, d, radius, scale):
     for share in (0.0, 0.05, 0.5, 0.95, 1.0):
         theta = float(near[int(share * (len(near) - 1))]) * (0.5 if share == 0.0 else 1.001)
         _note(units, N, dtype, d, scale, "theta", theta, parity.full_check(c, cask.Params(dist_threshold=theta, **kw)))
+
+
+@pytest.mark.parametrize("dtype,d,G,Wn", [("bf16", 128, 7, 64), ("bf16", 64, 3, 50), ("f32", 64, 2, 40)])
+def test_ragged_units_and_key_splits(dtype, d, G, Wn):
+    """Units of very different lengths, more than eight of them (parts of a unit are turned round from unit to
+    unit), several row blocks, the library's own key splits, an odd and an even number of them; scores and a
+    whole event's merges against the oracle.  Bar of the scores: 1e-4 of the largest, as everywhere."""
+    lens = [2700, 130, 1100, 260, 2048, 513, 65 + Wn, 1900, 400, 2600, 700, 150, 1300, 2100, 320, 900, 1025, 180, 2500]
+    c = _units(lens, [n // 7 for n in lens], head_dim=d, q_per_kv=G, window=Wn)
+    if dtype == "f32":
+        c = {k: (v.float() if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    row_off, prefix_len, K, V, Q = parity.host_arrays(c)
+    kw = dict(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60)
+    want = ref.score(parity.ref_params(cask.Params(**kw)), row_off, K, Q)
+    for splits, form in ((0, 0), (1, 0), (2, 0), (3, 0), (4, 0), (3, B.PATH_WIDE_ROWS), (4, B.PATH_WIDE_ROWS)):
+        p = cask.Params(score_splits=splits, path_flags=form | B.PATH_NO_FUSED_SWEEPS, **kw)
+        got = cask.score(parity.to_device(c, p)).cpu().numpy()
+        for u in range(len(lens)):
+            sl = slice(row_off[u], row_off[u + 1])
+            assert np.abs(got[sl] - want[sl]).max() <= 1e-4 * want[sl].max(), (splits, form, u)
+    _note(dtype, d, parity.full_check(c, cask.Params(**kw)))
