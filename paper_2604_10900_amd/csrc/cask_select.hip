@@ -545,6 +545,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   }
 }
 
+// IDX: rows a thread takes at a time; the smallest that covers the longest unit spreads it over all sixteen
+// waves (56 units of 6256 rows 7.4 -> 5.2 us).
+template <int IDX>
 __global__ __launch_bounds__(kSelThreads) void index_roles_kernel(KParams kp, const int64_t* __restrict__ row_off,
                                                                   const int32_t* __restrict__ prefix_len,
                                                                   const uint8_t* __restrict__ role, WalkArrays walk) {
@@ -552,7 +555,7 @@ __global__ __launch_bounds__(kSelThreads) void index_roles_kernel(KParams kp, co
   const int u = blockIdx.x;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0), P = prefix_len[u];
-  index_walk<kIdxPer>(kp.B, u, N, P, N - make_plan(kp, P, N).r_eff, role + row0, walk_out(walk, kp.B, u, row0), walk.out_len,
+  index_walk<IDX>(kp.B, u, N, P, N - make_plan(kp, P, N).r_eff, role + row0, walk_out(walk, kp.B, u, row0), walk.out_len,
                       walk.n_seeds, wsum);
 }
 
@@ -664,7 +667,13 @@ hipError_t launch_select(const KParams& kp, const Batch& b, const float* scores,
 
 hipError_t launch_index_roles(const KParams& kp, const Batch& b, const uint8_t* role, const WalkArrays& walk,
                               hipStream_t st) {
-  index_roles_kernel<<<dim3(b.n_units), dim3(kSelThreads), 0, st>>>(kp, b.row_off, b.prefix_len, role, walk);
+  auto go = [&](auto per) {
+    index_roles_kernel<decltype(per)::value><<<dim3(b.n_units), dim3(kSelThreads), 0, st>>>(kp, b.row_off, b.prefix_len, role, walk);
+  };
+  const int need = (b.max_unit_len + kSelThreads - 1) / kSelThreads;
+  if (need <= 4) go(std::integral_constant<int, 4>());
+  else if (need <= 8) go(std::integral_constant<int, 8>());
+  else go(std::integral_constant<int, kIdxPer>());
   return hipGetLastError();
 }
 

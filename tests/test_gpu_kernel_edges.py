@@ -556,3 +556,14 @@ def test_ragged_units_and_key_splits(dtype, d, G, Wn):
             sl = slice(row_off[u], row_off[u + 1])
             assert np.abs(got[sl] - want[sl]).max() <= 1e-4 * want[sl].max(), (splits, form, u)
     _note(dtype, d, parity.full_check(c, cask.Params(**kw)))
+
+
+@pytest.mark.parametrize("N", [4096, 4097, 8192, 8193])
+def test_roles_indexed_at_the_edges_of_the_instances(N):
+    """Slots and seed ordinals from given roles (consolidation on its own, and events with de-duplicated
+    seeding) for units of four and eight rows a thread, one row more, and one of 150 rows beside each."""
+    c = _units([N, 150], [300, 20], head_dim=64, q_per_kv=1, window=32)
+    kw = dict(head_dim=64, q_per_kv=1, window=32, budget=140)
+    _note(N, parity.full_check(c, cask.Params(sim_threshold=0.3, **kw)))
+    p = cask.Params(sim_threshold=2.0, seed_dedup=2, **kw)   # no cosine reaches it: every walk is decided by rank alone
+    _note(N, parity.full_check(c, p))
