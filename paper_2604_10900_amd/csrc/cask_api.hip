@@ -46,13 +46,16 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // read from LDS serves four products) when that leaves no more waves idle than 64 per wave
   // (256 per workgroup) does (W*G = 896, 1024, 512, 384: yes; 640, 768: no) and the model above
   // does not prefer the narrow form (small batches: twice as many workgroups fill more of the chip).
+  // With 64 channels the vector pipes are the bound and the operand reads that the wide form saves are not:
+  // narrow always.  Events, wide / narrow: 600 units of 2300 rows (W*G = 512) 375 / 339 us, 256 of 6300 (384)
+  // 307 / 293, 128 of 5378 (896, both sweeps) 268 / 257; 32 of 20 301 (896) 272 / 278.
   int sized;  // key splits the layout has room for on their own
   auto choose = [&](int shortest, int most) {
     double cost_n = 0.0, cost_w = 0.0;
     const int splits_n = best_splits(false, shortest, most, &cost_n), splits_w = best_splits(true, shortest, most, &cost_w);
     const int live_w = (kp.Mq + 127) / 128, all_w = (kp.Mq + 511) / 512 * 4;
     const int live_n = (kp.Mq + 63) / 64, all_n = (kp.Mq + 255) / 256 * 4;
-    w.wide_rows = (kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
+    w.wide_rows = (kp.d == 128 && kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) w.wide_rows = 1;
     if (kp.path_flags & CASK_PATH_NARROW_ROWS) w.wide_rows = 0;
     return w.wide_rows ? splits_w : splits_n;
@@ -122,10 +125,11 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     if (kp.score_qsplit >= 1) w.q_splits = kp.score_qsplit;
   }
   // Sweep B with 128 resident keys per wave (512 per workgroup) when that still leaves at least
-  // two rounds of workgroups
+  // two rounds of workgroups.  64 channels: where W*G is at most 512, eight stages to a workgroup (900 units of
+  // 4300 rows, W*G = 256, narrow / wide 561 / 548 us; 896: 48 of 14 301 262 / 268, 300 of 2300 262 / 265).
   {
     const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
-    w.wide_cols = (w.q_splits == 1 && wgs_wide >= 1024) ? 1 : 0;
+    w.wide_cols = (w.q_splits == 1 && wgs_wide >= 1024 && (kp.d == 128 || kp.Mq <= 512)) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) {
       w.wide_cols = 1;
       w.q_splits = 1;
