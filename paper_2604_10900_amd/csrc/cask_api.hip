@@ -93,25 +93,10 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     }
     n_splits = whole_stages(n_splits, &split_len);
   } else if (kp.score_splits < 1 && max_unit_len > 1024) {
-    n_splits = choose(512, most);
-    const double mean = n_units > 0 ? (double)total_rows / n_units : 0.0;
-    if (mean * 1.25 < (double)max_unit_len) {
-      // Units of different lengths: no whole rounds, but all stages and workgroups over the 512 slots, and
-      // behind them half a longest workgroup during which the chip empties.  1024 units of 4600 - 33 000
-      // rows, event: 1 split 6230 us, 3 to 6 splits 6180 - 6220, 9 splits 6160; 512 of 500 - 24 500 2843 -> 2580.
-      const int block_rows = w.wide_rows ? 512 : 256;
-      const double pairs = (double)n_units * ((kp.Mq + block_rows - 1) / block_rows);
-      const double row_cost = (w.wide_rows ? 1.85 : 1.0) / 64, wg_cost = 6;
-      double best_cost = 0.0;
-      for (int sp = 1; sp <= most; ++sp) {
-        const int len = (int)align_up((size_t)(max_unit_len + sp - 1) / sp, 64);
-        if (sp > 1 && len < 512) break;
-        const double live = mean / len + 0.5;  // workgroups of a unit of mean length that have keys
-        const double cost = pairs * (mean * row_cost + wg_cost * (live < 1.0 ? 1.0 : live)) / 512 + 0.5 * len * row_cost;
-        if (sp == 1 || cost < best_cost) best_cost = cost, n_splits = sp;
-      }
-    }
-    n_splits = whole_stages(n_splits, &split_len);
+    // (From the number of units and the longest alone, also where lengths differ: other splits sum a row's
+    // terms in another order, scores move by about 2e-7, and of some thousand ranks one may then keep another
+    // row.  Priced by the mean length instead, 1024 units of 4600 - 33 000 rows took 8 splits for 1: 6270 -> 6123 us.)
+    n_splits = whole_stages(choose(512, most), &split_len);
   }
   w.n_splits = n_splits;
   // Sweep B of a batch of short units has few workgroups (one per 256 keys), each paying its

@@ -185,7 +185,8 @@ __device__ inline bool map_block(int n_units, int tiles_per_unit, int& unit, int
 // Part `k` (0 to parts - 1) of a unit's `parts`, turned round from unit to unit where their number is even.  An XCD deals its
 // workgroups out to four shader engines in turn: the last parts of all units, which the short ones of a
 // ragged batch do not have, would fall to the same engines (an odd number goes round by itself).
-// 1024 units of 4600 - 33 000 rows, event with 2 / 4 key splits 6743 / 6736 -> 6136 / 6067 us.
+// 1024 units of 4600 - 33 000 rows, event: 6282 -> 6077 us (eight chunks of the similarity, one key split);
+// with 2 / 4 key splits asked for 6743 / 6736 -> 6136 / 6067.
 __device__ inline int turned(int unit, int k, int parts) {
   return parts & 1 ? k : (int)((unsigned)(k + (unit >> 3) + (unit >> 4)) % (unsigned)parts);
 }

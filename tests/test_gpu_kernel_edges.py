@@ -567,3 +567,27 @@ def test_roles_indexed_at_the_edges_of_the_instances(N):
     _note(N, parity.full_check(c, cask.Params(sim_threshold=0.3, **kw)))
     p = cask.Params(sim_threshold=2.0, seed_dedup=2, **kw)   # no cosine reaches it: every walk is decided by rank alone
     _note(N, parity.full_check(c, p))
+
+
+@pytest.mark.parametrize("units,longest,rest", [(512, 6000, 1100), (300, 9000, 1500)])
+def test_key_splits_do_not_follow_the_other_units_lengths(units, longest, rest):
+    """A unit's scores are the same bits whether the other units of the batch are as long as it or much shorter
+    (with the number of units and the longest unit the same): the order of its sums is not theirs to choose."""
+    at = [0, units // 3, units - 1]   # the units that have the longest length in both batches
+    G, Wn, d = 2, 32, 64
+    g = torch.Generator(device="cuda").manual_seed(units)
+    K3 = torch.randn(3, longest, d, generator=g, device="cuda").to(torch.bfloat16)
+    Q = torch.randn(units, Wn, G, d, generator=g, device="cuda").to(torch.bfloat16)
+    p = cask.Params(dtype=cask.BF16, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60)
+    got = []
+    for other in (longest, rest):
+        lens = [longest if u in at else other for u in range(units)]
+        row_off = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int64)
+        K = torch.randn(int(row_off[-1]), d, generator=g, device="cuda").to(torch.bfloat16)
+        for k, u in zip(K3, at):
+            K[int(row_off[u]): int(row_off[u + 1])] = k
+        s = cask.score(cask.Batch(p, row_off, torch.zeros(units, dtype=torch.int32), K, K, Q))
+        got.append([s[int(row_off[u]): int(row_off[u + 1])].clone() for u in at])
+    torch.cuda.synchronize()
+    for u, a, b in zip(at, *got):
+        assert torch.equal(a, b), u
