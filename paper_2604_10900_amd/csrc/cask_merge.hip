@@ -599,13 +599,14 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
 // Few pairs can win, and most of the others are told by the matrix cores first: a sum of non-negative
 // terms is at least their Euclidean norm, d >= |W (k_i - k_j)|_2 (W: each channel times its band's
 // weight), whose square is |W k_i|^2 + |W k_j|^2 - 2 <W k_i, W k_j>.  The product comes from W k rounded
-// to bf16: off by at most 2^-8 + 2^-18 of |W k_i| |W k_j|, twice that is at most 2^-8 + 2^-18 of the sum of
-// the squares, and kScreen covers it with the fp32 roundings.  A seed is left out for a donor only
+// to bf16, each channel off by at most 2^-8 of itself: a product is off by at most 2^-7 + 2^-16 of |W k_i| |W k_j|,
+// twice that is at most 2^-7 + 2^-16 = 0.00783 of the sum of the squares, and kScreen covers it with the fp32
+// roundings (some hundred of 2^-24).  A seed is left out for a donor only
 // where the bound is above theta; what is not finite, or out of the range where that holds, is never
 // left out.  The distances that remain are the ones above, seeds in ascending order: the same bits.
 // (112 units x 4352 rows, 128 channels, a threshold at the planted near-duplicates: 69 -> 48 us;
 // 112 x 8448 with 333 seeds 1120 -> 415.  Where every pair survives the screen costs 0 - 12 %.)
-constexpr float kScreen = 0.0042f;
+constexpr float kScreen = 0.008f;
 template <typename T>
 __device__ inline void load8(const T* p, float* out);
 template <>

@@ -591,3 +591,38 @@ def test_key_splits_do_not_follow_the_other_units_lengths(units, longest, rest):
     torch.cuda.synchronize()
     for u, a, b in zip(at, *got):
         assert torch.equal(a, b), u
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_band_distance_screen_at_the_worst_rounding_to_bf16(dtype, d):
+    """Keys whose weighted channels all lie half a bf16 ulp above a power of two, where rounding takes the most
+    off (2^-8 of a value, 2^-7 of a product): equal keys are at distance 0, and the screen must let them
+    through at a small threshold.  Copies are spread over forty patterns of signs; against the oracle."""
+    rng = np.random.default_rng(d)
+    N, Wn, M, n_core = 700, 32, 40, 30
+    pattern = rng.choice([-1.0, 1.0], (M, d)).astype(np.float32)
+    free = rng.permutation(N - Wn)
+    core, seeds = free[:n_core], free[n_core:n_core + M]
+    which = rng.integers(0, M, N)
+    which[seeds] = rng.permutation(M)
+    K = pattern[which] * np.float32(2.0) ** (which % 5)[:, None].astype(np.float32)
+    up = np.float32(1 + 2.0 ** -8)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    if dtype == "f32":
+        K = K * up
+    band = torch.full((d // 2,), float(up) if dtype == "bf16" else 1.0)
+    s = (1e-3 * (1.0 + rng.permutation(N))).astype(np.float32) / N
+    s[core] = 0.5 + 1e-3 * np.arange(n_core, dtype=np.float32)
+    s[seeds] = 0.25 + 1e-3 * np.arange(M, dtype=np.float32)
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=Wn + n_core + M, core=n_core,
+                    prefix_budget=0, merge_geometry=1, band_weight=band.cuda(), dist_threshold=0.25)
+    rp = parity.ref_params(p)
+    c = dict(K=torch.from_numpy(K).to(dt), V=torch.from_numpy(K).to(dt), Q=torch.zeros(1, Wn, 1, d, dtype=dt),
+             row_off=torch.tensor([0, N], dtype=torch.int64), prefix_len=torch.zeros(1, dtype=torch.int32))
+    row_off, prefix_len, Kb, Vb, Qb = parity.host_arrays(c)
+    want = ref.compress(rp, row_off, prefix_len, Kb, Vb, Qb, scores=s)
+    assert int((want["role"] == ref.SEED).sum()) == M and int((want["assign"] >= 0).sum()) == N   # every donor folds
+    out = cask.compress(parity.to_device(c, p), scores=torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(out.assign.cpu().numpy(), want["assign"])
