@@ -26,6 +26,12 @@ namespace {
 
 constexpr float kNegInf = -__builtin_inff();
 
+// Most a lane's sum against its fixed reference may reach; beyond, the wave takes its share again with a
+// running maximum.  Short of the fp32 range, because the sums of 2 lanes and up to 64 splits are still to be
+// added, and a share 126 octaves below another one's reference (itself at most 16 above its largest
+// logit) is dropped there: what is lost is below 2^(80 - 126 + 16) of the whole.
+constexpr float kMostSum = 0x1p80f;
+
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // (m, l) <- combination of two partial softmax statistics in base-2 units
@@ -594,7 +600,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     load_nl(nl0, slot_of(from), 0);
     if (kRowPass && !kMasked && from == 0) {
       // Nothing seen yet: the first logits of the lane's own row give the reference.  Too low shows
-      // as an infinite sum at the end and sends the wave through the exact recomputation; too
+      // as a sum out of range at the end and sends the wave through the exact recomputation; too
       // high only means every other term is negligible next to the first ones, which are themselves
       // part of the sum.
       chain(acc1, a0, 1);
@@ -737,10 +743,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
     slow_stage(it);
   }
   if (kRowPass && wave_live) {
-    // Range check of the fast epilogue, once per wave: a finite sum is exact.
+    // Range check of the fast epilogue, once per wave: a sum in range is exact.
     bool bad = false;
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) bad = bad || !(l_run[ct] < __builtin_inff());
+    for (int ct = 0; ct < CT; ++ct) bad = bad || !(l_run[ct] < kMostSum);
     if (__builtin_amdgcn_ballot_w64(bad) != 0ull) {
       // Recompute this wave's statistics with a true running maximum.  The ring belongs to the
       // whole workgroup, so the stream rows come straight from memory (same bounds-checked
@@ -1604,9 +1610,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
     plain(f1, n_stages);
   }
 
-  // ---- not finite somewhere: the wave's share again with fp32 products
+  // ---- not finite, or out of range, somewhere: the wave's share again with fp32 products
   const float total = MODE == 0 ? l_run : colsum;
-  if (__builtin_amdgcn_ballot_w64(wave_live && !(total < __builtin_inff())) != 0ull) {
+  if (__builtin_amdgcn_ballot_w64(wave_live && !(total < kMostSum)) != 0ull) {
     m_ref = kNegInf;
     l_run = colsum = 0.f;
     const float* bp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;

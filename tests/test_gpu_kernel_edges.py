@@ -626,3 +626,25 @@ def test_band_distance_screen_at_the_worst_rounding_to_bf16(dtype, d):
     out = cask.compress(parity.to_device(c, p), scores=torch.from_numpy(s).cuda())
     torch.cuda.synchronize()
     assert np.array_equal(out.assign.cpu().numpy(), want["assign"])
+
+
+@pytest.mark.parametrize("form", ["chosen", "wide", "one_launch"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("keys,splits", [((100, 104), 1), ((100, 300), 2), ((110, 300), 1)])
+def test_scores_where_only_the_sum_of_shares_leaves_the_range(keys, splits, dtype, d, form):
+    """Two keys 127.5 octaves above all others, seen by two lanes or by two key splits: each share of a row's sum
+    still fits fp32 against its first logit, their total does not.  Every row then gives half its mass to
+    either key, 2^-129 to any other."""
+    N, Wn, G = 512, 40, 2
+    K = torch.zeros(N, d)
+    K[list(keys), 3] = 127.5
+    Q = torch.zeros(1, Wn, G, d)
+    Q[..., 3] = 1.0
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    c = dict(K=K.to(dt), V=K.to(dt), Q=Q.to(dt), row_off=torch.tensor([0, N], dtype=torch.int64), prefix_len=torch.zeros(1, dtype=torch.int32))
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60,
+                    softmax_scale=float(np.log(2.0)), score_splits=splits, path_flags=SCORE_FORMS[form])
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    want = torch.zeros(N, dtype=torch.float64)
+    want[list(keys)] = 0.5
+    assert float((got - want).abs().max()) < 1e-4   # (a log-sum-exp of 128.5 in fp32: 2^-17 of an octave)
