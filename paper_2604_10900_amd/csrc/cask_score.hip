@@ -1247,8 +1247,10 @@ struct F32Geom {
   static constexpr int kItems = kStageRows * kPieces / kThreads;  // pieces a thread splits per stage
 };
 
-// x = hi + mid + lo, each rounded to bf16: 24 bits, so the three terms are x itself up to 2^-25 of it
-// (a value that rounds past the bf16 range gives an infinity and a NaN, like an infinity itself).
+// x = hi + mid + lo, each rounded to bf16: 24 bits, so the three terms are x itself up to 2^-25 of it, or up
+// to 2^-125 where that is more (bf16 ends where fp32's normal numbers do: below 2^-109 the third term, below
+// 2^-117 the second loses bits).  (A value that rounds past the bf16 range gives an infinity and a NaN,
+// like an infinity itself.)
 struct Split3 {
   bf16x8 hi, mid, lo;
 };
@@ -1283,7 +1285,8 @@ __device__ __forceinline__ Split3 split3(const f32x4& a, const f32x4& b) {
 // large one is rounded once per sixteen channels, not once per two: the result is closer to 64-bit sums
 // than the fp32 tiles' was.  A term that is not finite (an infinity or NaN in the cache, a value past
 // the bf16 range) makes the wave's sums NaN; the wave then takes its share again on the fp32 tiles,
-// operands straight from memory (rare, slow, exact).
+// operands straight from memory (rare, slow, exact).  So do the waves of a workgroup that meets a value so
+// large that what its partner lost below 2^-125 could show in a logit.
 //
 // Stream rows are split once per workgroup: a thread loads eight channels three stages ahead, splits them
 // and leaves the terms in LDS as three planes, one stage ahead; one barrier a stage.  The 16-byte piece p
@@ -1309,6 +1312,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
   constexpr int NK = D / 16;
   __shared__ __attribute__((aligned(16))) unsigned char stage_mem[2 * SG::kStageBytes];
   __shared__ __attribute__((aligned(16))) float negl[4][kStageRows];  // sweep B: -L of the rows of four stages
+  __shared__ int too_large;
   int unit, tile;
   if (!map_block(n_units, tiles_per_unit, unit, tile)) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1385,9 +1389,20 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
   auto store_negl = [&](const Raw& raw, int st) CASK_INLINE {
     if (MODE == 1 && tid < kStageRows) negl[st & 3][tid] = raw.nl;
   };
+  // the largest value this thread has split: 2^90 / c times 2^-125, over 128 channels and both operands, is
+  // 2^-27 of a logit in base 2
+  float largest = 0.f;
+  auto note_pair = [&](float x0, float x1) CASK_INLINE {
+    // (written out: fmaxf would first quiet a NaN in either value, an instruction each)
+    asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(x0), "v"(x1));
+  };
   auto store_rows = [&](const Raw& raw, int st) CASK_INLINE {
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) store_item(st, j, split3(raw.v[j][0], raw.v[j][1]));
+    for (int j = 0; j < kItems; ++j) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) note_pair(raw.v[j][q >> 1][(q & 1) * 2], raw.v[j][q >> 1][(q & 1) * 2 + 1]);
+      store_item(st, j, split3(raw.v[j][0], raw.v[j][1]));
+    }
   };
   const int rd = swizzle(c32, h);  // the lane's piece of k-step 0; k-step ks: 32 ks further in the row's order
   auto read_terms = [&](int st, int ks) CASK_INLINE {
@@ -1409,6 +1424,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
   // 32 rows at 32 bytes each), two waves' at a time.
   Split3 res[NK];
   Raw even, odd;
+  if (tid == 0) too_large = 0;  // (a barrier follows wherever there are stages)
   if (n_stages > 0) {
     Raw mine[kWaves];
 #pragma unroll
@@ -1576,6 +1592,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
         for (int e = 0; e < kTerms; ++e) sum += fast_exp2(__builtin_fmaf(old[ks * kTerms + e], c, MODE == 0 ? -m_ref : nl[e]));
         const int j = ks / 4, q = ks % 4;
         split_pair(raw.v[j][q >> 1][(q & 1) * 2], raw.v[j][q >> 1][(q & 1) * 2 + 1], t, q);
+        note_pair(raw.v[j][q >> 1][(q & 1) * 2], raw.v[j][q >> 1][(q & 1) * 2 + 1]);
         if (q == 3) store_item(it + 1, j, t);
         // (pinned: the optimiser would sink the sum out of the products it is meant to overlap with)
         asm volatile("" : "+v"(sum));
@@ -1612,7 +1629,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
 
   // ---- not finite, or out of range, somewhere: the wave's share again with fp32 products
   const float total = MODE == 0 ? l_run : colsum;
-  if (__builtin_amdgcn_ballot_w64(wave_live && !(total < kMostSum)) != 0ull) {
+  if (n_stages > 0 && !(largest * c < 0x1p90f)) too_large = 1;
+  __syncthreads();
+  if (too_large || __builtin_amdgcn_ballot_w64(wave_live && !(total < kMostSum)) != 0ull) {
     m_ref = kNegInf;
     l_run = colsum = 0.f;
     const float* bp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;

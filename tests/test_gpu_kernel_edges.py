@@ -648,3 +648,24 @@ def test_scores_where_only_the_sum_of_shares_leaves_the_range(keys, splits, dtyp
     want = torch.zeros(N, dtype=torch.float64)
     want[list(keys)] = 0.5
     assert float((got - want).abs().max()) < 1e-4   # (a log-sum-exp of 128.5 in fp32: 2^-17 of an octave)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("small", ["keys", "queries"])
+@pytest.mark.parametrize("e", [100, 112, 118])
+def test_fp32_scores_at_the_lower_end_of_the_range(e, small, d):
+    """One operand near 2^-e, the other near 2^e: from about 2^-109 on the smaller one's terms do not all fit bf16,
+    and the larger one sends its workgroups to the fp32 tiles.  Error against 64-bit sums as for ordinary
+    values (bound: test_fp32_scores_from_bf16_terms)."""
+    G, Wn, n, units = 4, 64, 1000, 4
+    c = _units([n] * units, [n // 8] * units, head_dim=d, q_per_kv=G, window=Wn)
+    noise = torch.Generator().manual_seed(d + e)
+    c = {k: (v.float() * (1 + 1e-3 * torch.randn(v.shape, generator=noise)) if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    s = e if small == "queries" else -e
+    c["K"], c["Q"] = c["K"] * 2.0 ** s, c["Q"] * 2.0 ** -s
+    want = _scores64(c, units, n, d, G, Wn)
+    p = cask.Params(dtype=cask.F32, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60)
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    err = float((got - want).norm() / want.norm())
+    _note(e, small, d, "error", err)
+    assert err < 4e-7
