@@ -42,7 +42,7 @@ struct SelectLds {
   int hist[3][2 * kBins];  // two copies of a bin side by side: scores crowd, and equal addresses serialise
   uint32_t cand[3][kCand];
   int n_cand[3];
-  int wave_tot[3][kSelWaves];
+  uint32_t wave_tot[3][kSelWaves];
   uint32_t wave_lo[kSelWaves], wave_hi[kSelWaves];
   int found[3][4];
 };
@@ -79,15 +79,16 @@ __device__ __forceinline__ uint32_t wave_reduce(uint32_t x, Op op) {  // op(x, x
   return (uint32_t)__builtin_amdgcn_readlane(v, 63);
 }
 // sum of w[0 .. wave) of sixteen per-wave totals, the same in every lane of the wave; *total: of all
-__device__ __forceinline__ int before_wave(const int* w, int wave, int* total) {
+// (unsigned: the totals may be two 16-bit counts in a word)
+__device__ __forceinline__ uint32_t before_wave(const uint32_t* w, int wave, uint32_t* total) {
   const int lane = threadIdx.x & 63;
-  int v = lane < kSelWaves ? w[lane] : 0;
-  v += dpp<0x111, 0xF>(0, v);
-  v += dpp<0x112, 0xF>(0, v);
-  v += dpp<0x114, 0xF>(0, v);
-  v += dpp<0x118, 0xF>(0, v);
-  *total = __builtin_amdgcn_readlane(v, kSelWaves - 1);
-  return wave > 0 ? __builtin_amdgcn_readlane(v, wave - 1) : 0;
+  uint32_t v = lane < kSelWaves ? w[lane] : 0u;
+  v += (uint32_t)dpp<0x111, 0xF>(0, (int)v);
+  v += (uint32_t)dpp<0x112, 0xF>(0, (int)v);
+  v += (uint32_t)dpp<0x114, 0xF>(0, (int)v);
+  v += (uint32_t)dpp<0x118, 0xF>(0, (int)v);
+  *total = (uint32_t)__builtin_amdgcn_readlane((int)v, kSelWaves - 1);
+  return wave > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)v, wave - 1) : 0u;
 }
 
 // keys of rows base + 64 PER wave + 64 e + lane, e < PER, rows outside [lo, hi) taken from its ends
@@ -199,7 +200,7 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
         lo_bin[j] = c.x + c.y;
         hi_bin[j] = c.z + c.w;
         const int incl = wave_scan(lo_bin[j] + hi_bin[j]);
-        if (lane == 63) L.wave_tot[j][wv] = incl;
+        if (lane == 63) L.wave_tot[j][wv] = (uint32_t)incl;
         above[j] = incl - lo_bin[j] - hi_bin[j];
       }
     }
@@ -207,8 +208,8 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       if (!open[j]) continue;
-      int total;
-      int before = above[j] + before_wave(L.wave_tot[kFirst && j == 2 ? 1 : j], wv, &total);
+      uint32_t total;
+      const int before = above[j] + (int)before_wave(L.wave_tot[kFirst && j == 2 ? 1 : j], wv, &total);
       if (before < rem[j] && rem[j] <= before + hi_bin[j] + lo_bin[j]) {
         const bool low = rem[j] > before + hi_bin[j];
         L.found[j][0] = kBins - 1 - 2 * tid - (low ? 1 : 0);
@@ -288,7 +289,7 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
 
 // Exclusive block scan of a small per-thread count (two 16-bit fields packed in one int).
 // Returns the exclusive prefix; *total receives the block total.  `wsum` is kSelWaves ints.
-__device__ inline int block_excl_scan(int v, int* wsum, int* total) {
+__device__ inline int block_excl_scan(int v, uint32_t* wsum, int* total) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int incl = v;
 #pragma unroll
@@ -296,11 +297,11 @@ __device__ inline int block_excl_scan(int v, int* wsum, int* total) {
     const int t = __shfl_up(incl, o, 64);
     if (lane >= o) incl += t;
   }
-  if (lane == 63) wsum[wv] = incl;
+  if (lane == 63) wsum[wv] = (uint32_t)incl;
   __syncthreads();
   int base = 0, tot = 0;
   for (int w = 0; w < kSelWaves; ++w) {
-    const int x = wsum[w];
+    const int x = (int)wsum[w];
     if (w < wv) base += x;
     tot += x;
   }
@@ -312,8 +313,9 @@ __device__ inline int block_excl_scan(int v, int* wsum, int* total) {
 // Ordered walk over the roles of a unit: output slot of every kept row, ordinal of every seed.
 // A wave owns IDX * 64 consecutive rows, read and written 64 consecutive rows at a time
 // (coalesced); positions inside the wave come from ballots with a running carry (kept rows in
-// the low half of a word, seeds in the high half: a wave sees at most 1024 rows per chunk), and
-// one exchange of the wave totals per chunk of kSelThreads * IDX rows orders the waves.
+// the low half of an unsigned word, seeds in the high half: a wave sees at most 2304 rows, a
+// chunk at most 36 864), and one exchange of the wave totals per chunk of kSelThreads * IDX rows
+// orders the waves.
 // Inlined on purpose: as a called function its pointers lose their address space and the
 // ballots' scalar registers are spilled lane by lane, which made the walk issue-bound.
 constexpr int kIdxPer = 16;
@@ -336,33 +338,33 @@ struct WalkOut {
 // are kept map to their slot or to themselves, all others to nothing: the donors that fold are entered
 // by whoever groups them.  Returns the chunk's totals (kept | seeds << 16).
 template <int IDX>
-__device__ __forceinline__ int index_rows(int B, int N, int P, int hi, int i0, int (&r)[IDX], int kept_before,
-                                          int seeds_before, const WalkOut& o, int* ws) {
+__device__ __forceinline__ uint32_t index_rows(int B, int N, int P, int hi, int i0, int (&r)[IDX], int kept_before,
+                                               int seeds_before, const WalkOut& o, uint32_t* ws) {
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  int pos[IDX];  // kept rows | seeds << 16 before this row inside the wave
-  int run = 0;
+  uint32_t pos[IDX];  // kept rows | seeds << 16 before this row inside the wave
+  uint32_t run = 0;
 #pragma unroll
   for (int e = 0; e < IDX; ++e) {
     const unsigned long long bk = __ballot(role_is_kept(r[e])), bs = __ballot(r[e] == CASK_ROLE_SEED);
-    const int nk = __builtin_amdgcn_mbcnt_hi((unsigned)(bk >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bk, 0));
-    const int ns = __builtin_amdgcn_mbcnt_hi((unsigned)(bs >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bs, 0));
+    const uint32_t nk = __builtin_amdgcn_mbcnt_hi((unsigned)(bk >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bk, 0));
+    const uint32_t ns = __builtin_amdgcn_mbcnt_hi((unsigned)(bs >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bs, 0));
     pos[e] = run + nk + (ns << 16);
-    run += __popcll(bk) + (__popcll(bs) << 16);
+    run += (uint32_t)__popcll(bk) + ((uint32_t)__popcll(bs) << 16);
     // the positions are final here: keep them from being recomputed behind the barrier out
     // of ballots that would have to be kept alive in scalar registers
     asm volatile("" : "+v"(pos[e]));
   }
   if ((threadIdx.x & 63) == 0) ws[wv] = run;
   __syncthreads();
-  int tot;
-  const int base = before_wave(ws, wv, &tot);
+  uint32_t tot;
+  const uint32_t base = before_wave(ws, wv, &tot);
   asm volatile("" : "+v"(i0));  // (see rank_select)
 #pragma unroll
   for (int e = 0; e < IDX; ++e) {
     asm volatile("" : "+v"(r[e]));
     const int i = i0 + e * 64;
-    const int at = base + pos[e];  // inside the chunk: at most 36 864 in either half
-    const int slot = kept_before + (at & 0xFFFF), ord = seeds_before + (int)((unsigned)at >> 16);
+    const uint32_t at = base + pos[e];  // inside the chunk: at most 36 864 in either half
+    const int slot = kept_before + (int)(at & 0xFFFFu), ord = seeds_before + (int)(at >> 16);
     const bool kept = role_is_kept(r[e]);
     // a caller-supplied role array could keep more rows than the budget: never write past
     // the unit's B output slots
@@ -384,7 +386,7 @@ __device__ __forceinline__ int index_rows(int B, int N, int P, int hi, int i0, i
 template <int IDX>
 __device__ __forceinline__ void index_walk(int B, int u, int N, int P, int hi, const uint8_t* __restrict__ ro,
                                            const WalkOut& o, int32_t* __restrict__ out_len, int32_t* __restrict__ n_seeds,
-                                           int (&wsum)[2][kSelWaves]) {
+                                           uint32_t (&wsum)[2][kSelWaves]) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   int kept_before = 0, seeds_before = 0;  // of the chunks walked so far
   for (int cb = 0; cb < N; cb += kSelThreads * IDX) {
@@ -393,9 +395,9 @@ __device__ __forceinline__ void index_walk(int B, int u, int N, int P, int hi, c
 #pragma unroll
     for (int e = 0; e < IDX; ++e) r[e] = (i0 + e * 64 < N) ? (int)ro[i0 + e * 64] : (int)CASK_ROLE_PREFIX_DROP;
     // two buffers: one barrier per chunk
-    const int tot = index_rows<IDX>(B, N, P, hi, i0, r, kept_before, seeds_before, o, wsum[(cb / (kSelThreads * IDX)) & 1]);
-    kept_before += tot & 0xFFFF;
-    seeds_before += (int)((unsigned)tot >> 16);
+    const uint32_t tot = index_rows<IDX>(B, N, P, hi, i0, r, kept_before, seeds_before, o, wsum[(cb / (kSelThreads * IDX)) & 1]);
+    kept_before += (int)(tot & 0xFFFFu);
+    seeds_before += (int)(tot >> 16);
   }
   if (tid == 0) {
     if (out_len) out_len[u] = kept_before < B ? kept_before : B;
@@ -423,7 +425,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     const float* __restrict__ scores, uint8_t* __restrict__ role, int32_t* __restrict__ status,
     int do_prefix, int do_decode, int do_index, WalkArrays walk) {
   __shared__ __attribute__((aligned(16))) SelectLds L;
-  __shared__ int wsum[2][kSelWaves];
+  __shared__ uint32_t wsum[2][kSelWaves];
   const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0);
@@ -486,10 +488,10 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
       if (i < N && (i < P ? do_prefix : do_decode)) ro[i] = (uint8_t)r[e];
     }
     if (do_index) {
-      const int tot = index_rows<PER>(kp.B, N, P, hi, i0, r, 0, 0, walk_out(walk, kp.B, u, row0), wsum[0]);
+      const uint32_t tot = index_rows<PER>(kp.B, N, P, hi, i0, r, 0, 0, walk_out(walk, kp.B, u, row0), wsum[0]);
       if (tid == 0) {
-        if (walk.out_len) walk.out_len[u] = min(tot & 0xFFFF, kp.B);
-        walk.n_seeds[u] = min((int)((unsigned)tot >> 16), kp.B);
+        if (walk.out_len) walk.out_len[u] = min((int)(tot & 0xFFFFu), kp.B);
+        walk.n_seeds[u] = min((int)(tot >> 16), kp.B);
       }
     }
     return;
@@ -551,7 +553,7 @@ template <int IDX>
 __global__ __launch_bounds__(kSelThreads) void index_roles_kernel(KParams kp, const int64_t* __restrict__ row_off,
                                                                   const int32_t* __restrict__ prefix_len,
                                                                   const uint8_t* __restrict__ role, WalkArrays walk) {
-  __shared__ int wsum[2][kSelWaves];
+  __shared__ uint32_t wsum[2][kSelWaves];
   const int u = blockIdx.x;
   const int64_t row0 = row_off[u];
   const int N = (int)(row_off[u + 1] - row0), P = prefix_len[u];

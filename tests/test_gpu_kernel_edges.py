@@ -669,3 +669,25 @@ def test_fp32_scores_at_the_lower_end_of_the_range(e, small, d):
     err = float((got - want).norm() / want.norm())
     _note(e, small, d, "error", err)
     assert err < 4e-7
+
+
+@pytest.mark.parametrize("N", [36864, 36865])
+def test_more_than_32767_seeds_in_one_chunk_of_the_walk(N):
+    """A unit that keeps 34 000 seeds and next to nothing else: the walk's packed count of seeds passes the sign
+    bit of a word (36 864 rows are its largest chunk; one row more takes the keys in chunks)."""
+    rng = np.random.default_rng(N)
+    Wn, M = 32, 34000
+    sc = rng.permutation(N).astype(np.float32)
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=Wn, budget=Wn + M, core=0, prefix_budget=0, sim_threshold=2.0)
+    K = torch.from_numpy(rng.standard_normal((N, 64)).astype(np.float32)).to(torch.bfloat16).cuda()
+    b = cask.Batch(p, torch.tensor([0, N], dtype=torch.int64), torch.zeros(1, dtype=torch.int32), K, K,
+                   torch.zeros(1, Wn, 1, 64, dtype=torch.bfloat16, device="cuda"))
+    out = cask.compress(b, scores=torch.from_numpy(sc).cuda())
+    torch.cuda.synchronize()
+    top = np.argsort(-sc[: N - Wn], kind="stable")[:M]
+    rows = np.concatenate([np.sort(top), np.arange(N - Wn, N)])
+    assert int(out.out_len[0]) == M + Wn and np.array_equal(out.out_src[0].cpu().numpy(), rows)
+    want = np.full(N, -1)
+    want[rows] = np.arange(M + Wn)
+    assert np.array_equal(out.assign.cpu().numpy(), want)
+    assert torch.equal(out.K_out[0].cpu(), K.cpu()[rows])
