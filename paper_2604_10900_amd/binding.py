@@ -394,7 +394,8 @@ def group_diagnostics(b: Batch, scores: torch.Tensor, assign: torch.Tensor, K_ou
     """(dispersion, lost_mass), each [n_units] float (cask_group_diagnostics).  K_out
     [n_units, stride, d] in the cache dtype, stride >= budget."""
     assert K_out.is_contiguous() and K_out.dim() == 3 and K_out.shape[0] == b.n_units
-    disp, lost = torch.empty(2, b.n_units, dtype=torch.float32, device=b.device).unbind()   # (the kernel writes every unit's)
+    disp = torch.empty(b.n_units, dtype=torch.float32, device=b.device)   # (the kernel writes every unit's, here and below)
+    lost = torch.empty(b.n_units, dtype=torch.float32, device=b.device)
     cp, cb = b.params.c(), b.c()
     rc = load().cask_group_diagnostics(C.byref(cp), C.byref(cb), _dptr(scores), _dptr(assign),
                                        _dptr(K_out), C.c_int32(K_out.shape[1]), _dptr(disp),

@@ -691,3 +691,12 @@ def test_more_than_32767_seeds_in_one_chunk_of_the_walk(N):
     want[rows] = np.arange(M + Wn)
     assert np.array_equal(out.assign.cpu().numpy(), want)
     assert torch.equal(out.K_out[0].cpu(), K.cpu()[rows])
+
+
+def test_diagnostics_are_tensors_of_their_own():
+    """Dispersion and lost mass share no storage: either can be resized, saved or kept without the other."""
+    c = _units([700, 900], [40, 0], head_dim=64, q_per_kv=1, window=32)
+    b = parity.to_device(c, cask.Params(head_dim=64, q_per_kv=1, window=32, budget=140))
+    out = cask.compress(b)
+    for t in B.group_diagnostics(b, out.scores, out.assign, out.K_out):
+        assert t._base is None and t.untyped_storage().nbytes() == 2 * 4
