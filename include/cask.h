@@ -29,8 +29,8 @@
  *   - Calls that share a workspace on different streams race; one workspace per stream.
  *   - The first launch of a kernel on a device raises that kernel's LDS limit (a function
  *     attribute, not a stream operation; the scoring sweeps, the one-launch scoring of larger
- *     batches and cask_attend): make one call of an entry point with the shapes in question
- *     before capturing the stream into a HIP graph.
+ *     batches, de-duplicated seeding of bf16 caches and cask_attend): make one call of an entry
+ *     point with the shapes in question before capturing the stream into a HIP graph.
  *   - Entry points may be called from several host threads (each on its own stream and
  *     workspace); the timing aid at the end of this header records one stream at a time.
  */

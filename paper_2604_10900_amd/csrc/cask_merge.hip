@@ -1932,12 +1932,10 @@ hipError_t launch_group_fold(const KParams& kp, const Batch& b, const uint8_t* r
   if ((long long)b.n_units * (wgs + shares) + 16 > 0x7fffffffLL) return hipErrorInvalidValue;
   const int folds = mapped_blocks(b.n_units, shares), blocks = folds + mapped_blocks(b.n_units, wgs);
   const int seeds = (plan_seed_bound(kp) + shares - 1) / shares;  // of a share
+  // at most 512 seeds a share, 27 KB: with the 17 KB of the other arrays well below the 64 KB that any launch may take
   const size_t lds = ((size_t)5 * seeds + (kFoldWaves * seeds > 2 * kFoldList ? kFoldWaves * seeds : 2 * kFoldList)) * sizeof(int);
   auto go = [&](auto t, auto d) {
     using T = decltype(t);
-    static LdsLimitOnce lim;
-    const hipError_t e = lim.ensure(reinterpret_cast<const void*>(&group_fold_kernel<T, decltype(d)::value>), 80 * 1024);
-    if (e != hipSuccess) return e;
     group_fold_kernel<T, decltype(d)::value><<<dim3((unsigned)blocks), dim3(kFoldThreads), lds, st>>>(
         kp, CASK_FOLD_PASS(T), b.n_units, (int)folds, shares, seeds, cj, b.row_off, b.prefix_len, assign_ord, slot_of, seed_rows, n_seeds,
         merged_row, merged_ord, seg_row, assign_out, status);

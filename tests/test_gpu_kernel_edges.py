@@ -700,3 +700,13 @@ def test_diagnostics_are_tensors_of_their_own():
     out = cask.compress(b)
     for t in B.group_diagnostics(b, out.scores, out.assign, out.K_out):
         assert t._base is None and t.untyped_storage().nbytes() == 2 * 4
+
+
+def test_grouping_and_fold_with_the_most_seeds_a_share_can_hold():
+    """129 units and more take two workgroups each; with 1024 seeds a unit either holds 512, the largest workspace
+    in LDS that grouping and fold in one launch ask for (no limit is raised for it); against the oracle."""
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=130, prefix=0, decode=1300, budget=1056, core=16, head_dim=64, q_per_kv=1, window=16,
+                      cluster_frac=0.5)
+    p = parity.params_of(w, sim_threshold=0.3)
+    assert cask.plan(p, 0, 1300)["seeds"] == 1024
+    _note(parity.full_check(caches.make(w, seed=77), p, expect_folds=True))
