@@ -377,12 +377,16 @@ def main():
         esz = outs.K_out.element_size()
         # The grouping launch also copies K and V of every kept row; emit reads K and V of the
         # seeds that fold and of their donors and writes the folded rows: together every kept row
-        # and folded donor is read and every kept row is written, over the two stages.
+        # and folded donor is read and every kept row is written, over the two stages.  Up to 256
+        # units of up to 8192 decode rows and 1024 seeds one launch does all of it, bracketed as
+        # `gather`; what `emit` then reads is the cost of an empty event pair.
         moved = 2.0 * p.head_dim * esz * (n_assigned + float(out_len.sum()))
-        both = stage_ms["gather"] + stage_ms["emit"]
+        one_fold = (n_units <= 256 and int((lens - b0.prefix_len_host.numpy()).max()) <= 8192
+                    and (p.budget - p.core if p.core >= 0 else (p.budget + 4) // 5) <= 1024)
+        moving_ms = stage_ms["gather"] + (0.0 if one_fold else stage_ms["emit"])
         fold_path.update({"gather_ms": round(stage_ms["gather"], 4), "emit_ms": round(stage_ms["emit"], 4),
-                          "copy_fold_row_bytes": moved,
-                          "copy_fold_GB/s": round(moved / (both * 1e-3) / 1e9, 1) if both > 0 else None})
+                          "fold_launches": 1 if one_fold else 2, "copy_fold_row_bytes": moved,
+                          "copy_fold_GB/s": round(moved / (moving_ms * 1e-3) / 1e9, 1) if moving_ms > 0 else None})
 
     # ---- roofline of the dominant kernel: one scoring sweep is one Q.K^T pass of
     # 2 * (W*G) * N * d flops per unit on the matrix cores

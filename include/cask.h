@@ -311,12 +311,15 @@ size_t cask_attend_workspace_bytes(const cask_params* params, int32_t n_units, i
  * events recorded on the caller's stream between its kernels.  Stage order: 0 score sweep A
  * (row statistics), 1 score sweep B (column mass; with the small kernel that combines the row
  * statistics of several key splits in front of it), 2 select (with the ordered walk over the
- * roles, which cask_compress runs in the same kernel), 3 index roles (zero in cask_compress),
- * 4 similarity, 5 gather merged donors (grouping by seed; the same launch copies the kept rows
- * to the output), 6 emit (folds the seeds that have donors).  A batch of short units (every unit at most
- * 1024 rows, B <= 1024, bf16, cosine geometry) runs stages 2-6 as one kernel: its time is
- * reported as stage 2 and stages 3-6 read as the cost of an empty event pair; stages 0 and 1 are
- * one kernel too, reported as stage 0.
+ * roles, which cask_compress runs in the same kernel), 3 index roles (the walk on its own behind
+ * de-duplicated seeding; else the cost of an empty event pair), 4 similarity, 5 gather merged
+ * donors (grouping by seed; the same launch copies the kept rows to the output), 6 emit (folds the
+ * seeds that have donors).  With at most 256 units, 8192 rows of decode trace in each and 1024
+ * seeds (B - core, or ceil(B / 5) for the default core) one launch groups, folds and copies: its time
+ * is reported as stage 5, and stage 6 reads as the cost of an empty event pair.  A batch of short
+ * units (every unit at most 1024 rows, B <= 1024, bf16, cosine geometry) runs stages 2-6 as one
+ * kernel: its time is reported as stage 2 and stages 3-6 read as the cost of an empty event pair;
+ * stages 0 and 1 are one kernel too, reported as stage 0.
  * cask_timing_enable(n > 0) creates events for the next n compress calls (n <= 4096) and
  * switches recording on; n <= 0 switches it off and destroys them.  Calls beyond n are not
  * recorded.  cask_timing_read waits for the recorded calls, writes the summed milliseconds

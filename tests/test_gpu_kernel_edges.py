@@ -710,3 +710,25 @@ def test_grouping_and_fold_with_the_most_seeds_a_share_can_hold():
     p = parity.params_of(w, sim_threshold=0.3)
     assert cask.plan(p, 0, 1300)["seeds"] == 1024
     _note(parity.full_check(caches.make(w, seed=77), p, expect_folds=True))
+
+
+@pytest.mark.parametrize("decode,launches", [(8100, 1), (8300, 2)])
+def test_stage_timing_of_the_fold(decode, launches):
+    """Every donor folds: with up to 8192 decode rows the grouping launch folds too and the last stage is an empty
+    event pair, with more the last stage is the folding launch (empty pairs cost some microseconds, the fold of
+    16 000 rows several times that)."""
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=2, prefix=0, decode=decode)
+    b = parity.to_device(caches.make(w), parity.params_of(w, sim_threshold=-1.0))
+    out = cask.compress(b)
+    torch.cuda.synchronize()
+    B.timing_enable(20)
+    for _ in range(20):
+        cask.compress(b, out)
+    ms, n = B.timing_read()
+    B.timing_enable(0)
+    _note(decode, {k: round(v * 1e3, 1) for k, v in ms.items()}, "us a call")
+    assert n == 20 and ms["gather"] > 2 * ms["index_roles"]      # (the walk runs in the selection: an empty pair)
+    if launches == 1:
+        assert ms["emit"] < 2 * ms["index_roles"]
+    else:
+        assert ms["emit"] > 2 * ms["index_roles"]
