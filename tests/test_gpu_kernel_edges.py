@@ -732,3 +732,100 @@ def test_stage_timing_of_the_fold(decode, launches):
         assert ms["emit"] < 2 * ms["index_roles"]
     else:
         assert ms["emit"] > 2 * ms["index_roles"]
+
+
+def _planted_folds(rng, N, Wn, n_core, M, sizes, d, zero=False):
+    """A unit whose seed j has exactly sizes[j] donors (its key, scaled): K, V, scores.  `zero`: all scores are zero,
+    so that rank is by row, and every group is averaged by its rows' counts."""
+    K = rng.integers(-4, 5, (N, d)).astype(np.float32)
+    V = rng.integers(-4, 5, (N, d)).astype(np.float32)
+    s = (1e-3 * (1.0 + rng.permutation(N))).astype(np.float32) / N       # distinct, small
+    free = np.arange(N - Wn) if zero else rng.permutation(N - Wn)
+    core, seeds, rest = free[:n_core], free[n_core:n_core + M], rng.permutation(free[n_core + M:])
+    s[core] = 0.5 + 1e-3 * np.arange(n_core, dtype=np.float32)
+    s[seeds] = 0.25 + 1e-3 * np.arange(M, dtype=np.float32)
+    at = 0
+    for j, n in enumerate(sizes):
+        K[rest[at:at + n]] = K[seeds[j]] * np.where(np.arange(n) % 2 == 1, 2.0, 1.0)[:, None]   # cosine 1 with that seed
+        at += n
+    return K, V, np.zeros_like(s) if zero else s
+
+
+@pytest.mark.parametrize("longest", [8100, 8300])
+@pytest.mark.parametrize("n_fold,dtype,d", [(1, "bf16", 128), (63, "f32", 64), (64, "bf16", 128), (64, "f32", 128), (65, "bf16", 64), (65, "f32", 128)])
+def test_step_folds_in_one_launch_and_in_two(n_fold, dtype, d, longest):
+    """Groups of 1, 63, 64, 65, 200 and 1500 donors, a unit where n_fold donors fold (the short list's 64 entries),
+    and a unit without score mass, all as a step with counts in and out and rows behind the budget: up to 8192
+    rows of decode trace one launch groups and folds, with more two do.  Scores injected; against the oracle."""
+    Wn, n_core, M = 64, 20, 16
+    rng = np.random.default_rng(n_fold + longest)
+    spread = [n_fold // M + (j < n_fold % M) for j in range(M)]
+    made = [_planted_folds(rng, 3000, Wn, n_core, M, [1, 63, 64, 65, 200, 1500], d), _planted_folds(rng, 2000, Wn, n_core, M, spread, d),
+            _planted_folds(rng, longest, Wn, n_core, M, [3, 70, 64, 0, 900], d, zero=True)]
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    K, V, s = (np.concatenate(x) for x in zip(*made))
+    cnt = rng.integers(1, 20, len(s)).astype(np.int32)
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=Wn + n_core + M, core=n_core,
+                    prefix_budget=0, sim_threshold=0.999)
+    S = p.budget + 37
+    c = dict(K=torch.from_numpy(K).to(dt), V=torch.from_numpy(V).to(dt), Q=torch.zeros(3, Wn, 1, d, dtype=dt),
+             row_off=torch.tensor(np.cumsum([0] + [len(m[0]) for m in made]), dtype=torch.int64), prefix_len=torch.zeros(3, dtype=torch.int32))
+    row_off, plen, Kb, Vb, Qb = parity.host_arrays(c)
+    rp = parity.ref_params(p)
+    want = ref.compress_step(rp, row_off, plen, Kb, Vb, Qb, in_count=cnt, scores=s, out_stride_rows=S)
+    folded = [int((want["assign"][row_off[u]:row_off[u + 1]] >= 0).sum() - want["out_len"][u]) for u in range(3)]
+    assert folded == [1893, n_fold, 1037], folded
+    b = parity.to_device(c, p)
+    for rep in range(2):
+        out = cask.Outputs(b)
+        Ko = torch.zeros(3, S, d, dtype=dt, device="cuda")
+        Vo = torch.zeros_like(Ko)
+        oc = torch.zeros(3, p.budget, dtype=torch.int32, device="cuda")
+        cask.compress_step(b, Ko, Vo, out, in_count=torch.from_numpy(cnt).cuda(), out_count=oc, scores=torch.from_numpy(s).cuda())
+        torch.cuda.synchronize()
+        got = dict(K_out=caches.host_bits(Ko), V_out=caches.host_bits(Vo), out_len=out.out_len.cpu().numpy(), out_src=out.out_src.cpu().numpy(),
+                   out_mass=out.out_mass.cpu().numpy(), assign=out.assign.cpu().numpy(), status=out.status.cpu().numpy(), count=oc.cpu().numpy())
+        assert rep == 0 or all(np.array_equal(got[k], first[k]) for k in got)          # the same bits on a second run
+        first = got
+    for k in ("out_len", "out_src", "assign", "status"):
+        assert np.array_equal(got[k], want[k]), k
+    assert np.array_equal(got["count"], want["out_count"])
+    assert not got["K_out"][:, p.budget:].any() and not got["V_out"][:, p.budget:].any()   # rows behind the output stay untouched
+    assert parity.check_values(p, got, want, Kb.reshape(-1, d), Vb.reshape(-1, d), row_off) == 6 + min(n_fold, M) + 4
+
+
+@pytest.mark.parametrize("longest", [8100, 8300])
+def test_dedup_step_in_one_launch_and_in_two(longest):
+    """De-duplicated seeding (fewer seeds than places may result), counts in and out, a row stride beyond the budget;
+    grouping and fold in one launch and in two, on injected scores against the oracle."""
+    c = _units([1500, longest], [70, 0], cluster_frac=0.6)
+    row_off, plen, K, V, Q = parity.host_arrays(c)
+    cnt = np.random.default_rng(12).integers(1, 6, int(row_off[-1])).astype(np.int32)
+    for dt in (0.0, 0.013, -0.017, 0.031, -0.029, 0.047):
+        p = cask.Params(dtype=cask.BF16, head_dim=128, q_per_kv=c["Q"].shape[2], window=c["Q"].shape[1], budget=320, sim_threshold=0.8 + dt, seed_dedup=4)
+        rp = parity.ref_params(p)
+        s = ref.score(rp, row_off, K, Q)
+        role0, _ = ref.prefix_evict(rp, row_off, plen, s)
+        if ref.partition_keys(rp, row_off, plen, K, s, role0)[2].min() >= 1e-3:
+            break
+    else:
+        pytest.fail("no clear threshold for this cache")
+    S = 448
+    want = ref.compress_step(rp, row_off, plen, K, V, Q, in_count=cnt, scores=s, out_stride_rows=S)
+    _, best, second = ref.consolidate(rp, row_off, plen, K, s, want["role"], want_sims=True)
+    b = parity.to_device(c, p)
+    out = cask.Outputs(b)
+    Ko = torch.zeros(2, S, 128, dtype=torch.bfloat16, device="cuda")
+    Vo, oc = torch.zeros_like(Ko), torch.zeros(2, p.budget, dtype=torch.int32, device="cuda")
+    cask.compress_step(b, Ko, Vo, out, in_count=torch.from_numpy(cnt).cuda(), out_count=oc, scores=torch.from_numpy(s).cuda())
+    torch.cuda.synchronize()
+    got = dict(K_out=caches.host_bits(Ko), V_out=caches.host_bits(Vo), out_len=out.out_len.cpu().numpy(), out_src=out.out_src.cpu().numpy(),
+               out_mass=out.out_mass.cpu().numpy(), assign=out.assign.cpu().numpy())
+    assert np.array_equal(got["out_len"], want["out_len"])
+    for u in range(2):
+        L, sl = int(want["out_len"][u]), slice(row_off[u], row_off[u + 1])
+        assert np.array_equal(got["out_src"][u, :L], want["out_src"][u, :L])
+        excused = parity.check_assign_excused(got["assign"][sl], want["assign"][sl], best[sl], second[sl], float(np.float32(p.sim_threshold)), f"unit {u}")
+        if excused == 0:
+            assert np.array_equal(oc.cpu().numpy()[u, :L], want["out_count"][u, :L])
+    assert parity.check_values(p, got, want, K.reshape(-1, 128), V.reshape(-1, 128), row_off) >= 5
