@@ -50,12 +50,12 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // narrow always.  Events, wide / narrow: 600 units of 2300 rows (W*G = 512) 375 / 339 us, 256 of 6300 (384)
   // 307 / 293, 128 of 5378 (896, both sweeps) 268 / 257; 32 of 20 301 (896) 272 / 278.
   int sized;  // key splits the layout has room for on their own
-  auto choose = [&](int shortest, int most) {
+  auto choose = [&](int shortest, int most, bool narrow) {
     double cost_n = 0.0, cost_w = 0.0;
     const int splits_n = best_splits(false, shortest, most, &cost_n), splits_w = best_splits(true, shortest, most, &cost_w);
     const int live_w = (kp.Mq + 127) / 128, all_w = (kp.Mq + 511) / 512 * 4;
     const int live_n = (kp.Mq + 63) / 64, all_n = (kp.Mq + 255) / 256 * 4;
-    w.wide_rows = (kp.d == 128 && kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
+    w.wide_rows = (!narrow && kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) w.wide_rows = 1;
     if (kp.path_flags & CASK_PATH_NARROW_ROWS) w.wide_rows = 0;
     return w.wide_rows ? splits_w : splits_n;
@@ -67,7 +67,10 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     const int k = (max_unit_len + len - 1) / len;
     return k < 1 ? 1 : k;
   };
-  int n_splits = choose(1024, 64), split_len;
+  const bool narrow_64 = kp.d == 64;
+  // (the layout has room for the splits of the form that the model chooses, whatever the head size: a batch
+  // whose workspace fits a limit with 128 channels fits it with 64)
+  int n_splits = choose(1024, 64, false), split_len;
   if (kp.score_splits >= 1) n_splits = kp.score_splits;
   sized = n_splits = whole_stages(n_splits, &split_len);
   // Row pitch of the one-launch scoring's partial sums (bf16 only; laid out below).
@@ -96,7 +99,9 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     // (From the number of units and the longest alone, also where lengths differ: other splits sum a row's
     // terms in another order, scores move by about 2e-7, and of some thousand ranks one may then keep another
     // row.  Priced by the mean length instead, 1024 units of 4600 - 33 000 rows took 8 splits for 1: 6270 -> 6123 us.)
-    n_splits = whole_stages(choose(512, most), &split_len);
+    n_splits = whole_stages(choose(512, most, narrow_64), &split_len);
+  } else {
+    (void)choose(1024, 64, narrow_64);  // (the form alone: splits that were asked for, or units of one split)
   }
   w.n_splits = n_splits;
   // Sweep B of a batch of short units has few workgroups (one per 256 keys), each paying its

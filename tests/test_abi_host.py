@@ -57,6 +57,20 @@ def test_binding_declares_every_signature(cask):
     assert lib.cask_workspace_bytes.restype is C.c_size_t
 
 
+def test_workspace_of_64_channels_is_no_larger_than_of_128(cask):
+    """The layout holds nothing that depends on the head size: the forms that the scoring takes with 64 channels
+    fit the room that the forms with 128 have, so that a batch near a limit (the fixed array of
+    cask_compress_static) is not refused for them.  Window rows and lengths where the forms differ."""
+    rng = np.random.default_rng(1)
+    shapes = [(103, 8649, 2048), (397, 2839, 448), (75, 11539, 448), (341, 2650, 800), (128, 5378, 896), (600, 2300, 512)]
+    shapes += [(int(2 ** rng.uniform(0, 11)), int(2 ** rng.uniform(8, 16)), int(rng.integers(2, 17)) * 64) for _ in range(2000)]
+    for units, rows, mq in shapes:
+        for dtype in (cask.BF16, cask.F32):
+            b64, b128 = (cask.binding.workspace_bytes(cask.Params(dtype=dtype, head_dim=d, q_per_kv=mq // 64, window=64, budget=400),
+                                                      units, units * rows, rows) for d in (64, 128))
+            assert b64 <= b128, (units, rows, mq, dtype)
+
+
 def test_workspace_sizes_of_4_gib_and_more_pass_the_boundary(cask):
     """A batch of cfg5's size needs a workspace beyond 2^32 bytes: the size comes back whole, and
     an entry point given that size (with an invalid batch) does not mistake it for a small one."""
