@@ -46,9 +46,11 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // read from LDS serves four products) when that leaves no more waves idle than 64 per wave
   // (256 per workgroup) does (W*G = 896, 1024, 512, 384: yes; 640, 768: no) and the model above
   // does not prefer the narrow form (small batches: twice as many workgroups fill more of the chip).
-  // With 64 channels the vector pipes are the bound and the operand reads that the wide form saves are not:
-  // narrow always.  Events, wide / narrow: 600 units of 2300 rows (W*G = 512) 375 / 339 us, 256 of 6300 (384)
-  // 307 / 293, 128 of 5378 (896, both sweeps) 268 / 257; 32 of 20 301 (896) 272 / 278.
+  // With 64 channels the vector pipes are the bound and the operand reads that the wide form saves are not: units of up
+  // to 6400 rows in two to eight rounds of the 512 slots (of sweep B's workgroups of 512 keys) take the narrow form
+  // in both sweeps.  Scores, wide / narrow: 600 units of 2300 rows (W*G = 512) 261 / 249 us, 256 of 6300 (384) 241 / 226,
+  // 128 of 5378 (896) 229 / 214.  Longer units and larger batches do as well or better with the model's choice: 64 of
+  // 20 000 (512) 220 / 230, 32 of 20 301 (896) 211 / 216, 100 of 33 000 (1024) 1038 / 1058.
   int sized;  // key splits the layout has room for on their own
   auto choose = [&](int shortest, int most, bool narrow) {
     double cost_n = 0.0, cost_w = 0.0;
@@ -67,7 +69,8 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     const int k = (max_unit_len + len - 1) / len;
     return k < 1 ? 1 : k;
   };
-  const bool narrow_64 = kp.d == 64;
+  const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
+  const bool narrow_64 = kp.d == 64 && kp.Mq > 256 && max_unit_len <= 6400 && wgs_wide >= 1024 && wgs_wide < 4096;
   // (the layout has room for the splits of the form that the model chooses, whatever the head size: a batch
   // whose workspace fits a limit with 128 channels fits it with 64)
   int n_splits = choose(1024, 64, false), split_len;
@@ -115,11 +118,9 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     if (kp.score_qsplit >= 1) w.q_splits = kp.score_qsplit;
   }
   // Sweep B with 128 resident keys per wave (512 per workgroup) when that still leaves at least
-  // two rounds of workgroups.  64 channels: where W*G is at most 512, eight stages to a workgroup (900 units of
-  // 4300 rows, W*G = 256, narrow / wide 561 / 548 us; 896: 48 of 14 301 262 / 268, 300 of 2300 262 / 265).
+  // two rounds of workgroups (64 channels: see above)
   {
-    const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
-    w.wide_cols = (w.q_splits == 1 && wgs_wide >= 1024 && (kp.d == 128 || kp.Mq <= 512)) ? 1 : 0;
+    w.wide_cols = (w.q_splits == 1 && wgs_wide >= 1024 && !narrow_64) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) {
       w.wide_cols = 1;
       w.q_splits = 1;
