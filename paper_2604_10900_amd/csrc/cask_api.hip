@@ -202,6 +202,7 @@ static int resolve_batch(const KParams& kp, const cask_batch* b, Batch* out, boo
   out->n_units = b->n_units;
   out->max_unit_len = 0;
   out->max_decode_len = 0;
+  out->max_prefix_len = 0;
   out->total_rows = 0;
   if (b->n_units == 0) return CASK_OK;
   if (!b->row_off || !b->prefix_len || !b->row_off_host || !b->prefix_len_host || !b->K) return CASK_EINVAL;
@@ -218,6 +219,7 @@ static int resolve_batch(const KParams& kp, const cask_batch* b, Batch* out, boo
     if (P < 0 || P > n) return CASK_EINVAL;
     if ((int)n > out->max_unit_len) out->max_unit_len = (int)n;
     if ((int)n - P > out->max_decode_len) out->max_decode_len = (int)n - P;
+    if (P > out->max_prefix_len) out->max_prefix_len = P;
   }
   out->total_rows = b->row_off_host[b->n_units];
   out->row_off = b->row_off;

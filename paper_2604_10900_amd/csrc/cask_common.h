@@ -257,6 +257,7 @@ struct Batch {
   const void* Q;
   int max_unit_len;
   int max_decode_len;  // longest decode trace N - P of the batch
+  int max_prefix_len;  // longest prefix P
   int64_t total_rows;
 };
 

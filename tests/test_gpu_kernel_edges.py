@@ -829,3 +829,24 @@ def test_dedup_step_in_one_launch_and_in_two(longest):
         if excused == 0:
             assert np.array_equal(oc.cpu().numpy()[u, :L], want["out_count"][u, :L])
     assert parity.check_values(p, got, want, K.reshape(-1, 128), V.reshape(-1, 128), row_off) >= 5
+
+
+@pytest.mark.parametrize("P", [0, 1, 4096, 4097, 6145, 36865])
+def test_prefix_stage_of_units_much_longer_than_their_prefixes(P):
+    """Stage 1 alone takes the instance of the selection that its longest prefix needs, whatever the units hold
+    behind it: edges of the instances, ties at the rank, a unit without a prefix; roles behind a prefix are
+    left as they are."""
+    rng = np.random.default_rng(P)
+    lens, pref = [40000, 3000, 20000], [P, min(P, 900), 0]
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    sc = np.floor(rng.random(int(row_off[-1])) * 300).astype(np.float32) / 300
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=64, budget=900, prefix_budget=600)
+    prefix = np.array(pref, dtype=np.int32)
+    want, _ = ref.prefix_evict(parity.ref_params(p), row_off, prefix, sc)
+    K = torch.zeros(int(row_off[-1]), 64, dtype=torch.bfloat16, device="cuda")
+    b = cask.Batch(p, torch.from_numpy(row_off), torch.from_numpy(prefix), K, K, torch.zeros(3, 64, 1, 64, dtype=torch.bfloat16, device="cuda"))
+    role, _ = cask.prefix_evict(b, torch.from_numpy(sc).cuda(), torch.full((int(row_off[-1]),), 77, dtype=torch.uint8, device="cuda"))
+    role = role.cpu().numpy()
+    for u in range(3):
+        lo, mid, hi = row_off[u], row_off[u] + pref[u], row_off[u + 1]
+        assert np.array_equal(role[lo:mid], want[lo:mid]) and (role[mid:hi] == 77).all()
