@@ -450,7 +450,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
   q.k[0] = pre_sel ? pl.p_keep : 0;
   q.k[1] = (dec_sel && C > 0) ? C : 0;
   q.k[2] = (dec_sel && !all_seed && CM > C) ? CM : 0;
-  const int i0 = (tid >> 6) * (64 * PER) + lane;
+  // (stage 2 alone: the keys start behind the prefix)
+  const int first_row = MANY || do_prefix || do_index ? 0 : P;
+  const int i0 = first_row + (tid >> 6) * (64 * PER) + lane;
   uint32_t key[PER];
 #pragma unroll
   for (int e = 0; e < PER; ++e) key[e] = 0u;
@@ -476,7 +478,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     return in_c ? CASK_ROLE_CORE : (in_cm ? CASK_ROLE_SEED : CASK_ROLE_DONOR);
   };
   if (!MANY && !pre_ties && !dec_ties) {
-    int r[PER], i0 = (tid >> 6) * (64 * PER) + lane;
+    int r[PER], i0 = first_row + (tid >> 6) * (64 * PER) + lane;
     asm volatile("" : "+v"(i0));
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
@@ -660,9 +662,9 @@ void with_select_instance(int rows, F&& f) {
 hipError_t launch_select(const KParams& kp, const Batch& b, const float* scores, uint8_t* role, int32_t* status,
                          bool do_prefix, bool do_decode, const WalkArrays* walk, hipStream_t st) {
   const WalkArrays w = walk ? *walk : WalkArrays{};
-  // (stage 1 alone looks at prefixes only: 16 units of 36 864 rows with 4608 in the prefix 20.1 us by the
-  // longest unit, 10.2 by the longest prefix)
-  const int rows = do_decode || walk ? b.max_unit_len : b.max_prefix_len;
+  // (one stage alone looks at prefixes, or at decode traces, only: 16 units of 36 864 rows, stage 1 of 4608 rows
+  // 20.4 us by the longest unit, 9.4 by the longest prefix; stage 2 of 6864 rows 24.6 and 11.3)
+  const int rows = walk || (do_prefix && do_decode) ? b.max_unit_len : (do_prefix ? b.max_prefix_len : b.max_decode_len);
   with_select_instance(rows, [&](auto per, auto many) {
     select_kernel<decltype(per)::value, decltype(many)::value><<<dim3(b.n_units), dim3(kSelThreads), 0, st>>>(
         kp, b.row_off, b.prefix_len, scores, role, status, do_prefix ? 1 : 0, do_decode ? 1 : 0, walk ? 1 : 0, w);

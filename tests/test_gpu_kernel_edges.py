@@ -850,3 +850,21 @@ def test_prefix_stage_of_units_much_longer_than_their_prefixes(P):
     for u in range(3):
         lo, mid, hi = row_off[u], row_off[u] + pref[u], row_off[u + 1]
         assert np.array_equal(role[lo:mid], want[lo:mid]) and (role[mid:hi] == 77).all()
+
+
+@pytest.mark.parametrize("D", [64, 65, 4096, 4097, 6145, 36865])
+def test_decode_stage_of_units_much_longer_than_their_traces(D):
+    """Stage 2 alone reads its keys from behind the prefix and takes the instance that its longest trace needs:
+    edges of the instances, ties at the ranks, a unit that is all trace, one whose trace is all kept; roles in
+    front are left as they are."""
+    rng = np.random.default_rng(D)
+    lens, trace = [40000, 3000, 20000], [D, min(D, 3000), min(D, 700)]
+    row_off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    prefix = np.array([n - t for n, t in zip(lens, trace)], dtype=np.int32)
+    sc = np.floor(rng.random(int(row_off[-1])) * 300).astype(np.float32) / 300
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=64, budget=900, prefix_budget=100)
+    want, _ = ref.partition(parity.ref_params(p), row_off, prefix, sc, np.full(int(row_off[-1]), 77, dtype=np.uint8))
+    K = torch.zeros(int(row_off[-1]), 64, dtype=torch.bfloat16, device="cuda")
+    b = cask.Batch(p, torch.from_numpy(row_off), torch.from_numpy(prefix), K, K, torch.zeros(3, 64, 1, 64, dtype=torch.bfloat16, device="cuda"))
+    role, _ = cask.partition(b, torch.from_numpy(sc).cuda(), torch.full((int(row_off[-1]),), 77, dtype=torch.uint8, device="cuda"))
+    assert np.array_equal(role.cpu().numpy(), want)
