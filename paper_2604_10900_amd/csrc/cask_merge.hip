@@ -605,7 +605,9 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
 // where the bound is above theta; what is not finite, or out of the range where that holds, is never
 // left out.  The distances that remain are the ones above, seeds in ascending order: the same bits.
 // (112 units x 4352 rows, 128 channels, a threshold at the planted near-duplicates: 69 -> 48 us;
-// 112 x 8448 with 333 seeds 1120 -> 415.  Where every pair survives the screen costs 0 - 12 %.)
+// 112 x 8448 with 333 seeds 1120 -> 415.  Where every pair survives the screen costs 5 - 16 %: 112 x 4352 with 128
+// seeds, 64 channels, 354 -> 410; 16 x 4352 fp32 with 45 108 -> 119.  Leaving it out for the block of seeds behind one
+// that nearly all pairs survived takes registers that 128 channels do not have: 48 -> 59 us above.)
 constexpr float kScreen = 0.008f;
 template <typename T>
 __device__ inline void load8(const T* p, float* out);
