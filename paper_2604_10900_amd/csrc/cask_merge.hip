@@ -605,9 +605,9 @@ __global__ __launch_bounds__(256, 3) void similarity_f32_kernel(
 // where the bound is above theta; what is not finite, or out of the range where that holds, is never
 // left out.  The distances that remain are the ones above, seeds in ascending order: the same bits.
 // (112 units x 4352 rows, 128 channels, a threshold at the planted near-duplicates: 69 -> 48 us;
-// 112 x 8448 with 333 seeds 1120 -> 415.  Where every pair survives the screen costs 5 - 16 %: 112 x 4352 with 128
-// seeds, 64 channels, 354 -> 410; 16 x 4352 fp32 with 45 108 -> 119.  Leaving it out for the block of seeds behind one
-// that nearly all pairs survived takes registers that 128 channels do not have: 48 -> 59 us above.)
+// 112 x 8448 with 333 seeds 1120 -> 415.  Where nearly every pair survives it costs 5 - 16 %, but for thresholds that
+// leave it off, below.  Leaving it out for the block of seeds behind one that nearly all pairs survived takes
+// registers that 128 channels do not have: 48 -> 59 us above.)
 constexpr float kScreen = 0.008f;
 template <typename T>
 __device__ inline void load8(const T* p, float* out);
@@ -629,7 +629,11 @@ __device__ inline void load8<uint16_t>(const uint16_t* p, float* out) {
   }
 }
 
-template <typename T, int D>
+// SCREEN: off from a threshold of 1e6 on, which the distances of no ordinary keys reach (every donor folds into its
+// nearest seed): nothing would be left out, and a row is loaded once instead of once for each block of
+// seeds.  The same bits either way; with / without the screen, every pair surviving: 112 x 4352 with 128 seeds, 64
+// channels, 410 / 354 us, 16 x 4352 fp32 with 45 119 / 107, 20 x 8448 with 333 1434 / 1344.
+template <typename T, int D, bool SCREEN>
 __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
     KParams kp, int n_units, int tiles_per_unit, const int64_t* __restrict__ row_off,
     const int32_t* __restrict__ prefix_len, const T* __restrict__ K,
@@ -686,6 +690,11 @@ __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
   auto usable = [](float n2) { return n2 > 1e-26f && n2 < 1e36f; };  // (false for NaN)
   float best = __builtin_inff();
   int best_ord = -1;
+  float k[D];
+  if (!SCREEN) {
+#pragma unroll
+    for (int c = 0; c < D; c += 8) load8<T>(Ku + (size_t)(donor ? i : P) * D + c, k + c);
+  }
   for (int s0 = 0; s0 < M; s0 += SEEDS) {
     const int lim = min(SEEDS, M - s0);
     float seed[SEEDS * PIECES / 256][8];  // this thread's pieces of the seeds: under way while the rows come in
@@ -701,7 +710,7 @@ __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
     bf16x8 wk[2][NK];
     float kc[2];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int t = 0; SCREEN && t < 2; ++t) {
       int at = min(base + (tid & ~63) + t * 32 + c32, hi - 1);
       asm volatile("" : "+v"(at));  // (else all of this is taken out of the loop)
       const T* row = Ku + (size_t)at * D;
@@ -730,10 +739,12 @@ __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         sk[sr][c + e] = v[e];
+        if (!SCREEN) continue;
         const float x = v[e] * wband[c % H + e];
         n2 = __builtin_fmaf(x, x, n2);
         x8[e] = (__bf16)x;
       }
+      if (!SCREEN) continue;
       sw[(q % PIECES) * SEEDS + sr] = x8;
 #pragma unroll
       for (int m = 1; m < PIECES; m *= 2) n2 += __shfl_xor(n2, m, 64);  // a row's pieces: neighbouring lanes
@@ -746,24 +757,27 @@ __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
     // ---- screen: 32 seeds against the wave's 64 rows.  A lane owns one row of a tile and the seeds
     // 8 (r / 4) + 4 h + r % 4: the ballot of register r holds seed s of 32 rows in its lower half and
     // seed s + 4 in its upper.
-    f32x16 acc0 = f32x16{0}, acc1 = f32x16{0};
+    uint32_t mine = donor ? 0xffffffffu : 0u;  // seeds left for this lane's row
+    if constexpr (SCREEN) {
+      f32x16 acc0 = f32x16{0}, acc1 = f32x16{0};
 #pragma unroll
-    for (int ks = 0; ks < NK; ++ks) {
-      const bf16x8 a = sw[(2 * ks + h) * SEEDS + c32];
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[0][ks], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[1][ks], acc1, 0, 0, 0);
-    }
-    const uint64_t d0 = (donors & 0xffffffffull) * 0x100000001ull, d1 = (donors >> 32) * 0x100000001ull;
-    uint32_t mine = 0;  // seeds left for this lane's row
+      for (int ks = 0; ks < NK; ++ks) {
+        const bf16x8 a = sw[(2 * ks + h) * SEEDS + c32];
+        acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[0][ks], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, wk[1][ks], acc1, 0, 0, 0);
+      }
+      mine = 0;
+      const uint64_t d0 = (donors & 0xffffffffull) * 0x100000001ull, d1 = (donors >> 32) * 0x100000001ull;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int s = (r >> 2) * 8 + (r & 3);
-      const float bs = sc[s + h * 4];
-      const uint64_t m0 = __builtin_amdgcn_ballot_w64(!(acc0[r] < kc[0] + bs)) & d0;
-      const uint64_t m1 = __builtin_amdgcn_ballot_w64(!(acc1[r] < kc[1] + bs)) & d1;
-      if ((m0 | m1) != 0) {
-        const uint64_t own = (h ? m1 : m0) >> c32;
-        mine |= (uint32_t)(own & 1u) << s | (uint32_t)((own >> 32) & 1u) << (s + 4);
+      for (int r = 0; r < 16; ++r) {
+        const int s = (r >> 2) * 8 + (r & 3);
+        const float bs = sc[s + h * 4];
+        const uint64_t m0 = __builtin_amdgcn_ballot_w64(!(acc0[r] < kc[0] + bs)) & d0;
+        const uint64_t m1 = __builtin_amdgcn_ballot_w64(!(acc1[r] < kc[1] + bs)) & d1;
+        if ((m0 | m1) != 0) {
+          const uint64_t own = (h ? m1 : m0) >> c32;
+          mine |= (uint32_t)(own & 1u) << s | (uint32_t)((own >> 32) & 1u) << (s + 4);
+        }
       }
     }
     if (lim < SEEDS) mine &= (1u << lim) - 1u;
@@ -779,11 +793,12 @@ __global__ __launch_bounds__(256, 2) void similarity_kappa_kernel(
     if (__builtin_amdgcn_ballot_w64(mine != 0) == 0) continue;
 
     // ---- the pairs that are left: every lane takes its own next seed, in ascending order
-    int from = mine != 0 ? i : P;  // (a row costs its cache lines again with every piece: lanes without a pair share one)
-    asm volatile("" : "+v"(from));  // (else the loads are taken out of the loop and spilled)
-    float k[D];
+    if constexpr (SCREEN) {
+      int from = mine != 0 ? i : P;  // (a row costs its cache lines again with every piece: lanes without a pair share one)
+      asm volatile("" : "+v"(from));  // (else the loads are taken out of the loop and spilled)
 #pragma unroll
-    for (int c = 0; c < D; c += 8) load8<T>(Ku + (size_t)from * D + c, k + c);
+      for (int c = 0; c < D; c += 8) load8<T>(Ku + (size_t)from * D + c, k + c);
+    }
     for (; __builtin_amdgcn_ballot_w64(mine != 0) != 0; mine &= mine - 1, skip_far()) {
       const bool in_reach = mine != 0;
       const int sr = in_reach ? __builtin_ctz(mine) : 0;
@@ -833,9 +848,9 @@ hipError_t launch_similarity_kappa(const KParams& kp, const Batch& b, const uint
                                    int32_t* assign_ord, hipStream_t st) {
   const int tiles = (b.max_decode_len + 255) / 256;
   if (tiles == 0) return hipSuccess;
-  similarity_kappa_kernel<T, D><<<dim3(mapped_blocks(b.n_units, tiles)), dim3(256), 0, st>>>(
-      kp, b.n_units, tiles, b.row_off, b.prefix_len, static_cast<const T*>(b.K), role, seed_rows,
-      n_seeds, assign_ord);
+  auto kern = kp.theta < 1e6f ? &similarity_kappa_kernel<T, D, true> : &similarity_kappa_kernel<T, D, false>;
+  kern<<<dim3(mapped_blocks(b.n_units, tiles)), dim3(256), 0, st>>>(kp, b.n_units, tiles, b.row_off, b.prefix_len, static_cast<const T*>(b.K),
+                                                                    role, seed_rows, n_seeds, assign_ord);
   return hipGetLastError();
 }
 

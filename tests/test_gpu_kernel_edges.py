@@ -868,3 +868,19 @@ def test_decode_stage_of_units_much_longer_than_their_traces(D):
     b = cask.Batch(p, torch.from_numpy(row_off), torch.from_numpy(prefix), K, K, torch.zeros(3, 64, 1, 64, dtype=torch.bfloat16, device="cuda"))
     role, _ = cask.partition(b, torch.from_numpy(sc).cuda(), torch.full((int(row_off[-1]),), 77, dtype=torch.uint8, device="cuda"))
     assert np.array_equal(role.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("theta,radius", [(float("inf"), 0), (1e6, 60), (999999.0, 60)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_band_distances_without_a_screen(dtype, d, theta, radius):
+    """Thresholds that fold every donor (within the radius) into its nearest seed: the form without the screen, from
+    1e6 on, and the last threshold with it; blocks of 32 seeds and a remainder, a last tile of rows."""
+    Wn = 32
+    w = caches.scaled(W["cfg2"], n_layers=1, n_kv_heads=2, prefix=30, decode=590, budget=230, head_dim=d, q_per_kv=1, window=Wn, cluster_frac=0.5)
+    c = caches.make(w, seed=d)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    c = {k: (v.to(dt) if k in ("K", "V", "Q") else v) for k, v in c.items()}
+    band = torch.rand(d // 2, generator=torch.Generator().manual_seed(d)) ** 2
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=230, core=100, merge_geometry=1,
+                    band_weight=band.cuda(), dist_threshold=theta, merge_radius=radius)
+    _note(dtype, d, theta, parity.full_check(c, p, expect_folds=True))
