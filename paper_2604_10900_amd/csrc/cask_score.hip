@@ -1283,10 +1283,9 @@ __device__ __forceinline__ Split3 split3(const f32x4& a, const f32x4& b) {
 // bf16 terms are exact in fp32, and six of them take 6 x 32 cycles for sixteen channels where the
 // fp32 tiles (32x32x2) take 8 x 64.  The five small ones have an accumulator of their own, so that the
 // large one is rounded once per sixteen channels, not once per two: the result is closer to 64-bit sums
-// than the fp32 tiles' was.  A term that is not finite (an infinity or NaN in the cache, a value past
-// the bf16 range) makes the wave's sums NaN; the wave then takes its share again on the fp32 tiles,
-// operands straight from memory (rare, slow, exact).  So do the waves of a workgroup that meets a value so
-// large that what its partner lost below 2^-125 could show in a logit.
+// than the fp32 tiles' was.  The waves of a workgroup that meets a value past the bf16 range, or so large that what its
+// partner lost below 2^-125 could show in a logit, take their share again on the fp32 tiles, operands
+// straight from memory (rare, slow, exact).
 //
 // Stream rows are split once per workgroup: a thread loads eight channels three stages ahead, splits them
 // and leaves the terms in LDS as three planes, one stage ahead; one barrier a stage.  The 16-byte piece p
@@ -1295,7 +1294,7 @@ __device__ __forceinline__ Split3 split3(const f32x4& a, const f32x4& b) {
 //
 // Bound: the matrix pipe (1536 cycles a tile of d = 128).  The clean stages are software-pipelined: the six products
 // of a k-step carry two logits of the tile before (fma, exp2, add: the reference is taken once, as in
-// the bf16 sweeps, and a sum out of range goes the way of a NaN) and two channels of the split of the
+// the bf16 sweeps, and a sum out of range is taken again) and two channels of the split of the
 // stage after.  32 units of 4096 rows, 256 window rows, d = 128: 50 + 53 us, 1.0 PFLOP/s of bf16 products, which
 // is what the bf16 sweeps reach (the clock under matrix load is 1.8 GHz); the fp32 tiles took 81 + 94.  Norm
 // of the scores' error against 64-bit sums over nine shapes: 1.7e-7 - 3.1e-7, with fp32 products 2.2e-7 - 6.8e-7.
@@ -1627,22 +1626,35 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
     plain(f1, n_stages);
   }
 
-  // ---- not finite, or out of range, somewhere: the wave's share again with fp32 products
+  // ---- out of range somewhere: the wave's share again with a running maximum, operands from memory.  The products
+  // are the same, so that a logit has the same bits in both sweeps (its rounding then cancels against that of
+  // the row's sum, which is most of it where one key has the row's mass); fp32 ones where a value is too large.
   const float total = MODE == 0 ? l_run : colsum;
-  if (n_stages > 0 && !(largest * c < 0x1p90f)) too_large = 1;
+  if (n_stages > 0 && !(largest * c < 0x1p90f && largest < 0x1.fep127f)) too_large = 1;
   __syncthreads();
-  if (too_large || __builtin_amdgcn_ballot_w64(wave_live && !(total < kMostSum)) != 0ull) {
+  const bool fp32_tiles = too_large != 0;
+  if (fp32_tiles || __builtin_amdgcn_ballot_w64(wave_live && !(total < kMostSum)) != 0ull) {
     m_ref = kNegInf;
     l_run = colsum = 0.f;
-    const float* bp = res_ptr + (size_t)min(res_row, res_limit - 1) * D + h * 4;
+    const float* bp = res_ptr + (size_t)min(res_row, res_limit - 1) * D;
     for (int it = sk; it < n_stages; ++it) {
       const int srow = s_begin + it * kStageRows;
-      const float* ap = str_ptr + (size_t)min(srow + c32, s_end - 1) * D + h * 4;
-      f32x16 acc = {0};
-      for (int p = 0; p < D / 8; ++p) {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(ap + p * 8), y = *reinterpret_cast<const f32x4*>(bp + p * 8);
+      const float* ap = str_ptr + (size_t)min(srow + c32, s_end - 1) * D;
+      if (fp32_tiles) {
+        acc = f32x16{0};
+        for (int p = 0; p < D / 8; ++p) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(ap + p * 8 + h * 4), y = *reinterpret_cast<const f32x4*>(bp + p * 8 + h * 4);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+          for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+        }
+      } else {
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+          const float* p = ap + ks * 16 + h * 8;
+          products(split3(*reinterpret_cast<const f32x4*>(p), *reinterpret_cast<const f32x4*>(p + 4)), ks);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] += small[r];
       }
       float nl[16];
       if (MODE == 1) {

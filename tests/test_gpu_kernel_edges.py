@@ -884,3 +884,23 @@ def test_band_distances_without_a_screen(dtype, d, theta, radius):
     p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=1, window=Wn, budget=230, core=100, merge_geometry=1,
                     band_weight=band.cuda(), dist_threshold=theta, merge_radius=radius)
     _note(dtype, d, theta, parity.full_check(c, p, expect_folds=True))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,Wn,splits", [(2, 16, 0), (1, 4, 3), (4, 64, 0)])
+def test_fp32_scores_with_steep_logits(G, Wn, splits, d):
+    """Keys thirty times as long: logits hundreds of octaves apart, so that most sums leave the range of their
+    first reference and are taken again.  A logit has the same bits in both sweeps, so that its own rounding
+    cancels in the one key that has a row's mass; what is left is half an ulp of the row's log-sum-exp L, twice
+    (as it is rounded, and as a maximum that it is added to): at most 2^-24 |L| ln 2 of a score."""
+    n, units = 1200, 3
+    g = torch.Generator().manual_seed(d + Wn)
+    K, Q = 30.0 * torch.randn(units * n, d, generator=g), 4.0 * torch.randn(units, Wn, G, d, generator=g)
+    c = dict(K=K, V=K, Q=Q, row_off=torch.arange(units + 1, dtype=torch.int64) * n, prefix_len=torch.zeros(units, dtype=torch.int32))
+    want = _scores64(c, units, n, d, G, Wn)
+    top = float((Q.double().reshape(units, -1, d) @ K.double().reshape(units, n, d).transpose(1, 2).contiguous()).max() / d ** 0.5 / np.log(2.0))
+    p = cask.Params(dtype=cask.F32, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60, score_splits=splits)
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    err = float((got - want).norm() / want.norm())
+    _note(G, Wn, d, "largest logit", top, "octaves, error", err, "bound", 2.0 ** -24 * top * np.log(2.0))
+    assert err < 2.0 ** -24 * top * np.log(2.0)
