@@ -27,19 +27,26 @@ namespace {
 constexpr float kNegInf = -__builtin_inff();
 
 // Most a lane's sum against its fixed reference may reach; beyond, the wave takes its share again with a
-// running maximum.  Short of the fp32 range, because the sums of 2 lanes and up to 64 splits are still to be
-// added, and a share 126 octaves below another one's reference (itself at most 16 above its largest
-// logit) is dropped there: what is lost is below 2^(80 - 126 + 16) of the whole.
-constexpr float kMostSum = 0x1p80f;
+// running maximum.  Short of the fp32 range by more than the sums of 2 lanes and 64 splits can add up to.
+constexpr float kMostSum = 0x1p120f;
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// (m, l) <- combination of two partial softmax statistics in base-2 units
+// (m, l) <- combination of two partial softmax statistics in base-2 units.  REF: the m are references that
+// a sum may lie far above, not maxima.
+template <bool REF>
 __device__ inline void ml_combine(float& m, float& l, float m2, float l2) {
   const float M = fmaxf(m, m2);
-  const float a = (m == kNegInf) ? 0.f : fast_exp2(m - M);
-  const float b = (m2 == kNegInf) ? 0.f : fast_exp2(m2 - M);
-  l = l * a + l2 * b;
+  float e = m - M, e2 = m2 - M;
+  if (REF) {
+    // 2^e by itself would be zero, and the sum may make up for it (further apart than 2 x 126 octaves nothing is
+    // left: a reference is at most 16 above a logit of its own)
+    if (e < -64.f) e *= 0.5f, l *= fast_exp2(e);
+    if (e2 < -64.f) e2 *= 0.5f, l2 *= fast_exp2(e2);
+  }
+  const float a = (m == kNegInf) ? 0.f : fast_exp2(e);
+  const float b = (m2 == kNegInf) ? 0.f : fast_exp2(e2);
+  l = __builtin_fmaf(l, a, l2 * b);
   m = M;
 }
 
@@ -90,7 +97,7 @@ __global__ __launch_bounds__(kBiasThreads) void score_bias_kernel(KParams kp, in
         for (int e = 0; e < 8; ++e) pr[e] = part[(size_t)min(s0 + e, n_splits - 1) * mq_pad + r];
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          if (s0 + e < n_splits) ml_combine(m, l, pr[e].x, pr[e].y);
+          if (s0 + e < n_splits) ml_combine<true>(m, l, pr[e].x, pr[e].y);
       }
       nl = -(m + log2f(l));
     }
@@ -795,7 +802,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const float m2 = __shfl_xor(m_ref[ct], 32, 64);
       const float l2 = __shfl_xor(l_run[ct], 32, 64);
       float mc = m_ref[ct], lc = l_run[ct];
-      ml_combine(mc, lc, m2, l2);
+      ml_combine<true>(mc, lc, m2, l2);
       m_ref[ct] = mc;
       l_run[ct] = lc;
       if (h == 0)
@@ -951,7 +958,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_mfma_kernel(
       const float m2 = __shfl_xor(m_ref[ct], 32, 64);
       const float l2 = __shfl_xor(l_run[ct], 32, 64);
       float mc = m_ref[ct], lc = l_run[ct];
-      ml_combine(mc, lc, m2, l2);
+      ml_combine<true>(mc, lc, m2, l2);
       m_ref[ct] = mc;
       l_run[ct] = lc;
       if (h == 0 && res_row_of(ct) < Mq)
@@ -1203,7 +1210,7 @@ __global__ __launch_bounds__(NW * 64, 2) void score_short_kernel(
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float2 o = stat_of(w)[my_row];
-      ml_combine(M, l_all, o.x, o.y);
+      ml_combine<false>(M, l_all, o.x, o.y);
     }
     publish(row_base + my_row < Mq ? fast_exp2(m - (M + log2f(l_all))) : 0.f);
   }
@@ -1668,7 +1675,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void score_f32_kernel(
 
   if (MODE == 0) {
     const float m2 = __shfl_xor(m_ref, 32, 64), l2 = __shfl_xor(l_run, 32, 64);
-    ml_combine(m_ref, l_run, m2, l2);
+    ml_combine<true>(m_ref, l_run, m2, l2);
     if (h == 0 && res_row < Mq)
       rowstat[((size_t)unit * n_splits + split) * mq_pad + res_row] = make_float2(m_ref, l_run);
     if (n_splits == 1 && h == 0 && res_row < mq_pad)  // a single split is the whole row

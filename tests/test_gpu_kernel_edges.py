@@ -904,3 +904,26 @@ def test_fp32_scores_with_steep_logits(G, Wn, splits, d):
     err = float((got - want).norm() / want.norm())
     _note(G, Wn, d, "largest logit", top, "octaves, error", err, "bound", 2.0 ** -24 * top * np.log(2.0))
     assert err < 2.0 ** -24 * top * np.log(2.0)
+
+
+@pytest.mark.parametrize("form", ["chosen", "wide", "one_launch"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("late,splits", [(100, 1), (104, 1), (300, 2)])
+def test_scores_of_a_share_far_below_another_ones_reference(late, splits, dtype, d, form):
+    """A lane (a key split) whose first logits are 0 and whose sum then reaches 2^119, beside a lane that starts at
+    127: the first one's reference lies 127 to 143 octaves below the second's, beyond what fp32's exponent
+    takes in one step, and its key still has 1/257 of every row."""
+    N, Wn, G = 512, 40, 2
+    K = torch.zeros(N, d)
+    first = 0 if late == 100 else 4   # (a lane holds keys 0 - 3, or 4 - 7, of every eight)
+    K[first, 3], K[late, 3] = 127.0, 119.0
+    Q = torch.zeros(1, Wn, G, d)
+    Q[..., 3] = 1.0
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    c = dict(K=K.to(dt), V=K.to(dt), Q=Q.to(dt), row_off=torch.tensor([0, N], dtype=torch.int64), prefix_len=torch.zeros(1, dtype=torch.int32))
+    p = cask.Params(dtype=cask.F32 if dtype == "f32" else cask.BF16, head_dim=d, q_per_kv=G, window=Wn, budget=Wn + 60,
+                    softmax_scale=float(np.log(2.0)), score_splits=splits, path_flags=SCORE_FORMS[form])
+    got = cask.score(parity.to_device(c, p)).cpu().double()
+    want = torch.zeros(N, dtype=torch.float64)
+    want[first], want[late] = 256.0 / 257.0, 1.0 / 257.0
+    assert float((got - want).abs().max()) < 2e-5   # (a log-sum-exp of 127 in fp32, and a logit of 127: 2^-18 of an octave each)
