@@ -46,18 +46,13 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
   // read from LDS serves four products) when that leaves no more waves idle than 64 per wave
   // (256 per workgroup) does (W*G = 896, 1024, 512, 384: yes; 640, 768: no) and the model above
   // does not prefer the narrow form (small batches: twice as many workgroups fill more of the chip).
-  // With 64 channels the vector pipes are the bound and the operand reads that the wide form saves are not: units of up
-  // to 6400 rows in two to eight rounds of the 512 slots (of sweep B's workgroups of 512 keys) take the narrow form
-  // in both sweeps.  Scores, wide / narrow: 600 units of 2300 rows (W*G = 512) 261 / 249 us, 256 of 6300 (384) 241 / 226,
-  // 128 of 5378 (896) 229 / 214.  Longer units and larger batches do as well or better with the model's choice: 64 of
-  // 20 000 (512) 220 / 230, 32 of 20 301 (896) 211 / 216, 100 of 33 000 (1024) 1038 / 1058.
   int sized;  // key splits the layout has room for on their own
-  auto choose = [&](int shortest, int most, bool narrow) {
+  auto choose = [&](int shortest, int most) {
     double cost_n = 0.0, cost_w = 0.0;
     const int splits_n = best_splits(false, shortest, most, &cost_n), splits_w = best_splits(true, shortest, most, &cost_w);
     const int live_w = (kp.Mq + 127) / 128, all_w = (kp.Mq + 511) / 512 * 4;
     const int live_n = (kp.Mq + 63) / 64, all_n = (kp.Mq + 255) / 256 * 4;
-    w.wide_rows = (!narrow && kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
+    w.wide_rows = (kp.Mq > 256 && (int64_t)live_w * all_n >= (int64_t)live_n * all_w && cost_w <= cost_n) ? 1 : 0;
     if (kp.path_flags & CASK_PATH_WIDE_ROWS) w.wide_rows = 1;
     if (kp.path_flags & CASK_PATH_NARROW_ROWS) w.wide_rows = 0;
     return w.wide_rows ? splits_w : splits_n;
@@ -69,11 +64,7 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     const int k = (max_unit_len + len - 1) / len;
     return k < 1 ? 1 : k;
   };
-  const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
-  const bool narrow_64 = kp.d == 64 && kp.Mq > 256 && max_unit_len <= 6400 && wgs_wide >= 1024 && wgs_wide < 4096;
-  // (the layout has room for the splits of the form that the model chooses, whatever the head size: a batch
-  // whose workspace fits a limit with 128 channels fits it with 64)
-  int n_splits = choose(1024, 64, false), split_len;
+  int n_splits = choose(1024, 64), split_len;
   if (kp.score_splits >= 1) n_splits = kp.score_splits;
   sized = n_splits = whole_stages(n_splits, &split_len);
   // Row pitch of the one-launch scoring's partial sums (bf16 only; laid out below).
@@ -102,11 +93,19 @@ Workspace layout_workspace(const KParams& kp, int n_units, int64_t total_rows, i
     // (From the number of units and the longest alone, also where lengths differ: other splits sum a row's
     // terms in another order, scores move by about 2e-7, and of some thousand ranks one may then keep another
     // row.  Priced by the mean length instead, 1024 units of 4600 - 33 000 rows took 8 splits for 1: 6270 -> 6123 us.)
-    n_splits = whole_stages(choose(512, most, narrow_64), &split_len);
-  } else {
-    (void)choose(1024, 64, narrow_64);  // (the form alone: splits that were asked for, or units of one split)
+    n_splits = whole_stages(choose(512, most), &split_len);
   }
   w.n_splits = n_splits;
+  // With 64 channels the vector pipes are the bound and the operand reads that the wide form saves are not: units of up
+  // to 6400 rows in two to eight rounds of the 512 slots (of sweep B's workgroups of 512 keys) take the narrow form
+  // in both sweeps.  Scores, wide / narrow: 436 units of 2145 rows (W*G = 800) 268 / 246 us, 256 of 6300 (384) 237 / 227,
+  // 128 of 5378 (896) 226 / 212.  Longer units and larger batches do as well or better with the model's choice: 64 of
+  // 20 000 (512) 220 / 230, 32 of 20 301 (896) 211 / 216, 100 of 33 000 (1024) 1038 / 1058.  The splits stay those that
+  // the model takes: the workspace is that of 128 channels, and the scores have the same bits in either form (with the
+  // narrow form's own splits, which are other ones for one shape in sixty, the times are 1 % longer besides).
+  const int64_t wgs_wide = (int64_t)n_units * ((max_unit_len + 511) / 512);
+  const bool narrow_64 = kp.d == 64 && kp.Mq > 256 && max_unit_len <= 6400 && wgs_wide >= 1024 && wgs_wide < 4096;
+  if (narrow_64 && !(kp.path_flags & CASK_PATH_WIDE_ROWS)) w.wide_rows = 0;
   // Sweep B of a batch of short units has few workgroups (one per 256 keys), each paying its
   // fixed cost for all W*G window rows: two workgroups then share a key tile, one half of the
   // window rows each, and add their column sums (two addends onto zero: the order cannot

@@ -593,6 +593,22 @@ def test_key_splits_do_not_follow_the_other_units_lengths(units, longest, rest):
         assert torch.equal(a, b), u
 
 
+@pytest.mark.parametrize("units,n,G,Wn", [(171, 5248, 6, 64), (303, 2817, 4, 128), (611, 1456, 7, 64), (128, 5378, 7, 128)])
+def test_narrow_sweeps_of_64_channels_sum_in_the_wide_forms_order(units, n, G, Wn):
+    """Batches that take the narrow form where the model prefers the wide one (their own best key splits would be
+    2, 2, 1 and 1 for 4, 5, 2 and 1): the scores are the wide form's, bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    K = torch.randn(units * n, 64, generator=g, device="cuda").to(torch.bfloat16)
+    Q = torch.randn(units, Wn, G, 64, generator=g, device="cuda").to(torch.bfloat16)
+    row_off = torch.arange(units + 1, dtype=torch.int64) * n
+    got = []
+    for flags in (0, B.PATH_WIDE_ROWS):
+        p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=G, window=Wn, budget=Wn + 60, path_flags=flags)
+        got.append(cask.score(cask.Batch(p, row_off, torch.zeros(units, dtype=torch.int32), K, K, Q)))
+    torch.cuda.synchronize()
+    assert torch.equal(*got)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_band_distance_screen_at_the_worst_rounding_to_bf16(dtype, d):
