@@ -1227,6 +1227,7 @@ __device__ __forceinline__ void fold_group(const FoldIo<T>& io, int u, int64_t r
       dk[q] = *reinterpret_cast<const Raw*>(io.K + (size_t)(row0 + drow[q]) * D + gl * EPL);
       dv[q] = *reinterpret_cast<const Raw*>(io.V + (size_t)(row0 + drow[q]) * D + gl * EPL);
     }
+    __builtin_amdgcn_sched_barrier(0);  // (all four rows on their way before the first is taken)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (idx + NG * q < s1) {
