@@ -43,7 +43,7 @@ struct SelectLds {
   uint32_t cand[3][kCand];
   int n_cand[3];
   uint32_t wave_tot[3][kSelWaves];
-  uint32_t wave_lo[kSelWaves], wave_hi[kSelWaves];
+  uint32_t wave_lo[3][kSelWaves], wave_hi[3][kSelWaves];
   int found[3][4];
 };
 
@@ -106,7 +106,9 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ s, int i0, i
 // Steps: the smallest and largest key; a histogram of 2048 equal bins between them (the bins follow
 // the keys that are there, where digits of fixed weight would put most of a unit's scores, a few
 // binades, into a few of them); per query the bin its rank falls into.  A bin of at most 64 keys is
-// ranked by one wave; a larger one gets a histogram of its own.  Each step costs a few vector
+// ranked by one wave; a larger one gets a histogram of its own, over the range that its keys occupy, and
+// none where that is one value (scores that many rows share: 16 units of 36 864 rows of two values,
+// stage 2, 59.5 us, 85.5 with the bin taken apart to the last bit).  Each step costs a few vector
 // instructions per key, and with sixteen waves to a compute unit an instruction per key is 16 cycles:
 // that, not the LDS, is the bound.  (A radix select of four 8-bit passes, about 48 instructions per
 // key and pass, took 3.4 us a pass at nine keys a thread.)
@@ -154,22 +156,25 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
   kmin = wave_reduce(kmin, smaller);
   kmax = wave_reduce(kmax, larger);
   if (lane == 0) {
-    L.wave_lo[wv] = kmin;
-    L.wave_hi[wv] = kmax;
+    L.wave_lo[0][wv] = kmin;
+    L.wave_hi[0][wv] = kmax;
   }
   __syncthreads();
-  kmin = wave_reduce(L.wave_lo[lane & (kSelWaves - 1)], smaller);
-  kmax = wave_reduce(L.wave_hi[lane & (kSelWaves - 1)], larger);
+  kmin = wave_reduce(L.wave_lo[0][lane & (kSelWaves - 1)], smaller);
+  kmax = wave_reduce(L.wave_hi[0][lane & (kSelWaves - 1)], larger);
 
-  // query j's k-th key lies in [base[j], base[j] + 2^shift), `eq[j]` keys of its range do, and `rem[j]` of
+  // query j's k-th key lies in [base[j], base[j] + ext[j]], `eq[j]` keys of its range do, and `rem[j]` of
   // them belong to the top k (the values are the same in every thread)
-  const uint32_t span = kmax - kmin;
-  int shift = span == 0u ? 0 : max(0, 32 - __clz((int)span) - 11);
-  uint32_t base[3] = {kmin, kmin, kmin};
+  auto bin_shift = [](uint32_t span) { return span == 0u ? 0 : max(0, 32 - __clz((int)span) - 11); };
+  int shift = bin_shift(kmax - kmin);
+  uint32_t base[3] = {kmin, kmin, kmin}, ext[3] = {kmax - kmin, kmax - kmin, kmax - kmin};
   int rem[3] = {q.k[0], q.k[1], q.k[2]}, eq[3] = {0, 0, 0};
   bool open[3] = {q.k[0] > 0, q.k[1] > 0, q.k[2] > 0};
   // queries 1 and 2 share the first histogram; from the second step on each has its own
-  auto count_step = [&](auto first_c, int coarser) {  // coarser: the shift of the bins that are taken apart
+  auto in_bin = [&](int j, uint32_t k, int row) {
+    return open[j] && k - base[j] <= ext[j] && (j == 0 ? row < q.P : row >= q.P && row < q.hi);
+  };
+  auto count_step = [&](auto first_c) {
     constexpr bool kFirst = decltype(first_c)::value;
     over_keys([&](int i) {
 #pragma unroll
@@ -181,9 +186,7 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
         } else {
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
-            const uint32_t off = key[e] - base[j];
-            if (open[j] && (off >> coarser) == 0u && (j == 0 ? row < q.P : row >= q.P && row < q.hi))
-              atomicAdd(&L.hist[j][(off >> shift) * 2 + (lane & 1)], 1);
+            if (in_bin(j, key[e], row)) atomicAdd(&L.hist[j][((key[e] - base[j]) >> shift) * 2 + (lane & 1)], 1);
           }
         }
       }
@@ -221,13 +224,15 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
 #pragma unroll
     for (int j = 0; j < 3; ++j)
       if (open[j]) {
-        base[j] += (uint32_t)__builtin_amdgcn_readfirstlane(L.found[j][0]) << shift;
+        const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane(L.found[j][0]) << shift;
+        base[j] += at;
+        ext[j] = smaller(ext[j] - at, (1u << shift) - 1u);
         rem[j] = __builtin_amdgcn_readfirstlane(L.found[j][1]);
         eq[j] = __builtin_amdgcn_readfirstlane(L.found[j][2]);
         if (shift == 0 || (early && rem[j] == eq[j])) open[j] = false;
       }
   };
-  count_step(std::true_type{}, 32);
+  count_step(std::true_type{});
   while (open[0] || open[1] || open[2]) {
     bool few = true;
 #pragma unroll
@@ -239,7 +244,7 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
           const int row = i + e * 64;
 #pragma unroll
           for (int j = 0; j < 3; ++j)
-            if (open[j] && ((key[e] - base[j]) >> shift) == 0u && (j == 0 ? row < q.P : row >= q.P && row < q.hi))
+            if (in_bin(j, key[e], row))
               L.cand[j][atomicAdd(&L.n_cand[j], 1)] = key[e];  // (their order does not matter)
         }
       });
@@ -270,12 +275,43 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
           open[j] = false;
         }
     } else {
+      // the range that the keys of each bin occupy
+      uint32_t low[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, top[3] = {0u, 0u, 0u};
+      over_keys([&](int i) {
 #pragma unroll
-      for (int j = 0; j < 3; ++j) *reinterpret_cast<int4*>(&L.hist[j][tid * 4]) = make_int4(0, 0, 0, 0);
+        for (int e = 0; e < PER; ++e) {
+          const int row = i + e * 64;
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const bool in = in_bin(j, key[e], row);
+            low[j] = smaller(low[j], in ? key[e] : 0xFFFFFFFFu);
+            top[j] = larger(top[j], in ? key[e] : 0u);
+          }
+        }
+      });
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        *reinterpret_cast<int4*>(&L.hist[j][tid * 4]) = make_int4(0, 0, 0, 0);
+        low[j] = wave_reduce(low[j], smaller);
+        top[j] = wave_reduce(top[j], larger);
+        if (lane == 0) {
+          L.wave_lo[j][wv] = low[j];
+          L.wave_hi[j][wv] = top[j];
+        }
+      }
       __syncthreads();
-      const int coarser = shift;
-      shift = max(0, shift - 11);
-      count_step(std::false_type{}, coarser);
+      uint32_t span = 0u;
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (!open[j]) continue;
+        base[j] = wave_reduce(L.wave_lo[j][lane & (kSelWaves - 1)], smaller);
+        ext[j] = wave_reduce(L.wave_hi[j][lane & (kSelWaves - 1)], larger) - base[j];
+        if (ext[j] == 0u) open[j] = false;
+        span = larger(span, ext[j]);
+      }
+      if (!(open[0] || open[1] || open[2])) break;
+      shift = bin_shift(span);
+      count_step(std::false_type{});
     }
   }
   __syncthreads();  // the caller may reuse the LDS

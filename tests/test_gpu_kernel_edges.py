@@ -434,6 +434,48 @@ def test_ranks_where_the_bins_are_uneven(N, P, spread):
         np.testing.assert_allclose(rho.cpu().numpy(), want_rho, rtol=2e-6)
 
 
+@pytest.mark.parametrize("kind", ["zeros", "two", "ulps", "end_of_a_bin"])
+@pytest.mark.parametrize("N,P", [(4096, 30), (9217, 5000), (36864, 300), (36865, 20000)])
+def test_ranks_where_many_rows_share_a_value(N, P, kind):
+    """Roles where a bin of the first histogram holds one value thousands of times, two values an ulp apart, or
+    keys up to its very end (two of them in the last bin of the next histogram, which would reach over the end to
+    the keys behind, but for the range that the first bin's keys occupy)."""
+    rng = np.random.default_rng(N)
+    p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=64, budget=900, sim_threshold=2.0)
+    C = cask.plan(p, P, N)["core"]
+    if kind == "zeros":
+        sc = np.where(rng.random(N) < 0.95, 0.0, rng.random(N))
+    elif kind == "two":
+        sc = np.where(rng.random(N) < 0.5, 1e-4, 2e-4)
+    elif kind == "ulps":
+        sc = (np.float32(1.0).view(np.uint32) + rng.integers(0, 2, N).astype(np.uint32)).view(np.float32)
+        sc[[3, N - 70]], sc[[4, N - 71]] = 3e38, -3e38
+    else:
+        least = int(np.float32(2.0 ** -20).view(np.uint32))
+        end = least + 40 * 65536                                       # bins of 2^16 from the smallest key on
+        top = least + 2 ** 27 - 1 - np.arange(C - 71)
+        behind, last = end + np.arange(70), np.array([end - 1, end - 3])
+        below = np.concatenate([[end - 65536 + 0x8003], end - 65536 + 0x8003 + rng.integers(0, 0x7000, 100), [least]])
+        keys = np.concatenate([top, behind, last, below])
+        n = N - 64 - P
+        keys = np.concatenate([keys, least + rng.integers(0, 30 * 65536, n - len(keys))]).astype(np.uint32)
+        sc = np.zeros(N, dtype=np.float32)
+        sc[P: P + n] = rng.permutation(keys).view(np.float32)
+    sc = sc.astype(np.float32)
+    rp, row_off, prefix = parity.ref_params(p), np.array([0, N], dtype=np.int64), np.array([P], dtype=np.int32)
+    role_w, _ = ref.prefix_evict(rp, row_off, prefix, sc)
+    role_w, _ = ref.partition(rp, row_off, prefix, sc, role_w)
+    K = torch.zeros(N, 64, dtype=torch.bfloat16, device="cuda")
+    b = cask.Batch(p, torch.from_numpy(row_off), torch.from_numpy(prefix), K, K, torch.zeros(1, 64, 1, 64, dtype=torch.bfloat16, device="cuda"))
+    sd = torch.from_numpy(sc).cuda()
+    role, _ = cask.prefix_evict(b, sd)
+    role, _ = cask.partition(b, sd, role)
+    src = cask.compress(b, scores=sd).out_src[0]
+    torch.cuda.synchronize()
+    assert np.array_equal(role.cpu().numpy(), role_w)
+    assert np.array_equal(src.cpu().numpy(), np.nonzero(np.isin(role_w, [1, 2, 3, 5]))[0])
+
+
 def _scores64(c, units, n, d, G, Wn):
     """Scores in 64 bits, on the CPU."""
     K, Q = c["K"].double().reshape(units, n, d), c["Q"].double().reshape(units, Wn * G, d)
