@@ -38,6 +38,7 @@ constexpr int kSelMany = 16;
 
 constexpr int kBins = 2048;
 constexpr int kCand = 64;  // candidates of a boundary bin that one wave ranks
+constexpr int kCrowd = 1024;
 struct SelectLds {
   int hist[3][2 * kBins];  // two copies of a bin side by side: scores crowd, and equal addresses serialise
   uint32_t cand[3][kCand];
@@ -106,9 +107,11 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ s, int i0, i
 // Steps: the smallest and largest key; a histogram of 2048 equal bins between them (the bins follow
 // the keys that are there, where digits of fixed weight would put most of a unit's scores, a few
 // binades, into a few of them); per query the bin its rank falls into.  A bin of at most 64 keys is
-// ranked by one wave; a larger one gets a histogram of its own, over the range that its keys occupy, and
-// none where that is one value (scores that many rows share: 16 units of 36 864 rows of two values,
-// stage 2, 59.5 us, 85.5 with the bin taken apart to the last bit).  Each step costs a few vector
+// ranked by one wave; a larger one gets a histogram of its own.  A bin of more than kCrowd keys is looked at first:
+// its histogram is over the range that its keys occupy, and there is none where that is one value (scores
+// that many rows share: 16 units of 36 864 rows of two values, stage 2, 59.5 us, 85.5 with the bin taken apart
+// to the last bit; smaller bins are seldom of one value, and the look costs as much as a step: 1 - 2 us of
+// an event on units of 5000 - 9000 rows).  Each step costs a few vector
 // instructions per key, and with sixteen waves to a compute unit an instruction per key is 16 cycles:
 // that, not the LDS, is the bound.  (A radix select of four 8-bit passes, about 48 instructions per
 // key and pass, took 3.4 us a pass at nine keys a thread.)
@@ -275,42 +278,51 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
           open[j] = false;
         }
     } else {
-      // the range that the keys of each bin occupy
-      uint32_t low[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, top[3] = {0u, 0u, 0u};
-      over_keys([&](int i) {
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int row = i + e * 64;
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            const bool in = in_bin(j, key[e], row);
-            low[j] = smaller(low[j], in ? key[e] : 0xFFFFFFFFu);
-            top[j] = larger(top[j], in ? key[e] : 0u);
-          }
-        }
-      });
+      bool crowd = false;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         *reinterpret_cast<int4*>(&L.hist[j][tid * 4]) = make_int4(0, 0, 0, 0);
-        low[j] = wave_reduce(low[j], smaller);
-        top[j] = wave_reduce(top[j], larger);
-        if (lane == 0) {
-          L.wave_lo[j][wv] = low[j];
-          L.wave_hi[j][wv] = top[j];
-        }
+        crowd = crowd || (open[j] && eq[j] > kCrowd);
       }
-      __syncthreads();
-      uint32_t span = 0u;
+      shift = max(0, shift - 11);
+      if (crowd) {  // the range that the keys of each bin occupy
+        uint32_t low[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, top[3] = {0u, 0u, 0u};
+        over_keys([&](int i) {
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        if (!open[j]) continue;
-        base[j] = wave_reduce(L.wave_lo[j][lane & (kSelWaves - 1)], smaller);
-        ext[j] = wave_reduce(L.wave_hi[j][lane & (kSelWaves - 1)], larger) - base[j];
-        if (ext[j] == 0u) open[j] = false;
-        span = larger(span, ext[j]);
+          for (int e = 0; e < PER; ++e) {
+            const int row = i + e * 64;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              const bool in = in_bin(j, key[e], row);
+              low[j] = smaller(low[j], in ? key[e] : 0xFFFFFFFFu);
+              top[j] = larger(top[j], in ? key[e] : 0u);
+            }
+          }
+        });
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          low[j] = wave_reduce(low[j], smaller);
+          top[j] = wave_reduce(top[j], larger);
+          if (lane == 0) {
+            L.wave_lo[j][wv] = low[j];
+            L.wave_hi[j][wv] = top[j];
+          }
+        }
+        __syncthreads();
+        uint32_t span = 0u;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          if (!open[j]) continue;
+          base[j] = wave_reduce(L.wave_lo[j][lane & (kSelWaves - 1)], smaller);
+          ext[j] = wave_reduce(L.wave_hi[j][lane & (kSelWaves - 1)], larger) - base[j];
+          if (ext[j] == 0u) open[j] = false;
+          span = larger(span, ext[j]);
+        }
+        if (!(open[0] || open[1] || open[2])) break;
+        shift = bin_shift(span);
+      } else {
+        __syncthreads();
       }
-      if (!(open[0] || open[1] || open[2])) break;
-      shift = bin_shift(span);
       count_step(std::false_type{});
     }
   }

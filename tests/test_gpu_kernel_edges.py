@@ -455,7 +455,7 @@ def test_ranks_where_many_rows_share_a_value(N, P, kind):
         end = least + 40 * 65536                                       # bins of 2^16 from the smallest key on
         top = least + 2 ** 27 - 1 - np.arange(C - 71)
         behind, last = end + np.arange(70), np.array([end - 1, end - 3])
-        below = np.concatenate([[end - 65536 + 0x8003], end - 65536 + 0x8003 + rng.integers(0, 0x7000, 100), [least]])
+        below = np.concatenate([[end - 65536 + 0x8003], end - 65536 + 0x8003 + rng.integers(0, 0x7000, 1100), [least]])
         keys = np.concatenate([top, behind, last, below])
         n = N - 64 - P
         keys = np.concatenate([keys, least + rng.integers(0, 30 * 65536, n - len(keys))]).astype(np.uint32)
