@@ -37,15 +37,20 @@ __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 template <bool REF>
 __device__ inline void ml_combine(float& m, float& l, float m2, float l2) {
   const float M = fmaxf(m, m2);
-  float e = m - M, e2 = m2 - M;
+  float a = (m == kNegInf) ? 0.f : fast_exp2(m - M);
+  float b = (m2 == kNegInf) ? 0.f : fast_exp2(m2 - M);
   if (REF) {
-    // 2^e by itself would be zero, and the sum may make up for it (further apart than 2 x 126 octaves nothing is
-    // left: a reference is at most 16 above a logit of its own)
-    if (e < -64.f) e *= 0.5f, l *= fast_exp2(e);
-    if (e2 < -64.f) e2 *= 0.5f, l2 *= fast_exp2(e2);
+    // Far apart, 2^e of the lower one by itself would be zero, and its sum may make up for it (further apart than
+    // 2 x 126 octaves nothing is left: a reference is at most 16 above a logit of its own).  (Rare, and out of
+    // the chain: event on 6 units of up to 25 900 rows 73.3 -> 71.9 us.)
+    const float apart = __builtin_fabsf(m - m2);
+    const bool far = apart > 64.f && apart < __builtin_inff();
+    if (__builtin_amdgcn_ballot_w64(far) != 0ull) {
+      const float half = fast_exp2(-0.5f * apart);
+      if (far && m < m2) l *= half, a = half;
+      if (far && m2 < m) l2 *= half, b = half;
+    }
   }
-  const float a = (m == kNegInf) ? 0.f : fast_exp2(e);
-  const float b = (m2 == kNegInf) ? 0.f : fast_exp2(e2);
   l = __builtin_fmaf(l, a, l2 * b);
   m = M;
 }
