@@ -44,7 +44,8 @@ struct SelectLds {
   uint32_t cand[3][kCand];
   int n_cand[3];
   uint32_t wave_tot[3][kSelWaves];
-  uint32_t wave_lo[3][kSelWaves], wave_hi[3][kSelWaves];
+  uint32_t wave_lo[kSelWaves], wave_hi[kSelWaves];
+  uint32_t bin_lo[3], bin_hi[3];  // of a crowded bin: its smallest and largest key
   int found[3][4];
 };
 
@@ -107,11 +108,10 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ s, int i0, i
 // Steps: the smallest and largest key; a histogram of 2048 equal bins between them (the bins follow
 // the keys that are there, where digits of fixed weight would put most of a unit's scores, a few
 // binades, into a few of them); per query the bin its rank falls into.  A bin of at most 64 keys is
-// ranked by one wave; a larger one gets a histogram of its own.  A bin of more than kCrowd keys is looked at first:
-// its histogram is over the range that its keys occupy, and there is none where that is one value (scores
-// that many rows share: 16 units of 36 864 rows of two values, stage 2, 59.5 us, 85.5 with the bin taken apart
-// to the last bit; smaller bins are seldom of one value, and the look costs as much as a step: 1 - 2 us of
-// an event on units of 5000 - 9000 rows).  Each step costs a few vector
+// ranked by one wave; a larger one gets a histogram of its own.  Where it holds more than kCrowd keys, they are first
+// looked at for being one value that many rows share, which ends the search (16 units of 36 864 rows of two
+// values, stage 2, 57.4 us, 85.5 with the bin taken apart to the last bit; smaller bins are seldom of one value,
+// and the look costs as much as a step).  Each step costs a few vector
 // instructions per key, and with sixteen waves to a compute unit an instruction per key is 16 cycles:
 // that, not the LDS, is the bound.  (A radix select of four 8-bit passes, about 48 instructions per
 // key and pass, took 3.4 us a pass at nine keys a thread.)
@@ -159,25 +159,22 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
   kmin = wave_reduce(kmin, smaller);
   kmax = wave_reduce(kmax, larger);
   if (lane == 0) {
-    L.wave_lo[0][wv] = kmin;
-    L.wave_hi[0][wv] = kmax;
+    L.wave_lo[wv] = kmin;
+    L.wave_hi[wv] = kmax;
   }
   __syncthreads();
-  kmin = wave_reduce(L.wave_lo[0][lane & (kSelWaves - 1)], smaller);
-  kmax = wave_reduce(L.wave_hi[0][lane & (kSelWaves - 1)], larger);
+  kmin = wave_reduce(L.wave_lo[lane & (kSelWaves - 1)], smaller);
+  kmax = wave_reduce(L.wave_hi[lane & (kSelWaves - 1)], larger);
 
-  // query j's k-th key lies in [base[j], base[j] + ext[j]], `eq[j]` keys of its range do, and `rem[j]` of
+  // query j's k-th key lies in [base[j], base[j] + 2^shift), `eq[j]` keys of its range do, and `rem[j]` of
   // them belong to the top k (the values are the same in every thread)
-  auto bin_shift = [](uint32_t span) { return span == 0u ? 0 : max(0, 32 - __clz((int)span) - 11); };
-  int shift = bin_shift(kmax - kmin);
-  uint32_t base[3] = {kmin, kmin, kmin}, ext[3] = {kmax - kmin, kmax - kmin, kmax - kmin};
+  const uint32_t span = kmax - kmin;
+  int shift = span == 0u ? 0 : max(0, 32 - __clz((int)span) - 11);
+  uint32_t base[3] = {kmin, kmin, kmin};
   int rem[3] = {q.k[0], q.k[1], q.k[2]}, eq[3] = {0, 0, 0};
   bool open[3] = {q.k[0] > 0, q.k[1] > 0, q.k[2] > 0};
   // queries 1 and 2 share the first histogram; from the second step on each has its own
-  auto in_bin = [&](int j, uint32_t k, int row) {
-    return open[j] && k - base[j] <= ext[j] && (j == 0 ? row < q.P : row >= q.P && row < q.hi);
-  };
-  auto count_step = [&](auto first_c) {
+  auto count_step = [&](auto first_c, int coarser) {  // coarser: the shift of the bins that are taken apart
     constexpr bool kFirst = decltype(first_c)::value;
     over_keys([&](int i) {
 #pragma unroll
@@ -189,7 +186,9 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
         } else {
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
-            if (in_bin(j, key[e], row)) atomicAdd(&L.hist[j][((key[e] - base[j]) >> shift) * 2 + (lane & 1)], 1);
+            const uint32_t off = key[e] - base[j];
+            if (open[j] && (off >> coarser) == 0u && (j == 0 ? row < q.P : row >= q.P && row < q.hi))
+              atomicAdd(&L.hist[j][(off >> shift) * 2 + (lane & 1)], 1);
           }
         }
       }
@@ -227,15 +226,13 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
 #pragma unroll
     for (int j = 0; j < 3; ++j)
       if (open[j]) {
-        const uint32_t at = (uint32_t)__builtin_amdgcn_readfirstlane(L.found[j][0]) << shift;
-        base[j] += at;
-        ext[j] = smaller(ext[j] - at, (1u << shift) - 1u);
+        base[j] += (uint32_t)__builtin_amdgcn_readfirstlane(L.found[j][0]) << shift;
         rem[j] = __builtin_amdgcn_readfirstlane(L.found[j][1]);
         eq[j] = __builtin_amdgcn_readfirstlane(L.found[j][2]);
         if (shift == 0 || (early && rem[j] == eq[j])) open[j] = false;
       }
   };
-  count_step(std::true_type{});
+  count_step(std::true_type{}, 32);
   while (open[0] || open[1] || open[2]) {
     bool few = true;
 #pragma unroll
@@ -247,7 +244,7 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
           const int row = i + e * 64;
 #pragma unroll
           for (int j = 0; j < 3; ++j)
-            if (in_bin(j, key[e], row))
+            if (open[j] && ((key[e] - base[j]) >> shift) == 0u && (j == 0 ? row < q.P : row >= q.P && row < q.hi))
               L.cand[j][atomicAdd(&L.n_cand[j], 1)] = key[e];  // (their order does not matter)
         }
       });
@@ -278,52 +275,45 @@ __device__ __forceinline__ void rank_select(const float* __restrict__ s, const R
           open[j] = false;
         }
     } else {
-      bool crowd = false;
 #pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        *reinterpret_cast<int4*>(&L.hist[j][tid * 4]) = make_int4(0, 0, 0, 0);
-        crowd = crowd || (open[j] && eq[j] > kCrowd);
-      }
-      shift = max(0, shift - 11);
-      if (crowd) {  // the range that the keys of each bin occupy
-        uint32_t low[3] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, top[3] = {0u, 0u, 0u};
-        over_keys([&](int i) {
+      for (int j = 0; j < 3; ++j) *reinterpret_cast<int4*>(&L.hist[j][tid * 4]) = make_int4(0, 0, 0, 0);
+      if (tid < 3) L.bin_lo[tid] = 0xFFFFFFFFu, L.bin_hi[tid] = 0u;
+      __syncthreads();
+      if ((open[0] && eq[0] > kCrowd) || (open[1] && eq[1] > kCrowd) || (open[2] && eq[2] > kCrowd)) {
+#pragma unroll 1
+        for (int j = 0; j < 3; ++j) {
+          if (!(j == 0 ? open[0] && eq[0] > kCrowd : j == 1 ? open[1] && eq[1] > kCrowd : open[2] && eq[2] > kCrowd)) continue;
+          const uint32_t from = j == 0 ? base[0] : j == 1 ? base[1] : base[2];
+          const int first = j == 0 ? 0 : q.P, end = j == 0 ? q.P : q.hi;
+          uint32_t low = 0xFFFFFFFFu, top = 0u;
+          over_keys([&](int i) {
 #pragma unroll
-          for (int e = 0; e < PER; ++e) {
-            const int row = i + e * 64;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              const bool in = in_bin(j, key[e], row);
-              low[j] = smaller(low[j], in ? key[e] : 0xFFFFFFFFu);
-              top[j] = larger(top[j], in ? key[e] : 0u);
+            for (int e = 0; e < PER; ++e) {
+              const int row = i + e * 64;
+              const bool in = ((key[e] - from) >> shift) == 0u && row >= first && row < end;
+              low = smaller(low, in ? key[e] : 0xFFFFFFFFu);
+              top = larger(top, in ? key[e] : 0u);
             }
-          }
-        });
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          low[j] = wave_reduce(low[j], smaller);
-          top[j] = wave_reduce(top[j], larger);
+          });
+          low = wave_reduce(low, smaller);
+          top = wave_reduce(top, larger);
           if (lane == 0) {
-            L.wave_lo[j][wv] = low[j];
-            L.wave_hi[j][wv] = top[j];
+            atomicMin(&L.bin_lo[j], low);
+            atomicMax(&L.bin_hi[j], top);
           }
         }
         __syncthreads();
-        uint32_t span = 0u;
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          if (!open[j]) continue;
-          base[j] = wave_reduce(L.wave_lo[j][lane & (kSelWaves - 1)], smaller);
-          ext[j] = wave_reduce(L.wave_hi[j][lane & (kSelWaves - 1)], larger) - base[j];
-          if (ext[j] == 0u) open[j] = false;
-          span = larger(span, ext[j]);
-        }
+        for (int j = 0; j < 3; ++j)
+          if (open[j] && eq[j] > kCrowd && L.bin_lo[j] == L.bin_hi[j]) {
+            base[j] = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.bin_lo[j]);
+            open[j] = false;
+          }
         if (!(open[0] || open[1] || open[2])) break;
-        shift = bin_shift(span);
-      } else {
-        __syncthreads();
       }
-      count_step(std::false_type{});
+      const int coarser = shift;
+      shift = max(0, shift - 11);
+      count_step(std::false_type{}, coarser);
     }
   }
   __syncthreads();  // the caller may reuse the LDS

@@ -437,9 +437,8 @@ def test_ranks_where_the_bins_are_uneven(N, P, spread):
 @pytest.mark.parametrize("kind", ["zeros", "two", "ulps", "end_of_a_bin"])
 @pytest.mark.parametrize("N,P", [(4096, 30), (9217, 5000), (36864, 300), (36865, 20000)])
 def test_ranks_where_many_rows_share_a_value(N, P, kind):
-    """Roles where a bin of the first histogram holds one value thousands of times, two values an ulp apart, or
-    keys up to its very end (two of them in the last bin of the next histogram, which would reach over the end to
-    the keys behind, but for the range that the first bin's keys occupy)."""
+    """Roles where a bin of the first histogram holds one value thousands of times, two values an ulp apart, or a
+    thousand different keys up to its very end, with the rank between its last two and others right behind it."""
     rng = np.random.default_rng(N)
     p = cask.Params(dtype=cask.BF16, head_dim=64, q_per_kv=1, window=64, budget=900, sim_threshold=2.0)
     C = cask.plan(p, P, N)["core"]
